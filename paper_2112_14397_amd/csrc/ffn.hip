@@ -14,7 +14,7 @@ hipError_t launch_expert_ffn(const Ctx& c, const evomoe_shape& s, const void* x,
                              const float* b1, const void* W2, const float* b2, void* H, void* A, void* O) {
     if (s.dtype == EVOMOE_BF16)
         return mfma_ffn_fwd(c, s, x, pair_token, expert_offsets, W1, b1, W2, b2, H, A, O);
-    return simple_ffn_fwd<float>(c, s, x, pair_token, expert_offsets, W1, b1, W2, b2, H, A, O);
+    return f32_ffn_fwd(c, s, x, pair_token, expert_offsets, W1, b1, W2, b2, H, A, O);
 }
 
 hipError_t launch_expert_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, const void* H,
@@ -26,7 +26,7 @@ hipError_t launch_expert_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void
     if (s.dtype == EVOMOE_BF16)
         return mfma_ffn_bwd(c, s, dO, H, A, x, pair_token, expert_offsets, W1, W2, dy, pair_gate, dW1, db1,
                             dW2, db2, dXp, accumulate, workspace);
-    return simple_ffn_bwd<float>(c, s, dO, H, A, x, pair_token, expert_offsets, W1, W2, dW1, db1, dW2,
+    return f32_ffn_bwd(c, s, dO, H, A, x, pair_token, expert_offsets, W1, W2, dW1, db1, dW2,
                                  db2, dXp, accumulate, workspace);
 }
 

@@ -1,0 +1,424 @@
+// Expert FFNs of a float32 layer (EvoMoE Eq. ffn per expert over its ragged row range, and its backward) on the
+// float32 matrix cores.  One grouped-GEMM kernel, v_mfma_f32_32x32x2_f32 (products and sums are float32 throughout):
+//
+//   NT  C[r,n] = sum_k A[arow(r),k] * W_g[n,k]          forward GEMMs (A rows optionally gathered by token)
+//   NN  C[r,n] = sum_k A[r,k]       * W_g[k,n]          dH = dO W2,  dXp = dH W1
+//   TN  C_g[m,n] = sum_{r in g} L[r,m] * R[rrow(r),n]   weight gradients (contraction over the ragged rows)
+//
+// What bounds it: the float32 matrix rate (256 flop per clock and CU, a sixteenth of bf16's), so neither LDS nor L2
+// needs more than plain double buffering: global -> registers -> LDS one slab ahead, several blocks per CU.  GEMM1 of
+// 11160 pairs, d = 512, F = 2048: 97 TFLOP/s; a 4096^3 library product reaches 137 on the same card, the float32-FMA
+// kernels that stood here before 25.  The weight-gradient launch also sums the columns of its left operand (the bias
+// gradients), which lies in LDS anyway.
+// A lane's four k's of one fragment come from one 16-byte LDS read where k is contiguous and from four 4-byte reads
+// where it is the row index; both operands use the same k order, so the order inside a slab is free.
+//
+// Tiles: 64x64 (four waves, 2 x 2), and 32x32 with the slab's k's split over the four waves for launches that would
+// leave most of the chip idle; cheapest() says which and why.
+#include "ffn_internal.h"
+
+namespace evomoe {
+
+namespace {
+
+enum { L_NT = 0, L_NN = 1, L_TN = 2 };
+enum { E_HA = 0, E_BIAS = 1, E_ACTGRAD = 2, E_NONE = 3, E_WGRAD = 4 };
+
+struct F32Args {
+    const float* A;  int lda;           // NT/NN: A rows [*,K];  TN: L [P,M]
+    const float* B;  int ldb;           // NT: W_g [N,K];  NN: W_g [K,N];  TN: R [*,N]
+    int64_t b_group_stride;             // NT/NN: elements between two experts' weight matrices
+    const int32_t* rows;                // NT: gather of A rows; TN: gather of R rows (or null)
+    int M, N, K;                        // M: TN only.  K: NT/NN only
+    const float* bias;                  // [E,N] or null
+    const float* Hin;                   // E_ACTGRAD: pre-activations [P,N]
+    float* out1;                        // C (H for E_HA); TN: null = only db is wanted
+    float* out2;                        // E_HA: act(H)
+    float* db;                          // TN: [E,M] column sums of L, or null
+};
+
+struct F32Pair { F32Args p[2]; };       // TN: two problems in one launch; NT/NN use the first
+
+// Where a tile lies: expert, first row (NT/NN) or contraction range (TN).
+// NT/NN row tiles are numbered expert by expert; lane e knows expert e's share, so the search is one scan over the
+// lanes and one ballot, without LDS.
+struct Offsets {
+    int begin, count;                   // of the lane's expert
+    int t_end, t_begin;                 // its row tiles [t_begin, t_end)
+};
+template <int BM> __device__ __forceinline__ Offsets scan_offsets(const int32_t* expert_offsets, int E, int64_t P_cap, int lane) {
+    Offsets o;
+    o.begin = lane < E ? clamp_pairs(expert_offsets[lane], P_cap) : 0;
+    o.count = lane < E ? clamp_pairs(expert_offsets[lane + 1], P_cap) - o.begin : 0;
+    const int nt = (o.count + BM - 1) / BM;
+    int incl = nt;
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) {
+        const int v = __shfl_up(incl, s, 64);
+        if (lane >= s) incl += v;
+    }
+    o.t_end = incl;
+    o.t_begin = incl - nt;
+    return o;
+}
+
+template <int LAYOUT, int EPI, int BM, int BN>
+__global__ __launch_bounds__(256) void grouped_gemm_f32(F32Pair q, int tiles0, int tiles_all,
+                                                        const int32_t* __restrict__ expert_offsets, int E, int64_t P_cap,
+                                                        int act, int accumulate)
+{
+    constexpr bool SPLIT = BM == 32;                    // 32x32: the four waves share one tile, a quarter of the k's each
+    constexpr int BK = SPLIT ? 64 : 32;
+    constexpr int TM = SPLIT ? 1 : BM / 64, TN_ = SPLIT ? 1 : BN / 64;     // 32x32 MFMA tiles per wave
+    constexpr bool A_KC = LAYOUT != L_TN, B_KC = LAYOUT == L_NT;
+    // LDS rows: [row][BK + 4] (16 lanes' 16-byte reads of one k chunk then cover all 64 banks) or [k][cols + 8]
+    // (the two k groups of a 4-byte read lie 32 banks apart)
+    constexpr int A_LD = A_KC ? BK + 4 : BM + 8, B_LD = B_KC ? BK + 4 : BN + 8;
+    constexpr int A_SZ = A_KC ? BM * A_LD : BK * A_LD, B_SZ = B_KC ? BN * B_LD : BK * B_LD;
+    constexpr int A_V = BM * BK / 1024, B_V = BN * BK / 1024;              // 16-byte vectors per thread and slab
+    constexpr int NG = (SPLIT ? BK / 4 : BK) / 8;                          // groups of 8 k's per wave and slab
+    __shared__ float smem[2 * (A_SZ + B_SZ)];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, kg = lane >> 5;
+    const int wm = SPLIT ? 0 : (wave >> 1) * (BM / 2), wn = SPLIT ? 0 : (wave & 1) * (BN / 2);
+    const int wk = SPLIT ? wave * (BK / 4) : 0;
+
+    const Offsets off = scan_offsets<BM>(expert_offsets, E, P_cap, lane);
+    const int row_tiles = __builtin_amdgcn_readlane(off.t_end, 63);
+
+    // Consecutive tiles share operand panels, and blocks are dealt round-robin to the 8 XCDs: each XCD walks one
+    // contiguous eighth of the tiles, so that its L2 sees the panels and no XCD gets a round more than another.
+    const int total = LAYOUT == L_TN ? tiles_all : row_tiles * ((q.p[0].N + BN - 1) / BN);
+    int tile = blockIdx.x, tile_end = total, step = gridDim.x;
+    if ((gridDim.x & 7) == 0) {
+        const int x = blockIdx.x & 7;
+        tile = (int)((int64_t)total * x / 8) + (blockIdx.x >> 3);
+        tile_end = (int)((int64_t)total * (x + 1) / 8);
+        step = gridDim.x >> 3;
+    }
+    for (; tile < tile_end; tile += step) {
+        const bool second = LAYOUT == L_TN && tile >= tiles0;
+        const F32Args& p = q.p[second];
+        const int nct = (p.N + BN - 1) / BN;
+        int g, row0 = 0, rows = 0, m0 = 0, n0, kbeg = 0, kend;
+        if (LAYOUT == L_TN) {
+            const int t = second ? tile - tiles0 : tile, nmt = (p.M + BM - 1) / BM;
+            g = t / (nmt * nct);
+            const int rem = t - g * nmt * nct;
+            m0 = rem / nct * BM;
+            n0 = rem % nct * BN;
+            kbeg = __builtin_amdgcn_readlane(off.begin, g);
+            kend = kbeg + __builtin_amdgcn_readlane(off.count, g);
+        } else {
+            const int rt = tile / nct;
+            n0 = (tile - rt * nct) * BN;
+            g = __ffsll((unsigned long long)__ballot(rt >= off.t_begin && rt < off.t_end)) - 1;
+            const int in = (rt - __builtin_amdgcn_readlane(off.t_begin, g)) * BM;
+            row0 = __builtin_amdgcn_readlane(off.begin, g) + in;
+            rows = min(BM, __builtin_amdgcn_readlane(off.count, g) - in);
+            kend = p.K;
+        }
+        const float* Bg = LAYOUT == L_TN ? p.B : p.B + (int64_t)g * p.b_group_stride;
+        const int nslab = (kend - kbeg + BK - 1) / BK;
+
+        // This thread's share of a slab: vector v of an operand is number tid + 256 v of the slab's 16-byte pieces.
+        // Rows and columns outside the tile are clamped onto valid ones (their products are never stored), k's outside
+        // the contraction range too; A is zero there.  No load sits in a branch, so a slab's loads go out together.
+        const float* arow[A_V];
+        const float* brow[B_V];
+        int bidx[B_V];                                          // TN with gathered R rows: the next slab's row numbers
+        const bool gathered = LAYOUT == L_TN && p.rows;
+#pragma unroll
+        for (int v = 0; v < A_V; ++v) {
+            const int i = tid + 256 * v;
+            if (A_KC) {
+                const int r = row0 + min(i / (BK / 4), rows - 1);
+                arow[v] = p.A + (int64_t)(p.rows ? p.rows[r] : r) * p.lda;
+            } else {
+                arow[v] = p.A + min(m0 + (i % (BM / 4)) * 4, p.M - 4);
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < B_V; ++v) {
+            const int i = tid + 256 * v;
+            if (B_KC) brow[v] = Bg + (int64_t)min(n0 + i / (BK / 4), p.N - 1) * p.ldb;
+            else brow[v] = Bg + min(n0 + (i % (BN / 4)) * 4, p.N - 4);
+        }
+        f32x4 ra[A_V], rb[B_V];
+        auto fetch_rows = [&](int k0) {
+#pragma unroll
+            for (int v = 0; v < B_V; ++v) bidx[v] = p.rows[min(k0 + (tid + 256 * v) / (BN / 4), kend - 1)];
+        };
+        auto fetch = [&](int k0) {
+#pragma unroll
+            for (int v = 0; v < A_V; ++v) {
+                const int i = tid + 256 * v;
+                if (A_KC) ra[v] = *reinterpret_cast<const f32x4*>(arow[v] + min(k0 + (i % (BK / 4)) * 4, kend - 4));
+                else ra[v] = *reinterpret_cast<const f32x4*>(arow[v] + (int64_t)min(k0 + i / (BM / 4), kend - 1) * p.lda);
+            }
+#pragma unroll
+            for (int v = 0; v < B_V; ++v) {
+                const int i = tid + 256 * v;
+                if (B_KC) {
+                    rb[v] = *reinterpret_cast<const f32x4*>(brow[v] + min(k0 + (i % (BK / 4)) * 4, kend - 4));
+                } else {
+                    const int k = gathered ? bidx[v] : min(k0 + i / (BN / 4), kend - 1);
+                    rb[v] = *reinterpret_cast<const f32x4*>(brow[v] + (int64_t)k * p.ldb);
+                }
+            }
+            if (gathered && k0 + BK < kend) fetch_rows(k0 + BK);
+            if (k0 + BK > kend) {                               // block-uniform: the last, partial slab
+#pragma unroll
+                for (int v = 0; v < A_V; ++v) {
+                    const int i = tid + 256 * v;
+                    if (k0 + (A_KC ? (i % (BK / 4)) * 4 : i / (BM / 4)) >= kend) ra[v] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
+        };
+        auto place = [&](float* sa, float* sb) {
+#pragma unroll
+            for (int v = 0; v < A_V; ++v) {
+                const int i = tid + 256 * v;
+                *reinterpret_cast<f32x4*>(A_KC ? sa + i / (BK / 4) * A_LD + (i % (BK / 4)) * 4
+                                               : sa + i / (BM / 4) * A_LD + (i % (BM / 4)) * 4) = ra[v];
+            }
+#pragma unroll
+            for (int v = 0; v < B_V; ++v) {
+                const int i = tid + 256 * v;
+                *reinterpret_cast<f32x4*>(B_KC ? sb + i / (BK / 4) * B_LD + (i % (BK / 4)) * 4
+                                               : sb + i / (BN / 4) * B_LD + (i % (BN / 4)) * 4) = rb[v];
+            }
+        };
+        f32x16 acc[TM][TN_];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN_; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+        // TN, first column tile: the column sums of L, which sits in LDS anyway (256 / BM threads per column)
+        const bool sums = LAYOUT == L_TN && p.db && n0 == 0;
+        constexpr int KP = 256 / BM;
+        float colsum = 0.f;
+
+        if (nslab > 0) {
+            if (gathered) fetch_rows(kbeg);
+            fetch(kbeg);
+            place(smem, smem + A_SZ);
+        }
+        __syncthreads();
+        for (int s = 0; s < nslab; ++s) {
+            const float* sa = smem + (s & 1) * (A_SZ + B_SZ);
+            const float* sb = sa + A_SZ;
+            if (s + 1 < nslab) fetch(kbeg + (s + 1) * BK);
+#pragma unroll
+            for (int gk = 0; gk < NG; ++gk) {
+                const int k = wk + gk * 8 + kg * 4;
+                f32x4 fa[TM], fb[TN_];
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const int m = wm + i * 32 + l32;
+                    if (A_KC) fa[i] = *reinterpret_cast<const f32x4*>(sa + m * A_LD + k);
+                    else fa[i] = f32x4{sa[k * A_LD + m], sa[(k + 1) * A_LD + m], sa[(k + 2) * A_LD + m], sa[(k + 3) * A_LD + m]};
+                }
+#pragma unroll
+                for (int j = 0; j < TN_; ++j) {
+                    const int n = wn + j * 32 + l32;
+                    if (B_KC) fb[j] = *reinterpret_cast<const f32x4*>(sb + n * B_LD + k);
+                    else fb[j] = f32x4{sb[k * B_LD + n], sb[(k + 1) * B_LD + n], sb[(k + 2) * B_LD + n], sb[(k + 3) * B_LD + n]};
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN_; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][u], fb[j][u], acc[i][j], 0, 0, 0);
+            }
+            if (sums) {
+#pragma unroll
+                for (int k = 0; k < BK / KP; ++k) colsum += sa[(tid / BM * (BK / KP) + k) * A_LD + tid % BM];
+            }
+            if (s + 1 < nslab) {
+                float* na = smem + ((s + 1) & 1) * (A_SZ + B_SZ);
+                place(na, na + A_SZ);
+            }
+            __syncthreads();
+        }
+
+        // ---------------- epilogue ----------------
+        // What the epilogue reads (bias, H, the old gradient) is loaded, at clamped addresses, before its first store.
+        const int lim_r = LAYOUT == L_TN ? p.M - m0 : rows;             // rows of the tile that exist
+        const int64_t origin = LAYOUT == L_TN ? ((int64_t)g * p.M + m0) * p.N : (int64_t)row0 * p.N;
+        const float* reads = EPI == E_ACTGRAD ? p.Hin + origin : EPI == E_WGRAD && accumulate ? p.out1 + origin : nullptr;
+        auto offset_of = [&](int tr, int n) { return (uint32_t)(min(tr, lim_r - 1) * p.N + min(n, p.N - 1)); };
+        auto bias_of = [&](int n) {
+            return (EPI == E_HA || EPI == E_BIAS) && p.bias ? p.bias[(int64_t)g * p.N + min(n, p.N - 1)] : 0.f;
+        };
+        auto finish = [&](int tr, int n, float v, float bias, float old) {
+            if (EPI == E_HA || EPI == E_BIAS) v += bias;
+            if (EPI == E_ACTGRAD) v *= act_grad(old, act);
+            if (EPI == E_WGRAD && accumulate) v += old;
+            const float a = EPI == E_HA ? act_fwd(v, act) : 0.f;
+            const uint32_t o = offset_of(tr, n);
+            if (tr < lim_r && n < p.N && (EPI != E_WGRAD || p.out1)) {
+                p.out1[origin + o] = v;
+                if (EPI == E_HA) p.out2[origin + o] = a;
+            }
+        };
+        if (SPLIT) {
+            // the four waves' partial tiles, added in wave order
+            constexpr int LD = 36;
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                smem[(wave * 32 + 8 * (r >> 2) + 4 * kg + (r & 3)) * LD + l32] = acc[0][0][r];
+            const float bias = bias_of(n0 + l32);
+            float old[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) old[u] = reads ? reads[offset_of((tid >> 5) + 8 * u, n0 + l32)] : 0.f;
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int tr = (tid >> 5) + 8 * u;
+                float v = 0.f;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) v += smem[(w * 32 + tr) * LD + l32];
+                finish(tr, n0 + l32, v, bias, old[u]);
+            }
+            __syncthreads();
+        } else {
+            float bias[TN_];
+#pragma unroll
+            for (int j = 0; j < TN_; ++j) bias[j] = bias_of(n0 + wn + j * 32 + l32);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN_; ++j) {
+                    const int n = n0 + wn + j * 32 + l32;
+                    float old[16];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        old[r] = reads ? reads[offset_of(wm + i * 32 + 8 * (r >> 2) + 4 * kg + (r & 3), n)] : 0.f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        finish(wm + i * 32 + 8 * (r >> 2) + 4 * kg + (r & 3), n, acc[i][j][r], bias[j], old[r]);
+                }
+        }
+        if (sums) {                                              // block-uniform
+            smem[tid] = colsum;
+            __syncthreads();
+            if (tid < BM && m0 + tid < p.M) {
+                float v = 0.f;
+#pragma unroll
+                for (int q = 0; q < KP; ++q) v += smem[q * BM + tid];
+                float* o = p.db + (int64_t)g * p.M + m0 + tid;
+                *o = accumulate ? *o + v : v;
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// Which tile.  A launch takes about (tiles each CU gets) x (work of a tile); 32x32 tiles pad and quantise less but take
+// about 1.25 times as long per output.  Measured (us, 64x64 / 32x32) at d = 256, E = 8, F = 1024: 5626 pairs GEMM1 44 / 50,
+// GEMM2 46 / 43, dXp 51 / 43, both dW 77 / 95; 1419 pairs GEMM2 30 / 18, dW 27 / 35; d = 512, E = 16, F = 2048, 11160 pairs
+// GEMM1 242 / 298, dW 519 / 667; d = 64, E = 4, F = 256, 533 pairs GEMM2 13 / 8.  128x128 tiles (GEMM1 63 and GEMM2 84 us
+// in the first of these, 286 and 309 in the third) were slower than 64x64 everywhere and are not kept.
+enum class Tile { T64, T32 };
+int64_t tiles_of(int64_t row_tiles, int n, int b) { return row_tiles * ((n + b - 1) / b); }
+Tile cheapest(const Ctx& c, int64_t t64, int64_t t32) {
+    auto rounds = [&](int64_t tiles) { return (double)((tiles + c.num_cu - 1) / c.num_cu); };
+    return rounds(t32) * (32 * 32 * 1.25) < rounds(t64) * (64 * 64) ? Tile::T32 : Tile::T64;
+}
+
+template <int LAYOUT, int EPI, int B>
+hipError_t launch(const Ctx& c, const evomoe_shape& s, const F32Args& a, int64_t t0, const F32Args& b, int64_t t1,
+                  const int32_t* expert_offsets, int accumulate) {
+    const int64_t cap = (int64_t)c.num_cu * 4, want = (t0 + t1 + 7) / 8 * 8;
+    hipLaunchKernelGGL((grouped_gemm_f32<LAYOUT, EPI, B, B>), dim3((unsigned)(want < cap ? want : cap)), dim3(256), 0,
+                       c.stream, F32Pair{{a, b}}, (int)t0, (int)(t0 + t1), expert_offsets, s.E, s.P_cap, s.act, accumulate);
+    return hipGetLastError();
+}
+
+// NT / NN: one problem over the row tiles of all experts
+template <int LAYOUT, int EPI>
+hipError_t launch_rows(const Ctx& c, const evomoe_shape& s, const F32Args& a, const int32_t* expert_offsets) {
+    const int64_t P = c.pair_hint > 0 && c.pair_hint < s.P_cap ? c.pair_hint : s.P_cap;
+    auto expected = [&](int b) { return tiles_of((P + b - 1) / b + s.E / 2, a.N, b); };
+    auto worst = [&](int b) { return tiles_of((s.P_cap + b - 1) / b + s.E, a.N, b); };
+    if (cheapest(c, expected(64), expected(32)) == Tile::T64)
+        return launch<LAYOUT, EPI, 64>(c, s, a, worst(64), a, 0, expert_offsets, 0);
+    return launch<LAYOUT, EPI, 32>(c, s, a, worst(32), a, 0, expert_offsets, 0);
+}
+
+}  // namespace
+
+hipError_t f32_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token,
+                       const int32_t* expert_offsets, const void* W1, const float* b1, const void* W2,
+                       const float* b2, void* H, void* A, void* O) {
+    hipError_t err;
+    {   // H = X W1^T + b1, A = act(H)
+        ProfScope ps(c, EVOMOE_K_FFN_GEMM1);
+        F32Args a{};
+        a.A = (const float*)x; a.lda = s.d; a.rows = pair_token;
+        a.B = (const float*)W1; a.ldb = s.d; a.b_group_stride = (int64_t)s.F * s.d;
+        a.N = s.F; a.K = s.d; a.bias = b1; a.out1 = (float*)H; a.out2 = (float*)A;
+        err = launch_rows<L_NT, E_HA>(c, s, a, expert_offsets);
+    }
+    if (err != hipSuccess || !O) return err;      // O == nullptr: recomputation of H and A only
+    // O = A W2^T + b2
+    ProfScope ps(c, EVOMOE_K_FFN_GEMM2);
+    F32Args a{};
+    a.A = (const float*)A; a.lda = s.F;
+    a.B = (const float*)W2; a.ldb = s.F; a.b_group_stride = (int64_t)s.d * s.F;
+    a.N = s.d; a.K = s.F; a.bias = b2; a.out1 = (float*)O;
+    return launch_rows<L_NT, E_BIAS>(c, s, a, expert_offsets);
+}
+
+hipError_t f32_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, const void* H, const void* A,
+                       const void* x, const int32_t* pair_token, const int32_t* expert_offsets, const void* W1,
+                       const void* W2, void* dW1, float* db1, void* dW2, float* db2, void* dXp, int accumulate,
+                       void* dH) {
+    hipError_t err;
+    {   // dH = (dO W2) * act'(H)
+        ProfScope ps(c, EVOMOE_K_FFN_BWD_DH);
+        F32Args a{};
+        a.A = (const float*)dO; a.lda = s.d; a.B = (const float*)W2; a.ldb = s.F;
+        a.b_group_stride = (int64_t)s.d * s.F; a.N = s.F; a.K = s.d; a.Hin = (const float*)H; a.out1 = (float*)dH;
+        err = launch_rows<L_NN, E_ACTGRAD>(c, s, a, expert_offsets);
+        if (err != hipSuccess) return err;
+    }
+    {   // dXp = dH W1
+        ProfScope ps(c, EVOMOE_K_FFN_BWD_DX);
+        F32Args a{};
+        a.A = (const float*)dH; a.lda = s.F; a.B = (const float*)W1; a.ldb = s.d;
+        a.b_group_stride = (int64_t)s.F * s.d; a.N = s.d; a.K = s.F; a.out1 = (float*)dXp;
+        err = launch_rows<L_NN, E_NONE>(c, s, a, expert_offsets);
+        if (err != hipSuccess) return err;
+    }
+    // dW2_g = dO_g^T A_g [d,F] (and db2 = column sums of dO), dW1_g = dH_g^T X_g [F,d] (and db1 = column sums of dH):
+    // one launch over both problems' tiles.  A bias gradient alone takes the same launch with one column tile, whose
+    // products are not stored; the tile size does not depend on what is asked for, so the sums' order does not either.
+    F32Args w[2]{};
+    int n = 0;
+    auto add = [&](const void* L, int M, const void* R, int N, const int32_t* rows, void* dW, float* db) {
+        if (!dW && !db) return;
+        F32Args& a = w[n++];
+        a.A = (const float*)L; a.lda = M; a.M = M; a.B = (const float*)R; a.ldb = N; a.N = dW ? N : 4; a.rows = rows;
+        a.out1 = (float*)dW; a.db = db;
+    };
+    add(dO, s.d, A, s.F, nullptr, dW2, db2);
+    add(dH, s.F, x, s.d, pair_token, dW1, db1);
+    if (n == 0) return hipSuccess;
+    ProfScope ps(c, dW2 ? EVOMOE_K_FFN_BWD_DW2 : dW1 ? EVOMOE_K_FFN_BWD_DW1 : EVOMOE_K_FFN_BWD_DB);
+    auto tiles = [&](const F32Args& a, int b) { return (int64_t)s.E * ((a.M + b - 1) / b) * ((a.N + b - 1) / b); };
+    auto both = [&](int b) { return 2 * (int64_t)s.E * ((s.d + b - 1) / b) * ((s.F + b - 1) / b); };
+    if (cheapest(c, both(64), both(32)) == Tile::T64)
+        return launch<L_TN, E_WGRAD, 64>(c, s, w[0], tiles(w[0], 64), w[1], n > 1 ? tiles(w[1], 64) : 0, expert_offsets,
+                                         accumulate);
+    return launch<L_TN, E_WGRAD, 32>(c, s, w[0], tiles(w[0], 32), w[1], n > 1 ? tiles(w[1], 32) : 0, expert_offsets,
+                                     accumulate);
+}
+
+}  // namespace evomoe

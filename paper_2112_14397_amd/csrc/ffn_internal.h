@@ -4,22 +4,17 @@
 
 namespace evomoe {
 
-template <typename TX>
-hipError_t simple_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token,
-                          const int32_t* expert_offsets, const void* W1, const float* b1,
-                          const void* W2, const float* b2, void* H, void* A, void* O);
-template <typename TX>
-hipError_t simple_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, const void* H,
-                          const void* A, const void* x, const int32_t* pair_token,
-                          const int32_t* expert_offsets, const void* W1, const void* W2, void* dW1,
-                          float* db1, void* dW2, float* db2, void* dXp, int accumulate, void* dH);
-template <typename TX>
-hipError_t launch_colsum(const Ctx& c, const evomoe_shape& s, const void* Mx, int N,
-                         const int32_t* expert_offsets, float* db, int accumulate, float* scratch);
+// float32 matrix-core path (ffn_f32.hip)
+hipError_t f32_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token,
+                       const int32_t* expert_offsets, const void* W1, const float* b1, const void* W2,
+                       const float* b2, void* H, void* A, void* O);
+hipError_t f32_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, const void* H, const void* A,
+                       const void* x, const int32_t* pair_token, const int32_t* expert_offsets, const void* W1,
+                       const void* W2, void* dW1, float* db1, void* dW2, float* db2, void* dXp, int accumulate,
+                       void* dH);
 // the streaming column sums split every expert's rows into this many ranges: part[split][g][n], added in order
 constexpr int kColsumSplit = 32;
-// first pass only: leaves part[kColsumSplit][E][N] in scratch
-template <typename TX>
+// leaves part[kColsumSplit][E][N] of the bf16 matrix Mx [P,N] in scratch
 hipError_t launch_colsum_part(const Ctx& c, const evomoe_shape& s, const void* Mx, int N,
                               const int32_t* expert_offsets, float* scratch);
 // [partials of the streaming column sums][bf16 layer: per-tile column sums of dH]; a multiple of 256

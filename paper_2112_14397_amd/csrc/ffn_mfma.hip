@@ -869,7 +869,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
     }
     if (err != hipSuccess) return err;
     ProfScope ps(c, EVOMOE_K_FFN_BWD_DB);
-    if (db2) err = launch_colsum_part<bf16_t>(c, s, dO, s.d, expert_offsets, scratch);
+    if (db2) err = launch_colsum_part(c, s, dO, s.d, expert_offsets, scratch);
     if (err != hipSuccess) return err;
     if (db1 || db2) {
         // one launch finishes both: E * gx1 blocks for db1 (if wanted), then gx2 blocks for db2 (if wanted)
