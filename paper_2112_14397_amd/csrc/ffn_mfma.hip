@@ -41,7 +41,7 @@ struct GemmArgs {
     const float* row_scale;             // E_ACTGRAD: per-row factor applied in f32 before act' (or null)
     bf16_t* out1;                       // C (H for E_HA)
     bf16_t* out2;                       // E_HA: A = act(H)
-    float* colpart;                     // E_ACTGRAD: per-tile column sums of C, [row tile][waves/2][N] (or null)
+    float* colpart;                     // E_ACTGRAD: per-tile column sums of C, [row tile][BM / 64][N] (or null)
     int act, accumulate;
     int col_group;                      // NT/NN: column tiles per group of the tile order (1 .. all of them)
 };
@@ -69,6 +69,10 @@ template <int LAYOUT, int BM, int BN, int BK, int NSTAGE, int NW = 4> struct Geo
     static constexpr int EPI_BYTES = NW * EPI_ROWS * EPI_LD * 4;
     static constexpr int MAIN = (NSTAGE * STAGE > EPI_BYTES ? NSTAGE * STAGE : EPI_BYTES);
     static constexpr int SMEM = MAIN;
+    // block key of row k of a k-strided tile with C columns (64 columns are only four blocks: two rows share a bank window)
+    template <int C> __device__ static __forceinline__ int ks_key(int k) { return C >= 128 ? 2 * (k & 3) : (k & 2); }
+    // rows of the act'(H) epilogue's table of column sums per row tile: one for every 64 rows
+    static constexpr int PARTS = BM / 64;
 };
 
 // Phi(h), the standard normal CDF, as 0.5 + hc*Q(hc^2) with hc = h clamped to |h| <= 4.2: degree-8 minimax
@@ -258,7 +262,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                 fa_off[i] = (wm * WM + i * 32 + l32) * (BK * 2);     // row base; the swizzled chunk is added per k-step
             } else {
                 const int lb = (wm * WM + i * 32 + ((lane >> 4) & 1) * 16) >> 4;       // logical 32 B block
-                fa_off[i] = (kg * 8 + (s16 >> 2)) * (BM * 2) + ((lb ^ (2 * (s16 >> 2))) << 5) + ((s16 & 3) << 3);
+                fa_off[i] = (kg * 8 + (s16 >> 2)) * (BM * 2) + ((lb ^ G::template ks_key<BM>(s16 >> 2)) << 5) + ((s16 & 3) << 3);
             }
         }
     #pragma unroll
@@ -267,7 +271,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                 fb_off[j] = (wn * WN + j * 32 + l32) * (BK * 2);
             } else {
                 const int lb = (wn * WN + j * 32 + ((lane >> 4) & 1) * 16) >> 4;
-                fb_off[j] = (kg * 8 + (s16 >> 2)) * (BN * 2) + ((lb ^ (2 * (s16 >> 2))) << 5) + ((s16 & 3) << 3);
+                fb_off[j] = (kg * 8 + (s16 >> 2)) * (BN * 2) + ((lb ^ G::template ks_key<BN>(s16 >> 2)) << 5) + ((s16 & 3) << 3);
             }
         }
         // swizzle key of this lane's fragment rows (tile rows start at multiples of 32)
@@ -281,7 +285,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         const int kc_key = (BK == 64) ? ((4 * (wave & 1) + (kc_row >> 1)) & 7) : ((kc_row >> 2) & 3);
         const int kc_chunk = (lane % KC_CH) ^ kc_key;                           // logical 16 B chunk (8 k's)
         const int ksA_row = lane / A_CPR, ksB_row = lane / B_CPR;
-        auto ks_col = [&](int pc, int krow) { return ((((pc >> 1) ^ (2 * (krow & 3))) << 1) | (pc & 1)) * 8; };
+        auto ks_col = [&](int pc, int key) { return ((((pc >> 1) ^ key) << 1) | (pc & 1)) * 8; };
 
         // ---------------- global addresses: one scalar base per operand + 32-bit per-lane byte offsets ----
         // Rows / columns outside the tile are clamped onto valid ones (their products are never stored);
@@ -303,7 +307,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
             }
         } else {
             a_base = reinterpret_cast<const unsigned char*>(p.A) + (int64_t)kbeg * p.lda * 2;
-            a_col = 2 * min(m0 + ks_col(lane % A_CPR, wave * A_RPI + ksA_row), p.M - 8);
+            a_col = 2 * min(m0 + ks_col(lane % A_CPR, G::template ks_key<BM>(wave * A_RPI + ksA_row)), p.M - 8);
         }
         if (G::B_KC) {
             b_base = reinterpret_cast<const unsigned char*>(Bg);
@@ -314,7 +318,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
             }
         } else {
             b_base = reinterpret_cast<const unsigned char*>(Bg) + (int64_t)kbeg * p.ldb * 2;
-            b_col = 2 * min(n0 + ks_col(lane % B_CPR, wave * B_RPI + ksB_row), p.N - 8);
+            b_col = 2 * min(n0 + ks_col(lane % B_CPR, G::template ks_key<BN>(wave * B_RPI + ksB_row)), p.N - 8);
         }
         const int klen = kend - kbeg;
         const int kc_lim = 2 * (kend - 8 - kc_chunk * 8);        // k-contiguous: last in-range chunk start (bytes)
@@ -610,9 +614,22 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                 for (int o = CPW; o < 64; o <<= 1)
 #pragma unroll
                     for (int q = 0; q < 8; ++q) cs[q] += __shfl_xor(cs[q], o, 64);
-                if (lane < CPW && col < p.N) {
+                if (WM == 32) {         // two waves share a table row: the upper one hands its sums over through LDS
+                    float* pass_on = reinterpret_cast<float*>(smem) + ((wave >> 2) * 2 + wn) * WN;
+                    block_sync_lds();
+                    if ((wm & 1) && lane < CPW) {
+                        *reinterpret_cast<f32x4*>(pass_on + lc) = f32x4{cs[0], cs[1], cs[2], cs[3]};
+                        *reinterpret_cast<f32x4*>(pass_on + lc + 4) = f32x4{cs[4], cs[5], cs[6], cs[7]};
+                    }
+                    block_sync_lds();
+                    if (!(wm & 1) && lane < CPW) {
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) cs[q] += pass_on[lc + q];
+                    }
+                }
+                if (lane < CPW && col < p.N && (WM >= 64 || !(wm & 1))) {
                     const int rt = tstart[g] + (row0 - offs[g]) / BM;
-                    float* dst = p.colpart + ((int64_t)rt * (NW / 2) + wm) * p.N + col_c;
+                    float* dst = p.colpart + ((int64_t)rt * G::PARTS + (WM >= 64 ? wm : wm >> 1)) * p.N + col_c;
                     *reinterpret_cast<f32x4*>(dst) = f32x4{cs[0], cs[1], cs[2], cs[3]};
                     *reinterpret_cast<f32x4*>(dst + 4) = f32x4{cs[4], cs[5], cs[6], cs[7]};
                 }
@@ -673,11 +690,22 @@ __global__ __launch_bounds__(256) void bias_grad_final_kernel(
 // faster than BIG4 for GEMM1 and 1 % for the weight gradients, 2 % slower for GEMM2, the same for dXp.
 // DUO: two blocks per compute unit (one's epilogue and stalls hide under the other's MFMAs).
 // LAT: for launches with no more tiles than compute units and a long contraction: what counts then is how fast
-// one block walks its K loop, and 64-wide slabs halve the number of load/barrier rounds of that walk.
+// one block walks its K loop, and 64-wide slabs halve the number of load/barrier rounds of that walk.  LAT8: worked by
+// eight waves, 2-7 % faster for dXp, the same for GEMM2.
+// The smaller tiles are for launches whose 256-column tiles would leave compute units idle or be mostly padding
+// (an expert with fewer than 128 rows): there the launch is as fast as its weights arrive, which takes blocks on every
+// unit, each with several slabs of 64 k in flight.  MID: 128x128, two blocks per unit or (MID64) one with four 64-wide
+// stages.  SML: 64x128, two per unit.  TNY: 64x64, two per unit with four stages or (TNY3) three per unit with three.
 struct CfgDuo { static constexpr int BM = 128, BN = 256, BK = 32, NSTAGE = 3, WPE = 2, NW = 4; };
 struct CfgBig4 { static constexpr int BM = 256, BN = 256, BK = 32, NSTAGE = 4, WPE = 1, NW = 4; };
 struct CfgOct { static constexpr int BM = 256, BN = 256, BK = 32, NSTAGE = 4, WPE = 1, NW = 8; };
 struct CfgLat { static constexpr int BM = 128, BN = 256, BK = 64, NSTAGE = 3, WPE = 1, NW = 4; };
+struct CfgLat8 { static constexpr int BM = 128, BN = 256, BK = 64, NSTAGE = 3, WPE = 1, NW = 8; };
+struct CfgMid { static constexpr int BM = 128, BN = 128, BK = 32, NSTAGE = 4, WPE = 2, NW = 4; };
+struct CfgMid64 { static constexpr int BM = 128, BN = 128, BK = 64, NSTAGE = 4, WPE = 1, NW = 4; };
+struct CfgSml { static constexpr int BM = 64, BN = 128, BK = 64, NSTAGE = 3, WPE = 2, NW = 4; };
+struct CfgTny { static constexpr int BM = 64, BN = 64, BK = 64, NSTAGE = 4, WPE = 2, NW = 4; };
+struct CfgTny3 { static constexpr int BM = 64, BN = 64, BK = 64, NSTAGE = 3, WPE = 3, NW = 4; };
 
 template <int LAYOUT, int EPI, class Cfg>
 hipError_t launch_gemm(const Ctx& c, const GemmArgs& a0, int64_t tiles0, const GemmArgs& a1, int64_t tiles1) {
@@ -709,14 +737,14 @@ template <class Cfg> int64_t mtiles(int m) { return (m + Cfg::BM - 1) / Cfg::BM;
 inline int64_t expected_pairs(const Ctx& c, const evomoe_shape& s) {
     return c.pair_hint > 0 && c.pair_hint < s.P_cap ? c.pair_hint : s.P_cap;
 }
+// About half a row tile per expert is padding; with fewer rows than that, every expert that has a row has a tile.
 template <class Cfg> int64_t expected_row_tiles(const Ctx& c, const evomoe_shape& s) {
-    return (expected_pairs(c, s) + Cfg::BM - 1) / Cfg::BM + s.E / 2;
+    const int64_t P = expected_pairs(c, s), spread = (P + Cfg::BM - 1) / Cfg::BM + s.E / 2, used = P < s.E ? P : s.E;
+    return spread > used ? spread : used;
 }
 
-using CfgGemm1 = CfgOct;
-using CfgGemm2 = CfgBig4;
+// the act'(H) launch's table of column sums is sized for these tiles, and no other shape's needs more
 using CfgDh = CfgDuo;
-using CfgDx = CfgBig4;
 using CfgDw = CfgOct;
 
 // Column tiles per group of the NT/NN tile order: as many weight panels (BN x K) as stay in one XCD's 4 MB L2 next to
@@ -730,28 +758,47 @@ template <class Cfg> int col_group_for(int n, int k) {
 }
 
 // Choice of tile shape per launch.  A persistent grid works through its tiles in rounds (one tile per resident
-// block), so a launch takes about rounds x (time of one tile): the finer 128-row tiles lose a little per flop but
-// waste less in the last, partly filled round and in the padding of each expert's last row tile.  The relative
-// tile times below were measured on the GPT-shaped layer (d = 768, F = 3072) at pair counts from 8 k to 58 k: a
-// 128x256x64 tile with a CU to itself takes 0.53 (NT) / 0.63 (NN) of a 256x256x32 tile; two co-resident 128x256x32
-// blocks take 1.06-1.2 times as long per round as one eight-wave 256x256 block when the contraction is short
-// (priced at 1.15; 1.2x and more when it is long, which never pays).  The weight-gradient launch and the act'(H)
-// launch keep one shape each: 256x256 tiles were 8-29 % faster than either 128-row shape for the former, and for
-// the latter two co-resident blocks are almost twice as fast as a four-wave 256x256 block and 2 % faster than an
-// eight-wave one.
-template <class Cfg> double launch_cost(const Ctx& c, const evomoe_shape& s, int n, double tile_time) {
-    const int64_t tiles = expected_row_tiles<Cfg>(c, s) * ctiles<Cfg>(n);
-    const int64_t slots = (int64_t)c.num_cu * Cfg::WPE;
-    return (double)((tiles + slots - 1) / slots) * tile_time;
+// block), so a launch takes about  fixed + rounds x (per_round + per_k x K / 1024)  microseconds: the finer tiles lose
+// a little per flop but leave less of the last, partly filled round idle and waste less in the padding of each
+// expert's last row tile.  Where several blocks share a compute unit and the last round does not give every unit all
+// of them, that round is cheaper: 0.55 of a round at least, rising with the blocks per unit that it needs.  The numbers
+// are fits to launches over d x F from 136 x 264 to 1024 x 4096, 1 to 64 experts and 1 to 90 000 pairs; the shape the
+// model picks is within 1-3.5 % of the best one measured on average (no launch of the sweep above 21 %), where
+// 256-column tiles alone were 40-190 % slower below about 200 rows per expert.  d = 768, F = 3072, 16 experts, us:
+//            pairs     48     512    2048   8192   58330
+//   GEMM1  256-wide    30     30     32     69     386          GEMM2  256-wide   37     40     45     53     269
+//          picked      18     18     30     69     386                 picked     18     20     31     53     269
+// The weight-gradient launch keeps one shape: 256x256 tiles were 8-29 % faster than either 128-row shape.
+struct RoundTime { double fixed, per_round, per_k; };
+template <class Cfg> double launch_cost(const Ctx& c, const evomoe_shape& s, const GemmArgs& a, const RoundTime& t) {
+    const int64_t tiles = expected_row_tiles<Cfg>(c, s) * ctiles<Cfg>(a.N);
+    const int64_t slots = (int64_t)c.num_cu * Cfg::WPE, last = tiles % slots;
+    double rounds = (double)(tiles / slots);
+    if (last) rounds += 0.55 + 0.45 * (double)((last + c.num_cu - 1) / c.num_cu) / Cfg::WPE;
+    return t.fixed + rounds * (t.per_round + t.per_k * a.K / 1024.0);
 }
-enum class Tile { Big, Duo, Lat };
-// short contraction (GEMM1): 256-row tiles or two co-resident 128-row blocks
-inline Tile pick_short_k(const Ctx& c, const evomoe_shape& s, int n) {
-    return launch_cost<CfgDuo>(c, s, n, 1.15) < launch_cost<CfgGemm1>(c, s, n, 1.0) ? Tile::Duo : Tile::Big;
+// Launches the cheapest of the shapes Cfgs (t: their times, in the same order); its row tile goes to *bm.
+template <int LAYOUT, int EPI, class Cfg>
+hipError_t launch_rows(const Ctx& c, const evomoe_shape& s, GemmArgs& a, int* bm) {
+    if (bm) *bm = Cfg::BM;
+    a.col_group = col_group_for<Cfg>(a.N, a.K);
+    return launch_gemm<LAYOUT, EPI, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(a.N));
 }
-// long contraction (GEMM2, dXp): 256-row tiles or 128-row tiles with 64-wide slabs, one block per CU
-inline Tile pick_long_k(const Ctx& c, const evomoe_shape& s, int n, double lat_time) {
-    return launch_cost<CfgLat>(c, s, n, lat_time) < launch_cost<CfgBig4>(c, s, n, 1.0) ? Tile::Lat : Tile::Big;
+// Launches the cheapest of the shapes Cfgs (t: their times, in the same order); its row tile goes to *bm.
+template <int LAYOUT, int EPI, class... Cfgs>
+hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const RoundTime (&t)[sizeof...(Cfgs)],
+                       int* bm = nullptr) {
+    int n = 0, best = 0;
+    double best_cost = 0.0;
+    auto consider = [&](double cost) {
+        if (n == 0 || cost < best_cost) { best_cost = cost; best = n; }
+        ++n;
+    };
+    (consider(launch_cost<Cfgs>(c, s, a, t[n])), ...);
+    hipError_t err = hipErrorInvalidValue;
+    n = 0;
+    (void)((n++ == best ? (err = launch_rows<LAYOUT, EPI, Cfgs>(c, s, a, bm), true) : false) || ...);
+    return err;
 }
 
 }  // namespace
@@ -769,29 +816,21 @@ hipError_t mfma_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, cons
     a.expert_offsets = expert_offsets; a.E = s.E; a.P_cap = s.P_cap; a.act = s.act;
     hipError_t err;
     {   // H = X W1^T + b1, A = act(H)
-        using Cfg = CfgGemm1;
         ProfScope ps(c, EVOMOE_K_FFN_GEMM1);
         a.A = (const bf16_t*)x; a.lda = s.d; a.a_rows = pair_token;
         a.B = (const bf16_t*)W1; a.ldb = s.d; a.b_group_stride = (int64_t)s.F * s.d;
         a.N = s.F; a.K = s.d; a.bias = b1; a.out1 = (bf16_t*)H; a.out2 = (bf16_t*)A;
-        a.col_group = col_group_for<Cfg>(s.F, s.d);
-        if (pick_short_k(c, s, s.F) == Tile::Duo)
-            err = launch_gemm<L_NT, E_HA, CfgDuo>(c, a, row_tiles<CfgDuo>(s) * ctiles<CfgDuo>(s.F));
-        else
-            err = launch_gemm<L_NT, E_HA, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(s.F));
+        static const RoundTime t[] = {{0, 11.5, 23.2}, {0, 11.6, 27.9}, {0, 8.8, 14.2}, {2.0, 4.4, 10.3}, {2.6, 3.2, 9.5}};
+        err = launch_best<L_NT, E_HA, CfgOct, CfgDuo, CfgMid, CfgSml, CfgTny3>(c, s, a, t);
         if (err != hipSuccess || !O) return err;      // O == nullptr: recomputation of H and A only
     }
     {   // O = A W2^T + b2
-        using Cfg = CfgGemm2;
         ProfScope ps(c, EVOMOE_K_FFN_GEMM2);
         a.A = (const bf16_t*)A; a.lda = s.F; a.a_rows = nullptr;
         a.B = (const bf16_t*)W2; a.ldb = s.F; a.b_group_stride = (int64_t)s.d * s.F;
         a.N = s.d; a.K = s.F; a.bias = b2; a.out1 = (bf16_t*)O; a.out2 = nullptr;
-        a.col_group = col_group_for<Cfg>(s.d, s.F);
-        if (pick_long_k(c, s, s.d, 0.53) == Tile::Lat)
-            err = launch_gemm<L_NT, E_BIAS, CfgLat>(c, a, row_tiles<CfgLat>(s) * ctiles<CfgLat>(s.d));
-        else
-            err = launch_gemm<L_NT, E_BIAS, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(s.d));
+        static const RoundTime t[] = {{0, 8.7, 20.3}, {0, 6.6, 12.5}, {0, 5.5, 7.9}, {0, 5.3, 10.6}, {0, 5.8, 6.1}};
+        err = launch_best<L_NT, E_BIAS, CfgBig4, CfgLat, CfgMid64, CfgSml, CfgTny>(c, s, a, t);
     }
     return err;
 }
@@ -803,6 +842,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
     GemmArgs a{};
     a.expert_offsets = expert_offsets; a.E = s.E; a.P_cap = s.P_cap; a.act = s.act;
     hipError_t err;
+    int dh_bm = CfgDh::BM;                // row tile of the dH launch (its table of column sums has BM / 64 rows for each)
     // workspace behind dH: [column-sum partials of the streaming kernel][per-tile column sums of dH][gathered x]
     float* scratch = reinterpret_cast<float*>(static_cast<char*>(dH) + dh_bytes(s));
     float* colpart = reinterpret_cast<float*>(static_cast<char*>(dH) + dh_bytes(s) + colsum_scratch_bytes(s) -
@@ -811,7 +851,6 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         // With dy and the pair weights at hand, dO W2 is taken as G_r * (dy[token(r)] W2): the rows of dy are
         // gathered on load and the weight is applied to the f32 accumulators, so that the rounding of the stored
         // dO (a product rounded to bf16) does not reach dH, dXp, dW1 and db1.
-        using Cfg = CfgDh;
         ProfScope ps(c, EVOMOE_K_FFN_BWD_DH);
         const bool from_dy = dy && pair_gate && pair_token;
         a.A = (const bf16_t*)(from_dy ? dy : dO); a.lda = s.d; a.a_rows = from_dy ? pair_token : nullptr;
@@ -819,22 +858,18 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         a.B = (const bf16_t*)W2; a.ldb = s.F;
         a.b_group_stride = (int64_t)s.d * s.F; a.N = s.F; a.K = s.d; a.Hin = (const bf16_t*)H;
         a.out1 = (bf16_t*)dH; a.colpart = db1 ? colpart : nullptr;
-        a.col_group = col_group_for<Cfg>(s.F, s.d);
-        err = launch_gemm<L_NN, E_ACTGRAD, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(s.F));
+        static const RoundTime t[] = {{0, 15.1, 26.6}, {0, 10.0, 14.5}, {2.0, 5.8, 10.8}, {2.5, 4.8, 9.4}};
+        err = launch_best<L_NN, E_ACTGRAD, CfgDuo, CfgMid, CfgSml, CfgTny3>(c, s, a, t, &dh_bm);
         a.colpart = nullptr; a.a_rows = nullptr; a.row_scale = nullptr;
         if (err != hipSuccess) return err;
     }
     {   // dXp = dH W1
-        using Cfg = CfgDx;
         ProfScope ps(c, EVOMOE_K_FFN_BWD_DX);
         a.A = (const bf16_t*)dH; a.lda = s.F; a.B = (const bf16_t*)W1; a.ldb = s.d;
         a.b_group_stride = (int64_t)s.F * s.d; a.N = s.d; a.K = s.F; a.Hin = nullptr;
         a.out1 = (bf16_t*)dXp;
-        a.col_group = col_group_for<Cfg>(s.d, s.F);
-        if (pick_long_k(c, s, s.d, 0.63) == Tile::Lat)
-            err = launch_gemm<L_NN, E_NONE, CfgLat>(c, a, row_tiles<CfgLat>(s) * ctiles<CfgLat>(s.d));
-        else
-            err = launch_gemm<L_NN, E_NONE, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(s.d));
+        static const RoundTime t[] = {{0, 8.1, 20.7}, {0, 6.6, 14.0}, {0, 5.6, 7.9}, {0, 5.8, 10.8}, {0, 5.6, 6.3}};
+        err = launch_best<L_NN, E_NONE, CfgBig4, CfgLat8, CfgMid64, CfgSml, CfgTny>(c, s, a, t);
         if (err != hipSuccess) return err;
     }
     a.accumulate = accumulate;
@@ -876,7 +911,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         const size_t n2 = db2 ? (size_t)s.E * s.d : 0;
         const int gx1 = db1 ? (s.F + 255) / 256 : 0, gx2 = (int)((n2 + 255) / 256);
         hipLaunchKernelGGL(bias_grad_final_kernel, dim3(s.E * gx1 + gx2), dim3(256), 0, c.stream, colpart,
-                           expert_offsets, s.E, s.P_cap, s.F, (int)CfgDh::BM, (int)CfgDh::NW / 2, gx1, db1, scratch, n2, db2,
+                           expert_offsets, s.E, s.P_cap, s.F, dh_bm, dh_bm / 64, gx1, db1, scratch, n2, db2,
                            accumulate);
         err = hipGetLastError();
     }
