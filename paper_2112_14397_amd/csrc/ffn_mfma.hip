@@ -6,7 +6,7 @@
 //   TN  C_g[m,n] = sum_{r in g} L[r,m] * R[rrow(r),n]   weight gradients (contraction over the ragged rows)
 //
 // Block = 4 waves (2 x 2) or 8 waves (4 x 2), block tile BM x BN, K slabs of BK, NSTAGE LDS stages filled by direct
-// global->LDS loads (no staging registers) that run NSTAGE-1 slabs ahead of the MFMAs.  Operands whose
+// global->LDS loads (no staging registers) that run NSTAGE-1 slabs (two stages: one to one and a quarter) ahead of the MFMAs.  Operands whose
 // contraction index is contiguous in memory sit in LDS as [row][BK k] with an XOR swizzle of the 16-byte
 // chunks and are read with ds_read_b128; operands whose contraction index is the row index sit as
 // [k][cols] with a swizzle of 32-byte blocks and are read with the transposing LDS load
@@ -150,6 +150,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
     constexpr int A_CPR = BM / 8, A_RPI = 64 / A_CPR;        // k-strided A: 16 B chunks per k-row, k-rows per instruction
     constexpr int B_CPR = BN / 8, B_RPI = 64 / B_CPR;
     constexpr int NMF = TM * TN_, NFR = TM + TN_, NLD = A_LD + B_LD;
+    constexpr bool EARLY = NSTAGE == 2;
+    constexpr int EARLY_LD = NLD / 2;
     constexpr bool SPLIT_LD = NSTAGE >= 3;          // half of a slab's loads before the barrier, half after
     static_assert(BK == 32 || BK == 64, "slab");
     static_assert(NW == 4 || NW == 8, "waves");
@@ -440,7 +442,11 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
             for (int s = 0; s < NSTAGE - 1; ++s) {
                 if (s < nslab) issue(s);
             }
-            if (nslab >= NSTAGE - 1) wait_vmcnt<(NSTAGE - 2) * NLD>(); else wait_vmcnt<0>();
+            if (EARLY && nslab > 1) {
+#pragma unroll
+                for (int idx = 0; idx < EARLY_LD; ++idx) issue_one(idx, 1);
+                wait_vmcnt<EARLY_LD>();
+            } else if (nslab >= NSTAGE - 1) wait_vmcnt<(NSTAGE - 2) * NLD>(); else wait_vmcnt<0>();
             block_sync_lds();
             if (nslab == 1 && ragged) {
                 zero_tail();
@@ -455,6 +461,23 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         // s-1 has finished with; before the last k-step the block makes sure slab s+1 has landed.
         auto slab_body = [&](int slab, auto loads_c) {
             constexpr bool LOADS = decltype(loads_c)::value;
+            if constexpr (EARLY) {
+                // two stages: a slab's first loads go out as soon as its stage is released, under the last k-step of
+                // the slab before the one they are loaded under (LOADS: there is a slab + 2)
+                KSTEP(fa0, fb0, true, fa1, fb1, slab, 1, EARLY_LD, NLD, slab + 1);
+                if (KS == 4) {
+                    KSTEP(fa1, fb1, true, fa0, fb0, slab, 2, 0, 0, 0);
+                    KSTEP(fa0, fb0, true, fa1, fb1, slab, 3, 0, 0, 0);
+                }
+                wait_vmcnt<0>();
+                block_sync_lds();
+                if (slab + 2 == nslab && ragged) {
+                    zero_tail();
+                    block_sync_lds();
+                }
+                KSTEP(fa1, fb1, true, fa0, fb0, slab + 1, 0, 0, LOADS ? EARLY_LD : 0, slab + 2);
+                return;
+            }
             // with three or more stages the second half of a slab's loads goes out after the barrier
             // (its stage was released one slab earlier), which keeps the load unit evenly busy
             constexpr int L0 = !LOADS ? 0 : (SPLIT_LD ? NLD / 2 : NLD), L1 = LOADS ? NLD : 0;
@@ -475,7 +498,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         int slab = 0;
         // two blocks per CU: the wave that is feeding the matrix pipe goes ahead of its neighbour's epilogue
         if (WPE > 1) __builtin_amdgcn_s_setprio(1);
-        for (; slab + NSTAGE - 1 < nslab; ++slab) slab_body(slab, std::true_type{});
+        for (; slab + NSTAGE - (EARLY ? 0 : 1) < nslab; ++slab) slab_body(slab, std::true_type{});
         for (; slab + 1 < nslab; ++slab) slab_body(slab, std::false_type{});
         if (nslab > 0) {           // last slab: nothing left to fetch or to read ahead
             KSTEP(fa0, fb0, true, fa1, fb1, slab, 1, 0, 0, 0);
@@ -685,23 +708,29 @@ __global__ __launch_bounds__(256) void bias_grad_final_kernel(
     db1[(int64_t)g * N1 + n] = sum;
 }
 
-// Tile configurations.  BIG4: one block per compute unit, 256 accumulator registers per lane.
-// OCT: the same tile and stages worked by eight waves (64x128 each, two per SIMD, 128 accumulator registers): 4 %
-// faster than BIG4 for GEMM1 and 1 % for the weight gradients, 2 % slower for GEMM2, the same for dXp.
+// Tile configurations.  BIG: one block per compute unit, two stages of 64 k, 256 accumulator registers per lane.
+// BIG8: the same tile worked by eight waves (64x128 each, two per SIMD, 128 accumulator registers): the waves of a SIMD
+// fill each other's stalls and share the epilogue, which is half of a short contraction's tile.
+// A 64-wide slab takes whole 128-byte lines of a k-contiguous operand: with four stages of 32 k the L1 fetched every
+// line twice (its other half was gone by the next slab), 64 B/clk per compute unit at the matrix pipe's own rate, which
+// is all it can take.  BIG8 against 32-wide slabs: GEMM1 404 -> 366 us at d = 768, F = 3072, 58 330 pairs, 1603 -> 1473
+// at d = 1024, F = 4096, 131 072 pairs; BIG: GEMM2 270 -> 254 and 1026 -> 964 us, dXp 261 -> 252 and 994 -> 962 us.
+// OCT: BIG8 with four stages of 32 k, for the weight gradients (k-strided operands are whole lines at any slab width).
 // DUO: two blocks per compute unit (one's epilogue and stalls hide under the other's MFMAs).
 // LAT: for launches with no more tiles than compute units and a long contraction: what counts then is how fast
 // one block walks its K loop, and 64-wide slabs halve the number of load/barrier rounds of that walk.  LAT8: worked by
 // eight waves, 2-7 % faster for dXp, the same for GEMM2.
 // The smaller tiles are for launches whose 256-column tiles would leave compute units idle or be mostly padding
 // (an expert with fewer than 128 rows): there the launch is as fast as its weights arrive, which takes blocks on every
-// unit, each with several slabs of 64 k in flight.  MID: 128x128, two blocks per unit or (MID64) one with four 64-wide
-// stages.  SML: 64x128, two per unit.  TNY: 64x64, two per unit with four stages or (TNY3) three per unit with three.
+// unit, each with several slabs of 64 k in flight.  MID: 128x128, two blocks per unit with two stages or (MID64) one with
+// four.  SML: 64x128, two per unit.  TNY: 64x64, two per unit with four stages or (TNY3) three per unit with three.
 struct CfgDuo { static constexpr int BM = 128, BN = 256, BK = 32, NSTAGE = 3, WPE = 2, NW = 4; };
-struct CfgBig4 { static constexpr int BM = 256, BN = 256, BK = 32, NSTAGE = 4, WPE = 1, NW = 4; };
+struct CfgBig { static constexpr int BM = 256, BN = 256, BK = 64, NSTAGE = 2, WPE = 1, NW = 4; };
+struct CfgBig8 { static constexpr int BM = 256, BN = 256, BK = 64, NSTAGE = 2, WPE = 1, NW = 8; };
 struct CfgOct { static constexpr int BM = 256, BN = 256, BK = 32, NSTAGE = 4, WPE = 1, NW = 8; };
 struct CfgLat { static constexpr int BM = 128, BN = 256, BK = 64, NSTAGE = 3, WPE = 1, NW = 4; };
 struct CfgLat8 { static constexpr int BM = 128, BN = 256, BK = 64, NSTAGE = 3, WPE = 1, NW = 8; };
-struct CfgMid { static constexpr int BM = 128, BN = 128, BK = 32, NSTAGE = 4, WPE = 2, NW = 4; };
+struct CfgMid { static constexpr int BM = 128, BN = 128, BK = 64, NSTAGE = 2, WPE = 2, NW = 4; };
 struct CfgMid64 { static constexpr int BM = 128, BN = 128, BK = 64, NSTAGE = 4, WPE = 1, NW = 4; };
 struct CfgSml { static constexpr int BM = 64, BN = 128, BK = 64, NSTAGE = 3, WPE = 2, NW = 4; };
 struct CfgTny { static constexpr int BM = 64, BN = 64, BK = 64, NSTAGE = 4, WPE = 2, NW = 4; };
@@ -763,11 +792,11 @@ template <class Cfg> int col_group_for(int n, int k) {
 // expert's last row tile.  Where several blocks share a compute unit and the last round does not give every unit all
 // of them, that round is cheaper: 0.55 of a round at least, rising with the blocks per unit that it needs.  The numbers
 // are fits to launches over d x F from 136 x 264 to 1024 x 4096, 1 to 64 experts and 1 to 90 000 pairs; the shape the
-// model picks is within 1-3.5 % of the best one measured on average (no launch of the sweep above 21 %), where
+// model picks is within 1-3 % of the best one measured on average (no launch of the sweep above 27 %, those of 10 us or 20 us), where
 // 256-column tiles alone were 40-190 % slower below about 200 rows per expert.  d = 768, F = 3072, 16 experts, us:
 //            pairs     48     512    2048   8192   58330
-//   GEMM1  256-wide    30     30     32     69     386          GEMM2  256-wide   37     40     45     53     269
-//          picked      18     18     30     69     386                 picked     18     20     31     53     269
+//   GEMM1  256-wide    30     30     32     69     366          GEMM2  256-wide   37     40     45     53     254
+//          picked      18     18     30     69     366                 picked     18     20     31     53     254
 // The weight-gradient launch keeps one shape: 256x256 tiles were 8-29 % faster than either 128-row shape.
 struct RoundTime { double fixed, per_round, per_k; };
 template <class Cfg> double launch_cost(const Ctx& c, const evomoe_shape& s, const GemmArgs& a, const RoundTime& t) {
@@ -820,8 +849,8 @@ hipError_t mfma_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, cons
         a.A = (const bf16_t*)x; a.lda = s.d; a.a_rows = pair_token;
         a.B = (const bf16_t*)W1; a.ldb = s.d; a.b_group_stride = (int64_t)s.F * s.d;
         a.N = s.F; a.K = s.d; a.bias = b1; a.out1 = (bf16_t*)H; a.out2 = (bf16_t*)A;
-        static const RoundTime t[] = {{0, 11.5, 23.2}, {0, 11.6, 27.9}, {0, 8.8, 14.2}, {2.0, 4.4, 10.3}, {2.6, 3.2, 9.5}};
-        err = launch_best<L_NT, E_HA, CfgOct, CfgDuo, CfgMid, CfgSml, CfgTny3>(c, s, a, t);
+        static const RoundTime t[] = {{0, 12.2, 21.9}, {0, 12.4, 27.8}, {0, 9.2, 12.8}, {2.5, 4.4, 10.0}, {3.0, 3.4, 9.0}};
+        err = launch_best<L_NT, E_HA, CfgBig8, CfgDuo, CfgMid, CfgSml, CfgTny3>(c, s, a, t);
         if (err != hipSuccess || !O) return err;      // O == nullptr: recomputation of H and A only
     }
     {   // O = A W2^T + b2
@@ -829,8 +858,8 @@ hipError_t mfma_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, cons
         a.A = (const bf16_t*)A; a.lda = s.F; a.a_rows = nullptr;
         a.B = (const bf16_t*)W2; a.ldb = s.F; a.b_group_stride = (int64_t)s.d * s.F;
         a.N = s.d; a.K = s.F; a.bias = b2; a.out1 = (bf16_t*)O; a.out2 = nullptr;
-        static const RoundTime t[] = {{0, 8.7, 20.3}, {0, 6.6, 12.5}, {0, 5.5, 7.9}, {0, 5.3, 10.6}, {0, 5.8, 6.1}};
-        err = launch_best<L_NT, E_BIAS, CfgBig4, CfgLat, CfgMid64, CfgSml, CfgTny>(c, s, a, t);
+        static const RoundTime t[] = {{0, 8.8, 20.5}, {0, 6.7, 12.5}, {0, 5.9, 7.8}, {0, 5.9, 10.5}, {0, 5.8, 6.1}};
+        err = launch_best<L_NT, E_BIAS, CfgBig, CfgLat, CfgMid64, CfgSml, CfgTny>(c, s, a, t);
     }
     return err;
 }
@@ -858,7 +887,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         a.B = (const bf16_t*)W2; a.ldb = s.F;
         a.b_group_stride = (int64_t)s.d * s.F; a.N = s.F; a.K = s.d; a.Hin = (const bf16_t*)H;
         a.out1 = (bf16_t*)dH; a.colpart = db1 ? colpart : nullptr;
-        static const RoundTime t[] = {{0, 15.1, 26.6}, {0, 10.0, 14.5}, {2.0, 5.8, 10.8}, {2.5, 4.8, 9.4}};
+        static const RoundTime t[] = {{0, 15.6, 26.0}, {0.3, 10.4, 13.2}, {2.6, 5.4, 10.7}, {2.8, 5.0, 8.8}};
         err = launch_best<L_NN, E_ACTGRAD, CfgDuo, CfgMid, CfgSml, CfgTny3>(c, s, a, t, &dh_bm);
         a.colpart = nullptr; a.a_rows = nullptr; a.row_scale = nullptr;
         if (err != hipSuccess) return err;
@@ -868,8 +897,8 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         a.A = (const bf16_t*)dH; a.lda = s.F; a.B = (const bf16_t*)W1; a.ldb = s.d;
         a.b_group_stride = (int64_t)s.F * s.d; a.N = s.d; a.K = s.F; a.Hin = nullptr;
         a.out1 = (bf16_t*)dXp;
-        static const RoundTime t[] = {{0, 8.1, 20.7}, {0, 6.6, 14.0}, {0, 5.6, 7.9}, {0, 5.8, 10.8}, {0, 5.6, 6.3}};
-        err = launch_best<L_NN, E_NONE, CfgBig4, CfgLat8, CfgMid64, CfgSml, CfgTny>(c, s, a, t);
+        static const RoundTime t[] = {{0, 8.6, 20.3}, {0, 6.2, 13.1}, {0, 5.8, 7.7}, {0, 5.9, 10.7}, {0, 5.6, 6.2}};
+        err = launch_best<L_NN, E_NONE, CfgBig, CfgLat8, CfgMid64, CfgSml, CfgTny>(c, s, a, t);
         if (err != hipSuccess) return err;
     }
     a.accumulate = accumulate;

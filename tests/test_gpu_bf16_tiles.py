@@ -1,4 +1,4 @@
-"""The bf16 expert FFN at the edges of its small tiles (64x64, 64x128, 128x128, 128x256), against the oracle.  The launch
+"""The bf16 expert FFN at the edges of its tiles (64x64 to 256x256), against the oracle.  The launch
 picks a tile from the sizes, so each case names those it reaches: (GEMM1, GEMM2, dH, dXp)."""
 import pytest
 
@@ -8,13 +8,14 @@ import synth_inputs as synth  # noqa: E402
 
 # name, T, d, E, F: Top-1 through c = 0.9, so the single expert of an E = 1 layer owns exactly T rows
 CASES = [
-    ("64-few-rows", 9, 64, 1, 64),               # 64x64, 64x128, 64x64, 64x64
+    ("64-few-rows", 9, 64, 1, 64),               # 64x64 throughout
     ("64-below", 63, 72, 1, 136),                # 64x64 throughout; one vector past a slab of 64 and past two tiles
     ("64-above", 65, 64, 1, 192),                # 64x64 throughout; one row past a tile
     ("64x128-long", 2497, 392, 1, 264),          # 64x64, 64x128, 64x64, 64x128
     ("64x128-short", 1900, 776, 16, 1544),       # 64x128, 64x64, 64x128, 64x64
     ("128-below", 4095, 512, 4, 1032),           # 128x128 throughout, the long contractions with 64-wide slabs
     ("128x256-above", 4100, 1032, 1, 1032),      # 128x128, 128x256 with four waves, 128x128, 128x256 with eight
+    ("256-above", 16900, 1032, 1, 520),          # 256x256 with eight waves, with four, 128x256, 256x256 with four
 ]
 
 
