@@ -16,18 +16,21 @@ CASES = [
     ("128-below", 4095, 512, 4, 1032),           # 128x128 throughout, the long contractions with 64-wide slabs
     ("128x256-above", 4100, 1032, 1, 1032),      # 128x128, 128x256 with four waves, 128x128, 128x256 with eight
     ("256-above", 16900, 1032, 1, 520),          # 256x256 with eight waves, with four, 128x256, 256x256 with four
+    # the tile is picked for the buffers' capacity where no pair count is announced: 256x256 for dH as well
+    ("256-dh-one", 299, 1032, 1, 264, 200000),   # one full row tile and a ragged one
+    ("256-dh-three", 700, 1032, 3, 264, 200000),
 ]
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_bf16_ffn_at_tile_edges(case):
     import gpu_harness as h
-    name, T, d, E, F = case
+    name, T, d, E, F = case[:5]
     cfg = synth.LayerConfig(name, T=T, d=d, E=E, F=F, act="gelu", dtype="bf16", taus=(1.0,), threshold=0.9, seed=311,
                             bias_std=0.02)
     inp = synth.make_layer_inputs(cfg)
     # the pair buffers hold a row for each token (Top-1): the launch picks its tiles for that many pairs
-    gl = h.GpuLayer(inp, P_cap=T)
+    gl = h.GpuLayer(inp, P_cap=case[5] if len(case) > 5 else T)
     fwd, P, _, _ = h.compare_forward(gl, inp, 1.0, 0.9)
     gl.backward(1.0)
     # the FFN's own gradients (the gate's are sums over tokens of terms of either sign: a small one carries the rounding
