@@ -92,6 +92,29 @@ __device__ __forceinline__ int clamp_pairs(int P, int64_t P_cap) {
     return (int64_t)P > P_cap ? (int)P_cap : P;
 }
 
+// x_perm[r,:] = x[pair_token[r],:] for r < P, by block `blk` of `nblk` (256 threads, 16 bytes each).  Four vectors of a
+// thread are in flight at a time: the index and then the vector are each a trip to memory.
+__device__ __forceinline__ void gather_rows(const u32x4* __restrict__ x, const int32_t* __restrict__ pair_token, int P,
+                                            int vec_per_row, u32x4* __restrict__ x_perm, int blk, int nblk) {
+    const int64_t total = (int64_t)P * vec_per_row, step = (int64_t)nblk * 256;
+    for (int64_t i = (int64_t)blk * 256 + threadIdx.x; i < total; i += 4 * step) {
+        int tok[4], v[4];
+        u32x4 val[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t iu = i + u * step < total ? i + u * step : i;
+            const int r = (int)(iu / vec_per_row);
+            v[u] = (int)(iu - (int64_t)r * vec_per_row);
+            tok[u] = pair_token[r];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) val[u] = x[(size_t)tok[u] * vec_per_row + v[u]];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i + u * step < total) x_perm[i + u * step] = val[u];
+    }
+}
+
 // Optional per-kernel timing with HIP events on the context's stream (measurement aid).
 struct ProfRecord { int id; hipEvent_t start, stop; };
 struct Prof {

@@ -174,26 +174,26 @@ __global__ __launch_bounds__(256) void dispatch_scatter_kernel(
     }
 }
 
-// Optional materialisation of the permuted input: x_perm[r,:] = x[pair_token[r],:], 16 bytes per thread.
+// Optional materialisation of the permuted input.
 __global__ __launch_bounds__(256) void gather_rows_kernel(
     const u32x4* __restrict__ x, const int32_t* __restrict__ pair_token,
     const int32_t* __restrict__ expert_offsets, int E, int64_t P_cap, int vec_per_row,
     u32x4* __restrict__ x_perm)
 {
-    const int P = clamp_pairs(expert_offsets[E], P_cap);
-    const int64_t total = (int64_t)P * vec_per_row;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        const int r = (int)(i / vec_per_row), v = (int)(i % vec_per_row);
-        x_perm[i] = x[(size_t)pair_token[r] * vec_per_row + v];
-    }
+    gather_rows(x, pair_token, clamp_pairs(expert_offsets[E], P_cap), vec_per_row, x_perm, blockIdx.x, gridDim.x);
+}
+
+int gather_grid(const Ctx& c, const evomoe_shape& s) {
+    const int esz = s.dtype == EVOMOE_BF16 ? 2 : 4;
+    const int64_t want = (s.P_cap * (s.d * esz / 16) + 255) / 256, cap = (int64_t)c.num_cu * 8;
+    return (int)(want < cap ? want : cap);
 }
 
 hipError_t launch_gather_rows(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token,
                               const int32_t* expert_offsets, void* x_perm) {
     const int esz = s.dtype == EVOMOE_BF16 ? 2 : 4;
-    const int vec_per_row = s.d * esz / 16;
-    hipLaunchKernelGGL(gather_rows_kernel, dim3(c.num_cu * 8), dim3(256), 0, c.stream, (const u32x4*)x,
-                       pair_token, expert_offsets, s.E, s.P_cap, vec_per_row, (u32x4*)x_perm);
+    hipLaunchKernelGGL(gather_rows_kernel, dim3(gather_grid(c, s)), dim3(256), 0, c.stream, (const u32x4*)x,
+                       pair_token, expert_offsets, s.E, s.P_cap, s.d * esz / 16, (u32x4*)x_perm);
     return hipGetLastError();
 }
 

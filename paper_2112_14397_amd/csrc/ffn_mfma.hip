@@ -46,6 +46,54 @@ struct GemmArgs {
     int col_group;                      // NT/NN: column tiles per group of the tile order (1 .. all of them)
 };
 
+// The last sums of both bias gradients, as further tiles behind the weight gradients' (TN launches).  The first tiles1
+// (expert g = b / gx1, NW * 64 columns each): db1[g, n] (+)= sum over expert g's row tiles of the per-tile column sums
+// written by the dH GEMM, in row order.  The rest: db2[i] (+)= sum over the splits of the streaming column sums of dO, in
+// split order.  Reproducible bit for bit.
+struct BiasFinal {
+    const float* part1; float* db1;     // [row tile][parts][N1] -> [E,N1]
+    const float* part2; float* db2;     // [kColsumSplit][n2] -> [n2]
+    size_t n2;
+    int N1, BM, parts;                  // BM: row tile of the dH GEMM, parts: rows of its table for each
+    int gx1, tiles1, tiles;             // column blocks per expert, tiles of db1, of both
+    int accumulate;
+    const int32_t* offsets;             // expert_offsets
+};
+__device__ __forceinline__ void bias_final_tile(const BiasFinal& q, int b, const int* offs, int nthr) {
+    if (b >= q.tiles1) {
+        const size_t i = (size_t)(b - q.tiles1) * nthr + threadIdx.x;
+        if (i >= q.n2) return;
+        float s = q.accumulate ? q.db2[i] : 0.f;
+        for (int k0 = 0; k0 < kColsumSplit; k0 += 8) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = q.part2[(size_t)(k0 + u) * q.n2 + i];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        q.db2[i] = s;
+        return;
+    }
+    const int g = b / q.gx1;
+    const int n = (b % q.gx1) * nthr + threadIdx.x;
+    if (n >= q.N1) return;
+    int t0 = 0;                          // first row tile of expert g
+    for (int e = 0; e < g; ++e) t0 += (offs[e + 1] - offs[e] + q.BM - 1) / q.BM;
+    const int nt = (offs[g + 1] - offs[g] + q.BM - 1) / q.BM;
+    const float* src = q.part1 + (int64_t)t0 * q.parts * q.N1 + n;
+    float sum = q.accumulate ? q.db1[(int64_t)g * q.N1 + n] : 0.f;
+    int i = 0;
+    for (; i + 8 <= q.parts * nt; i += 8) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(i + u) * q.N1];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += v[u];
+    }
+    for (; i < q.parts * nt; ++i) sum += src[(int64_t)i * q.N1];
+    q.db1[(int64_t)g * q.N1 + n] = sum;
+}
+
 // ---- LDS geometry -------------------------------------------------------------------------------
 // Operand tiles are written by direct global->LDS loads (64 lanes x 16 B land contiguously), so a stage
 // is a dense array and bank conflicts are avoided by permuting 16-byte chunks on the global side:
@@ -150,10 +198,11 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 }
 
 template <int LAYOUT, int EPI, int BM, int BN, int BK, int NSTAGE, int WPE, int NW = 4>
-__global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, GemmArgs q1, int tiles0)
+__global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, GemmArgs q1, int tiles0, int tiles_all, BiasFinal qb)
 {
     // TN launches carry two independent problems (dW2 and dW1) in one grid, tiles [0, tiles0) and
-    // [tiles0, ...), which evens out the last round of the persistent schedule; other layouts use q0 only.
+    // [tiles0, tiles_all), which evens out the last round of the persistent schedule, and behind them the bias
+    // gradients' last sums; other layouts use q0 only.
     using G = Geo<LAYOUT, BM, BN, BK, NSTAGE, NW>;
     constexpr int WM = G::WM, WN = G::WN;
     constexpr int TM = WM / 32, TN_ = WN / 32;               // MFMA tiles per wave
@@ -222,6 +271,11 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
 
     for (int vtile = vblock;; vtile += gridDim.x, seq += seq_step) {
         // ---------------- tile -> (problem, expert, origin, contraction range) ----------------
+        if (LAYOUT == L_TN && vtile >= tiles_all) {
+            if (vtile - tiles_all >= qb.tiles) break;
+            bias_final_tile(qb, vtile - tiles_all, offs, NW * 64);
+            continue;
+        }
         const bool second = (LAYOUT == L_TN) && vtile >= tiles0;
         const GemmArgs& p = second ? q1 : q0;
         const int tile = second ? vtile - tiles0 : vtile;
@@ -229,7 +283,6 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         const int nmt = (LAYOUT == L_TN) ? (p.M + BM - 1) / BM : 1;
         int g = 0, row0 = 0, rows = 0, n0 = 0, m0 = 0, kbeg = 0, kend = 0;
         if (LAYOUT == L_TN) {
-            if (tile >= p.E * nmt * nct) break;
             g = tile / (nmt * nct);
             const int rem = tile % (nmt * nct);
             m0 = (rem / nct) * BM;
@@ -675,52 +728,6 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
     }
 }
 
-// Both bias gradients in one launch.  The first E * gx1 blocks (expert g = b / gx1, 256 columns each):
-// db1[g, n] (+)= sum over expert g's row tiles (`parts` partial rows each) of the per-tile column sums written by the
-// dH GEMM, in row order.  The remaining blocks: db2[i] (+)= sum over the splits of the streaming column sums of
-// dO, in split order.  Reproducible bit for bit.
-__global__ __launch_bounds__(256) void bias_grad_final_kernel(
-    const float* __restrict__ part1, const int32_t* __restrict__ expert_offsets, int E, int64_t P_cap, int N1,
-    int BM, int parts, int gx1, float* __restrict__ db1, const float* __restrict__ part2, size_t n2, float* __restrict__ db2,
-    int accumulate)
-{
-    if ((int)blockIdx.x >= E * gx1) {
-        const size_t i = (size_t)(blockIdx.x - E * gx1) * 256 + threadIdx.x;
-        if (i >= n2) return;
-        float s = accumulate ? db2[i] : 0.f;
-        for (int k0 = 0; k0 < kColsumSplit; k0 += 8) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = part2[(size_t)(k0 + u) * n2 + i];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
-        }
-        db2[i] = s;
-        return;
-    }
-    const int g = blockIdx.x / gx1;
-    const int n = (blockIdx.x % gx1) * 256 + threadIdx.x;
-    __shared__ int offs[65];
-    if ((int)threadIdx.x <= E) offs[threadIdx.x] = clamp_pairs(expert_offsets[threadIdx.x], P_cap);
-    __syncthreads();
-    if (n >= N1) return;
-    int t0 = 0;                          // first row tile of expert g
-    for (int e = 0; e < g; ++e) t0 += (offs[e + 1] - offs[e] + BM - 1) / BM;
-    const int nt = (offs[g + 1] - offs[g] + BM - 1) / BM;
-    const float* src = part1 + (int64_t)t0 * parts * N1 + n;
-    float sum = accumulate ? db1[(int64_t)g * N1 + n] : 0.f;
-    int i = 0;
-    for (; i + 8 <= parts * nt; i += 8) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(i + u) * N1];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) sum += v[u];
-    }
-    for (; i < parts * nt; ++i) sum += src[(int64_t)i * N1];
-    db1[(int64_t)g * N1 + n] = sum;
-}
-
 // Tile configurations.  BIG: one block per compute unit, two stages of 64 k, 256 accumulator registers per lane.
 // BIG8: the same tile worked by eight waves (64x128 each, two per SIMD, 128 accumulator registers): the waves of a SIMD
 // fill each other's stalls and share the epilogue, which is half of a short contraction's tile.
@@ -750,7 +757,8 @@ struct CfgTny { static constexpr int BM = 64, BN = 64, BK = 64, NSTAGE = 4, WPE 
 struct CfgTny3 { static constexpr int BM = 64, BN = 64, BK = 64, NSTAGE = 3, WPE = 3, NW = 4; };
 
 template <int LAYOUT, int EPI, class Cfg>
-hipError_t launch_gemm(const Ctx& c, const GemmArgs& a0, int64_t tiles0, const GemmArgs& a1, int64_t tiles1) {
+hipError_t launch_gemm(const Ctx& c, const GemmArgs& a0, int64_t tiles0, const GemmArgs& a1, int64_t tiles1,
+                       BiasFinal b = BiasFinal{}) {
     using G = Geo<LAYOUT, Cfg::BM, Cfg::BN, Cfg::BK, Cfg::NSTAGE, Cfg::NW>;
     auto kern = grouped_gemm_bf16<LAYOUT, EPI, Cfg::BM, Cfg::BN, Cfg::BK, Cfg::NSTAGE, Cfg::WPE, Cfg::NW>;
     static bool configured = false;
@@ -760,9 +768,12 @@ hipError_t launch_gemm(const Ctx& c, const GemmArgs& a0, int64_t tiles0, const G
         if (e != hipSuccess) return e;
         configured = true;
     }
-    const int64_t cap = (int64_t)c.num_cu * Cfg::WPE, worst = tiles0 + tiles1;
+    if (b.db1) { b.gx1 = (b.N1 + Cfg::NW * 64 - 1) / (Cfg::NW * 64); b.tiles1 = a0.E * b.gx1; }
+    b.tiles = b.tiles1 + (b.db2 ? (int)((b.n2 + Cfg::NW * 64 - 1) / (Cfg::NW * 64)) : 0);
+    const int64_t cap = (int64_t)c.num_cu * Cfg::WPE, worst = tiles0 + tiles1 + b.tiles;
     const int grid = (int)(worst < cap ? worst : cap);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(Cfg::NW * 64), G::SMEM, c.stream, a0, a1, (int)tiles0);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(Cfg::NW * 64), G::SMEM, c.stream, a0, a1, (int)tiles0, (int)(tiles0 + tiles1),
+                       b);
     return hipGetLastError();
 }
 template <int LAYOUT, int EPI, class Cfg>
@@ -788,7 +799,6 @@ template <class Cfg> int64_t expected_row_tiles(const Ctx& c, const evomoe_shape
 // the act'(H) launch's table of column sums (BM / 64 rows for each row tile) is sized for these tiles, and no other shape's
 // needs more
 using CfgDh = CfgBig8;
-using CfgDw = CfgOct;
 
 // Column tiles per group of the NT/NN tile order: as many weight panels (BN x K) as stay in one XCD's 4 MB L2 next to
 // the row panels streaming past them; all of them when a row panel (BM x K) is itself so large (long contractions)
@@ -811,14 +821,15 @@ template <class Cfg> int col_group_for(int n, int k) {
 //            pairs     48     512    2048   8192   58330
 //   GEMM1  256-wide    30     30     32     69     366          GEMM2  256-wide   37     40     45     53     254
 //          picked      18     18     30     69     366                 picked     18     20     31     53     254
-// The weight-gradient launch keeps one shape: 256x256 tiles were 8-29 % faster than either 128-row shape.
 struct RoundTime { double fixed, per_round, per_k; };
-template <class Cfg> double launch_cost(const Ctx& c, const evomoe_shape& s, const GemmArgs& a, const RoundTime& t) {
-    const int64_t tiles = expected_row_tiles<Cfg>(c, s) * ctiles<Cfg>(a.N);
+template <class Cfg> double round_cost(const Ctx& c, int64_t tiles, double k, const RoundTime& t) {
     const int64_t slots = (int64_t)c.num_cu * Cfg::WPE, last = tiles % slots;
     double rounds = (double)(tiles / slots);
     if (last) rounds += 0.55 + 0.45 * (double)((last + c.num_cu - 1) / c.num_cu) / Cfg::WPE;
-    return t.fixed + rounds * (t.per_round + t.per_k * a.K / 1024.0);
+    return t.fixed + rounds * (t.per_round + t.per_k * k / 1024.0);
+}
+template <class Cfg> double launch_cost(const Ctx& c, const evomoe_shape& s, const GemmArgs& a, const RoundTime& t) {
+    return round_cost<Cfg>(c, expected_row_tiles<Cfg>(c, s) * ctiles<Cfg>(a.N), a.K, t);
 }
 // Launches the cheapest of the shapes Cfgs (t: their times, in the same order); its row tile goes to *bm.
 template <int LAYOUT, int EPI, class Cfg>
@@ -842,6 +853,37 @@ hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const R
     n = 0;
     (void)((n++ == best ? (err = launch_rows<LAYOUT, EPI, Cfgs>(c, s, a, bm), true) : false) || ...);
     return err;
+}
+
+// Weight gradients: the contraction runs over an expert's rows, P / E of them on average, and the tiles are those of the
+// matrices.  256x256 tiles (eight waves) are the fastest per flop by far -- 8-29 % ahead of 128-row tiles wherever they
+// fill the chip -- but layers with few experts or narrow matrices have fewer of them than compute units: there the finer
+// tiles spread the same rows over more units.  The same model as for the other launches, fitted to 16 layers with 64 to
+// 1024 columns, 1 to 64 experts and 32 to 16384 rows per expert; it picks the fastest of the three at each.  us
+// (pairs, d, E, F):  777,136,7,264  8192,256,8,1024  16384,128,8,512  16384,256,1,1024  8192,512,4,2048  4096,1024,4,4096
+//   256x256               9.7             27.8             44.7             290               53.0            69.8
+//   128x128               6.7             16.4             19.8             108               44.8            96.5
+//   64x64                 5.4             19.9             17.6              60               65.8           157
+template <class Cfg> int64_t wgrad_tiles(const GemmArgs& a) { return (int64_t)a.E * mtiles<Cfg>(a.M) * ctiles<Cfg>(a.N); }
+hipError_t launch_wgrad(const Ctx& c, const evomoe_shape& s, const GemmArgs* w2, const GemmArgs* w1, const BiasFinal& bf) {
+    GemmArgs none{};        // no weight gradient wanted: the launch carries the bias gradients only
+    none.E = s.E; none.P_cap = s.P_cap; none.expert_offsets = bf.offsets;
+    const GemmArgs& q0 = w2 ? *w2 : w1 ? *w1 : none;
+    const GemmArgs& q1 = w1 ? *w1 : q0;
+    const double k = (double)expected_pairs(c, s) / s.E;
+    auto run = [&](auto cfg, bool launch, const RoundTime& t, double* cost) {
+        using Cfg = decltype(cfg);
+        const int64_t t0 = w2 || w1 ? wgrad_tiles<Cfg>(q0) : 0, t1 = w2 && w1 ? wgrad_tiles<Cfg>(q1) : 0;
+        if (!launch) { *cost = round_cost<Cfg>(c, t0 + t1, k, t); return hipSuccess; }
+        return launch_gemm<L_TN, E_WGRAD, Cfg>(c, q0, t0, q1, t1, bf);
+    };
+    static const RoundTime t[] = {{4.0, 5.0, 24.0}, {2.5, 4.0, 8.0}, {2.0, 2.0, 7.6}};
+    double c0, c1, c2;
+    (void)run(CfgOct{}, false, t[0], &c0);
+    (void)run(CfgMid64{}, false, t[1], &c1);
+    (void)run(CfgTny{}, false, t[2], &c2);
+    if (c0 <= c1 && c0 <= c2) return run(CfgOct{}, true, t[0], &c0);
+    return c1 <= c2 ? run(CfgMid64{}, true, t[1], &c1) : run(CfgTny{}, true, t[2], &c2);
 }
 
 }  // namespace
@@ -916,49 +958,32 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         if (err != hipSuccess) return err;
     }
     a.accumulate = accumulate;
-    using CfgW = CfgDw;
     GemmArgs w2 = a, w1 = a;
     // dW2_g = dO_g^T A_g   [d,F]
     w2.A = (const bf16_t*)dO; w2.lda = s.d; w2.B = (const bf16_t*)A; w2.ldb = s.F;
     w2.M = s.d; w2.N = s.F; w2.out1 = (bf16_t*)dW2;
-    const int64_t t2 = (int64_t)s.E * mtiles<CfgW>(s.d) * ctiles<CfgW>(s.F);
     // dW1_g = dH_g^T X_g   [F,d]; the token rows are gathered once into a dense copy so that the GEMM
     // streams them like any other operand
     const bf16_t* xg = (const bf16_t*)x;
+    bf16_t* xp = nullptr;
     if (dW1 && pair_token) {
-        ProfScope ps(c, EVOMOE_K_FFN_BWD_DW1);
-        bf16_t* xp = reinterpret_cast<bf16_t*>(static_cast<char*>(dH) + dh_bytes(s) + colsum_scratch_bytes(s));
-        err = launch_gather_rows(c, s, x, pair_token, expert_offsets, xp);
-        if (err != hipSuccess) return err;
+        xp = reinterpret_cast<bf16_t*>(static_cast<char*>(dH) + dh_bytes(s) + colsum_scratch_bytes(s));
         xg = xp;
+    }
+    if (xp || db2) {      // one launch: the gather, and the split column sums of dO for db2
+        ProfScope ps(c, xp ? EVOMOE_K_FFN_BWD_DW1 : EVOMOE_K_FFN_BWD_DB);
+        err = launch_gather_colsum(c, s, xp ? x : nullptr, pair_token, xp, db2 ? dO : nullptr, s.d, expert_offsets, scratch);
+        if (err != hipSuccess) return err;
     }
     w1.A = (const bf16_t*)dH; w1.lda = s.F; w1.B = xg; w1.ldb = s.d;
     w1.M = s.F; w1.N = s.d; w1.out1 = (bf16_t*)dW1;
-    const int64_t t1 = (int64_t)s.E * mtiles<CfgW>(s.F) * ctiles<CfgW>(s.d);
-    if (dW2 && dW1) {
-        ProfScope ps(c, EVOMOE_K_FFN_BWD_DW2);
-        err = launch_gemm<L_TN, E_WGRAD, CfgW>(c, w2, t2, w1, t1);
-    } else if (dW2) {
-        ProfScope ps(c, EVOMOE_K_FFN_BWD_DW2);
-        err = launch_gemm<L_TN, E_WGRAD, CfgW>(c, w2, t2);
-    } else if (dW1) {
-        ProfScope ps(c, EVOMOE_K_FFN_BWD_DW1);
-        err = launch_gemm<L_TN, E_WGRAD, CfgW>(c, w1, t1);
-    }
-    if (err != hipSuccess) return err;
-    ProfScope ps(c, EVOMOE_K_FFN_BWD_DB);
-    if (db2) err = launch_colsum_part(c, s, dO, s.d, expert_offsets, scratch);
-    if (err != hipSuccess) return err;
-    if (db1 || db2) {
-        // one launch finishes both: E * gx1 blocks for db1 (if wanted), then gx2 blocks for db2 (if wanted)
-        const size_t n2 = db2 ? (size_t)s.E * s.d : 0;
-        const int gx1 = db1 ? (s.F + 255) / 256 : 0, gx2 = (int)((n2 + 255) / 256);
-        hipLaunchKernelGGL(bias_grad_final_kernel, dim3(s.E * gx1 + gx2), dim3(256), 0, c.stream, colpart,
-                           expert_offsets, s.E, s.P_cap, s.F, dh_bm, dh_bm / 64, gx1, db1, scratch, n2, db2,
-                           accumulate);
-        err = hipGetLastError();
-    }
-    return err;
+    BiasFinal bf{};
+    bf.part1 = colpart; bf.db1 = db1; bf.N1 = s.F; bf.BM = dh_bm; bf.parts = dh_bm / 64;
+    bf.part2 = scratch; bf.db2 = db2; bf.n2 = (size_t)s.E * s.d; bf.accumulate = accumulate;
+    bf.offsets = expert_offsets;
+    if (!dW2 && !dW1 && !db1 && !db2) return hipSuccess;
+    ProfScope ps(c, dW2 ? EVOMOE_K_FFN_BWD_DW2 : dW1 ? EVOMOE_K_FFN_BWD_DW1 : EVOMOE_K_FFN_BWD_DB);
+    return launch_wgrad(c, s, dW2 ? &w2 : nullptr, dW1 ? &w1 : nullptr, bf);
 }
 
 }  // namespace evomoe

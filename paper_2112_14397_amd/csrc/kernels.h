@@ -26,6 +26,7 @@ hipError_t launch_dispatch(const Ctx& c, const evomoe_shape& s, const uint64_t* 
                            int32_t* pair_token, float* pair_gate, int32_t* tok_off, int32_t* tok_rows,
                            int64_t* num_pairs, const void* x, void* x_perm, int32_t* hist_scratch);
 int dispatch_blocks(const evomoe_shape& s);     // 256-token groups: rows of a block_hist table
+int gather_grid(const Ctx& c, const evomoe_shape& s);   // blocks of 256 threads that gather rows of d elements
 // device address, on `device` (which must be current), of the library's static histogram table
 hipError_t static_hist_table(int device, int32_t** table);
 hipError_t launch_gather_rows(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token,
