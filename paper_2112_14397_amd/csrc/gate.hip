@@ -5,7 +5,8 @@
 // move), + bias + Gumbel noise, temperature softmax,
 // strict threshold with the arg-max fallback, bit mask, per-token k, and the per-expert histogram
 // (integer atomics into counts[E] and, if asked for, into the per-256-token histograms the dispatch
-// starts from; both are cleared by gate_prep_kernel right before).
+// starts from; both are cleared by gate_prep_kernel right before, or, where one block of 1024 threads works on all
+// tokens, written by it outright).
 #include <type_traits>
 
 #include "kernels.h"
@@ -21,7 +22,9 @@ namespace evomoe {
 // token apply bias, noise, temperature softmax, the strict threshold and the arg-max fallback, write
 // g', weights, mask and k, and add the block's per-expert counts to counts[E] and to the histogram row of the
 // 256-token group the block lies in (integer atomics: the sums do not depend on their order).
-template <int NE, int RT>
+// SUB > 1: SUB such groups of 256 threads in one block that owns every token of the call (at most 256): its counts are
+// the totals, stored without atomics or clearing.
+template <int NE, int RT, int SUB>
 __device__ __forceinline__ void gate_finish(
     f32x4 (&acc)[RT][NE], const float* __restrict__ bg, const float* __restrict__ noise, float tau, float c,
     int T, int E, float* __restrict__ gprime, float* __restrict__ gate_w, uint64_t* __restrict__ mask_bits,
@@ -32,13 +35,15 @@ __device__ __forceinline__ void gate_finish(
     constexpr int LDZ = EP + 4;            // LDS row stride (bank-conflict-free tile writes)
     constexpr int TPT = 256 / TPB;         // threads per token in the softmax phase
     constexpr int EPT = EP / TPT;          // experts per thread there
-    __shared__ float zsum[TPB * LDZ];
+    __shared__ float zsum_all[SUB * TPB * LDZ];
     __shared__ int cnt[64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
     const int i16 = lane & 15, q = lane >> 4;
-    const int t0 = blockIdx.x * TPB;
+    const int sub_blk = SUB > 1 ? threadIdx.x >> 8 : 0;
+    const int t0 = (blockIdx.x * SUB + sub_blk) * TPB;
+    float* zsum = zsum_all + sub_blk * TPB * LDZ;
 
-    if (tid < 64) cnt[tid] = 0;
+    if (threadIdx.x < 64) cnt[threadIdx.x] = 0;
     // add the four waves' partial tiles in wave order (fixed order => reproducible bits)
     for (int w = 0; w < 4; ++w) {
         if (wave == w) {
@@ -129,7 +134,12 @@ __device__ __forceinline__ void gate_finish(
     __syncthreads();
 
     // ---- per-expert histogram ----
-    if (tid < E && cnt[tid]) {
+    if (SUB > 1) {
+        if ((int)threadIdx.x < E) {
+            counts[threadIdx.x] = cnt[threadIdx.x];
+            if (block_hist) block_hist[threadIdx.x] = cnt[threadIdx.x];
+        }
+    } else if (tid < E && cnt[tid]) {
         atomicAdd(&counts[tid], cnt[tid]);
         if (block_hist) atomicAdd(&block_hist[(size_t)(t0 / kDispatchTokens) * E + tid], cnt[tid]);
     }
@@ -137,8 +147,8 @@ __device__ __forceinline__ void gate_finish(
 
 // float32 layer: logits with v_mfma_f32_16x16x4_f32 (exact float32 products).  Block = 4 waves; the
 // block owns 16*RT consecutive tokens; each wave takes every 4th K-slab of all of them.
-template <typename TX, int NE, int RT>
-__global__ __launch_bounds__(256) void dts_gate_kernel(
+template <typename TX, int NE, int RT, int SUB = 1>
+__global__ __launch_bounds__(256 * SUB) void dts_gate_kernel(
     const TX* __restrict__ x, const float* __restrict__ Wg, const float* __restrict__ bg,
     const float* __restrict__ noise, float tau, float c, int T, int d, int E,
     float* __restrict__ gprime, float* __restrict__ gate_w, uint64_t* __restrict__ mask_bits,
@@ -147,9 +157,9 @@ __global__ __launch_bounds__(256) void dts_gate_kernel(
     constexpr int KV = Elem<TX>::kVec;     // k's per 16-byte load
     constexpr int KB = 4 * KV;             // k's per slab (4 lane groups x KV)
     constexpr int TPB = 16 * RT;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
     const int i16 = lane & 15, q = lane >> 4;
-    const int t0 = blockIdx.x * TPB;
+    const int t0 = (blockIdx.x * SUB + (SUB > 1 ? threadIdx.x >> 8 : 0)) * TPB;
 
     f32x4 acc[RT][NE];
 #pragma unroll
@@ -183,7 +193,7 @@ __global__ __launch_bounds__(256) void dts_gate_kernel(
             }
         }
     }
-    gate_finish<NE, RT>(acc, bg, noise, tau, c, T, E, gprime, gate_w, mask_bits, k_per_token, counts, block_hist);
+    gate_finish<NE, RT, SUB>(acc, bg, noise, tau, c, T, E, gprime, gate_w, mask_bits, k_per_token, counts, block_hist);
 }
 
 // bf16 layer.  x is exact in bf16, so W_g is split into three bf16 terms (hi + mid + lo carry all 24
@@ -220,17 +230,22 @@ __global__ __launch_bounds__(256) void gate_prep_kernel(const float* __restrict_
     planes[base + (size_t)2 * NE * 512] = (uint16_t)lo;
 }
 
-template <int NE, int RT>
-__global__ __launch_bounds__(256) void dts_gate_bf16_kernel(
-    const bf16_t* __restrict__ x, const bf16_t* __restrict__ planes, const float* __restrict__ bg,
+// SUB > 1 (one block, at most 16 experts): there is no split copy; every wave reads the float32 weights of its k-blocks
+// together with x and splits them itself, into the same three terms.
+template <int NE, int RT, int SUB = 1>
+__global__ __launch_bounds__(256 * SUB) void dts_gate_bf16_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ planes, const float* __restrict__ Wg,
+    const float* __restrict__ bg,
     const float* __restrict__ noise, float tau, float c, int T, int d, int E,
     float* __restrict__ gprime, float* __restrict__ gate_w, uint64_t* __restrict__ mask_bits,
     int32_t* __restrict__ k_per_token, int32_t* __restrict__ counts, int32_t* __restrict__ block_hist)
 {
-    constexpr int TPB = 16 * RT, EP = 16 * NE;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int TPB = 16 * RT;
+    constexpr bool OWN = SUB > 1;          // splits W_g itself
+    static_assert(!OWN || NE == 1, "one block: one tile of experts");
+    const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
     const int i16 = lane & 15, q = lane >> 4;
-    const int t0 = blockIdx.x * TPB;
+    const int t0 = (blockIdx.x * SUB + (SUB > 1 ? threadIdx.x >> 8 : 0)) * TPB;
     f32x4 acc[RT][NE];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -241,7 +256,7 @@ __global__ __launch_bounds__(256) void dts_gate_bf16_kernel(
     // k-blocks of 32, dealt round-robin to the four waves; lane group q holds k = 32*kb + 8q .. +7.
     // XU k-blocks per round: their x fragments are fetched together (one trip to memory per round), and the
     // W_g terms of the next k-block are fetched while the current one multiplies.
-    constexpr int XU = RT * NE >= 8 ? 2 : (RT * NE >= 4 ? 4 : 8);
+    constexpr int XU = OWN ? (RT == 1 ? 6 : RT == 2 ? 2 : 1) : RT * NE >= 8 ? 2 : (RT * NE >= 4 ? 4 : 8);
     auto load_planes = [&](int kb, bf16x8 (&b)[NE][3]) {
         const bool kok = kb * 32 < d;
         const bf16_t* wp = planes + ((size_t)(kok ? kb : 0) * 3 * NE) * 512 + lane * 8;
@@ -262,6 +277,34 @@ __global__ __launch_bounds__(256) void dts_gate_bf16_kernel(
                 a[u][rt] = (k0 < d && t < T) ? *reinterpret_cast<const bf16x8*>(x + (size_t)t * d + k0) : zero8;
             }
         }
+        if constexpr (OWN) {
+            float w[XU][8];
+#pragma unroll
+            for (int u = 0; u < XU; ++u)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int k = (kb0 + 4 * u) * 32 + q * 8 + j;
+                    w[u][j] = (k < d && i16 < E) ? Wg[(size_t)k * E + i16] : 0.f;
+                }
+#pragma unroll
+            for (int u = 0; u < XU; ++u) {
+                bf16x8 hi, mid, lo;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    hi[j] = (bf16_t)w[u][j];
+                    const float r1 = w[u][j] - (float)hi[j];
+                    mid[j] = (bf16_t)r1;
+                    lo[j] = (bf16_t)(r1 - (float)mid[j]);
+                }
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    acc[rt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u][rt], lo, acc[rt][0], 0, 0, 0);
+                    acc[rt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u][rt], mid, acc[rt][0], 0, 0, 0);
+                    acc[rt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u][rt], hi, acc[rt][0], 0, 0, 0);
+                }
+            }
+            continue;
+        }
         bf16x8 b[2][NE][3];
         load_planes(kb0, b[0]);
 #pragma unroll
@@ -277,7 +320,7 @@ __global__ __launch_bounds__(256) void dts_gate_bf16_kernel(
                 }
         }
     }
-    gate_finish<NE, RT>(acc, bg, noise, tau, c, T, E, gprime, gate_w, mask_bits, k_per_token, counts, block_hist);
+    gate_finish<NE, RT, SUB>(acc, bg, noise, tau, c, T, E, gprime, gate_w, mask_bits, k_per_token, counts, block_hist);
 }
 
 static int pick_rt(const Ctx& c, const evomoe_shape& s) {
@@ -303,7 +346,7 @@ static hipError_t gate_launch_t(const Ctx& c, const evomoe_shape& s, const void*
         hipLaunchKernelGGL(gate_prep_kernel, dim3((n + 255) / 256), dim3(256), 0, c.stream, Wg, s.d, s.E, NE,
                            c.wg_planes, counts, block_hist, n_hist);
         hipLaunchKernelGGL((dts_gate_bf16_kernel<NE, RT>), dim3(blocks), dim3(256), 0, c.stream,
-                           (const bf16_t*)x, (const bf16_t*)c.wg_planes, bg, noise, tau, thr, s.T, s.d, s.E,
+                           (const bf16_t*)x, (const bf16_t*)c.wg_planes, Wg, bg, noise, tau, thr, s.T, s.d, s.E,
                            gprime, gate_w, mask_bits, k_per_token, counts, block_hist);
     } else {
         const int n = n_hist > s.E ? n_hist : s.E;
@@ -340,10 +383,37 @@ static hipError_t gate_launch_ne(const Ctx& c, const evomoe_shape& s, const void
     }
 }
 
+// The smallest calls are launches and latency: one block of 1024 threads then does all of it, in one launch instead of
+// two, and the split of W_g and the clearing of the counts, which gate_prep_kernel is for, fall away.  The histogram has
+// one row up to 256 tokens and one tile holds 16 experts; up to 256 columns one compute unit reads x and W_g in the time
+// that the launch took (a whole forward pass: T = 256, d = 64, E = 4 in float32 32.0 -> 27.9 us; T = 256, d = 256, E = 8 in
+// bf16 31.9 -> 29.2; T = 128, d = 256, E = 4 in float32 32.1 -> 28.9).  Beyond, it no longer does: T = 48, d = 768, E = 16
+// in bf16 58.1 -> 63.5, T = 100, d = 512, E = 16 31.8 -> 32.7, T = 64, d = 512, E = 8 in float32 31.3 -> 32.0.
+static bool gate_one_block(const evomoe_shape& s) {
+    return s.T <= kDispatchTokens && s.E <= 16 && s.d <= 256;
+}
+template <int RT>
+static hipError_t gate_launch_one(const Ctx& c, const evomoe_shape& s, const void* x, const float* Wg, const float* bg,
+                                  const float* noise, float tau, float thr, float* gp, float* gw, uint64_t* mb,
+                                  int32_t* cn, int32_t* kt, int32_t* bh) {
+    ProfScope ps(c, EVOMOE_K_GATE);
+    if (s.dtype == EVOMOE_BF16)
+        hipLaunchKernelGGL((dts_gate_bf16_kernel<1, RT, 4>), dim3(1), dim3(1024), 0, c.stream, (const bf16_t*)x,
+                           (const bf16_t*)nullptr, Wg, bg, noise, tau, thr, s.T, s.d, s.E, gp, gw, mb, kt, cn, bh);
+    else
+        hipLaunchKernelGGL((dts_gate_kernel<float, 1, RT, 4>), dim3(1), dim3(1024), 0, c.stream, (const float*)x, Wg,
+                           bg, noise, tau, thr, s.T, s.d, s.E, gp, gw, mb, kt, cn, bh);
+    return hipGetLastError();
+}
+
 hipError_t launch_dts_gate(const Ctx& c, const evomoe_shape& s, const void* x, const float* Wg,
                            const float* bg, const float* noise, float tau, float threshold,
                            float* gprime, float* gate_w, uint64_t* mask_bits, int32_t* counts,
                            int32_t* k_per_token, int32_t* block_hist) {
+    if (gate_one_block(s)) {
+        auto one = s.T <= 64 ? gate_launch_one<1> : s.T <= 128 ? gate_launch_one<2> : gate_launch_one<4>;
+        return one(c, s, x, Wg, bg, noise, tau, threshold, gprime, gate_w, mask_bits, counts, k_per_token, block_hist);
+    }
     if (s.dtype == EVOMOE_BF16)
         return gate_launch_ne<bf16_t>(c, s, x, Wg, bg, noise, tau, threshold, gprime, gate_w,
                                       mask_bits, counts, k_per_token, block_hist);
