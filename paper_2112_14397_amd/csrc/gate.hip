@@ -828,14 +828,21 @@ static hipError_t gate_bwd_t(const Ctx& c, const evomoe_shape& s, const float* d
                              const float* Wg, void* dx, float* dWg_part, float* dbg_part, int tc,
                              int nchunk) {
     const int ep = ((s.E + 15) / 16) * 16;
-    const int cpt = ep == 16 ? 4 : ep == 32 ? 2 : 1;         // columns per thread (register budget: 2*CPT*EP)
+    // Columns per thread: as many as the registers hold (2*CPT*EP), but no more than leave every thread of a block some:
+    // each thread walks the chunk's tokens one after another, so columns that idle threads could take make the launch
+    // longer (d = 256 with 4 columns for each of 64 threads: 16.8 us at T = 2048, E = 8).
+    int cpt = ep == 16 ? 4 : ep == 32 ? 2 : 1;
+    while (cpt > 1 && 256 * cpt > s.d) cpt >>= 1;
     dim3 grid(nchunk, (s.d + 256 * cpt - 1) / (256 * cpt));
     const size_t lds = (size_t)tc * ep * sizeof(float);
 #define EVOMOE_GB(EPV, CPTV)                                                                     \
     hipLaunchKernelGGL((gate_bwd_kernel<TX, EPV, CPTV>), grid, dim3(256), lds, c.stream, dz,     \
                        (const TX*)x, Wg, s.T, s.d, s.E, tc, (TX*)dx, dWg_part, dbg_part)
-    if (ep == 16) EVOMOE_GB(16, 4);
-    else if (ep == 32) EVOMOE_GB(32, 2);
+    if (ep == 16 && cpt == 4) EVOMOE_GB(16, 4);
+    else if (ep == 16 && cpt == 2) EVOMOE_GB(16, 2);
+    else if (ep == 16) EVOMOE_GB(16, 1);
+    else if (ep == 32 && cpt == 2) EVOMOE_GB(32, 2);
+    else if (ep == 32) EVOMOE_GB(32, 1);
     else if (ep == 48) EVOMOE_GB(48, 1);
     else EVOMOE_GB(64, 1);
 #undef EVOMOE_GB
