@@ -41,7 +41,7 @@ DOMINANT_PROFILE_NAME = "grouped_gemm_bf16<2, 4,"
 
 def _gemm_kernels():
     # expert-FFN GEMM launches and how many 2*P*d*F-flop contractions each carries
-    # (ffn_bwd_dw2 is the merged dW2 + dW1 launch; ffn_bwd_dw1 is only the gather of x feeding it)
+    # (ffn_bwd_dw2 is the merged dW2 + dW1 launch; ffn_bwd_dw1 is only the gather of x feeding it, with dO's column sums)
     return {"ffn_gemm1": 1, "ffn_gemm2": 1, "ffn_bwd_dh": 1, "ffn_bwd_dx": 1, "ffn_bwd_dw2": 2}
 
 
@@ -322,11 +322,10 @@ def main():
             "dispatch_hist": T * 8, "dispatch_scatter": T * 12 + Pavg * 16,
             "combine": Pavg * d * sz + T * d * sz + Pavg * 8,
             "combine_bwd": 2 * Pavg * d * sz + T * d * sz + Pavg * 12,
-            "ffn_bwd_dw1": 2 * Pavg * d * sz + Pavg * 4,
-            # bf16 layer: db1 comes from per-tile column sums the dH GEMM leaves behind (two rows of F floats per
-            # 128-row tile, written there, read here); only dO is streamed again
-            "ffn_bwd_db": (Pavg * d * sz + (Pavg / 128 + E) * 2 * F * 4) if cfg.dtype == "bf16"
-                          else Pavg * (F + d) * sz,
+            # bf16 layer: the gather of x and the column sums of dO in one launch (db1 comes from column sums the dH GEMM
+            # leaves behind; the last sums of both bias gradients are part of the weight-gradient launch)
+            "ffn_bwd_dw1": (3 if cfg.dtype == "bf16" else 2) * Pavg * d * sz + Pavg * 4,
+            "ffn_bwd_db": Pavg * (F + d) * sz,
             "dispatch_bwd": Pavg * d * sz + T * d * sz,
             "gate_bwd_dz": T * E * 8 + Pavg * 8 + T * 12,
             "gate_bwd_main": T * d * sz * 3 + T * E * 4,
