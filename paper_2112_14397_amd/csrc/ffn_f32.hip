@@ -251,7 +251,10 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32(F32Pair q, int tiles0, i
         // What the epilogue reads (bias, H, the old gradient) is loaded, at clamped addresses, before its first store.
         const int lim_r = LAYOUT == L_TN ? p.M - m0 : rows;             // rows of the tile that exist
         const int64_t origin = LAYOUT == L_TN ? ((int64_t)g * p.M + m0) * p.N : (int64_t)row0 * p.N;
-        const float* reads = EPI == E_ACTGRAD ? p.Hin + origin : EPI == E_WGRAD && accumulate ? p.out1 + origin : nullptr;
+        // (no old gradient where only the column sums are wanted: null plus an offset is not null)
+        const float* reads = EPI == E_ACTGRAD                            ? p.Hin + origin
+                             : EPI == E_WGRAD && accumulate && p.out1 ? p.out1 + origin
+                                                                      : nullptr;
         auto offset_of = [&](int tr, int n) { return (uint32_t)(min(tr, lim_r - 1) * p.N + min(n, p.N - 1)); };
         auto bias_of = [&](int n) {
             return (EPI == E_HA || EPI == E_BIAS) && p.bias ? p.bias[(int64_t)g * p.N + min(n, p.N - 1)] : 0.f;
