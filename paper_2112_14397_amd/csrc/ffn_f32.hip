@@ -14,7 +14,8 @@
 // where it is the row index; both operands use the same k order, so the order inside a slab is free.
 //
 // Tiles: 64x64 (four waves, 2 x 2), and 32x32 with the slab's k's split over the four waves for launches that would
-// leave most of the chip idle; cheapest() says which and why.
+// leave most of the chip idle; cheapest() says which and why.  Both add the products of one output in the same order, so
+// that results do not depend on the pair count announced, nor on how many rows a call has.
 #include "ffn_internal.h"
 
 namespace evomoe {
@@ -62,26 +63,32 @@ template <int BM> __device__ __forceinline__ Offsets scan_offsets(const int32_t*
     return o;
 }
 
+// Four blocks per CU (128 registers) fill the stalls that one's loads and barriers leave; the act'(H) epilogue spills 19
+// there (d = 256, E = 8, F = 1024, 5626 pairs: 56 us for dH, with three blocks 51), the others nothing.
 template <int LAYOUT, int EPI, int BM, int BN>
-__global__ __launch_bounds__(256) void grouped_gemm_f32(F32Pair q, int tiles0, int tiles_all,
-                                                        const int32_t* __restrict__ expert_offsets, int E, int64_t P_cap,
-                                                        int act, int accumulate)
+__global__ __launch_bounds__(256, EPI == E_ACTGRAD && BM == 64 ? 3 : 4) void grouped_gemm_f32(
+    F32Pair q, int tiles0, int tiles_all, const int32_t* __restrict__ expert_offsets, int E, int64_t P_cap, int act,
+    int accumulate)
 {
     constexpr bool SPLIT = BM == 32;                    // 32x32: the four waves share one tile, a quarter of the k's each
     constexpr int BK = SPLIT ? 64 : 32;
-    constexpr int TM = SPLIT ? 1 : BM / 64, TN_ = SPLIT ? 1 : BN / 64;     // 32x32 MFMA tiles per wave
+    static_assert(BM == BN && (BM == 32 || BM == 64), "tile");
     constexpr bool A_KC = LAYOUT != L_TN, B_KC = LAYOUT == L_NT;
     // LDS rows: [row][BK + 4] (16 lanes' 16-byte reads of one k chunk then cover all 64 banks) or [k][cols + 8]
     // (the two k groups of a 4-byte read lie 32 banks apart)
     constexpr int A_LD = A_KC ? BK + 4 : BM + 8, B_LD = B_KC ? BK + 4 : BN + 8;
     constexpr int A_SZ = A_KC ? BM * A_LD : BK * A_LD, B_SZ = B_KC ? BN * B_LD : BK * B_LD;
     constexpr int A_V = BM * BK / 1024, B_V = BN * BK / 1024;              // 16-byte vectors per thread and slab
-    constexpr int NG = (SPLIT ? BK / 4 : BK) / 8;                          // groups of 8 k's per wave and slab
+    // Groups of 8 k's are dealt round-robin to four partial sums, which are added in order at the end.  In the 32x32 tile
+    // each wave has one of them, in the 64x64 tile every wave has all four for its quarter of the tile: the order of the
+    // additions, and with it every bit of the result, is the same in both.  (One sum per output in the 64x64 tile, as long as
+    // the whole contraction, took 1 % less for the GEMMs and 2-4 % for dXp, and gave other bits than the 32x32 tile.)
+    constexpr int NP = SPLIT ? 1 : 4, NG = BK / 32;                        // partial sums per wave, groups of each per slab
     __shared__ float smem[2 * (A_SZ + B_SZ)];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, kg = lane >> 5;
     const int wm = SPLIT ? 0 : (wave >> 1) * (BM / 2), wn = SPLIT ? 0 : (wave & 1) * (BN / 2);
-    const int wk = SPLIT ? wave * (BK / 4) : 0;
+    const int wk = SPLIT ? wave * 8 : 0;
 
     const Offsets off = scan_offsets<BM>(expert_offsets, E, P_cap, lane);
     const int row_tiles = __builtin_amdgcn_readlane(off.t_end, 63);
@@ -189,13 +196,11 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32(F32Pair q, int tiles0, i
                                                : sb + i / (BN / 4) * B_LD + (i % (BN / 4)) * 4) = rb[v];
             }
         };
-        f32x16 acc[TM][TN_];
+        f32x16 acc[NP];
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int q = 0; q < NP; ++q)
 #pragma unroll
-            for (int j = 0; j < TN_; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
 
         // TN, first column tile: the column sums of L, which sits in LDS anyway (256 / BM threads per column)
         const bool sums = LAYOUT == L_TN && p.db && n0 == 0;
@@ -213,28 +218,16 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32(F32Pair q, int tiles0, i
             const float* sb = sa + A_SZ;
             if (s + 1 < nslab) fetch(kbeg + (s + 1) * BK);
 #pragma unroll
-            for (int gk = 0; gk < NG; ++gk) {
-                const int k = wk + gk * 8 + kg * 4;
-                f32x4 fa[TM], fb[TN_];
-#pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    const int m = wm + i * 32 + l32;
-                    if (A_KC) fa[i] = *reinterpret_cast<const f32x4*>(sa + m * A_LD + k);
-                    else fa[i] = f32x4{sa[k * A_LD + m], sa[(k + 1) * A_LD + m], sa[(k + 2) * A_LD + m], sa[(k + 3) * A_LD + m]};
-                }
-#pragma unroll
-                for (int j = 0; j < TN_; ++j) {
-                    const int n = wn + j * 32 + l32;
-                    if (B_KC) fb[j] = *reinterpret_cast<const f32x4*>(sb + n * B_LD + k);
-                    else fb[j] = f32x4{sb[k * B_LD + n], sb[(k + 1) * B_LD + n], sb[(k + 2) * B_LD + n], sb[(k + 3) * B_LD + n]};
-                }
+            for (int gk = 0; gk < NG * NP; ++gk) {
+                const int k = wk + gk * (SPLIT ? 32 : 8) + kg * 4, m = wm + l32, n = wn + l32;
+                f32x4 fa, fb;
+                if (A_KC) fa = *reinterpret_cast<const f32x4*>(sa + m * A_LD + k);
+                else fa = f32x4{sa[k * A_LD + m], sa[(k + 1) * A_LD + m], sa[(k + 2) * A_LD + m], sa[(k + 3) * A_LD + m]};
+                if (B_KC) fb = *reinterpret_cast<const f32x4*>(sb + n * B_LD + k);
+                else fb = f32x4{sb[k * B_LD + n], sb[(k + 1) * B_LD + n], sb[(k + 2) * B_LD + n], sb[(k + 3) * B_LD + n]};
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN_; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][u], fb[j][u], acc[i][j], 0, 0, 0);
+                    acc[gk % NP] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u], fb[u], acc[gk % NP], 0, 0, 0);
             }
             if (sums) {
 #pragma unroll
@@ -249,6 +242,10 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32(F32Pair q, int tiles0, i
 
         // ---------------- epilogue ----------------
         // What the epilogue reads (bias, H, the old gradient) is loaded, at clamped addresses, before its first store.
+        // Its lane constants come from an opaque copy of the lane number: they are not carried through the main loop.
+        int lane_e = tid & 63;
+        asm volatile("" : "+v"(lane_e));
+        const int l32e = lane_e & 31, rowe = wm + 4 * (lane_e >> 5);
         const int lim_r = LAYOUT == L_TN ? p.M - m0 : rows;             // rows of the tile that exist
         const int64_t origin = LAYOUT == L_TN ? ((int64_t)g * p.M + m0) * p.N : (int64_t)row0 * p.N;
         // (no old gradient where only the column sums are wanted: null plus an offset is not null)
@@ -275,7 +272,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32(F32Pair q, int tiles0, i
             constexpr int LD = 36;
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                smem[(wave * 32 + 8 * (r >> 2) + 4 * kg + (r & 3)) * LD + l32] = acc[0][0][r];
+                smem[(wave * 32 + 8 * (r >> 2) + 4 * kg + (r & 3)) * LD + l32] = acc[0][r];
             const float bias = bias_of(n0 + l32);
             float old[4];
 #pragma unroll
@@ -291,22 +288,19 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32(F32Pair q, int tiles0, i
             }
             __syncthreads();
         } else {
-            float bias[TN_];
+            const int n = n0 + wn + l32e;
+            float sum[16], old[16];
 #pragma unroll
-            for (int j = 0; j < TN_; ++j) bias[j] = bias_of(n0 + wn + j * 32 + l32);
+            for (int r = 0; r < 16; ++r) {
+                sum[r] = 0.f;
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+                for (int q = 0; q < NP; ++q) sum[r] += acc[q][r];
+            }
+            const float bias = bias_of(n);
 #pragma unroll
-                for (int j = 0; j < TN_; ++j) {
-                    const int n = n0 + wn + j * 32 + l32;
-                    float old[16];
+            for (int r = 0; r < 16; ++r) old[r] = reads ? reads[offset_of(rowe + 8 * (r >> 2) + (r & 3), n)] : 0.f;
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        old[r] = reads ? reads[offset_of(wm + i * 32 + 8 * (r >> 2) + 4 * kg + (r & 3), n)] : 0.f;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        finish(wm + i * 32 + 8 * (r >> 2) + 4 * kg + (r & 3), n, acc[i][j][r], bias[j], old[r]);
-                }
+            for (int r = 0; r < 16; ++r) finish(rowe + 8 * (r >> 2) + (r & 3), n, sum[r], bias, old[r]);
         }
         if (sums) {                                              // block-uniform
             smem[tid] = colsum;
