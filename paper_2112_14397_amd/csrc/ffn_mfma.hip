@@ -606,7 +606,15 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                 bias8[4] = b1.x; bias8[5] = b1.y; bias8[6] = b1.z; bias8[7] = b1.w;
             }
         }
-        // E_ACTGRAD: column sums of the tile's valid rows (the bias gradient's share of this tile), f32
+        // E_ACTGRAD: column sums of the tile's valid rows (the bias gradient's share of this tile), f32.  Every tile adds
+        // the 64 rows behind one row of the partial table in the same order -- rows 4 apart one after another, then
+        // (0 + 1) + (2 + 3) -- so that the bias gradient does not depend on the tile that was picked.  Waves of 64 rows by
+        // 128 columns meet their rows in that order and add in registers.  Where a lane's next row is 8 further on (64 columns),
+        // the row in between lies in the wave's other half: exchanging halves gives each half four of the columns, with all
+        // its rows (128x128 tile, 11000 pairs, d = 768, F = 3072: 96 us, through LDS 99.6).  Waves of 32 rows, two to a row
+        // of the table, leave the finished values in the staging rows, and one of the two adds from there.
+        constexpr bool SUM_REGS = WM >= 64 && RPI == 4, SUM_HALVES = WM >= 64 && RPI == 8;
+        static_assert(EPI != E_ACTGRAD || SUM_REGS || SUM_HALVES || WM == ER, "column sums: one pass");
         float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int pass = 0; pass < WM / ER; ++pass) {
@@ -676,8 +684,21 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                             for (int q = 0; q < 8; ++q) v[q] *= sc * act_grad_fast(h[q], EVOMOE_GELU_ERF);
                         }
                         const float rv = trow < rows ? 1.f : 0.f;     // rows beyond the tile repeat its last row
+                        if (SUM_REGS) {
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) cs[q] = fmaf(v[q], rv, cs[q]);
+                            for (int q = 0; q < 8; ++q) cs[q] = fmaf(v[q], rv, cs[q]);
+                        } else if (SUM_HALVES) {
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[q] * rv),
+                                                                                __float_as_uint(v[q + 4] * rv), false, false);
+                                cs[q] = (cs[q] + __uint_as_float(w[0])) + __uint_as_float(w[1]);
+                            }
+                        } else if (p.colpart) {
+                            float* keep = stg + lr * G::EPI_LD + lc;
+                            *reinterpret_cast<f32x4*>(keep) = f32x4{v[0] * rv, v[1] * rv, v[2] * rv, v[3] * rv};
+                            *reinterpret_cast<f32x4*>(keep + 4) = f32x4{v[4] * rv, v[5] * rv, v[6] * rv, v[7] * rv};
+                        }
                     }
                     if (ok) store_out(p.out1 + grow * p.N + col_c, v);
                     if (EPI == E_HA) {
@@ -696,31 +717,47 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
             __builtin_amdgcn_wave_barrier();
         }
         if (EPI == E_ACTGRAD && LAYOUT != L_TN) {
-            // the RPI lane groups hold different rows of the same columns: add them up, lane group 0 writes
-            // this wave's sums (rows wm*WM .. +WM-1 of the tile) as one row of the partial table
             if (p.colpart) {
+                const int rt = tstart[g] + (row0 - offs[g]) / BM;
+                float* dst = p.colpart + ((int64_t)rt * G::PARTS + (WM >= 64 ? wm : wm >> 1)) * p.N;
+                if (SUM_REGS) {
+                    // the four lane groups hold different rows of the same columns: add them up, lane group 0 writes
+                    // this wave's sums (rows wm*WM .. +WM-1 of the tile) as one row of the partial table
 #pragma unroll
-                for (int o = CPW; o < 64; o <<= 1)
+                    for (int o = CPW; o < 64; o <<= 1)
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) cs[q] += __shfl_xor(cs[q], o, 64);
-                if (WM == 32) {         // two waves share a table row: the upper one hands its sums over through LDS
-                    float* pass_on = reinterpret_cast<float*>(smem) + ((wave >> 2) * 2 + wn) * WN;
-                    block_sync_lds();
-                    if ((wm & 1) && lane < CPW) {
-                        *reinterpret_cast<f32x4*>(pass_on + lc) = f32x4{cs[0], cs[1], cs[2], cs[3]};
-                        *reinterpret_cast<f32x4*>(pass_on + lc + 4) = f32x4{cs[4], cs[5], cs[6], cs[7]};
+                        for (int q = 0; q < 8; ++q) cs[q] += __shfl_xor(cs[q], o, 64);
+                    if (lane < CPW && col < p.N) {
+                        *reinterpret_cast<f32x4*>(dst + col_c) = f32x4{cs[0], cs[1], cs[2], cs[3]};
+                        *reinterpret_cast<f32x4*>(dst + col_c + 4) = f32x4{cs[4], cs[5], cs[6], cs[7]};
                     }
-                    block_sync_lds();
-                    if (!(wm & 1) && lane < CPW) {
+                } else if (SUM_HALVES) {
+                    const int half = (lane >> 5) * 4;             // columns 0..3 of the lane's eight, or 4..7
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) cs[q] += pass_on[lc + q];
+                    for (int o = CPW; o < 32; o <<= 1)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) cs[q] += __shfl_xor(cs[q], o, 64);
+                    if ((lane & 31) < CPW && col < p.N)
+                        *reinterpret_cast<f32x4*>(dst + col_c + half) = f32x4{cs[0], cs[1], cs[2], cs[3]};
+                } else {
+                    // lane = (chain, four columns); the upper wave's rows lie further on in the staging area
+                    constexpr int CL = WN / 4;
+                    const int chain = lane / CL, c4 = lane % CL * 4, n = n0 + wn * WN + c4;
+                    block_sync_lds();
+                    if (chain < 4 && !(wm & 1)) {
+                        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) {
+                            const int wave_of = i * 4 / WM;       // 1: the wave two further on (wave = 2 wm + wn)
+                            sum += *reinterpret_cast<const f32x4*>(
+                                stg + (wave_of * 2 * ER + i * 4 % WM + chain) * G::EPI_LD + c4);
+                        }
+#pragma unroll
+                        for (int o = CL; o < 4 * CL; o <<= 1)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) sum[q] += __shfl_xor(sum[q], o, 64);
+                        if (chain == 0 && n < p.N) *reinterpret_cast<f32x4*>(dst + n) = sum;
                     }
-                }
-                if (lane < CPW && col < p.N && (WM >= 64 || !(wm & 1))) {
-                    const int rt = tstart[g] + (row0 - offs[g]) / BM;
-                    float* dst = p.colpart + ((int64_t)rt * G::PARTS + (WM >= 64 ? wm : wm >> 1)) * p.N + col_c;
-                    *reinterpret_cast<f32x4*>(dst) = f32x4{cs[0], cs[1], cs[2], cs[3]};
-                    *reinterpret_cast<f32x4*>(dst + 4) = f32x4{cs[4], cs[5], cs[6], cs[7]};
                 }
             }
         }

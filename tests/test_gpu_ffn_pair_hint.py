@@ -10,6 +10,8 @@ import synth_inputs as synth  # noqa: E402
 CASES = {
     "f32": [(1900, 508, 3, 508, 1900, (0, 1, 900)),
             (300, 68, 4, 132, 300, (0, 1))],
+    "bf16": [(1900, 776, 3, 520, 200000, (0, 1, 600, 1900, 8000, 40000, 120000)),
+             (700, 136, 5, 264, 50000, (0, 1, 700, 9000))],
 }
 
 
