@@ -66,6 +66,7 @@ __global__ __launch_bounds__(256) void gather_colsum_kernel(
 }
 
 size_t colsum_scratch_bytes(const evomoe_shape& s) {
+    if (s.dtype != EVOMOE_BF16) return ((size_t)kF32ColsumSplit * s.E * (s.d + s.F) * sizeof(float) + 255) & ~(size_t)255;
     return (((size_t)kColsumSplit * s.E * (s.d > s.F ? s.d : s.F) * sizeof(float) + 255) & ~(size_t)255) +
            dh_colpart_bytes(s);
 }

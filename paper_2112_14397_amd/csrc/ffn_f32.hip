@@ -8,8 +8,8 @@
 // What bounds it: the float32 matrix rate (256 flop per clock and CU, a sixteenth of bf16's), so neither LDS nor L2
 // needs more than plain double buffering: global -> registers -> LDS one slab ahead, several blocks per CU.  GEMM1 of
 // 11160 pairs, d = 512, F = 2048: 97 TFLOP/s; a 4096^3 library product reaches 137 on the same card, the float32-FMA
-// kernels that stood here before 25.  The weight-gradient launch also sums the columns of its left operand (the bias
-// gradients), which lies in LDS anyway.
+// kernels that stood here before 25.  The bias gradients' column sums are further tiles behind dXp's and behind the weight
+// gradients': colsum_tile().
 // A lane's four k's of one fragment come from one 16-byte LDS read where k is contiguous and from four 4-byte reads
 // where it is the row index; both operands use the same k order, so the order inside a slab is free.
 //
@@ -33,9 +33,8 @@ struct F32Args {
     int M, N, K;                        // M: TN only.  K: NT/NN only
     const float* bias;                  // [E,N] or null
     const float* Hin;                   // E_ACTGRAD: pre-activations [P,N]
-    float* out1;                        // C (H for E_HA); TN: null = only db is wanted
+    float* out1;                        // C (H for E_HA)
     float* out2;                        // E_HA: act(H)
-    float* db;                          // TN: [E,M] column sums of L, or null
 };
 
 struct F32Pair { F32Args p[2]; };       // TN: two problems in one launch; NT/NN use the first
@@ -47,6 +46,73 @@ struct Offsets {
     int begin, count;                   // of the lane's expert
     int t_end, t_begin;                 // its row tiles [t_begin, t_end)
 };
+// Column sums of dO and dH over every expert's rows (the bias gradients).  The dXp launch leaves part[split][expert][column]
+// of both matrices, the weight-gradient launch adds the splits in order.
+// An expert of n rows is cut into ceil(n / 64) ranges, kSumSplit at most: a block's loads for one of 64 rows go out together.
+// Sums inside the weight-gradient tiles, whose left operand the matrices are, cost no extra pass, but there every row of an
+// expert passes through one block: a backward with the bias gradients alone took 220 us at d = 64, E = 1, F = 256, 16384
+// pairs (now 41, without them 34), and chains of 4096 additions had eight times the error (1.1e-6 relative rms; now 1.3e-7).
+constexpr int kSumSplit = kF32ColsumSplit, kSumCols = 128;
+struct F32Sums {
+    const float* m[2];                  // dO [P,N0], dH [P,N1]
+    int N[2], blocks[2];                // columns; column blocks (0: not wanted)
+    float* part[2];                     // [kSumSplit][E][N]
+    float* db[2];                       // [E,N]
+};
+__device__ __forceinline__ int sum_splits(int rows) { return max(1, min(kSumSplit, (rows + 63) / 64)); }
+
+// Tile b of the first pass: (split, expert, column block).
+__device__ __forceinline__ void colsum_tile(const F32Sums& q, int b, const Offsets& off, int E, float* red) {
+    const int nb = q.blocks[0] + q.blocks[1];
+    const int g = b / nb % E, split = b / nb / E, i = b % nb >= q.blocks[0];
+    const int begin = __builtin_amdgcn_readlane(off.begin, g), count = __builtin_amdgcn_readlane(off.count, g);
+    const int splits = sum_splits(count);
+    if (split >= splits) return;                                  // block-uniform
+    const int N = q.N[i], n0 = (b % nb - (i ? q.blocks[0] : 0)) * kSumCols;
+    const int CL = min(kSumCols, N) / 4, RL = min(32, 256 / CL);  // column lanes (16 bytes each), row lanes
+    const int cl = threadIdx.x % CL, rl = threadIdx.x / CL, n = n0 + cl * 4;
+    const int per = (count + splits - 1) / splits, rb = begin + split * per, re = min(begin + count, rb + per);
+    const bool on = rl < RL && n < N;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    if (on) {
+        const float* src = q.m[i] + n;
+        for (int r = rb + rl; r < re; r += 8 * RL) {
+            f32x4 v[8], t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f32x4*>(src + (int64_t)min(r + u * RL, re - 1) * N);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (r + u * RL < re) t += v[u];
+            sum += t;
+        }
+        *reinterpret_cast<f32x4*>(red + (rl * CL + cl) * 4) = sum;
+    }
+    __syncthreads();
+    if (rl == 0 && n < N) {
+        sum = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int l = 0; l < RL; ++l) sum += *reinterpret_cast<const f32x4*>(red + (l * CL + cl) * 4);
+        *reinterpret_cast<f32x4*>(q.part[i] + ((int64_t)split * E + g) * N + n) = sum;
+    }
+    __syncthreads();
+}
+// Second pass: column i of both matrices' E * N.
+__device__ __forceinline__ void colsum_final(const F32Sums& q, int64_t i, const int32_t* expert_offsets, int E, int64_t P_cap,
+                                             int accumulate) {
+    const int64_t n0 = q.blocks[0] ? (int64_t)E * q.N[0] : 0;
+    const int k = i >= n0;
+    const int64_t j = k ? i - n0 : i, stride = (int64_t)E * q.N[k];
+    const int g = (int)(j / q.N[k]);
+    const int splits = sum_splits(clamp_pairs(expert_offsets[g + 1], P_cap) - clamp_pairs(expert_offsets[g], P_cap));
+    float v[kSumSplit], s = 0.f;
+    const float old = accumulate ? q.db[k][j] : 0.f;
+#pragma unroll
+    for (int u = 0; u < kSumSplit; ++u) v[u] = q.part[k][(int64_t)min(u, splits - 1) * stride + j];
+#pragma unroll
+    for (int u = 0; u < kSumSplit; ++u)
+        if (u < splits) s += v[u];
+    q.db[k][j] = accumulate ? old + s : s;
+}
+
 template <int BM> __device__ __forceinline__ Offsets scan_offsets(const int32_t* expert_offsets, int E, int64_t P_cap, int lane) {
     Offsets o;
     o.begin = lane < E ? clamp_pairs(expert_offsets[lane], P_cap) : 0;
@@ -67,8 +133,8 @@ template <int BM> __device__ __forceinline__ Offsets scan_offsets(const int32_t*
 // there (d = 256, E = 8, F = 1024, 5626 pairs: 56 us for dH, with three blocks 51), the others nothing.
 template <int LAYOUT, int EPI, int BM, int BN>
 __global__ __launch_bounds__(256, EPI == E_ACTGRAD && BM == 64 ? 3 : 4) void grouped_gemm_f32(
-    F32Pair q, int tiles0, int tiles_all, const int32_t* __restrict__ expert_offsets, int E, int64_t P_cap, int act,
-    int accumulate)
+    F32Pair q, int tiles0, int tiles_all, F32Sums sums, const int32_t* __restrict__ expert_offsets, int E, int64_t P_cap,
+    int act, int accumulate)
 {
     constexpr bool SPLIT = BM == 32;                    // 32x32: the four waves share one tile, a quarter of the k's each
     constexpr int BK = SPLIT ? 64 : 32;
@@ -202,11 +268,6 @@ __global__ __launch_bounds__(256, EPI == E_ACTGRAD && BM == 64 ? 3 : 4) void gro
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
 
-        // TN, first column tile: the column sums of L, which sits in LDS anyway (256 / BM threads per column)
-        const bool sums = LAYOUT == L_TN && p.db && n0 == 0;
-        constexpr int KP = 256 / BM;
-        float colsum = 0.f;
-
         if (nslab > 0) {
             if (gathered) fetch_rows(kbeg);
             fetch(kbeg);
@@ -229,10 +290,6 @@ __global__ __launch_bounds__(256, EPI == E_ACTGRAD && BM == 64 ? 3 : 4) void gro
                 for (int u = 0; u < 4; ++u)
                     acc[gk % NP] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u], fb[u], acc[gk % NP], 0, 0, 0);
             }
-            if (sums) {
-#pragma unroll
-                for (int k = 0; k < BK / KP; ++k) colsum += sa[(tid / BM * (BK / KP) + k) * A_LD + tid % BM];
-            }
             if (s + 1 < nslab) {
                 float* na = smem + ((s + 1) & 1) * (A_SZ + B_SZ);
                 place(na, na + A_SZ);
@@ -248,10 +305,7 @@ __global__ __launch_bounds__(256, EPI == E_ACTGRAD && BM == 64 ? 3 : 4) void gro
         const int l32e = lane_e & 31, rowe = wm + 4 * (lane_e >> 5);
         const int lim_r = LAYOUT == L_TN ? p.M - m0 : rows;             // rows of the tile that exist
         const int64_t origin = LAYOUT == L_TN ? ((int64_t)g * p.M + m0) * p.N : (int64_t)row0 * p.N;
-        // (no old gradient where only the column sums are wanted: null plus an offset is not null)
-        const float* reads = EPI == E_ACTGRAD                            ? p.Hin + origin
-                             : EPI == E_WGRAD && accumulate && p.out1 ? p.out1 + origin
-                                                                      : nullptr;
+        const float* reads = EPI == E_ACTGRAD ? p.Hin + origin : EPI == E_WGRAD && accumulate ? p.out1 + origin : nullptr;
         auto offset_of = [&](int tr, int n) { return (uint32_t)(min(tr, lim_r - 1) * p.N + min(n, p.N - 1)); };
         auto bias_of = [&](int n) {
             return (EPI == E_HA || EPI == E_BIAS) && p.bias ? p.bias[(int64_t)g * p.N + min(n, p.N - 1)] : 0.f;
@@ -262,7 +316,7 @@ __global__ __launch_bounds__(256, EPI == E_ACTGRAD && BM == 64 ? 3 : 4) void gro
             if (EPI == E_WGRAD && accumulate) v += old;
             const float a = EPI == E_HA ? act_fwd(v, act) : 0.f;
             const uint32_t o = offset_of(tr, n);
-            if (tr < lim_r && n < p.N && (EPI != E_WGRAD || p.out1)) {
+            if (tr < lim_r && n < p.N) {
                 p.out1[origin + o] = v;
                 if (EPI == E_HA) p.out2[origin + o] = a;
             }
@@ -302,18 +356,17 @@ __global__ __launch_bounds__(256, EPI == E_ACTGRAD && BM == 64 ? 3 : 4) void gro
 #pragma unroll
             for (int r = 0; r < 16; ++r) finish(rowe + 8 * (r >> 2) + (r & 3), n, sum[r], bias, old[r]);
         }
-        if (sums) {                                              // block-uniform
-            smem[tid] = colsum;
-            __syncthreads();
-            if (tid < BM && m0 + tid < p.M) {
-                float v = 0.f;
-#pragma unroll
-                for (int q = 0; q < KP; ++q) v += smem[q * BM + tid];
-                float* o = p.db + (int64_t)g * p.M + m0 + tid;
-                *o = accumulate ? *o + v : v;
-            }
-            __syncthreads();
-        }
+    }
+    // the column sums, dealt from the last block on: those have a tile less, or none
+    if (EPI == E_NONE) {
+        const int tiles = kSumSplit * E * (sums.blocks[0] + sums.blocks[1]);
+        if (tiles) __syncthreads();
+        for (int b = gridDim.x - 1 - blockIdx.x; b < tiles; b += gridDim.x) colsum_tile(sums, b, off, E, smem);
+    }
+    if (LAYOUT == L_TN) {
+        const int64_t n = (int64_t)E * ((sums.blocks[0] ? sums.N[0] : 0) + (sums.blocks[1] ? sums.N[1] : 0));
+        for (int64_t i = (int64_t)(gridDim.x - 1 - blockIdx.x) * 256 + tid; i < n; i += (int64_t)gridDim.x * 256)
+            colsum_final(sums, i, expert_offsets, E, P_cap, accumulate);
     }
 }
 
@@ -331,22 +384,25 @@ Tile cheapest(const Ctx& c, int64_t t64, int64_t t32) {
 
 template <int LAYOUT, int EPI, int B>
 hipError_t launch(const Ctx& c, const evomoe_shape& s, const F32Args& a, int64_t t0, const F32Args& b, int64_t t1,
-                  const int32_t* expert_offsets, int accumulate) {
-    const int64_t cap = (int64_t)c.num_cu * 4, want = (t0 + t1 + 7) / 8 * 8;
+                  const F32Sums& sums, int64_t sum_tiles, const int32_t* expert_offsets, int accumulate) {
+    const int64_t cap = (int64_t)c.num_cu * 4, want = (t0 + t1 + sum_tiles + 7) / 8 * 8;
     hipLaunchKernelGGL((grouped_gemm_f32<LAYOUT, EPI, B, B>), dim3((unsigned)(want < cap ? want : cap)), dim3(256), 0,
-                       c.stream, F32Pair{{a, b}}, (int)t0, (int)(t0 + t1), expert_offsets, s.E, s.P_cap, s.act, accumulate);
+                       c.stream, F32Pair{{a, b}}, (int)t0, (int)(t0 + t1), sums, expert_offsets, s.E, s.P_cap, s.act,
+                       accumulate);
     return hipGetLastError();
 }
 
 // NT / NN: one problem over the row tiles of all experts
 template <int LAYOUT, int EPI>
-hipError_t launch_rows(const Ctx& c, const evomoe_shape& s, const F32Args& a, const int32_t* expert_offsets) {
+hipError_t launch_rows(const Ctx& c, const evomoe_shape& s, const F32Args& a, const int32_t* expert_offsets,
+                       const F32Sums& sums = F32Sums{}) {
     const int64_t P = c.pair_hint > 0 && c.pair_hint < s.P_cap ? c.pair_hint : s.P_cap;
     auto expected = [&](int b) { return tiles_of((P + b - 1) / b + s.E / 2, a.N, b); };
     auto worst = [&](int b) { return tiles_of((s.P_cap + b - 1) / b + s.E, a.N, b); };
+    const int64_t st = (int64_t)kSumSplit * s.E * (sums.blocks[0] + sums.blocks[1]);
     if (cheapest(c, expected(64), expected(32)) == Tile::T64)
-        return launch<LAYOUT, EPI, 64>(c, s, a, worst(64), a, 0, expert_offsets, 0);
-    return launch<LAYOUT, EPI, 32>(c, s, a, worst(32), a, 0, expert_offsets, 0);
+        return launch<LAYOUT, EPI, 64>(c, s, a, worst(64), a, 0, sums, st, expert_offsets, 0);
+    return launch<LAYOUT, EPI, 32>(c, s, a, worst(32), a, 0, sums, st, expert_offsets, 0);
 }
 
 }  // namespace
@@ -386,36 +442,41 @@ hipError_t f32_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, cons
         err = launch_rows<L_NN, E_ACTGRAD>(c, s, a, expert_offsets);
         if (err != hipSuccess) return err;
     }
+    // db2 = column sums of dO, db1 = column sums of dH
+    F32Sums sums{};
+    float* part = reinterpret_cast<float*>(static_cast<char*>(dH) + dh_bytes(s));
+    sums.m[0] = (const float*)dO; sums.N[0] = s.d; sums.db[0] = db2; sums.part[0] = part;
+    sums.m[1] = (const float*)dH; sums.N[1] = s.F; sums.db[1] = db1; sums.part[1] = part + (size_t)kSumSplit * s.E * s.d;
+    for (int i = 0; i < 2; ++i) sums.blocks[i] = sums.db[i] ? (sums.N[i] + kSumCols - 1) / kSumCols : 0;
     {   // dXp = dH W1
         ProfScope ps(c, EVOMOE_K_FFN_BWD_DX);
         F32Args a{};
         a.A = (const float*)dH; a.lda = s.F; a.B = (const float*)W1; a.ldb = s.d;
         a.b_group_stride = (int64_t)s.F * s.d; a.N = s.d; a.K = s.F; a.out1 = (float*)dXp;
-        err = launch_rows<L_NN, E_NONE>(c, s, a, expert_offsets);
+        err = launch_rows<L_NN, E_NONE>(c, s, a, expert_offsets, sums);
         if (err != hipSuccess) return err;
     }
-    // dW2_g = dO_g^T A_g [d,F] (and db2 = column sums of dO), dW1_g = dH_g^T X_g [F,d] (and db1 = column sums of dH):
-    // one launch over both problems' tiles.  A bias gradient alone takes the same launch with one column tile, whose
-    // products are not stored; the tile size does not depend on what is asked for, so the sums' order does not either.
+    // dW2_g = dO_g^T A_g [d,F], dW1_g = dH_g^T X_g [F,d]: one launch over both problems' tiles.  The tile size does not
+    // depend on which of them are wanted.
     F32Args w[2]{};
     int n = 0;
-    auto add = [&](const void* L, int M, const void* R, int N, const int32_t* rows, void* dW, float* db) {
-        if (!dW && !db) return;
+    auto add = [&](const void* L, int M, const void* R, int N, const int32_t* rows, void* dW) {
+        if (!dW) return;
         F32Args& a = w[n++];
-        a.A = (const float*)L; a.lda = M; a.M = M; a.B = (const float*)R; a.ldb = N; a.N = dW ? N : 4; a.rows = rows;
-        a.out1 = (float*)dW; a.db = db;
+        a.A = (const float*)L; a.lda = M; a.M = M; a.B = (const float*)R; a.ldb = N; a.N = N; a.rows = rows;
+        a.out1 = (float*)dW;
     };
-    add(dO, s.d, A, s.F, nullptr, dW2, db2);
-    add(dH, s.F, x, s.d, pair_token, dW1, db1);
-    if (n == 0) return hipSuccess;
+    add(dO, s.d, A, s.F, nullptr, dW2);
+    add(dH, s.F, x, s.d, pair_token, dW1);
+    const int64_t st = ((int64_t)s.E * ((db2 ? s.d : 0) + (db1 ? s.F : 0)) + 255) / 256;
+    if (n == 0 && st == 0) return hipSuccess;
     ProfScope ps(c, dW2 ? EVOMOE_K_FFN_BWD_DW2 : dW1 ? EVOMOE_K_FFN_BWD_DW1 : EVOMOE_K_FFN_BWD_DB);
-    auto tiles = [&](const F32Args& a, int b) { return (int64_t)s.E * ((a.M + b - 1) / b) * ((a.N + b - 1) / b); };
-    auto both = [&](int b) { return 2 * (int64_t)s.E * ((s.d + b - 1) / b) * ((s.F + b - 1) / b); };
-    if (cheapest(c, both(64), both(32)) == Tile::T64)
-        return launch<L_TN, E_WGRAD, 64>(c, s, w[0], tiles(w[0], 64), w[1], n > 1 ? tiles(w[1], 64) : 0, expert_offsets,
-                                         accumulate);
-    return launch<L_TN, E_WGRAD, 32>(c, s, w[0], tiles(w[0], 32), w[1], n > 1 ? tiles(w[1], 32) : 0, expert_offsets,
-                                     accumulate);
+    auto tiles = [&](int b) { return (int64_t)s.E * ((s.d + b - 1) / b) * ((s.F + b - 1) / b); };     // of either problem
+    auto run = [&](auto launcher, int b) {
+        return launcher(c, s, w[0], n > 0 ? tiles(b) : 0, w[1], n > 1 ? tiles(b) : 0, sums, st, expert_offsets, accumulate);
+    };
+    return cheapest(c, 2 * tiles(64), 2 * tiles(32)) == Tile::T64 ? run(launch<L_TN, E_WGRAD, 64>, 64)
+                                                                  : run(launch<L_TN, E_WGRAD, 32>, 32);
 }
 
 }  // namespace evomoe

@@ -12,13 +12,16 @@ hipError_t f32_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, cons
                        const void* x, const int32_t* pair_token, const int32_t* expert_offsets, const void* W1,
                        const void* W2, void* dW1, float* db1, void* dW2, float* db2, void* dXp, int accumulate,
                        void* dH);
-// the streaming column sums split every expert's rows into this many ranges: part[split][g][n], added in order
+// the float32 layer's column sums: row ranges per expert (at most)
+constexpr int kF32ColsumSplit = 16;
+// the bf16 layer's streaming column sums split every expert's rows into this many ranges: part[split][g][n], added in order
 constexpr int kColsumSplit = 32;
 // leaves part[kColsumSplit][E][N] of the bf16 matrix Mx [P,N] in scratch and the rows x[pair_token[r]] in x_perm (either
 // one is left out if Mx or x is null)
 hipError_t launch_gather_colsum(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token, void* x_perm,
                                 const void* Mx, int N, const int32_t* expert_offsets, float* scratch);
-// [partials of the streaming column sums][bf16 layer: per-tile column sums of dH]; a multiple of 256
+// bf16 layer: [partials of the streaming column sums][per-tile column sums of dH]; float32 layer: partial column sums of dO
+// and of dH; a multiple of 256
 size_t colsum_scratch_bytes(const evomoe_shape& s);
 size_t dh_colpart_bytes(const evomoe_shape& s);       // the second part alone (0 for a float32 layer)
 // the backward workspace is [dH : P_cap x F elements, rounded up to 256 B][bias-gradient partial sums]

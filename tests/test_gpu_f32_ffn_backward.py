@@ -1,4 +1,4 @@
-"""The float32 expert FFN's backward with some of its outputs left out, accumulating into the others."""
+"""The float32 expert FFN's backward: some of its outputs left out, accumulating into the others, and its bias gradients' error."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -30,3 +30,25 @@ def test_f32_gradients_accumulate_with_others_left_out(keep):
     torch.cuda.synchronize()
     for n in keep:
         assert torch.equal(got[n], 2 * getattr(b, n)), n
+
+
+@pytest.mark.parametrize("T,d,F", [(16384, 64, 64), (700, 64, 64), (16384, 256, 1024)])
+def test_f32_bias_gradients_are_summed_in_short_chains(T, d, F):
+    """A chain of n additions of N(0,1) values has a relative error of about 2.5e-8 sqrt(n / 2) (rounding errors of 0.42 * 2^-24
+    of the running sum each); levels of chains add up under the root.  Chains of 8, 32, 16 and 8 terms, what one expert's
+    16384 rows take at most, make 1.4e-7, twice that is the bound.  One chain of 4096 terms would be at 1.1e-6."""
+    import torch
+    h, gl = _layer(T, d, 1, F, threshold=0.9)
+    assert gl.forward(1.0, 0.9) == T
+    gl.backward(1.0)
+    b, p, B = gl.buf, gl.params, h.B
+    dO = torch.randn(T, d, generator=torch.Generator("cuda").manual_seed(5), device="cuda")
+    B.evomoe_expert_ffn_bwd(gl.ctx, gl.shape, dO, b.H, b.A, gl.x, b.pair_token, b.expert_offsets, p.W1, p.W2, None, None,
+                            b.dW1, b.db1, b.dW2, b.db2, b.dXp, False, b.workspace)
+    dH = b.workspace[:T * F * 4].view(torch.float32).view(T, F)        # the workspace begins with dH
+    for what, got, rows in (("db2", b.db2, dO), ("db1", b.db1, dH)):
+        want = rows.double().sum(0)
+        scale = (rows.double() ** 2).sum(0).sqrt()                     # what the sum is worth if its terms are independent
+        err = (((got[0].double() - want) / scale) ** 2).mean().sqrt().item()
+        print(what, T, d, F, f"{err:.3g}")
+        assert err <= 2.8e-7, (what, err)
