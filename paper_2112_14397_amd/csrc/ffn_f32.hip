@@ -196,7 +196,8 @@ __global__ __launch_bounds__(256, EPI == E_ACTGRAD && BM == 64 ? 3 : 4) void gro
 
         // This thread's share of a slab: vector v of an operand is number tid + 256 v of the slab's 16-byte pieces.
         // Rows and columns outside the tile are clamped onto valid ones (their products are never stored), k's outside
-        // the contraction range too; A is zero there.  No load sits in a branch, so a slab's loads go out together.
+        // the contraction range too; both operands are zero there (0 times an infinity in the clamped element of the other
+        // would be NaN).  No load sits in a branch, so a slab's loads go out together.
         const float* arow[A_V];
         const float* brow[B_V];
         int bidx[B_V];                                          // TN with gathered R rows: the next slab's row numbers
@@ -245,6 +246,11 @@ __global__ __launch_bounds__(256, EPI == E_ACTGRAD && BM == 64 ? 3 : 4) void gro
                 for (int v = 0; v < A_V; ++v) {
                     const int i = tid + 256 * v;
                     if (k0 + (A_KC ? (i % (BK / 4)) * 4 : i / (BM / 4)) >= kend) ra[v] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+#pragma unroll
+                for (int v = 0; v < B_V; ++v) {
+                    const int i = tid + 256 * v;
+                    if (k0 + (B_KC ? (i % (BK / 4)) * 4 : i / (BN / 4)) >= kend) rb[v] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
             }
         };
