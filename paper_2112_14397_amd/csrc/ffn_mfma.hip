@@ -357,7 +357,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
 
         // ---------------- global addresses: one scalar base per operand + 32-bit per-lane byte offsets ----
         // Rows / columns outside the tile are clamped onto valid ones (their products are never stored);
-        // the tail of the contraction range is clamped too and then zeroed in LDS (A operand only).
+        // the tail of the contraction range is clamped too and then zeroed in LDS.
         // k-contiguous operand: offset of (row, chunk) at k = 0, one register per load instruction.
         // k-strided operand   : offset = k-row * row bytes + column bytes; every load instruction of a lane
         //                       has the same column, its k-row is kr0 + a constant.
@@ -418,12 +418,14 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
 #pragma unroll
             for (int idx = 0; idx < NLD; ++idx) issue_one(idx, slab);
         };
-        // zero the A operand beyond the end of the contraction range (last slab only)
+        // zero both operands beyond the end of the contraction range (last slab only; with one of them zero, an infinity in
+        // the clamped elements of the other would make 0 * Inf = NaN of a result that is infinite)
         // (always the tile's last slab: its position comes from the tile, not from the loop counter, so that
         // no per-lane induction variable is carried through the main loop for this rare path)
         auto zero_tail = [&]() {
             const int slab = nslab - 1;
             unsigned char* sa = smem + (slab % NSTAGE) * G::STAGE + wave * 1024;
+            unsigned char* sb = sa + G::A_BYTES;
             const int k0 = kbeg + slab * BK;
             const u32x4 z = {0u, 0u, 0u, 0u};
             if (G::A_KC) {
@@ -436,6 +438,17 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                 for (int i = 0; i < A_LD; ++i)
                     if (k0 + (wave + NW * i) * A_RPI + ksA_row >= kend)
                         *reinterpret_cast<u32x4*>(sa + i * (NW * 1024) + lane * 16) = z;
+            }
+            if (G::B_KC) {
+                if (k0 + kc_chunk * 8 >= kend) {
+#pragma unroll
+                    for (int i = 0; i < B_LD; ++i) *reinterpret_cast<u32x4*>(sb + i * (NW * 1024) + lane * 16) = z;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < B_LD; ++i)
+                    if (k0 + (wave + NW * i) * B_RPI + ksB_row >= kend)
+                        *reinterpret_cast<u32x4*>(sb + i * (NW * 1024) + lane * 16) = z;
             }
         };
         // operand fragment number f (A tiles 0..TM-1, then B tiles) of k-step ks of slab `slab`
@@ -537,7 +550,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                 }
                 wait_vmcnt<0>();
                 block_sync_lds();
-                if (slab + 2 == nslab && ragged) {
+                if (!LOADS && slab + 2 == nslab && ragged) {      // (with LOADS there is a slab + 2)
                     zero_tail();
                     block_sync_lds();
                 }
@@ -555,7 +568,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
             // everything issued after slab+1's loads may still be in flight
             if (LOADS) wait_vmcnt<(NSTAGE - 2) * NLD - (NLD - L0)>(); else wait_vmcnt<0>();
             block_sync_lds();
-            if (slab + 2 == nslab && ragged) {
+            if (!LOADS && slab + 2 == nslab && ragged) {      // (with LOADS there is a slab + 2)
                 zero_tail();
                 block_sync_lds();
             }

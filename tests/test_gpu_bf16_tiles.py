@@ -63,3 +63,62 @@ def test_one_weight_gradient_alone_accumulates_once(which):
                                 b.dXp, True, b.workspace)
     torch.cuda.synchronize()
     assert torch.equal(got.float(), 2 * want)         # g + g is exact
+
+
+@pytest.mark.parametrize("T,d,E,F,hint", [(45, 96, 1, 160, 0), (45, 72, 1, 264, 0), (45, 96, 1, 160, 100000), (300, 1056, 3, 544, 100000)])
+def test_infinite_operands_stay_infinite_in_partial_slabs(T, d, E, F, hint):
+    """No contraction length is a multiple of a slab of 64 here, some are of 32.  An infinity in the last element of a
+    contraction must reach the result as in plain arithmetic: a slab's padding must not turn it into 0 * Inf."""
+    import torch
+    import gpu_harness as h
+    cfg = synth.LayerConfig("inf", T=T, d=d, E=E, F=F, act="gelu", dtype="bf16", taus=(1.0,), threshold=0.9, seed=523,
+                            bias_std=0.02)
+    gl = h.GpuLayer(synth.make_layer_inputs(cfg), P_cap=max(T, hint))
+    P = gl.forward(1.0, 0.9)
+    assert P == T
+    b, p, B, inf = gl.buf, gl.params, h.B, float("inf")
+    n = int(b.expert_offsets[1])                   # rows of expert 0
+    assert n % 64
+    f64 = lambda t: t.double().cpu()
+
+    def same(got, want, what):
+        got, want = f64(got), want.cpu()
+        assert not torch.isnan(want).any() and torch.isinf(want).any(), what
+        assert torch.equal(torch.isinf(got), torch.isinf(want)) and not torch.isnan(got).any(), what
+        assert torch.equal(got[torch.isinf(want)], want[torch.isinf(want)]), what
+
+    tok = b.pair_token[:n].long()
+    A = b.A.clone()
+    A[A == 0] = 1.0
+    W1, W2 = p.W1.clone(), p.W2.clone()
+    W1[0, 7, d - 1] = inf
+    W2[0, 9, F - 1] = inf
+    H, A2, O = torch.zeros_like(b.H), torch.zeros_like(b.A), torch.zeros_like(b.O)
+    B.evomoe_expert_ffn(gl.ctx, gl.shape, gl.x, b.pair_token, b.expert_offsets, W1, p.b1, p.W2, p.b2, H, A2, O)
+    same(H[:n], f64(gl.x[tok]) @ f64(W1[0]).T, "H")
+    B.evomoe_expert_ffn(gl.ctx, gl.shape, gl.x, b.pair_token, b.expert_offsets, p.W1, p.b1, W2, p.b2, H, A2, O)
+    same(O[:n], f64(A2[:n]) @ f64(W2[0]).T, "O")
+
+    dO = torch.randn(gl.shape.P_cap, d, generator=torch.Generator("cuda").manual_seed(6), device="cuda").bfloat16()
+    dW1, dW2, H0 = torch.zeros_like(p.W1), torch.zeros_like(p.W2), torch.zeros_like(b.H)
+
+    def backward(A=A, x=gl.x, W1=p.W1, W2=p.W2):
+        B.evomoe_expert_ffn_bwd(gl.ctx, gl.shape, dO, H0, A, x, b.pair_token, b.expert_offsets, W1, W2, None, None, dW1, None,
+                                dW2, None, b.dXp, False, b.workspace)
+        torch.cuda.synchronize()
+
+    W2 = p.W2.clone()
+    W2[0, d - 1, 5] = inf                          # dH = (dO W2) * act'(0), act'(0) = 1/2
+    backward(W2=W2)
+    dH = b.workspace[:n * F * 2].view(torch.bfloat16).view(n, F)         # the workspace begins with dH
+    same(dH, f64(dO[:n]) @ f64(W2[0]) * 0.5, "dH")
+    W1 = p.W1.clone()
+    W1[0, F - 1, 5] = inf
+    backward(W1=W1)
+    same(b.dXp[:n], f64(dH) @ f64(W1[0]), "dXp")
+    Ai, x = A.clone(), gl.x.clone()
+    Ai[n - 1, 3] = inf
+    x[tok[n - 1], 4] = inf
+    backward(A=Ai, x=x)
+    same(dW2[0], f64(dO[:n]).T @ f64(Ai[:n]), "dW2")
+    same(dW1[0], f64(dH).T @ f64(x[tok]), "dW1")
