@@ -67,8 +67,7 @@ __global__ __launch_bounds__(256) void gather_colsum_kernel(
 
 size_t colsum_scratch_bytes(const evomoe_shape& s) {
     if (s.dtype != EVOMOE_BF16) return ((size_t)kF32ColsumSplit * s.E * (s.d + s.F) * sizeof(float) + 255) & ~(size_t)255;
-    return (((size_t)kColsumSplit * s.E * (s.d > s.F ? s.d : s.F) * sizeof(float) + 255) & ~(size_t)255) +
-           dh_colpart_bytes(s);
+    return (((size_t)kColsumSplit * s.E * s.d * sizeof(float) + 255) & ~(size_t)255) + dh_colpart_bytes(s);
 }
 
 hipError_t launch_gather_colsum(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token, void* x_perm,

@@ -41,20 +41,24 @@ struct GemmArgs {
     const float* row_scale;             // E_ACTGRAD: per-row factor applied in f32 before act' (or null)
     bf16_t* out1;                       // C (H for E_HA)
     bf16_t* out2;                       // E_HA: A = act(H)
-    float* colpart;                     // E_ACTGRAD: per-tile column sums of C, [row tile][BM / 64][N] (or null)
+    float* colpart;                     // E_ACTGRAD: column sums of C for each 64 rows, [part_row()][N] (or null)
     int act, accumulate;
     int col_group;                      // NT/NN: column tiles per group of the tile order (1 .. all of them)
 };
 
+// Row, in dH's table of column sums, of the first 64 rows of the expert whose rows begin at `begin`; its further ones follow.
+// Expert g + 1 begins no earlier than expert g ends, and the table ends at P / 64 + E, whatever the tile.
+__device__ __forceinline__ int part_row(int g, int begin) { return begin / 64 + g; }
+
 // The last sums of both bias gradients, as further tiles behind the weight gradients' (TN launches).  The first tiles1
-// (expert g = b / gx1, NW * 64 columns each): db1[g, n] (+)= sum over expert g's row tiles of the per-tile column sums
+// (expert g = b / gx1, NW * 64 columns each): db1[g, n] (+)= sum over expert g's rows of the table of column sums
 // written by the dH GEMM, in row order.  The rest: db2[i] (+)= sum over the splits of the streaming column sums of dO, in
 // split order.  Reproducible bit for bit.
 struct BiasFinal {
-    const float* part1; float* db1;     // [row tile][parts][N1] -> [E,N1]
+    const float* part1; float* db1;     // [part_row()][N1] -> [E,N1]
     const float* part2; float* db2;     // [kColsumSplit][n2] -> [n2]
     size_t n2;
-    int N1, BM, parts;                  // BM: row tile of the dH GEMM, parts: rows of its table for each
+    int N1;
     int gx1, tiles1, tiles;             // column blocks per expert, tiles of db1, of both
     int accumulate;
     const int32_t* offsets;             // expert_offsets
@@ -77,20 +81,18 @@ __device__ __forceinline__ void bias_final_tile(const BiasFinal& q, int b, const
     const int g = b / q.gx1;
     const int n = (b % q.gx1) * nthr + threadIdx.x;
     if (n >= q.N1) return;
-    int t0 = 0;                          // first row tile of expert g
-    for (int e = 0; e < g; ++e) t0 += (offs[e + 1] - offs[e] + q.BM - 1) / q.BM;
-    const int nt = (offs[g + 1] - offs[g] + q.BM - 1) / q.BM;
-    const float* src = q.part1 + (int64_t)t0 * q.parts * q.N1 + n;
+    const int rows = (offs[g + 1] - offs[g] + 63) / 64;
+    const float* src = q.part1 + (int64_t)part_row(g, offs[g]) * q.N1 + n;
     float sum = q.accumulate ? q.db1[(int64_t)g * q.N1 + n] : 0.f;
     int i = 0;
-    for (; i + 8 <= q.parts * nt; i += 8) {
+    for (; i + 8 <= rows; i += 8) {
         float v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(i + u) * q.N1];
 #pragma unroll
         for (int u = 0; u < 8; ++u) sum += v[u];
     }
-    for (; i < q.parts * nt; ++i) sum += src[(int64_t)i * q.N1];
+    for (; i < rows; ++i) sum += src[(int64_t)i * q.N1];
     q.db1[(int64_t)g * q.N1 + n] = sum;
 }
 
@@ -119,8 +121,6 @@ template <int LAYOUT, int BM, int BN, int BK, int NSTAGE, int NW = 4> struct Geo
     static constexpr int SMEM = MAIN;
     // block key of row k of a k-strided tile with C columns (64 columns are only four blocks: two rows share a bank window)
     template <int C> __device__ static __forceinline__ int ks_key(int k) { return C >= 128 ? 2 * (k & 3) : (k & 2); }
-    // rows of the act'(H) epilogue's table of column sums per row tile: one for every 64 rows
-    static constexpr int PARTS = BM / 64;
 };
 
 // Phi(h), the standard normal CDF, as 0.5 + hc*Q(hc^2) with hc = h clamped to |h| <= 4.2: degree-8 minimax
@@ -731,8 +731,9 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         }
         if (EPI == E_ACTGRAD && LAYOUT != L_TN) {
             if (p.colpart) {
-                const int rt = tstart[g] + (row0 - offs[g]) / BM;
-                float* dst = p.colpart + ((int64_t)rt * G::PARTS + (WM >= 64 ? wm : wm >> 1)) * p.N;
+                const int part = WM >= 64 ? wm : wm >> 1;         // which 64 rows of the tile
+                const bool any = part * 64 < rows;                // (the others have no row in the table)
+                float* dst = p.colpart + (int64_t)(part_row(g, offs[g]) + (row0 - offs[g]) / 64 + part) * p.N;
                 if (SUM_REGS) {
                     // the four lane groups hold different rows of the same columns: add them up, lane group 0 writes
                     // this wave's sums (rows wm*WM .. +WM-1 of the tile) as one row of the partial table
@@ -740,7 +741,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                     for (int o = CPW; o < 64; o <<= 1)
 #pragma unroll
                         for (int q = 0; q < 8; ++q) cs[q] += __shfl_xor(cs[q], o, 64);
-                    if (lane < CPW && col < p.N) {
+                    if (lane < CPW && col < p.N && any) {
                         *reinterpret_cast<f32x4*>(dst + col_c) = f32x4{cs[0], cs[1], cs[2], cs[3]};
                         *reinterpret_cast<f32x4*>(dst + col_c + 4) = f32x4{cs[4], cs[5], cs[6], cs[7]};
                     }
@@ -750,7 +751,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                     for (int o = CPW; o < 32; o <<= 1)
 #pragma unroll
                         for (int q = 0; q < 4; ++q) cs[q] += __shfl_xor(cs[q], o, 64);
-                    if ((lane & 31) < CPW && col < p.N)
+                    if ((lane & 31) < CPW && col < p.N && any)
                         *reinterpret_cast<f32x4*>(dst + col_c + half) = f32x4{cs[0], cs[1], cs[2], cs[3]};
                 } else {
                     // lane = (chain, four columns); the upper wave's rows lie further on in the staging area
@@ -769,7 +770,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                         for (int o = CL; o < 4 * CL; o <<= 1)
 #pragma unroll
                             for (int q = 0; q < 4; ++q) sum[q] += __shfl_xor(sum[q], o, 64);
-                        if (chain == 0 && n < p.N) *reinterpret_cast<f32x4*>(dst + n) = sum;
+                        if (chain == 0 && n < p.N && any) *reinterpret_cast<f32x4*>(dst + n) = sum;
                     }
                 }
             }
@@ -846,10 +847,6 @@ template <class Cfg> int64_t expected_row_tiles(const Ctx& c, const evomoe_shape
     return spread > used ? spread : used;
 }
 
-// the act'(H) launch's table of column sums (BM / 64 rows for each row tile) is sized for these tiles, and no other shape's
-// needs more
-using CfgDh = CfgBig8;
-
 // Column tiles per group of the NT/NN tile order: as many weight panels (BN x K) as stay in one XCD's 4 MB L2 next to
 // the row panels streaming past them; all of them when a row panel (BM x K) is itself so large (long contractions)
 // that reading it once per group would cost more than re-reading the weights.
@@ -881,17 +878,14 @@ template <class Cfg> double round_cost(const Ctx& c, int64_t tiles, double k, co
 template <class Cfg> double launch_cost(const Ctx& c, const evomoe_shape& s, const GemmArgs& a, const RoundTime& t) {
     return round_cost<Cfg>(c, expected_row_tiles<Cfg>(c, s) * ctiles<Cfg>(a.N), a.K, t);
 }
-// Launches the cheapest of the shapes Cfgs (t: their times, in the same order); its row tile goes to *bm.
 template <int LAYOUT, int EPI, class Cfg>
-hipError_t launch_rows(const Ctx& c, const evomoe_shape& s, GemmArgs& a, int* bm) {
-    if (bm) *bm = Cfg::BM;
+hipError_t launch_rows(const Ctx& c, const evomoe_shape& s, GemmArgs& a) {
     a.col_group = col_group_for<Cfg>(a.N, a.K);
     return launch_gemm<LAYOUT, EPI, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(a.N));
 }
-// Launches the cheapest of the shapes Cfgs (t: their times, in the same order); its row tile goes to *bm.
+// Launches the cheapest of the shapes Cfgs (t: their times, in the same order).
 template <int LAYOUT, int EPI, class... Cfgs>
-hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const RoundTime (&t)[sizeof...(Cfgs)],
-                       int* bm = nullptr) {
+hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const RoundTime (&t)[sizeof...(Cfgs)]) {
     int n = 0, best = 0;
     double best_cost = 0.0;
     auto consider = [&](double cost) {
@@ -901,7 +895,7 @@ hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const R
     (consider(launch_cost<Cfgs>(c, s, a, t[n])), ...);
     hipError_t err = hipErrorInvalidValue;
     n = 0;
-    (void)((n++ == best ? (err = launch_rows<LAYOUT, EPI, Cfgs>(c, s, a, bm), true) : false) || ...);
+    (void)((n++ == best ? (err = launch_rows<LAYOUT, EPI, Cfgs>(c, s, a), true) : false) || ...);
     return err;
 }
 
@@ -938,10 +932,10 @@ hipError_t launch_wgrad(const Ctx& c, const evomoe_shape& s, const GemmArgs* w2,
 
 }  // namespace
 
-// per-tile column sums of dH: one row of F floats per wave row of each row tile of the dH GEMM
+// column sums of dH: a row of F floats for every 64 rows of an expert (part_row())
 size_t dh_colpart_bytes(const evomoe_shape& s) {
     if (s.dtype != EVOMOE_BF16) return 0;
-    return ((size_t)row_tiles<CfgDh>(s) * (CfgDh::BM / 64) * s.F * sizeof(float) + 255) & ~(size_t)255;
+    return (((size_t)s.P_cap / 64 + s.E) * s.F * sizeof(float) + 255) & ~(size_t)255;
 }
 
 hipError_t mfma_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token,
@@ -977,12 +971,11 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
     GemmArgs a{};
     a.expert_offsets = expert_offsets; a.E = s.E; a.P_cap = s.P_cap; a.act = s.act;
     hipError_t err;
-    int dh_bm = CfgDh::BM;                // row tile of the dH launch (its table of column sums has BM / 64 rows for each)
-    // workspace behind dH: [column-sum partials of the streaming kernel][per-tile column sums of dH][gathered x]
+    // workspace behind dH: [column-sum partials of the streaming kernel][column sums of dH][gathered x]
     float* scratch = reinterpret_cast<float*>(static_cast<char*>(dH) + dh_bytes(s));
     float* colpart = reinterpret_cast<float*>(static_cast<char*>(dH) + dh_bytes(s) + colsum_scratch_bytes(s) -
                                               dh_colpart_bytes(s));
-    {   // dH = (dO W2) * act'(H); its epilogue also leaves the column sums of every tile (for db1).
+    {   // dH = (dO W2) * act'(H); its epilogue also leaves the column sums of every 64 rows (for db1).
         // With dy and the pair weights at hand, dO W2 is taken as G_r * (dy[token(r)] W2): the rows of dy are
         // gathered on load and the weight is applied to the f32 accumulators, so that the rounding of the stored
         // dO (a product rounded to bf16) does not reach dH, dXp, dW1 and db1.
@@ -994,7 +987,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         a.b_group_stride = (int64_t)s.d * s.F; a.N = s.F; a.K = s.d; a.Hin = (const bf16_t*)H;
         a.out1 = (bf16_t*)dH; a.colpart = db1 ? colpart : nullptr;
         static const RoundTime t[] = {{20.8, 13.5, 22.3}, {0, 15.6, 26.0}, {0.3, 10.4, 13.2}, {2.6, 5.4, 10.7}, {2.8, 5.0, 8.8}};
-        err = launch_best<L_NN, E_ACTGRAD, CfgBig8, CfgDuo, CfgMid, CfgSml, CfgTny3>(c, s, a, t, &dh_bm);
+        err = launch_best<L_NN, E_ACTGRAD, CfgBig8, CfgDuo, CfgMid, CfgSml, CfgTny3>(c, s, a, t);
         a.colpart = nullptr; a.a_rows = nullptr; a.row_scale = nullptr;
         if (err != hipSuccess) return err;
     }
@@ -1028,7 +1021,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
     w1.A = (const bf16_t*)dH; w1.lda = s.F; w1.B = xg; w1.ldb = s.d;
     w1.M = s.F; w1.N = s.d; w1.out1 = (bf16_t*)dW1;
     BiasFinal bf{};
-    bf.part1 = colpart; bf.db1 = db1; bf.N1 = s.F; bf.BM = dh_bm; bf.parts = dh_bm / 64;
+    bf.part1 = colpart; bf.db1 = db1; bf.N1 = s.F;
     bf.part2 = scratch; bf.db2 = db2; bf.n2 = (size_t)s.E * s.d; bf.accumulate = accumulate;
     bf.offsets = expert_offsets;
     if (!dW2 && !dW1 && !db1 && !db2) return hipSuccess;
