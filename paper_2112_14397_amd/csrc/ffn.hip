@@ -52,3 +52,14 @@ hipError_t launch_expert_ffn_bwd_recompute(const Ctx& c, const evomoe_shape& s, 
 }
 
 }  // namespace evomoe
+
+// Not part of the ABI: lets the tests see on the host which kernel a call reaches.  tile: rows, columns, waves.
+extern "C" int evomoe_test_ffn_tile(const evomoe_shape* shape, int num_cu, int64_t announced_pairs, int kernel, int* tile) {
+    evomoe::Ctx c{};
+    c.num_cu = num_cu;
+    c.pair_hint = announced_pairs;
+    const evomoe::FfnTile t = shape->dtype == EVOMOE_BF16 ? evomoe::mfma_ffn_tile(c, *shape, kernel)
+                                                          : evomoe::f32_ffn_tile(c, *shape, kernel);
+    tile[0] = t.rows; tile[1] = t.cols; tile[2] = t.waves;
+    return t.rows > 0;
+}

@@ -399,19 +399,36 @@ hipError_t launch(const Ctx& c, const evomoe_shape& s, const F32Args& a, int64_t
 }
 
 // NT / NN: one problem over the row tiles of all experts
+Tile rows_tile(const Ctx& c, const evomoe_shape& s, int n) {
+    const int64_t P = c.pair_hint > 0 && c.pair_hint < s.P_cap ? c.pair_hint : s.P_cap;
+    auto expected = [&](int b) { return tiles_of((P + b - 1) / b + s.E / 2, n, b); };
+    return cheapest(c, expected(64), expected(32));
+}
 template <int LAYOUT, int EPI>
 hipError_t launch_rows(const Ctx& c, const evomoe_shape& s, const F32Args& a, const int32_t* expert_offsets,
                        const F32Sums& sums = F32Sums{}) {
-    const int64_t P = c.pair_hint > 0 && c.pair_hint < s.P_cap ? c.pair_hint : s.P_cap;
-    auto expected = [&](int b) { return tiles_of((P + b - 1) / b + s.E / 2, a.N, b); };
     auto worst = [&](int b) { return tiles_of((s.P_cap + b - 1) / b + s.E, a.N, b); };
     const int64_t st = (int64_t)kSumSplit * s.E * (sums.blocks[0] + sums.blocks[1]);
-    if (cheapest(c, expected(64), expected(32)) == Tile::T64)
+    if (rows_tile(c, s, a.N) == Tile::T64)
         return launch<LAYOUT, EPI, 64>(c, s, a, worst(64), a, 0, sums, st, expert_offsets, 0);
     return launch<LAYOUT, EPI, 32>(c, s, a, worst(32), a, 0, sums, st, expert_offsets, 0);
 }
+// TN: the tiles of one of the two problems; both count for the choice, whichever is wanted
+int64_t wgrad_tiles(const evomoe_shape& s, int b) { return (int64_t)s.E * ((s.d + b - 1) / b) * ((s.F + b - 1) / b); }
+Tile wgrad_tile(const Ctx& c, const evomoe_shape& s) { return cheapest(c, 2 * wgrad_tiles(s, 64), 2 * wgrad_tiles(s, 32)); }
 
 }  // namespace
+
+FfnTile f32_ffn_tile(const Ctx& c, const evomoe_shape& s, int kernel) {
+    Tile t;
+    switch (kernel) {
+        case EVOMOE_K_FFN_GEMM1: case EVOMOE_K_FFN_BWD_DH: t = rows_tile(c, s, s.F); break;
+        case EVOMOE_K_FFN_GEMM2: case EVOMOE_K_FFN_BWD_DX: t = rows_tile(c, s, s.d); break;
+        case EVOMOE_K_FFN_BWD_DW2: t = wgrad_tile(c, s); break;
+        default: return {};
+    }
+    return t == Tile::T64 ? FfnTile{64, 64, 4} : FfnTile{32, 32, 4};
+}
 
 hipError_t f32_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token,
                        const int32_t* expert_offsets, const void* W1, const float* b1, const void* W2,
@@ -462,8 +479,7 @@ hipError_t f32_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, cons
         err = launch_rows<L_NN, E_NONE>(c, s, a, expert_offsets, sums);
         if (err != hipSuccess) return err;
     }
-    // dW2_g = dO_g^T A_g [d,F], dW1_g = dH_g^T X_g [F,d]: one launch over both problems' tiles.  The tile size does not
-    // depend on which of them are wanted.
+    // dW2_g = dO_g^T A_g [d,F], dW1_g = dH_g^T X_g [F,d]: one launch over both problems' tiles
     F32Args w[2]{};
     int n = 0;
     auto add = [&](const void* L, int M, const void* R, int N, const int32_t* rows, void* dW) {
@@ -477,12 +493,11 @@ hipError_t f32_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, cons
     const int64_t st = ((int64_t)s.E * ((db2 ? s.d : 0) + (db1 ? s.F : 0)) + 255) / 256;
     if (n == 0 && st == 0) return hipSuccess;
     ProfScope ps(c, dW2 ? EVOMOE_K_FFN_BWD_DW2 : dW1 ? EVOMOE_K_FFN_BWD_DW1 : EVOMOE_K_FFN_BWD_DB);
-    auto tiles = [&](int b) { return (int64_t)s.E * ((s.d + b - 1) / b) * ((s.F + b - 1) / b); };     // of either problem
     auto run = [&](auto launcher, int b) {
-        return launcher(c, s, w[0], n > 0 ? tiles(b) : 0, w[1], n > 1 ? tiles(b) : 0, sums, st, expert_offsets, accumulate);
+        return launcher(c, s, w[0], n > 0 ? wgrad_tiles(s, b) : 0, w[1], n > 1 ? wgrad_tiles(s, b) : 0, sums, st, expert_offsets,
+                        accumulate);
     };
-    return cheapest(c, 2 * tiles(64), 2 * tiles(32)) == Tile::T64 ? run(launch<L_TN, E_WGRAD, 64>, 64)
-                                                                  : run(launch<L_TN, E_WGRAD, 32>, 32);
+    return wgrad_tile(c, s) == Tile::T64 ? run(launch<L_TN, E_WGRAD, 64>, 64) : run(launch<L_TN, E_WGRAD, 32>, 32);
 }
 
 }  // namespace evomoe

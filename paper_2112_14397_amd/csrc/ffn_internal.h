@@ -4,6 +4,12 @@
 
 namespace evomoe {
 
+// Which tile (rows, columns, waves) an expert-FFN launch takes on c.num_cu compute units for c.pair_hint announced pairs; the
+// weight-gradient launch (EVOMOE_K_FFN_BWD_DW2) with both gradients wanted.  Host only: the launchers ask the same rule.
+struct FfnTile { int rows, cols, waves; };
+FfnTile mfma_ffn_tile(const Ctx& c, const evomoe_shape& s, int kernel);
+FfnTile f32_ffn_tile(const Ctx& c, const evomoe_shape& s, int kernel);
+
 // float32 matrix-core path (ffn_f32.hip)
 hipError_t f32_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token,
                        const int32_t* expert_offsets, const void* W1, const float* b1, const void* W2,

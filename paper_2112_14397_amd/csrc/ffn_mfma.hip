@@ -875,29 +875,41 @@ template <class Cfg> double round_cost(const Ctx& c, int64_t tiles, double k, co
     if (last) rounds += 0.55 + 0.45 * (double)((last + c.num_cu - 1) / c.num_cu) / Cfg::WPE;
     return t.fixed + rounds * (t.per_round + t.per_k * k / 1024.0);
 }
-template <class Cfg> double launch_cost(const Ctx& c, const evomoe_shape& s, const GemmArgs& a, const RoundTime& t) {
-    return round_cost<Cfg>(c, expected_row_tiles<Cfg>(c, s) * ctiles<Cfg>(a.N), a.K, t);
+// A launch's candidates and their times.
+template <class... Cfgs> struct Choice { RoundTime t[sizeof...(Cfgs)]; };
+template <class Cfg> FfnTile tile_of() { return {Cfg::BM, Cfg::BN, Cfg::NW}; }
+// The cheapest candidate's position; tiles(cfg): how many tiles of that shape the launch is expected to have.
+template <class F, class... Cfgs> int cheapest(const Ctx& c, double k, const Choice<Cfgs...>& ch, F&& tiles) {
+    int i = 0, best = 0;
+    const double cost[] = {round_cost<Cfgs>(c, tiles(Cfgs{}), k, ch.t[i++])...};       // (a braced list: left to right)
+    for (i = 1; i < (int)sizeof...(Cfgs); ++i)
+        if (cost[i] < cost[best]) best = i;
+    return best;
 }
-template <int LAYOUT, int EPI, class Cfg>
-hipError_t launch_rows(const Ctx& c, const evomoe_shape& s, GemmArgs& a) {
-    a.col_group = col_group_for<Cfg>(a.N, a.K);
-    return launch_gemm<LAYOUT, EPI, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(a.N));
+template <class... Cfgs> int cheapest_rows(const Ctx& c, const evomoe_shape& s, int n, int k, const Choice<Cfgs...>& ch) {
+    return cheapest(c, k, ch, [&](auto cfg) { return expected_row_tiles<decltype(cfg)>(c, s) * ctiles<decltype(cfg)>(n); });
 }
-// Launches the cheapest of the shapes Cfgs (t: their times, in the same order).
+// Launches the cheapest of the candidates.
 template <int LAYOUT, int EPI, class... Cfgs>
-hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const RoundTime (&t)[sizeof...(Cfgs)]) {
-    int n = 0, best = 0;
-    double best_cost = 0.0;
-    auto consider = [&](double cost) {
-        if (n == 0 || cost < best_cost) { best_cost = cost; best = n; }
-        ++n;
-    };
-    (consider(launch_cost<Cfgs>(c, s, a, t[n])), ...);
+hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const Choice<Cfgs...>& ch) {
+    const int best = cheapest_rows(c, s, a.N, a.K, ch);
     hipError_t err = hipErrorInvalidValue;
-    n = 0;
-    (void)((n++ == best ? (err = launch_rows<LAYOUT, EPI, Cfgs>(c, s, a), true) : false) || ...);
+    auto run = [&](auto cfg) {
+        using Cfg = decltype(cfg);
+        a.col_group = col_group_for<Cfg>(a.N, a.K);
+        err = launch_gemm<LAYOUT, EPI, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(a.N));
+    };
+    int n = 0;
+    (void)((n++ == best ? (run(Cfgs{}), true) : false) || ...);
     return err;
 }
+constexpr Choice<CfgBig8, CfgDuo, CfgMid, CfgSml, CfgTny3>
+    kGemm1{{{0, 12.2, 21.9}, {0, 12.4, 27.8}, {0, 9.2, 12.8}, {2.5, 4.4, 10.0}, {3.0, 3.4, 9.0}}},
+    kDh{{{20.8, 13.5, 22.3}, {0, 15.6, 26.0}, {0.3, 10.4, 13.2}, {2.6, 5.4, 10.7}, {2.8, 5.0, 8.8}}};
+constexpr Choice<CfgBig, CfgLat, CfgMid64, CfgSml, CfgTny>
+    kGemm2{{{0, 8.8, 20.5}, {0, 6.7, 12.5}, {0, 5.9, 7.8}, {0, 5.9, 10.5}, {0, 5.8, 6.1}}};
+constexpr Choice<CfgBig, CfgLat8, CfgMid64, CfgSml, CfgTny>
+    kDx{{{0, 8.6, 20.3}, {0, 6.2, 13.1}, {0, 5.8, 7.7}, {0, 5.9, 10.7}, {0, 5.6, 6.2}}};
 
 // Weight gradients: the contraction runs over an expert's rows, P / E of them on average, and the tiles are those of the
 // matrices.  256x256 tiles (eight waves) are the fastest per flop by far -- 8-29 % ahead of 128-row tiles wherever they
@@ -908,26 +920,34 @@ hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const R
 //   256x256               9.7             27.8             44.7             290               53.0            69.8
 //   128x128               6.7             16.4             19.8             108               44.8            96.5
 //   64x64                 5.4             19.9             17.6              60               65.8           157
-template <class Cfg> int64_t wgrad_tiles(const GemmArgs& a) { return (int64_t)a.E * mtiles<Cfg>(a.M) * ctiles<Cfg>(a.N); }
+constexpr Choice<CfgOct, CfgMid64, CfgTny> kWgrad{{{4.0, 5.0, 24.0}, {2.5, 4.0, 8.0}, {2.0, 2.0, 7.6}}};
+template <class Cfg> int64_t wgrad_tiles(const evomoe_shape& s, int m, int n) { return (int64_t)s.E * mtiles<Cfg>(m) * ctiles<Cfg>(n); }
+int cheapest_wgrad(const Ctx& c, const evomoe_shape& s, bool w2, bool w1) {
+    return cheapest(c, (double)expected_pairs(c, s) / s.E, kWgrad, [&](auto cfg) {
+        using Cfg = decltype(cfg);
+        return (w2 ? wgrad_tiles<Cfg>(s, s.d, s.F) : 0) + (w1 ? wgrad_tiles<Cfg>(s, s.F, s.d) : 0);
+    });
+}
 hipError_t launch_wgrad(const Ctx& c, const evomoe_shape& s, const GemmArgs* w2, const GemmArgs* w1, const BiasFinal& bf) {
     GemmArgs none{};        // no weight gradient wanted: the launch carries the bias gradients only
     none.E = s.E; none.P_cap = s.P_cap; none.expert_offsets = bf.offsets;
     const GemmArgs& q0 = w2 ? *w2 : w1 ? *w1 : none;
     const GemmArgs& q1 = w1 ? *w1 : q0;
-    const double k = (double)expected_pairs(c, s) / s.E;
-    auto run = [&](auto cfg, bool launch, const RoundTime& t, double* cost) {
+    auto run = [&](auto cfg) {
         using Cfg = decltype(cfg);
-        const int64_t t0 = w2 || w1 ? wgrad_tiles<Cfg>(q0) : 0, t1 = w2 && w1 ? wgrad_tiles<Cfg>(q1) : 0;
-        if (!launch) { *cost = round_cost<Cfg>(c, t0 + t1, k, t); return hipSuccess; }
-        return launch_gemm<L_TN, E_WGRAD, Cfg>(c, q0, t0, q1, t1, bf);
+        return launch_gemm<L_TN, E_WGRAD, Cfg>(c, q0, w2 || w1 ? wgrad_tiles<Cfg>(s, q0.M, q0.N) : 0, q1,
+                                               w2 && w1 ? wgrad_tiles<Cfg>(s, q1.M, q1.N) : 0, bf);
     };
-    static const RoundTime t[] = {{4.0, 5.0, 24.0}, {2.5, 4.0, 8.0}, {2.0, 2.0, 7.6}};
-    double c0, c1, c2;
-    (void)run(CfgOct{}, false, t[0], &c0);
-    (void)run(CfgMid64{}, false, t[1], &c1);
-    (void)run(CfgTny{}, false, t[2], &c2);
-    if (c0 <= c1 && c0 <= c2) return run(CfgOct{}, true, t[0], &c0);
-    return c1 <= c2 ? run(CfgMid64{}, true, t[1], &c1) : run(CfgTny{}, true, t[2], &c2);
+    switch (cheapest_wgrad(c, s, w2, w1)) {
+        case 0: return run(CfgOct{});
+        case 1: return run(CfgMid64{});
+        default: return run(CfgTny{});
+    }
+}
+
+template <class... Cfgs> FfnTile tile_at(const Choice<Cfgs...>&, int i) {
+    const FfnTile t[] = {tile_of<Cfgs>()...};
+    return t[i];
 }
 
 }  // namespace
@@ -936,6 +956,17 @@ hipError_t launch_wgrad(const Ctx& c, const evomoe_shape& s, const GemmArgs* w2,
 size_t dh_colpart_bytes(const evomoe_shape& s) {
     if (s.dtype != EVOMOE_BF16) return 0;
     return (((size_t)s.P_cap / 64 + s.E) * s.F * sizeof(float) + 255) & ~(size_t)255;
+}
+
+FfnTile mfma_ffn_tile(const Ctx& c, const evomoe_shape& s, int kernel) {
+    switch (kernel) {
+        case EVOMOE_K_FFN_GEMM1: return tile_at(kGemm1, cheapest_rows(c, s, s.F, s.d, kGemm1));
+        case EVOMOE_K_FFN_GEMM2: return tile_at(kGemm2, cheapest_rows(c, s, s.d, s.F, kGemm2));
+        case EVOMOE_K_FFN_BWD_DH: return tile_at(kDh, cheapest_rows(c, s, s.F, s.d, kDh));
+        case EVOMOE_K_FFN_BWD_DX: return tile_at(kDx, cheapest_rows(c, s, s.d, s.F, kDx));
+        case EVOMOE_K_FFN_BWD_DW2: return tile_at(kWgrad, cheapest_wgrad(c, s, true, true));
+    }
+    return {};
 }
 
 hipError_t mfma_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token,
@@ -949,8 +980,7 @@ hipError_t mfma_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, cons
         a.A = (const bf16_t*)x; a.lda = s.d; a.a_rows = pair_token;
         a.B = (const bf16_t*)W1; a.ldb = s.d; a.b_group_stride = (int64_t)s.F * s.d;
         a.N = s.F; a.K = s.d; a.bias = b1; a.out1 = (bf16_t*)H; a.out2 = (bf16_t*)A;
-        static const RoundTime t[] = {{0, 12.2, 21.9}, {0, 12.4, 27.8}, {0, 9.2, 12.8}, {2.5, 4.4, 10.0}, {3.0, 3.4, 9.0}};
-        err = launch_best<L_NT, E_HA, CfgBig8, CfgDuo, CfgMid, CfgSml, CfgTny3>(c, s, a, t);
+        err = launch_best<L_NT, E_HA>(c, s, a, kGemm1);
         if (err != hipSuccess || !O) return err;      // O == nullptr: recomputation of H and A only
     }
     {   // O = A W2^T + b2
@@ -958,8 +988,7 @@ hipError_t mfma_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, cons
         a.A = (const bf16_t*)A; a.lda = s.F; a.a_rows = nullptr;
         a.B = (const bf16_t*)W2; a.ldb = s.F; a.b_group_stride = (int64_t)s.d * s.F;
         a.N = s.d; a.K = s.F; a.bias = b2; a.out1 = (bf16_t*)O; a.out2 = nullptr;
-        static const RoundTime t[] = {{0, 8.8, 20.5}, {0, 6.7, 12.5}, {0, 5.9, 7.8}, {0, 5.9, 10.5}, {0, 5.8, 6.1}};
-        err = launch_best<L_NT, E_BIAS, CfgBig, CfgLat, CfgMid64, CfgSml, CfgTny>(c, s, a, t);
+        err = launch_best<L_NT, E_BIAS>(c, s, a, kGemm2);
     }
     return err;
 }
@@ -986,8 +1015,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         a.B = (const bf16_t*)W2; a.ldb = s.F;
         a.b_group_stride = (int64_t)s.d * s.F; a.N = s.F; a.K = s.d; a.Hin = (const bf16_t*)H;
         a.out1 = (bf16_t*)dH; a.colpart = db1 ? colpart : nullptr;
-        static const RoundTime t[] = {{20.8, 13.5, 22.3}, {0, 15.6, 26.0}, {0.3, 10.4, 13.2}, {2.6, 5.4, 10.7}, {2.8, 5.0, 8.8}};
-        err = launch_best<L_NN, E_ACTGRAD, CfgBig8, CfgDuo, CfgMid, CfgSml, CfgTny3>(c, s, a, t);
+        err = launch_best<L_NN, E_ACTGRAD>(c, s, a, kDh);
         a.colpart = nullptr; a.a_rows = nullptr; a.row_scale = nullptr;
         if (err != hipSuccess) return err;
     }
@@ -996,8 +1024,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         a.A = (const bf16_t*)dH; a.lda = s.F; a.B = (const bf16_t*)W1; a.ldb = s.d;
         a.b_group_stride = (int64_t)s.F * s.d; a.N = s.d; a.K = s.F; a.Hin = nullptr;
         a.out1 = (bf16_t*)dXp;
-        static const RoundTime t[] = {{0, 8.6, 20.3}, {0, 6.2, 13.1}, {0, 5.8, 7.7}, {0, 5.9, 10.7}, {0, 5.6, 6.2}};
-        err = launch_best<L_NN, E_NONE, CfgBig, CfgLat8, CfgMid64, CfgSml, CfgTny>(c, s, a, t);
+        err = launch_best<L_NN, E_NONE>(c, s, a, kDx);
         if (err != hipSuccess) return err;
     }
     a.accumulate = accumulate;

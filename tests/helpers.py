@@ -1,4 +1,6 @@
 """Shared comparison helpers for the test-suite."""
+import ctypes
+
 import numpy as np
 
 
@@ -42,3 +44,19 @@ def tol_stats(got, ref, rtol, per_tensor=False):
 def assert_close(got, ref, rtol, what=""):
     ok, worst = tol_ok(got, ref, rtol)
     assert ok, f"{what}: worst |err|/bound = {worst:.3g} at rtol={rtol}"
+
+
+FFN_LAUNCHES = ("ffn_gemm1", "ffn_gemm2", "ffn_bwd_dh", "ffn_bwd_dx", "ffn_bwd_dw2")
+
+
+def ffn_tiles(shape, announced_pairs=0, num_cu=256):
+    """The tiles ("rows x columns / waves") that the expert-FFN launches take for a shape, in the order of FFN_LAUNCHES; the
+    library answers on the host, by the rule its launchers use."""
+    from paper_2112_14397_amd import binding as B
+    out = []
+    for name in FFN_LAUNCHES:
+        t = (ctypes.c_int * 3)()
+        assert B.lib().evomoe_test_ffn_tile(ctypes.byref(shape), num_cu, ctypes.c_int64(announced_pairs),
+                                            B.KERNEL_IDS.index(name), t) == 1
+        out.append("%dx%d/%d" % tuple(t))
+    return tuple(out)

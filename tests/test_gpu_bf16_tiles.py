@@ -1,36 +1,41 @@
-"""The bf16 expert FFN at the edges of its tiles (64x64 to 256x256), against the oracle.  The launch
-picks a tile from the sizes, so each case names those it reaches: (GEMM1, GEMM2, dH, dXp; weight gradients)."""
+"""The bf16 expert FFN at the edges of its tiles (64x64 to 256x256), against the oracle.  The launch picks a tile from the
+sizes; each case names those it reaches, and the test asks the library whether it does."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 import synth_inputs as synth  # noqa: E402
+from helpers import ffn_tiles  # noqa: E402
 
-# name, T, d, E, F: Top-1 through c = 0.9, so the single expert of an E = 1 layer owns exactly T rows
+TINY = ("64x64/4",) * 5
+# name, T, d, E, F, rows of the pair buffers, tiles of GEMM1, GEMM2, dH, dXp and the weight gradients.
+# Top-1 through c = 0.9, so the single expert of an E = 1 layer owns exactly T rows.  Where no pair count is announced the
+# tiles are picked for the buffers' rows.
 CASES = [
-    ("64-few-rows", 9, 64, 1, 64),               # 64x64 throughout, here and below the weight gradients' too
-    ("64-below", 63, 72, 1, 136),                # 64x64 throughout; one vector past a slab of 64 and past two tiles
-    ("64-above", 65, 64, 1, 192),                # 64x64 throughout; one row past a tile
-    ("64x128-long", 2497, 392, 1, 264),          # 64x64, 64x128, 64x64, 64x128
-    ("64x128-short", 1900, 776, 16, 1544),       # 64x128, 64x64, 64x128, 64x64; 256x256
-    ("128-below", 4095, 512, 4, 1032),           # 128x128 throughout, the long contractions with 64-wide slabs
-    ("128x256-above", 4100, 1032, 1, 1032),      # 128x128, 128x256 with four waves, 128x128, 128x256 with eight; 128x128
-    ("256-above", 16900, 1032, 1, 520),          # 256x256 with eight waves, with four, 128x256, 256x256 with four; 64x64
-    # the tile is picked for the buffers' capacity where no pair count is announced: 256x256 for dH as well
-    ("256-dh-one", 299, 1032, 1, 264, 200000),   # one full row tile and a ragged one
-    ("256-dh-three", 700, 1032, 3, 264, 200000),
+    ("64-few-rows", 9, 64, 1, 64, 9, TINY),
+    ("64-below", 63, 72, 1, 136, 63, TINY),      # one vector past a slab of 64 and past two tiles
+    ("64-above", 65, 64, 1, 192, 65, TINY),      # one row past a tile
+    ("64x128-long", 2497, 392, 1, 264, 2497, ("64x64/4", "64x128/4", "64x64/4", "64x128/4", "64x64/4")),
+    ("64x128-short", 1900, 776, 16, 1544, 1900, ("64x128/4", "64x64/4", "64x128/4", "64x64/4", "256x256/8")),
+    ("128-below", 4095, 512, 4, 1032, 4095, ("128x128/4",) * 5),
+    ("128x256-above", 4100, 1032, 1, 1032, 4100, ("128x128/4", "128x256/4", "128x128/4", "128x256/8", "128x128/4")),
+    ("256-above", 16900, 1032, 1, 520, 16900, ("256x256/8", "256x256/4", "128x256/4", "256x256/4", "64x64/4")),
+    ("128x256-gemm1", 300, 72, 1, 504, 40000, ("128x256/4", "256x256/4", "128x256/4", "256x256/4", "64x64/4")),
+    # one full row tile and a ragged one, one expert and three
+    ("256-dh-one", 299, 1032, 1, 504, 200000, ("256x256/8", "256x256/4", "256x256/8", "256x256/4", "64x64/4")),
+    ("256-dh-three", 700, 1032, 3, 504, 200000, ("256x256/8", "256x256/4", "256x256/8", "256x256/4", "128x128/4")),
 ]
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_bf16_ffn_at_tile_edges(case):
     import gpu_harness as h
-    name, T, d, E, F = case[:5]
+    name, T, d, E, F, rows, tiles = case
     cfg = synth.LayerConfig(name, T=T, d=d, E=E, F=F, act="gelu", dtype="bf16", taus=(1.0,), threshold=0.9, seed=311,
                             bias_std=0.02)
     inp = synth.make_layer_inputs(cfg)
-    # the pair buffers hold a row for each token (Top-1): the launch picks its tiles for that many pairs
-    gl = h.GpuLayer(inp, P_cap=case[5] if len(case) > 5 else T)
+    gl = h.GpuLayer(inp, P_cap=rows)
+    assert ffn_tiles(gl.shape, num_cu=h.torch.cuda.get_device_properties(0).multi_processor_count) == tiles
     fwd, P, _, _ = h.compare_forward(gl, inp, 1.0, 0.9)
     gl.backward(1.0)
     # the FFN's own gradients (the gate's are sums over tokens of terms of either sign: a small one carries the rounding
@@ -65,15 +70,15 @@ def test_one_weight_gradient_alone_accumulates_once(which):
     assert torch.equal(got.float(), 2 * want)         # g + g is exact
 
 
-@pytest.mark.parametrize("T,d,E,F,hint", [(45, 96, 1, 160, 0), (45, 72, 1, 264, 0), (45, 96, 1, 160, 100000), (300, 1056, 3, 544, 100000)])
-def test_infinite_operands_stay_infinite_in_partial_slabs(T, d, E, F, hint):
+@pytest.mark.parametrize("T,d,E,F,rows", [(45, 96, 1, 160, 45), (45, 72, 1, 264, 45), (45, 96, 1, 160, 100000), (300, 1056, 3, 544, 100000)])
+def test_infinite_operands_stay_infinite_in_partial_slabs(T, d, E, F, rows):
     """No contraction length is a multiple of a slab of 64 here, some are of 32.  An infinity in the last element of a
     contraction must reach the result as in plain arithmetic: a slab's padding must not turn it into 0 * Inf."""
     import torch
     import gpu_harness as h
     cfg = synth.LayerConfig("inf", T=T, d=d, E=E, F=F, act="gelu", dtype="bf16", taus=(1.0,), threshold=0.9, seed=523,
                             bias_std=0.02)
-    gl = h.GpuLayer(synth.make_layer_inputs(cfg), P_cap=max(T, hint))
+    gl = h.GpuLayer(synth.make_layer_inputs(cfg), P_cap=rows)
     P = gl.forward(1.0, 0.9)
     assert P == T
     b, p, B, inf = gl.buf, gl.params, h.B, float("inf")

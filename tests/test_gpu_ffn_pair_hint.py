@@ -6,11 +6,12 @@ pytestmark = pytest.mark.gpu
 
 import synth_inputs as synth  # noqa: E402
 
-# T, d, E, F, P_cap, announced pair counts (0: none, the tiles are picked for P_cap)
+# T, d, E, F, P_cap, announced pair counts (0: none, the tiles are picked for P_cap).  The first case of each type reaches
+# every tile of every forward launch, dH and dXp.
 CASES = {
     "f32": [(1900, 508, 3, 508, 1900, (0, 1, 900)),
             (300, 68, 4, 132, 300, (0, 1))],
-    "bf16": [(1900, 776, 3, 520, 200000, (0, 1, 600, 1900, 8000, 40000, 120000)),
+    "bf16": [(700, 392, 3, 392, 200000, (0, 1, 2400, 7500, 8250, 17800, 42000, 195700)),
              (700, 136, 5, 264, 50000, (0, 1, 700, 9000))],
 }
 
