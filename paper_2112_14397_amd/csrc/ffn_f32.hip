@@ -129,10 +129,14 @@ template <int BM> __device__ __forceinline__ Offsets scan_offsets(const int32_t*
     return o;
 }
 
-// Four blocks per CU (128 registers) fill the stalls that one's loads and barriers leave; the act'(H) epilogue spills 19
-// there (d = 256, E = 8, F = 1024, 5626 pairs: 56 us for dH, with three blocks 51), the others nothing.
+// Blocks per CU, for the registers and for the grid: four (128 registers) fill the stalls that one's loads and barriers
+// leave; 64x64 tiles of dH, whose act'(H) epilogue spills there, and of GEMM2 take three.  us at d = 512, F = 2048, 11160 /
+// 8126 / 30000 pairs, and d = 256, F = 1024, 5626: dH with four 266 / - / - / 56, with three and a grid for four 291 / 215 /
+// 758 / 51, with three 268 / 198 / 700 / 51; GEMM2 with four 236 / 167 / 570 / 44, with three 229 / 166 / 557 / 44; dXp and
+// the weight gradients are 2-5 % slower with three.
+template <int EPI, int B> constexpr int blocks_per_cu() { return B == 64 && (EPI == E_ACTGRAD || EPI == E_BIAS) ? 3 : 4; }
 template <int LAYOUT, int EPI, int BM, int BN>
-__global__ __launch_bounds__(256, EPI == E_ACTGRAD && BM == 64 ? 3 : 4) void grouped_gemm_f32(
+__global__ __launch_bounds__(256, (blocks_per_cu<EPI, BM>())) void grouped_gemm_f32(
     F32Pair q, int tiles0, int tiles_all, F32Sums sums, const int32_t* __restrict__ expert_offsets, int E, int64_t P_cap,
     int act, int accumulate)
 {
@@ -391,7 +395,7 @@ Tile cheapest(const Ctx& c, int64_t t64, int64_t t32) {
 template <int LAYOUT, int EPI, int B>
 hipError_t launch(const Ctx& c, const evomoe_shape& s, const F32Args& a, int64_t t0, const F32Args& b, int64_t t1,
                   const F32Sums& sums, int64_t sum_tiles, const int32_t* expert_offsets, int accumulate) {
-    const int64_t cap = (int64_t)c.num_cu * 4, want = (t0 + t1 + sum_tiles + 7) / 8 * 8;
+    const int64_t cap = (int64_t)c.num_cu * blocks_per_cu<EPI, B>(), want = (t0 + t1 + sum_tiles + 7) / 8 * 8;
     hipLaunchKernelGGL((grouped_gemm_f32<LAYOUT, EPI, B, B>), dim3((unsigned)(want < cap ? want : cap)), dim3(256), 0,
                        c.stream, F32Pair{{a, b}}, (int)t0, (int)(t0 + t1), sums, expert_offsets, s.E, s.P_cap, s.act,
                        accumulate);
