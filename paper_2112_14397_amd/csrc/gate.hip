@@ -385,12 +385,16 @@ static hipError_t gate_launch_ne(const Ctx& c, const evomoe_shape& s, const void
 
 // The smallest calls are launches and latency: one block of 1024 threads then does all of it, in one launch instead of
 // two, and the split of W_g and the clearing of the counts, which gate_prep_kernel is for, fall away.  The histogram has
-// one row up to 256 tokens and one tile holds 16 experts; up to 256 columns one compute unit reads x and W_g in the time
-// that the launch took (a whole forward pass: T = 256, d = 64, E = 4 in float32 32.0 -> 27.9 us; T = 256, d = 256, E = 8 in
-// bf16 31.9 -> 29.2; T = 128, d = 256, E = 4 in float32 32.1 -> 28.9).  Beyond, it no longer does: T = 48, d = 768, E = 16
-// in bf16 58.1 -> 63.5, T = 100, d = 512, E = 16 31.8 -> 32.7, T = 64, d = 512, E = 8 in float32 31.3 -> 32.0.
+// one row up to 256 tokens and one tile holds 16 experts; up to 256 columns one compute unit reads a token's x and W_g in the
+// time that the launch took (a whole bf16 forward pass, us, one block / two launches, kept busy and each waited for:
+// 256,256,4 28.9 / 30.7 and 40.9 / 41.8, 128,256,16 32.9 / 34.0 and 44.1 / 46.8, 256,256,16 37.6 / 36.4 and 49.5 / 49.7).  More
+// columns: T = 48, d = 768, E = 16 58.1 -> 63.5, T = 100, d = 512, E = 16 31.8 -> 32.7, T = 64, d = 512, E = 8 in float32 31.3 ->
+// 32.0.  In float32 the products run at a fourth of the bf16 rate and x is twice as large: the line follows T d and, for the
+// softmax, T E (256,64,16 27.9 / 31.4 and 39.2 / 40.5; 256,136,4 29.9 / 30.9 and 42.1 / 43.2; 128,256,4 30.9 / 30.9 and 43.5 /
+// 44.8; 200,136,16 34.2 / 31.9 and 46.8 / 47.0; 160,256,4 34.3 / 31.0 and 47.1 / 45.9; 256,256,4 36.8 / 31.6 and 49.5 / 46.0).
 static bool gate_one_block(const evomoe_shape& s) {
-    return s.T <= kDispatchTokens && s.E <= 16 && s.d <= 256;
+    return s.T <= kDispatchTokens && s.E <= 16 && s.d <= 256 &&
+           (s.dtype == EVOMOE_BF16 || s.T * (s.d + 4 * s.E) <= 39 * 1024);
 }
 template <int RT>
 static hipError_t gate_launch_one(const Ctx& c, const evomoe_shape& s, const void* x, const float* Wg, const float* bg,

@@ -6,12 +6,14 @@ pytestmark = pytest.mark.gpu
 
 import synth_inputs as synth  # noqa: E402
 
-# T, d, E, dtype; the one block holds T <= 256 tokens, E <= 16 experts and d <= 256, at 16, 32 or 64 tokens per wave group
+# T, d, E, dtype; the one block holds T <= 256 tokens, E <= 16 experts and d <= 256, at 16, 32 or 64 tokens per wave group, in
+# float32 with T (d + 4 E) <= 39 * 1024
 CASES = [
     (1, 64, 1, "bf16"), (15, 72, 16, "bf16"), (64, 256, 16, "bf16"), (65, 200, 7, "bf16"), (128, 256, 15, "bf16"),
     (129, 136, 4, "bf16"), (256, 256, 16, "bf16"),
     (48, 256, 17, "bf16"), (86, 264, 16, "bf16"), (257, 64, 4, "bf16"),
-    (17, 64, 16, "f32"), (100, 68, 5, "f32"), (256, 256, 4, "f32"), (256, 260, 4, "f32"), (257, 64, 4, "f32"),
+    (17, 64, 16, "f32"), (100, 68, 5, "f32"), (146, 256, 4, "f32"), (156, 192, 16, "f32"), (256, 64, 16, "f32"),
+    (147, 256, 4, "f32"), (157, 192, 16, "f32"), (256, 256, 4, "f32"), (256, 260, 4, "f32"), (257, 64, 4, "f32"),
 ]
 
 
