@@ -15,7 +15,7 @@ __global__ __launch_bounds__(256) void gather_colsum_kernel(
     const int32_t* __restrict__ pair_token, int vec_per_row, u32x4* __restrict__ x_perm)
 {
     if ((int)blockIdx.x >= sum_blocks) {
-        gather_rows(x, pair_token, clamp_pairs(expert_offsets[E], P_cap), vec_per_row, x_perm,
+        gather_rows<2>(x, pair_token, clamp_pairs(expert_offsets[E], P_cap), vec_per_row, x_perm,
                     (int)blockIdx.x - sum_blocks, (int)gridDim.x - sum_blocks);
         return;
     }
