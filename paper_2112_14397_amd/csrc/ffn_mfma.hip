@@ -422,34 +422,24 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         // the clamped elements of the other would make 0 * Inf = NaN of a result that is infinite)
         // (always the tile's last slab: its position comes from the tile, not from the loop counter, so that
         // no per-lane induction variable is carried through the main loop for this rare path)
+        // Short loops and a fresh copy of the lane number: unrolled, the addresses of this rare path cost dXp 1-2 %.
         auto zero_tail = [&]() {
             const int slab = nslab - 1;
-            unsigned char* sa = smem + (slab % NSTAGE) * G::STAGE + wave * 1024;
+            int lane_z = lane_id;
+            asm volatile("" : "+v"(lane_z));
+            unsigned char* sa = smem + (slab % NSTAGE) * G::STAGE + wave * 1024 + lane_z * 16;
             unsigned char* sb = sa + G::A_BYTES;
-            const int k0 = kbeg + slab * BK;
+            const int left = klen - slab * BK;                    // k's of the last slab that exist
+            const bool chunk_out = kc_chunk * 8 >= left;
             const u32x4 z = {0u, 0u, 0u, 0u};
-            if (G::A_KC) {
-                if (k0 + kc_chunk * 8 >= kend) {
-#pragma unroll
-                    for (int i = 0; i < A_LD; ++i) *reinterpret_cast<u32x4*>(sa + i * (NW * 1024) + lane * 16) = z;
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < A_LD; ++i)
-                    if (k0 + (wave + NW * i) * A_RPI + ksA_row >= kend)
-                        *reinterpret_cast<u32x4*>(sa + i * (NW * 1024) + lane * 16) = z;
-            }
-            if (G::B_KC) {
-                if (k0 + kc_chunk * 8 >= kend) {
-#pragma unroll
-                    for (int i = 0; i < B_LD; ++i) *reinterpret_cast<u32x4*>(sb + i * (NW * 1024) + lane * 16) = z;
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < B_LD; ++i)
-                    if (k0 + (wave + NW * i) * B_RPI + ksB_row >= kend)
-                        *reinterpret_cast<u32x4*>(sb + i * (NW * 1024) + lane * 16) = z;
-            }
+#pragma unroll 1
+            for (int i = 0; i < A_LD; ++i)
+                if (G::A_KC ? chunk_out : (wave + NW * i) * A_RPI + lane_z / A_CPR >= left)
+                    *reinterpret_cast<u32x4*>(sa + i * (NW * 1024)) = z;
+#pragma unroll 1
+            for (int i = 0; i < B_LD; ++i)
+                if (G::B_KC ? chunk_out : (wave + NW * i) * B_RPI + lane_z / B_CPR >= left)
+                    *reinterpret_cast<u32x4*>(sb + i * (NW * 1024)) = z;
         };
         // operand fragment number f (A tiles 0..TM-1, then B tiles) of k-step ks of slab `slab`
         auto read_frag = [&](int f, int slab, int ks, bf16x8* fa, bf16x8* fb) {
