@@ -322,10 +322,9 @@ def main():
             "dispatch_hist": T * 8, "dispatch_scatter": T * 12 + Pavg * 16,
             "combine": Pavg * d * sz + T * d * sz + Pavg * 8,
             "combine_bwd": 2 * Pavg * d * sz + T * d * sz + Pavg * 12,
-            # bf16 layer: the gather of x and the column sums of dO in one launch (db1 comes from column sums the dH GEMM
-            # leaves behind; the last sums of both bias gradients are part of the weight-gradient launch)
-            "ffn_bwd_dw1": (3 if cfg.dtype == "bf16" else 2) * Pavg * d * sz + Pavg * 4,
-            "ffn_bwd_db": Pavg * (F + d) * sz,
+            # (bf16 layer) the gather of x and the column sums of dO, one launch; both types take the bias gradients' other sums
+            # inside the GEMM launches
+            "ffn_bwd_dw1": 3 * Pavg * d * sz + Pavg * 4,
             "dispatch_bwd": Pavg * d * sz + T * d * sz,
             "gate_bwd_dz": T * E * 8 + Pavg * 8 + T * 12,
             "gate_bwd_main": T * d * sz * 3 + T * E * 4,

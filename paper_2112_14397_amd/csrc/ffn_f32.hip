@@ -7,7 +7,7 @@
 //
 // What bounds it: the float32 matrix rate (256 flop per clock and CU, a sixteenth of bf16's), so neither LDS nor L2
 // needs more than plain double buffering: global -> registers -> LDS one slab ahead, several blocks per CU.  GEMM1 of
-// 11160 pairs, d = 512, F = 2048: 97 TFLOP/s; a 4096^3 library product reaches 137 on the same card, the float32-FMA
+// 11160 pairs, d = 512, F = 2048: 100 TFLOP/s; a 4096^3 library product reaches 137 on the same card, the float32-FMA
 // kernels that stood here before 25.  The bias gradients' column sums are further tiles behind dXp's and behind the weight
 // gradients': colsum_tile().
 // A lane's four k's of one fragment come from one 16-byte LDS read where k is contiguous and from four 4-byte reads
@@ -381,9 +381,9 @@ __global__ __launch_bounds__(256, (blocks_per_cu<EPI, BM>())) void grouped_gemm_
 }
 
 // Which tile.  A launch takes about (tiles each CU gets) x (work of a tile); 32x32 tiles pad and quantise less but take
-// about 1.25 times as long per output.  Measured (us, 64x64 / 32x32) at d = 256, E = 8, F = 1024: 5626 pairs GEMM1 44 / 50,
-// GEMM2 46 / 43, dXp 51 / 43, both dW 77 / 95; 1419 pairs GEMM2 30 / 18, dW 27 / 35; d = 512, E = 16, F = 2048, 11160 pairs
-// GEMM1 242 / 298, dW 519 / 667; d = 64, E = 4, F = 256, 533 pairs GEMM2 13 / 8.  128x128 tiles (GEMM1 63 and GEMM2 84 us
+// about 1.25 times as long per output.  Measured (us, 64x64 / 32x32) at d = 256, E = 8, F = 1024: 5626 pairs GEMM1 46 / 50,
+// GEMM2 47 / 44, dXp 54 / 47, both dW 72 / 85; 1419 pairs GEMM2 30 / 18, dW 28 / 35; d = 512, E = 16, F = 2048, 11160 pairs
+// GEMM1 233 / 289, dW 476 / 600; d = 64, E = 4, F = 256, 533 pairs GEMM2 12 / 7.  128x128 tiles (GEMM1 63 and GEMM2 84 us
 // in the first of these, 286 and 309 in the third) were slower than 64x64 everywhere and are not kept.
 enum class Tile { T64, T32 };
 int64_t tiles_of(int64_t row_tiles, int n, int b) { return row_tiles * ((n + b - 1) / b); }

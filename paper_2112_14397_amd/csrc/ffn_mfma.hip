@@ -497,12 +497,12 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         __builtin_amdgcn_sched_barrier(0);                                                       \
     }
 
-        // previous tile's epilogue has left the LDS; its global stores stay in flight under this tile's
-        // first loads (a full barrier would drain them first)
+        // the previous tile's epilogue has left the LDS
         block_sync_lds();
         // Every load the compiler itself issued during the tile set-up (row indices, spill reloads) has to be
         // complete, and known to it as complete, before the pipeline starts: a wait that it places inside
-        // the main loop for one of its own loads would also wait for the tile loads issued there.
+        // the main loop for one of its own loads would also wait for the tile loads issued there.  (The same counter covers
+        // the previous tile's stores: they are drained here as well.)
         __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
         bf16x8 fa0[TM], fb0[TN_], fa1[TM], fb1[TN_];
         if (nslab > 0) {
@@ -773,8 +773,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
 // BIG8: the same tile worked by eight waves (64x128 each, two per SIMD, 128 accumulator registers): the waves of a SIMD
 // fill each other's stalls and share the epilogue, which is half of a short contraction's tile.
 // A 64-wide slab takes whole 128-byte lines of a k-contiguous operand: with four stages of 32 k the L1 fetched every
-// line twice (its other half was gone by the next slab), 64 B/clk per compute unit at the matrix pipe's own rate, which
-// is all it can take.  BIG8 against 32-wide slabs: GEMM1 404 -> 366 us at d = 768, F = 3072, 58 330 pairs, 1603 -> 1473
+// line twice (its other half was gone by the next slab; 2831 MB from the L2 per GEMM1 launch at 38 969 pairs, now 1470).  BIG8 against 32-wide slabs: GEMM1 404 -> 366 us at d = 768, F = 3072, 58 330 pairs, 1603 -> 1473
 // at d = 1024, F = 4096, 131 072 pairs; BIG: GEMM2 270 -> 254 and 1026 -> 964 us, dXp 261 -> 252 and 994 -> 962 us.
 // OCT: BIG8 with four stages of 32 k, for the weight gradients (k-strided operands are whole lines at any slab width).
 // DUO: two blocks per compute unit (one's epilogue and stalls hide under the other's MFMAs).
