@@ -7,7 +7,7 @@
 //
 // What bounds it: the float32 matrix rate (256 flop per clock and CU, a sixteenth of bf16's), so neither LDS nor L2
 // needs more than plain double buffering: global -> registers -> LDS one slab ahead, several blocks per CU.  GEMM1 of
-// 11160 pairs, d = 512, F = 2048: 100 TFLOP/s; a 4096^3 library product reaches 137 on the same card, the float32-FMA
+// 11160 pairs, d = 512, F = 2048: 102 TFLOP/s; a 4096^3 library product reaches 137 on the same card, the float32-FMA
 // kernels that stood here before 25.  The bias gradients' column sums are further tiles behind dXp's and behind the weight
 // gradients': colsum_tile().
 // A lane's four k's of one fragment come from one 16-byte LDS read where k is contiguous and from four 4-byte reads
@@ -133,7 +133,7 @@ template <int BM> __device__ __forceinline__ Offsets scan_offsets(const int32_t*
 // leave; 64x64 tiles of dH, whose act'(H) epilogue spills there, and of GEMM2 take three.  us at d = 512, F = 2048, 11160 /
 // 8126 / 30000 pairs, and d = 256, F = 1024, 5626: dH with four 266 / - / - / 56, with three and a grid for four 291 / 215 /
 // 758 / 51, with three 268 / 198 / 700 / 51; GEMM2 with four 236 / 167 / 570 / 44, with three 229 / 166 / 557 / 44; dXp and
-// the weight gradients are 2-5 % slower with three.
+// the weight gradients are 2-5 % slower with three.  (All before the fragments were read ahead: NP below.)
 template <int EPI, int B> constexpr int blocks_per_cu() { return B == 64 && (EPI == E_ACTGRAD || EPI == E_BIAS) ? 3 : 4; }
 template <int LAYOUT, int EPI, int BM, int BN>
 __global__ __launch_bounds__(256, (blocks_per_cu<EPI, BM>())) void grouped_gemm_f32(
@@ -154,6 +154,10 @@ __global__ __launch_bounds__(256, (blocks_per_cu<EPI, BM>())) void grouped_gemm_
     // additions, and with it every bit of the result, is the same in both.  (One sum per output in the 64x64 tile, as long as
     // the whole contraction, took 1 % less for the GEMMs and 2-4 % for dXp, and gave other bits than the 32x32 tile.)
     constexpr int NP = SPLIT ? 1 : 4, NG = BK / 32;                        // partial sums per wave, groups of each per slab
+    // A group's fragments are read under the MFMAs of the group before, which the scheduler keeps to where registers allow:
+    // 64x64 tiles of GEMM1, GEMM2 and dH at d = 512, F = 2048, 30000 pairs 608, 561 and 700 -> 592, 543 and 686 us, dXp's
+    // 590 -> 618 if it is held to it, the weight gradients' 1205 -> 1266, and 150 -> 155 in 32x32 tiles if they read ahead.
+    constexpr bool AHEAD = LAYOUT != L_TN, PIN = AHEAD && !SPLIT && EPI != E_NONE;
     __shared__ float smem[2 * (A_SZ + B_SZ)];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, kg = lane >> 5;
@@ -288,17 +292,25 @@ __global__ __launch_bounds__(256, (blocks_per_cu<EPI, BM>())) void grouped_gemm_
             const float* sa = smem + (s & 1) * (A_SZ + B_SZ);
             const float* sb = sa + A_SZ;
             if (s + 1 < nslab) fetch(kbeg + (s + 1) * BK);
+            f32x4 fa[2], fb[2];
+            auto frags = [&](int gk) {
+                const int k = wk + gk * (SPLIT ? 32 : 8) + kg * 4, m = wm + l32, n = wn + l32;
+                f32x4 &a = fa[gk & 1], &b = fb[gk & 1];
+                if (A_KC) a = *reinterpret_cast<const f32x4*>(sa + m * A_LD + k);
+                else a = f32x4{sa[k * A_LD + m], sa[(k + 1) * A_LD + m], sa[(k + 2) * A_LD + m], sa[(k + 3) * A_LD + m]};
+                if (B_KC) b = *reinterpret_cast<const f32x4*>(sb + n * B_LD + k);
+                else b = f32x4{sb[k * B_LD + n], sb[(k + 1) * B_LD + n], sb[(k + 2) * B_LD + n], sb[(k + 3) * B_LD + n]};
+            };
+            if (AHEAD) frags(0);
 #pragma unroll
             for (int gk = 0; gk < NG * NP; ++gk) {
-                const int k = wk + gk * (SPLIT ? 32 : 8) + kg * 4, m = wm + l32, n = wn + l32;
-                f32x4 fa, fb;
-                if (A_KC) fa = *reinterpret_cast<const f32x4*>(sa + m * A_LD + k);
-                else fa = f32x4{sa[k * A_LD + m], sa[(k + 1) * A_LD + m], sa[(k + 2) * A_LD + m], sa[(k + 3) * A_LD + m]};
-                if (B_KC) fb = *reinterpret_cast<const f32x4*>(sb + n * B_LD + k);
-                else fb = f32x4{sb[k * B_LD + n], sb[(k + 1) * B_LD + n], sb[(k + 2) * B_LD + n], sb[(k + 3) * B_LD + n]};
+                if (!AHEAD) frags(gk);
+                else if (gk + 1 < NG * NP) frags(gk + 1);
+                if (PIN) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    acc[gk % NP] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u], fb[u], acc[gk % NP], 0, 0, 0);
+                    acc[gk % NP] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[gk & 1][u], fb[gk & 1][u], acc[gk % NP], 0, 0, 0);
+                if (PIN) __builtin_amdgcn_sched_barrier(0);
             }
             if (s + 1 < nslab) {
                 float* na = smem + ((s + 1) & 1) * (A_SZ + B_SZ);
@@ -383,7 +395,7 @@ __global__ __launch_bounds__(256, (blocks_per_cu<EPI, BM>())) void grouped_gemm_
 // Which tile.  A launch takes about (tiles each CU gets) x (work of a tile); 32x32 tiles pad and quantise less but take
 // about 1.25 times as long per output.  Measured (us, 64x64 / 32x32) at d = 256, E = 8, F = 1024: 5626 pairs GEMM1 46 / 50,
 // GEMM2 47 / 44, dXp 54 / 47, both dW 72 / 85; 1419 pairs GEMM2 30 / 18, dW 28 / 35; d = 512, E = 16, F = 2048, 11160 pairs
-// GEMM1 233 / 289, dW 476 / 600; d = 64, E = 4, F = 256, 533 pairs GEMM2 12 / 7.  128x128 tiles (GEMM1 63 and GEMM2 84 us
+// GEMM1 230 / 289, dW 479 / 600; d = 64, E = 4, F = 256, 533 pairs GEMM2 12 / 7.  128x128 tiles (GEMM1 63 and GEMM2 84 us
 // in the first of these, 286 and 309 in the third) were slower than 64x64 everywhere and are not kept.
 enum class Tile { T64, T32 };
 int64_t tiles_of(int64_t row_tiles, int n, int b) { return row_tiles * ((n + b - 1) / b); }
