@@ -1,21 +1,30 @@
-// Expert FFNs of a float32 layer (EvoMoE Eq. ffn per expert over its ragged row range, and its backward) on the
-// float32 matrix cores.  One grouped-GEMM kernel, v_mfma_f32_32x32x2_f32 (products and sums are float32 throughout):
+// Expert FFNs of a float32 layer (EvoMoE Eq. ffn per expert over its ragged row range, and its backward) on the bf16 matrix
+// cores, at float32 accuracy:
 //
 //   NT  C[r,n] = sum_k A[arow(r),k] * W_g[n,k]          forward GEMMs (A rows optionally gathered by token)
 //   NN  C[r,n] = sum_k A[r,k]       * W_g[k,n]          dH = dO W2,  dXp = dH W1
 //   TN  C_g[m,n] = sum_{r in g} L[r,m] * R[rrow(r),n]   weight gradients (contraction over the ragged rows)
 //
-// What bounds it: the float32 matrix rate (256 flop per clock and CU, a sixteenth of bf16's), so neither LDS nor L2
-// needs more than plain double buffering: global -> registers -> LDS one slab ahead, several blocks per CU.  GEMM1 of
-// 11160 pairs, d = 512, F = 2048: 102 TFLOP/s; a 4096^3 library product reaches 137 on the same card, the float32-FMA
-// kernels that stood here before 25.  The bias gradients' column sums are further tiles behind dXp's and behind the weight
-// gradients': colsum_tile().
-// A lane's four k's of one fragment come from one 16-byte LDS read where k is contiguous and from four 4-byte reads
-// where it is the row index; both operands use the same k order, so the order inside a slab is free.
+// Every float32 value is taken apart into three bf16 values whose sum it is, and a product a * b into the six of the nine
+// products of their terms that are above 2^-24 of it: bf16 MFMAs run at sixteen times the rate of float32 ones, so six of them
+// take 0.38 of the time.  The products are exact and each of four partial sums per output has one rounding per 16 k's (the
+// small products have a sum of their own), where float32 MFMAs round for every k: relative rms error against float64 at 5632
+// pairs, d = 256, E = 8, F = 1024 (float32 MFMAs / here; smaller at every size measured, 64 to 2048 k's): H 1.5e-7 / 7.2e-8,
+// O 2.9e-7 / 1.0e-7, dH 1.6e-7 / 8.2e-8, dXp 2.9e-7 / 1.1e-7, dW 2.4e-7 / 9.7e-8.  With one sum for all six products the
+// contractions of 64 k's had larger errors than float32 MFMAs (H 9.5e-8 against 8.8e-8).
 //
-// Tiles: 64x64 (four waves, 2 x 2), and 32x32 with the slab's k's split over the four waves for launches that would
-// leave most of the chip idle; cheapest() says which and why.  Both add the products of one output in the same order, so
-// that results do not depend on the pair count announced, nor on how many rows a call has.
+// What bounds it: a 64x64 tile's slab of 64 k's takes 768 clocks of the matrix pipes, about as many of the VALU for taking the
+// operands apart, and 32 KB from the L2; two blocks per CU overlap these in part.  The operands go to the LDS as they are, by
+// asynchronous loads, one slab ahead.  A wave has 16 of a slab's k's for the whole tile: what it takes apart no other wave
+// needs.  (The terms in the LDS, each taken apart by one thread: six bytes per value instead of four, two barriers per slab
+// and the loads through registers: 244 us instead of 217 for the step below.)  us, float32 MFMAs / here, GEMM1, GEMM2, dH,
+// dXp, both dW, whole training step: 5632 pairs, d = 256, E = 8, F = 1024: 42 / 36, 42 / 29, 48 / 37, 44 / 33, 73 / 50, 272 /
+// 217; 11000 pairs, d = 512, E = 16, F = 2048: 228 / 175, 238 / 152, 258 / 184, 259 / 171, 472 / 338, 1451 / 1078.
+// The bias gradients' column sums are further tiles behind dXp's and behind the weight gradients': colsum_tile().
+//
+// Tiles: 64x64, and 32x32 for launches that would leave most of the chip idle; cheapest() says which and why.  Both add the
+// products of one output in the same order, so that results do not depend on the pair count announced, nor on how many rows
+// a call has.
 #include "ffn_internal.h"
 
 namespace evomoe {
@@ -129,40 +138,58 @@ template <int BM> __device__ __forceinline__ Offsets scan_offsets(const int32_t*
     return o;
 }
 
-// Blocks per CU, for the registers and for the grid: four (128 registers) fill the stalls that one's loads and barriers
-// leave; 64x64 tiles of dH, whose act'(H) epilogue spills there, and of GEMM2 take three.  us at d = 512, F = 2048, 11160 /
-// 8126 / 30000 pairs, and d = 256, F = 1024, 5626: dH with four 266 / - / - / 56, with three and a grid for four 291 / 215 /
-// 758 / 51, with three 268 / 198 / 700 / 51; GEMM2 with four 236 / 167 / 570 / 44, with three 229 / 166 / 557 / 44; dXp and
-// the weight gradients are 2-5 % slower with three.  (All before the fragments were read ahead: NP below.)
-template <int EPI, int B> constexpr int blocks_per_cu() { return B == 64 && (EPI == E_ACTGRAD || EPI == E_BIAS) ? 3 : 4; }
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+// The three bf16 terms of eight float32 values: hi (cut off, so that no finite value becomes infinite) + mid (rounded) + lo
+// (what is left, eight bits at most) is the value itself.  An infinity or a NaN gives NaN terms behind itself.
+__device__ __forceinline__ void split8(const float* v, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
+    u32x4 h, m, l;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t b0 = __float_as_uint(v[2 * i]), b1 = __float_as_uint(v[2 * i + 1]);
+        const float r0 = v[2 * i] - __uint_as_float(b0 & 0xffff0000u), r1 = v[2 * i + 1] - __uint_as_float(b1 & 0xffff0000u);
+        h[i] = __builtin_amdgcn_perm(b1, b0, 0x07060302);
+        asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(m[i]) : "v"(r0), "v"(r1));      // (seen through, it would be made twice)
+        l[i] = pack_bf16x2(r0 - lo_bf16(m[i]), r1 - hi_bf16(m[i]));
+    }
+    hi = __builtin_bit_cast(bf16x8, h);
+    mid = __builtin_bit_cast(bf16x8, m);
+    lo = __builtin_bit_cast(bf16x8, l);
+}
+
+// 16 bytes per lane, global -> LDS: lane l's data lands at lds + 16 l.  Inline assembly, so that the compiler does not guard
+// every LDS read of the other stage with a wait for it; the kernel waits itself.
+__device__ __forceinline__ void load_to_lds(const float* from, const unsigned char* lds_wave_base) {
+    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)lds_wave_base;
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(from), "s"(at) : "m0", "memory");
+}
+// For every wave of the block: its loads have landed, and it is done with the LDS it was reading.  The wait is the builtin: the
+// compiler, which counts its own loads, would wait again later, for the next slab's too, if it did not know of it.
+__device__ __forceinline__ void all_landed() {
+    __builtin_amdgcn_s_waitcnt(0x0070);     // vmcnt(0) lgkmcnt(0)
+    asm volatile("s_barrier" ::: "memory");
+}
+
+// Blocks per CU, for the registers, the LDS and the grid.
+template <int B> constexpr int blocks_per_cu() { return B == 64 ? 2 : 4; }
+
 template <int LAYOUT, int EPI, int BM, int BN>
-__global__ __launch_bounds__(256, (blocks_per_cu<EPI, BM>())) void grouped_gemm_f32(
+__global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
     F32Pair q, int tiles0, int tiles_all, F32Sums sums, const int32_t* __restrict__ expert_offsets, int E, int64_t P_cap,
     int act, int accumulate)
 {
-    constexpr bool SPLIT = BM == 32;                    // 32x32: the four waves share one tile, a quarter of the k's each
-    constexpr int BK = SPLIT ? 64 : 32;
-    static_assert(BM == BN && (BM == 32 || BM == 64), "tile");
+    constexpr int B = BM, BK = 64;                      // wave w takes the 16 k's from 16 w on of every slab, for the whole tile
+    static_assert(BM == BN && (B == 32 || B == 64), "tile");
     constexpr bool A_KC = LAYOUT != L_TN, B_KC = LAYOUT == L_NT;
-    // LDS rows: [row][BK + 4] (16 lanes' 16-byte reads of one k chunk then cover all 64 banks) or [k][cols + 8]
-    // (the two k groups of a 4-byte read lie 32 banks apart)
-    constexpr int A_LD = A_KC ? BK + 4 : BM + 8, B_LD = B_KC ? BK + 4 : BN + 8;
-    constexpr int A_SZ = A_KC ? BM * A_LD : BK * A_LD, B_SZ = B_KC ? BN * B_LD : BK * B_LD;
-    constexpr int A_V = BM * BK / 1024, B_V = BN * BK / 1024;              // 16-byte vectors per thread and slab
-    // Groups of 8 k's are dealt round-robin to four partial sums, which are added in order at the end.  In the 32x32 tile
-    // each wave has one of them, in the 64x64 tile every wave has all four for its quarter of the tile: the order of the
-    // additions, and with it every bit of the result, is the same in both.  (One sum per output in the 64x64 tile, as long as
-    // the whole contraction, took 1 % less for the GEMMs and 2-4 % for dXp, and gave other bits than the 32x32 tile.)
-    constexpr int NP = SPLIT ? 1 : 4, NG = BK / 32;                        // partial sums per wave, groups of each per slab
-    // A group's fragments are read under the MFMAs of the group before, which the scheduler keeps to where registers allow:
-    // 64x64 tiles of GEMM1, GEMM2 and dH at d = 512, F = 2048, 30000 pairs 608, 561 and 700 -> 592, 543 and 686 us, dXp's
-    // 590 -> 618 if it is held to it, the weight gradients' 1205 -> 1266, and 150 -> 155 in 32x32 tiles if they read ahead.
-    constexpr bool AHEAD = LAYOUT != L_TN, PIN = AHEAD && !SPLIT && EPI != E_NONE;
-    __shared__ float smem[2 * (A_SZ + B_SZ)];
+    constexpr int TM = B / 32;                          // 32x32 pieces along a side of the tile
+    constexpr int OPERAND = B * BK * 4, STAGE = 2 * OPERAND;
+    constexpr int NI = OPERAND / 4096;                  // 1 KB load instructions per wave, operand and slab
+    // An operand whose contraction index is contiguous in memory lies as [row][64 k], its 16-byte chunk c at c ^ (row & 15):
+    // sixteen rows that read the same chunk cover all 64 banks.  One whose contraction index is the row index lies as
+    // [k][columns]; 32 lanes read 32 columns of a row, or 64 in pairs: then piece i of the tile has the columns 2 l + i.
+    constexpr bool A_PAIR = !A_KC && TM == 2, B_PAIR = !B_KC && TM == 2;
+    __shared__ __align__(16) unsigned char smem[2 * STAGE];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, kg = lane >> 5;
-    const int wm = SPLIT ? 0 : (wave >> 1) * (BM / 2), wn = SPLIT ? 0 : (wave & 1) * (BN / 2);
-    const int wk = SPLIT ? wave * 8 : 0;
 
     const Offsets off = scan_offsets<BM>(expert_offsets, E, P_cap, lane);
     const int row_tiles = __builtin_amdgcn_readlane(off.t_end, 63);
@@ -177,213 +204,260 @@ __global__ __launch_bounds__(256, (blocks_per_cu<EPI, BM>())) void grouped_gemm_
         tile_end = (int)((int64_t)total * (x + 1) / 8);
         step = gridDim.x >> 3;
     }
-    for (; tile < tile_end; tile += step) {
-        const bool second = LAYOUT == L_TN && tile >= tiles0;
-        const F32Args& p = q.p[second];
+    struct Tile { int second, g, row0, rows, m0, n0, kbeg, kend; };
+    auto locate = [&](int tile) {
+        Tile t{};
+        t.second = LAYOUT == L_TN && tile >= tiles0;
+        const F32Args& p = q.p[t.second];
         const int nct = (p.N + BN - 1) / BN;
-        int g, row0 = 0, rows = 0, m0 = 0, n0, kbeg = 0, kend;
         if (LAYOUT == L_TN) {
-            const int t = second ? tile - tiles0 : tile, nmt = (p.M + BM - 1) / BM;
-            g = t / (nmt * nct);
-            const int rem = t - g * nmt * nct;
-            m0 = rem / nct * BM;
-            n0 = rem % nct * BN;
-            kbeg = __builtin_amdgcn_readlane(off.begin, g);
-            kend = kbeg + __builtin_amdgcn_readlane(off.count, g);
+            const int i = t.second ? tile - tiles0 : tile, nmt = (p.M + BM - 1) / BM;
+            t.g = i / (nmt * nct);
+            const int rem = i - t.g * nmt * nct;
+            t.m0 = rem / nct * BM;
+            t.n0 = rem % nct * BN;
+            t.kbeg = __builtin_amdgcn_readlane(off.begin, t.g);
+            t.kend = t.kbeg + __builtin_amdgcn_readlane(off.count, t.g);
         } else {
             const int rt = tile / nct;
-            n0 = (tile - rt * nct) * BN;
-            g = __ffsll((unsigned long long)__ballot(rt >= off.t_begin && rt < off.t_end)) - 1;
-            const int in = (rt - __builtin_amdgcn_readlane(off.t_begin, g)) * BM;
-            row0 = __builtin_amdgcn_readlane(off.begin, g) + in;
-            rows = min(BM, __builtin_amdgcn_readlane(off.count, g) - in);
-            kend = p.K;
+            t.n0 = (tile - rt * nct) * BN;
+            t.g = __ffsll((unsigned long long)__ballot(rt >= off.t_begin && rt < off.t_end)) - 1;
+            const int in = (rt - __builtin_amdgcn_readlane(off.t_begin, t.g)) * BM;
+            t.row0 = __builtin_amdgcn_readlane(off.begin, t.g) + in;
+            t.rows = min(BM, __builtin_amdgcn_readlane(off.count, t.g) - in);
+            t.kend = p.K;
         }
-        const float* Bg = LAYOUT == L_TN ? p.B : p.B + (int64_t)g * p.b_group_stride;
-        const int nslab = (kend - kbeg + BK - 1) / BK;
-
-        // This thread's share of a slab: vector v of an operand is number tid + 256 v of the slab's 16-byte pieces.
-        // Rows and columns outside the tile are clamped onto valid ones (their products are never stored), k's outside
-        // the contraction range too; both operands are zero there (0 times an infinity in the clamped element of the other
-        // would be NaN).  No load sits in a branch, so a slab's loads go out together.
-        const float* arow[A_V];
-        const float* brow[B_V];
-        int bidx[B_V];                                          // TN with gathered R rows: the next slab's row numbers
-        const bool gathered = LAYOUT == L_TN && p.rows;
+        return t;
+    };
+    // This lane's part in load instruction number wave + 4 i of an operand.  k-contiguous: row 4 (wave + 4 i) + lane / 16, chunk
+    // lane % 16 (holding the one that the swizzle puts there: it does not depend on i).  k-strided: k-row
+    // (wave + 4 i) * KPI + lane / CPR, chunk lane % CPR.
+    constexpr int CPR = B / 4, KPI = 64 / CPR;
+    const int kc_row = wave * 4 + lane / 16, kc_k = ((lane % 16) ^ (kc_row & 15)) * 4;
+    const int ks_row = wave * KPI + lane / CPR, ks_col = lane % CPR * 4;
+    const float* pa[A_KC ? NI : 1];
+    const float* pb[B_KC ? NI : 1];
+    int lda = 0, ldb = 0;                               // of the tile that is being fetched, kept in registers: a TN launch
+    const int32_t* rows = nullptr;                      // would read its problem's from memory for every slab
+    int bidx[NI];                                       // TN with gathered R rows: the next slab's row numbers
+    // Rows and columns outside the tile are clamped onto valid ones (their products are never stored), k's outside the
+    // contraction range too; those are zeroed in both operands (0 times an infinity in the clamped element of the
+    // other would be NaN).
+    auto fetch_rows = [&](const Tile& t, int k0) {
 #pragma unroll
-        for (int v = 0; v < A_V; ++v) {
-            const int i = tid + 256 * v;
-            if (A_KC) {
-                const int r = row0 + min(i / (BK / 4), rows - 1);
-                arow[v] = p.A + (int64_t)(p.rows ? p.rows[r] : r) * p.lda;
-            } else {
-                arow[v] = p.A + min(m0 + (i % (BM / 4)) * 4, p.M - 4);
-            }
-        }
+        for (int i = 0; i < NI; ++i) bidx[i] = rows[min(k0 + ks_row + i * 4 * KPI, t.kend - 1)];
+    };
+    auto aim = [&](const Tile& t) {
+        const F32Args& p = q.p[t.second];
+        lda = p.lda; ldb = p.ldb; rows = p.rows;
+        asm volatile("" : "+s"(lda), "+s"(ldb), "+s"(rows));
+        const float* Bg = LAYOUT == L_TN ? p.B : p.B + (int64_t)t.g * p.b_group_stride;
+        if (A_KC) {
+            int r[NI];
 #pragma unroll
-        for (int v = 0; v < B_V; ++v) {
-            const int i = tid + 256 * v;
-            if (B_KC) brow[v] = Bg + (int64_t)min(n0 + i / (BK / 4), p.N - 1) * p.ldb;
-            else brow[v] = Bg + min(n0 + (i % (BN / 4)) * 4, p.N - 4);
-        }
-        f32x4 ra[A_V], rb[B_V];
-        auto fetch_rows = [&](int k0) {
+            for (int i = 0; i < NI; ++i) r[i] = t.row0 + min(kc_row + 16 * i, t.rows - 1);
+            if (rows)
 #pragma unroll
-            for (int v = 0; v < B_V; ++v) bidx[v] = p.rows[min(k0 + (tid + 256 * v) / (BN / 4), kend - 1)];
-        };
-        auto fetch = [&](int k0) {
+                for (int i = 0; i < NI; ++i) r[i] = rows[r[i]];
 #pragma unroll
-            for (int v = 0; v < A_V; ++v) {
-                const int i = tid + 256 * v;
-                if (A_KC) ra[v] = *reinterpret_cast<const f32x4*>(arow[v] + min(k0 + (i % (BK / 4)) * 4, kend - 4));
-                else ra[v] = *reinterpret_cast<const f32x4*>(arow[v] + (int64_t)min(k0 + i / (BM / 4), kend - 1) * p.lda);
-            }
-#pragma unroll
-            for (int v = 0; v < B_V; ++v) {
-                const int i = tid + 256 * v;
-                if (B_KC) {
-                    rb[v] = *reinterpret_cast<const f32x4*>(brow[v] + min(k0 + (i % (BK / 4)) * 4, kend - 4));
-                } else {
-                    const int k = gathered ? bidx[v] : min(k0 + i / (BN / 4), kend - 1);
-                    rb[v] = *reinterpret_cast<const f32x4*>(brow[v] + (int64_t)k * p.ldb);
-                }
-            }
-            if (gathered && k0 + BK < kend) fetch_rows(k0 + BK);
-            if (k0 + BK > kend) {                               // block-uniform: the last, partial slab
-#pragma unroll
-                for (int v = 0; v < A_V; ++v) {
-                    const int i = tid + 256 * v;
-                    if (k0 + (A_KC ? (i % (BK / 4)) * 4 : i / (BM / 4)) >= kend) ra[v] = f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-#pragma unroll
-                for (int v = 0; v < B_V; ++v) {
-                    const int i = tid + 256 * v;
-                    if (k0 + (B_KC ? (i % (BK / 4)) * 4 : i / (BN / 4)) >= kend) rb[v] = f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-            }
-        };
-        auto place = [&](float* sa, float* sb) {
-#pragma unroll
-            for (int v = 0; v < A_V; ++v) {
-                const int i = tid + 256 * v;
-                *reinterpret_cast<f32x4*>(A_KC ? sa + i / (BK / 4) * A_LD + (i % (BK / 4)) * 4
-                                               : sa + i / (BM / 4) * A_LD + (i % (BM / 4)) * 4) = ra[v];
-            }
-#pragma unroll
-            for (int v = 0; v < B_V; ++v) {
-                const int i = tid + 256 * v;
-                *reinterpret_cast<f32x4*>(B_KC ? sb + i / (BK / 4) * B_LD + (i % (BK / 4)) * 4
-                                               : sb + i / (BN / 4) * B_LD + (i % (BN / 4)) * 4) = rb[v];
-            }
-        };
-        f32x16 acc[NP];
-#pragma unroll
-        for (int q = 0; q < NP; ++q)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
-
-        if (nslab > 0) {
-            if (gathered) fetch_rows(kbeg);
-            fetch(kbeg);
-            place(smem, smem + A_SZ);
-        }
-        __syncthreads();
-        for (int s = 0; s < nslab; ++s) {
-            const float* sa = smem + (s & 1) * (A_SZ + B_SZ);
-            const float* sb = sa + A_SZ;
-            if (s + 1 < nslab) fetch(kbeg + (s + 1) * BK);
-            f32x4 fa[2], fb[2];
-            auto frags = [&](int gk) {
-                const int k = wk + gk * (SPLIT ? 32 : 8) + kg * 4, m = wm + l32, n = wn + l32;
-                f32x4 &a = fa[gk & 1], &b = fb[gk & 1];
-                if (A_KC) a = *reinterpret_cast<const f32x4*>(sa + m * A_LD + k);
-                else a = f32x4{sa[k * A_LD + m], sa[(k + 1) * A_LD + m], sa[(k + 2) * A_LD + m], sa[(k + 3) * A_LD + m]};
-                if (B_KC) b = *reinterpret_cast<const f32x4*>(sb + n * B_LD + k);
-                else b = f32x4{sb[k * B_LD + n], sb[(k + 1) * B_LD + n], sb[(k + 2) * B_LD + n], sb[(k + 3) * B_LD + n]};
-            };
-            if (AHEAD) frags(0);
-#pragma unroll
-            for (int gk = 0; gk < NG * NP; ++gk) {
-                if (!AHEAD) frags(gk);
-                else if (gk + 1 < NG * NP) frags(gk + 1);
-                if (PIN) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    acc[gk % NP] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[gk & 1][u], fb[gk & 1][u], acc[gk % NP], 0, 0, 0);
-                if (PIN) __builtin_amdgcn_sched_barrier(0);
-            }
-            if (s + 1 < nslab) {
-                float* na = smem + ((s + 1) & 1) * (A_SZ + B_SZ);
-                place(na, na + A_SZ);
-            }
-            __syncthreads();
-        }
-
-        // ---------------- epilogue ----------------
-        // What the epilogue reads (bias, H, the old gradient) is loaded, at clamped addresses, before its first store.
-        // Its lane constants come from an opaque copy of the lane number: they are not carried through the main loop.
-        int lane_e = tid & 63;
-        asm volatile("" : "+v"(lane_e));
-        const int l32e = lane_e & 31, rowe = wm + 4 * (lane_e >> 5);
-        const int lim_r = LAYOUT == L_TN ? p.M - m0 : rows;             // rows of the tile that exist
-        const int64_t origin = LAYOUT == L_TN ? ((int64_t)g * p.M + m0) * p.N : (int64_t)row0 * p.N;
-        const float* reads = EPI == E_ACTGRAD ? p.Hin + origin : EPI == E_WGRAD && accumulate ? p.out1 + origin : nullptr;
-        auto offset_of = [&](int tr, int n) { return (uint32_t)(min(tr, lim_r - 1) * p.N + min(n, p.N - 1)); };
-        auto bias_of = [&](int n) {
-            return (EPI == E_HA || EPI == E_BIAS) && p.bias ? p.bias[(int64_t)g * p.N + min(n, p.N - 1)] : 0.f;
-        };
-        auto finish = [&](int tr, int n, float v, float bias, float old) {
-            if (EPI == E_HA || EPI == E_BIAS) v += bias;
-            if (EPI == E_ACTGRAD) v *= act_grad(old, act);
-            if (EPI == E_WGRAD && accumulate) v += old;
-            const float a = EPI == E_HA ? act_fwd(v, act) : 0.f;
-            const uint32_t o = offset_of(tr, n);
-            if (tr < lim_r && n < p.N) {
-                p.out1[origin + o] = v;
-                if (EPI == E_HA) p.out2[origin + o] = a;
-            }
-        };
-        if (SPLIT) {
-            // the four waves' partial tiles, added in wave order
-            constexpr int LD = 36;
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                smem[(wave * 32 + 8 * (r >> 2) + 4 * kg + (r & 3)) * LD + l32] = acc[0][r];
-            const float bias = bias_of(n0 + l32);
-            float old[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) old[u] = reads ? reads[offset_of((tid >> 5) + 8 * u, n0 + l32)] : 0.f;
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int tr = (tid >> 5) + 8 * u;
-                float v = 0.f;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) v += smem[(w * 32 + tr) * LD + l32];
-                finish(tr, n0 + l32, v, bias, old[u]);
-            }
-            __syncthreads();
+            for (int i = 0; i < NI; ++i) pa[A_KC ? i : 0] = p.A + (int64_t)r[i] * lda;
         } else {
-            const int n = n0 + wn + l32e;
-            float sum[16], old[16];
+            pa[0] = p.A + min(t.m0 + ks_col, p.M - 4);
+        }
+        if (B_KC) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                sum[r] = 0.f;
+            for (int i = 0; i < NI; ++i) pb[B_KC ? i : 0] = Bg + (int64_t)min(t.n0 + kc_row + 16 * i, p.N - 1) * ldb;
+        } else {
+            pb[0] = Bg + min(t.n0 + ks_col, p.N - 4);
+        }
+        if (LAYOUT == L_TN && rows && t.kbeg < t.kend) fetch_rows(t, t.kbeg);
+    };
+    auto issue = [&](const Tile& t, int k0, int stage) {
+        unsigned char* sa = smem + stage * STAGE + wave * 1024;
+        unsigned char* sb = sa + OPERAND;
+        const int kc = min(k0 + kc_k, t.kend - 4);
 #pragma unroll
-                for (int q = 0; q < NP; ++q) sum[r] += acc[q][r];
+        for (int i = 0; i < NI; ++i) {
+            const int ks = min(k0 + ks_row + i * 4 * KPI, t.kend - 1);
+            load_to_lds(A_KC ? pa[A_KC ? i : 0] + kc : pa[0] + (int64_t)ks * lda, sa + i * 4096);
+        }
+        const bool gathered = LAYOUT == L_TN && rows;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int ks = gathered ? bidx[i] : min(k0 + ks_row + i * 4 * KPI, t.kend - 1);
+            load_to_lds(B_KC ? pb[B_KC ? i : 0] + kc : pb[0] + (int64_t)ks * ldb, sb + i * 4096);
+        }
+        if (gathered && k0 + BK < t.kend) fetch_rows(t, k0 + BK);
+    };
+
+    // both operands beyond the end of the contraction (`left` k's into the slab): each lane clears what it has loaded
+    auto zero_tail = [&](int stage, int left) {
+        unsigned char* sa = smem + stage * STAGE + wave * 1024 + lane * 16;
+        unsigned char* sb = sa + OPERAND;
+        const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int i = 0; i < NI; ++i) {
+            const bool out = ks_row + i * 4 * KPI >= left;
+            if (A_KC ? kc_k >= left : out) *reinterpret_cast<f32x4*>(sa + i * 4096) = z;
+            if (B_KC ? kc_k >= left : out) *reinterpret_cast<f32x4*>(sb + i * 4096) = z;
+        }
+    };
+
+    int first = 0;                                      // stage of the tile's first slab
+    auto start = [&](const Tile& t) {
+        aim(t);
+        if (t.kbeg < t.kend) issue(t, t.kbeg, first);
+    };
+    Tile next{};
+    if (tile < tile_end) {
+        next = locate(tile);
+        start(next);
+    }
+    for (; tile < tile_end; tile += step) {
+        const Tile t = next;
+        const F32Args& p = q.p[t.second];
+        const int kbeg = t.kbeg, kend = t.kend, nslab = (kend - kbeg + BK - 1) / BK;
+        const bool more = tile + step < tile_end;
+        if (more) next = locate(tile + step);
+
+        f32x16 acc[TM][TM], small[TM][TM];              // hi * hi; the five smaller products
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = small[i][j][r] = 0.f;
+
+        for (int s = 0; s < nslab; ++s) {
+            all_landed();                               // slab s is there, and everyone is done with the other stage
+            const int stage = first ^ (s & 1), k0 = kbeg + s * BK;
+            if (s + 1 < nslab) issue(t, k0 + BK, stage ^ 1);
+            if (k0 + BK > kend) {                       // block-uniform: the contraction ends inside this slab
+                zero_tail(stage, kend - k0);
+                __syncthreads();
             }
-            const float bias = bias_of(n);
+            const float* sa = reinterpret_cast<const float*>(smem + stage * STAGE);
+            const float* sb = sa + OPERAND / 4;
+            const int kw = k0 + wave * 16;              // this wave's 16 k's
+            if (kw < kend) {
+                // raw fragments: eight k's of a row (column) per lane
+                float va[TM][8], vb[TM][8];
+                auto read = [&](const float* operand, bool k_contiguous, int i, float (&out)[TM][8]) {
+                    float* v = out[i];
+                    if (k_contiguous) {
+                        const float* row = operand + (i * 32 + l32) * BK;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) old[r] = reads ? reads[offset_of(rowe + 8 * (r >> 2) + (r & 3), n)] : 0.f;
+                        for (int h = 0; h < 2; ++h) {
+                            const f32x4 c = *reinterpret_cast<const f32x4*>(row + ((wave * 4 + kg * 2 + h) ^ (l32 & 15)) * 4);
+                            v[4 * h] = c.x; v[4 * h + 1] = c.y; v[4 * h + 2] = c.z; v[4 * h + 3] = c.w;
+                        }
+                    } else if (TM == 1) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) finish(rowe + 8 * (r >> 2) + (r & 3), n, sum[r], bias, old[r]);
+                        for (int e = 0; e < 8; ++e) v[e] = operand[(wave * 16 + kg * 8 + e) * B + l32];
+                    } else if (i == 0) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const f32x2 c = *reinterpret_cast<const f32x2*>(operand + (wave * 16 + kg * 8 + e) * B + 2 * l32);
+                            out[0][e] = c.x;
+                            out[TM - 1][e] = c.y;
+                        }
+                    }
+                };
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    read(sa, A_KC, i, va);
+                    read(sb, B_KC, i, vb);
+                }
+                bf16x8 fa[3][TM], fb[3][TM];
+                auto products = [&](int i, int j) {
+#pragma unroll
+                    for (int u = 0; u < 6; ++u) {
+                        constexpr int TA[6] = {0, 0, 1, 1, 0, 2}, TB[6] = {0, 1, 0, 1, 2, 0};
+                        f32x16& c = u == 0 ? acc[i][j] : small[i][j];
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[TA[u]][i], fb[TB[u]][j], c, 0, 0, 0);
+                    }
+                };
+                // the next fragment is split under the products of the ones before it: eight VALU slots per MFMA
+                auto spread = [&]() {
+#pragma unroll
+                    for (int u = 0; u < 6; ++u) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                split8(va[0], fa[0][0], fa[1][0], fa[2][0]);
+                split8(vb[0], fb[0][0], fb[1][0], fb[2][0]);
+                __builtin_amdgcn_sched_barrier(0);
+                products(0, 0);
+                if (TM == 2) {
+                    split8(va[TM - 1], fa[0][TM - 1], fa[1][TM - 1], fa[2][TM - 1]);
+                    spread();
+                    products(TM - 1, 0);
+                    split8(vb[TM - 1], fb[0][TM - 1], fb[1][TM - 1], fb[2][TM - 1]);
+                    spread();
+                    products(0, TM - 1);
+                    products(TM - 1, TM - 1);
+                }
+            }
+        }
+        first ^= nslab & 1;
+        if (more) start(next);                          // the next tile's first slab is fetched under this tile's epilogue
+
+        // ---------------- epilogue: the four waves' partial tiles, added in wave order, 32 rows at a time ----------------
+        const int lim_r = LAYOUT == L_TN ? p.M - t.m0 : t.rows;         // rows of the tile that exist
+        const int64_t origin = LAYOUT == L_TN ? ((int64_t)t.g * p.M + t.m0) * p.N : (int64_t)t.row0 * p.N;
+        const float* reads = EPI == E_ACTGRAD ? p.Hin + origin : EPI == E_WGRAD && accumulate ? p.out1 + origin : nullptr;
+        float* red = reinterpret_cast<float*>(smem + (first ^ 1) * STAGE);      // the stage that the next tile does not start in
+        // behind an infinite or NaN operand the smaller products are NaN; the large ones have what float32 products would give
+        auto both = [](float large, float small) {
+            const float v = large + small;
+            return fabsf(v) <= 3.402823466e38f ? v : large;
+        };
+        auto row_of = [](int i, int r) { return A_PAIR ? 2 * r + i : i * 32 + r; };     // of row r of pass i
+        constexpr int NO = B / 32;                      // vectors of four outputs per thread and pass
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    red[(wave * 32 + 8 * (r >> 2) + 4 * kg + (r & 3)) * B + (B_PAIR ? 2 * l32 + j : j * 32 + l32)] =
+                        both(acc[i][j][r], small[i][j][r]);
+            f32x4 old[NO], bias[NO];
+#pragma unroll
+            for (int u = 0; u < NO; ++u) {
+                const int o = tid + 256 * u, tr = min(row_of(i, o / (B / 4)), lim_r - 1), n = min(t.n0 + o % (B / 4) * 4, p.N - 4);
+                old[u] = bias[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (reads) old[u] = *reinterpret_cast<const f32x4*>(reads + (int64_t)tr * p.N + n);
+                if ((EPI == E_HA || EPI == E_BIAS) && p.bias) bias[u] = *reinterpret_cast<const f32x4*>(p.bias + (int64_t)t.g * p.N + n);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < NO; ++u) {
+                const int o = tid + 256 * u, tr = row_of(i, o / (B / 4)), n = t.n0 + o % (B / 4) * 4;
+                if (tr >= lim_r || n >= p.N) continue;
+                f32x4 v = {0.f, 0.f, 0.f, 0.f}, a;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) v += *reinterpret_cast<const f32x4*>(red + (w * 32 + o / (B / 4)) * B + o % (B / 4) * 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (EPI == E_HA || EPI == E_BIAS) v[e] += bias[u][e];
+                    if (EPI == E_ACTGRAD) v[e] *= act_grad(old[u][e], act);
+                    if (EPI == E_WGRAD && accumulate) v[e] += old[u][e];
+                    a[e] = EPI == E_HA ? act_fwd(v[e], act) : 0.f;
+                }
+                *reinterpret_cast<f32x4*>(p.out1 + origin + (int64_t)tr * p.N + n) = v;
+                if (EPI == E_HA) *reinterpret_cast<f32x4*>(p.out2 + origin + (int64_t)tr * p.N + n) = a;
+            }
         }
     }
     // the column sums, dealt from the last block on: those have a tile less, or none
     if (EPI == E_NONE) {
         const int tiles = kSumSplit * E * (sums.blocks[0] + sums.blocks[1]);
         if (tiles) __syncthreads();
-        for (int b = gridDim.x - 1 - blockIdx.x; b < tiles; b += gridDim.x) colsum_tile(sums, b, off, E, smem);
+        for (int b = gridDim.x - 1 - blockIdx.x; b < tiles; b += gridDim.x) colsum_tile(sums, b, off, E, reinterpret_cast<float*>(smem));
     }
     if (LAYOUT == L_TN) {
         const int64_t n = (int64_t)E * ((sums.blocks[0] ? sums.N[0] : 0) + (sums.blocks[1] ? sums.N[1] : 0));
@@ -392,22 +466,23 @@ __global__ __launch_bounds__(256, (blocks_per_cu<EPI, BM>())) void grouped_gemm_
     }
 }
 
-// Which tile.  A launch takes about (tiles each CU gets) x (work of a tile); 32x32 tiles pad and quantise less but take
-// about 1.25 times as long per output.  Measured (us, 64x64 / 32x32) at d = 256, E = 8, F = 1024: 5626 pairs GEMM1 46 / 50,
-// GEMM2 47 / 44, dXp 54 / 47, both dW 72 / 85; 1419 pairs GEMM2 30 / 18, dW 28 / 35; d = 512, E = 16, F = 2048, 11160 pairs
-// GEMM1 230 / 289, dW 479 / 600; d = 64, E = 4, F = 256, 533 pairs GEMM2 12 / 7.  128x128 tiles (GEMM1 63 and GEMM2 84 us
-// in the first of these, 286 and 309 in the third) were slower than 64x64 everywhere and are not kept.
-enum class Tile { T64, T32 };
+// Which tile.  A launch takes about (tiles each CU gets) x (work of a tile); 32x32 tiles pad and quantise less, but take twice
+// as many operands apart and fetch twice as much: 1.4 times as long per output, 1.25 where the contraction is short (its
+// start and end then count) and for the weight gradients.  Measured (us, 64x64 / 32x32) at d = 256, E = 8, F = 1024: 5632
+// pairs GEMM1 37 / 41, GEMM2 30 / 33, dXp 33 / 36, both dW 51 / 72; 1340 pairs GEMM1 19 / 17, GEMM2 21 / 15, dW 24 / 28;
+// d = 512, E = 16, F = 2048, 11000 pairs GEMM1 181 / 236, dW 351 / 499; d = 64, E = 4, F = 256, 650 pairs GEMM2 11 / 7;
+// d = 64, E = 1, F = 256, 4096 pairs dW 69 / 40.
+enum class Size { T64, T32 };
 int64_t tiles_of(int64_t row_tiles, int n, int b) { return row_tiles * ((n + b - 1) / b); }
-Tile cheapest(const Ctx& c, int64_t t64, int64_t t32) {
+Size cheapest(const Ctx& c, int64_t t64, int64_t t32, double per_output) {
     auto rounds = [&](int64_t tiles) { return (double)((tiles + c.num_cu - 1) / c.num_cu); };
-    return rounds(t32) * (32 * 32 * 1.25) < rounds(t64) * (64 * 64) ? Tile::T32 : Tile::T64;
+    return rounds(t32) * (32 * 32 * per_output) < rounds(t64) * (64 * 64) ? Size::T32 : Size::T64;
 }
 
 template <int LAYOUT, int EPI, int B>
 hipError_t launch(const Ctx& c, const evomoe_shape& s, const F32Args& a, int64_t t0, const F32Args& b, int64_t t1,
                   const F32Sums& sums, int64_t sum_tiles, const int32_t* expert_offsets, int accumulate) {
-    const int64_t cap = (int64_t)c.num_cu * blocks_per_cu<EPI, B>(), want = (t0 + t1 + sum_tiles + 7) / 8 * 8;
+    const int64_t cap = (int64_t)c.num_cu * blocks_per_cu<B>(), want = (t0 + t1 + sum_tiles + 7) / 8 * 8;
     hipLaunchKernelGGL((grouped_gemm_f32<LAYOUT, EPI, B, B>), dim3((unsigned)(want < cap ? want : cap)), dim3(256), 0,
                        c.stream, F32Pair{{a, b}}, (int)t0, (int)(t0 + t1), sums, expert_offsets, s.E, s.P_cap, s.act,
                        accumulate);
@@ -415,35 +490,35 @@ hipError_t launch(const Ctx& c, const evomoe_shape& s, const F32Args& a, int64_t
 }
 
 // NT / NN: one problem over the row tiles of all experts
-Tile rows_tile(const Ctx& c, const evomoe_shape& s, int n) {
+Size rows_tile(const Ctx& c, const evomoe_shape& s, int n, int k) {
     const int64_t P = c.pair_hint > 0 && c.pair_hint < s.P_cap ? c.pair_hint : s.P_cap;
     auto expected = [&](int b) { return tiles_of((P + b - 1) / b + s.E / 2, n, b); };
-    return cheapest(c, expected(64), expected(32));
+    return cheapest(c, expected(64), expected(32), k < 512 ? 1.25 : 1.4);
 }
 template <int LAYOUT, int EPI>
 hipError_t launch_rows(const Ctx& c, const evomoe_shape& s, const F32Args& a, const int32_t* expert_offsets,
                        const F32Sums& sums = F32Sums{}) {
     auto worst = [&](int b) { return tiles_of((s.P_cap + b - 1) / b + s.E, a.N, b); };
     const int64_t st = (int64_t)kSumSplit * s.E * (sums.blocks[0] + sums.blocks[1]);
-    if (rows_tile(c, s, a.N) == Tile::T64)
+    if (rows_tile(c, s, a.N, a.K) == Size::T64)
         return launch<LAYOUT, EPI, 64>(c, s, a, worst(64), a, 0, sums, st, expert_offsets, 0);
     return launch<LAYOUT, EPI, 32>(c, s, a, worst(32), a, 0, sums, st, expert_offsets, 0);
 }
 // TN: the tiles of one of the two problems; both count for the choice, whichever is wanted
 int64_t wgrad_tiles(const evomoe_shape& s, int b) { return (int64_t)s.E * ((s.d + b - 1) / b) * ((s.F + b - 1) / b); }
-Tile wgrad_tile(const Ctx& c, const evomoe_shape& s) { return cheapest(c, 2 * wgrad_tiles(s, 64), 2 * wgrad_tiles(s, 32)); }
+Size wgrad_tile(const Ctx& c, const evomoe_shape& s) { return cheapest(c, 2 * wgrad_tiles(s, 64), 2 * wgrad_tiles(s, 32), 1.25); }
 
 }  // namespace
 
 FfnTile f32_ffn_tile(const Ctx& c, const evomoe_shape& s, int kernel) {
-    Tile t;
+    Size t;
     switch (kernel) {
-        case EVOMOE_K_FFN_GEMM1: case EVOMOE_K_FFN_BWD_DH: t = rows_tile(c, s, s.F); break;
-        case EVOMOE_K_FFN_GEMM2: case EVOMOE_K_FFN_BWD_DX: t = rows_tile(c, s, s.d); break;
+        case EVOMOE_K_FFN_GEMM1: case EVOMOE_K_FFN_BWD_DH: t = rows_tile(c, s, s.F, s.d); break;
+        case EVOMOE_K_FFN_GEMM2: case EVOMOE_K_FFN_BWD_DX: t = rows_tile(c, s, s.d, s.F); break;
         case EVOMOE_K_FFN_BWD_DW2: t = wgrad_tile(c, s); break;
         default: return {};
     }
-    return t == Tile::T64 ? FfnTile{64, 64, 4} : FfnTile{32, 32, 4};
+    return t == Size::T64 ? FfnTile{64, 64, 4} : FfnTile{32, 32, 4};
 }
 
 hipError_t f32_ffn_fwd(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token,
@@ -513,7 +588,7 @@ hipError_t f32_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, cons
         return launcher(c, s, w[0], n > 0 ? wgrad_tiles(s, b) : 0, w[1], n > 1 ? wgrad_tiles(s, b) : 0, sums, st, expert_offsets,
                         accumulate);
     };
-    return wgrad_tile(c, s) == Tile::T64 ? run(launch<L_TN, E_WGRAD, 64>, 64) : run(launch<L_TN, E_WGRAD, 32>, 32);
+    return wgrad_tile(c, s) == Size::T64 ? run(launch<L_TN, E_WGRAD, 64>, 64) : run(launch<L_TN, E_WGRAD, 32>, 32);
 }
 
 }  // namespace evomoe

@@ -1,0 +1,59 @@
+"""The float32 expert FFN takes its operands apart into bf16 terms: accuracy over contraction lengths and magnitudes."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+import synth_inputs as synth  # noqa: E402
+
+
+@pytest.mark.parametrize("T,d,E,F,scale", [(300, 64, 2, 64, 1.0), (500, 4, 1, 4, 1.0), (260, 256, 4, 516, 1.0),
+                                           (700, 516, 2, 1024, 1.0), (260, 256, 4, 516, 1e18), (260, 256, 4, 516, 1e-18)])
+def test_f32_contractions_are_as_exact_as_float32_sums(T, d, E, F, scale):
+    """Float32 products added one k at a time in four partial sums have a relative rms error of about 2.6e-8 sqrt(K / 8), the
+    additions of the partial sums and the bias a few roundings more: sqrt(K / 8 + 6) in all.  Nothing may be above that."""
+    import torch
+    import gpu_harness as h
+    cfg = synth.LayerConfig("split", T=T, d=d, E=E, F=F, act="relu", dtype="f32", taus=(1.0,), threshold=0.9, seed=77,
+                            bias_std=0.0)
+    gl = h.GpuLayer(synth.make_layer_inputs(cfg))
+    P = gl.forward(1.0, 0.9)
+    assert P == T
+    b, p, B = gl.buf, gl.params, h.B
+    x, dO = gl.x * scale, torch.randn(gl.shape.P_cap, d, generator=torch.Generator("cuda").manual_seed(5), device="cuda") * scale
+    H, A, O = torch.zeros_like(b.H), torch.zeros_like(b.A), torch.zeros_like(b.O)
+    B.evomoe_expert_ffn(gl.ctx, gl.shape, x, b.pair_token, b.expert_offsets, p.W1, None, p.W2, None, H, A, O)
+    B.evomoe_expert_ffn_bwd(gl.ctx, gl.shape, dO, H, A, x, b.pair_token, b.expert_offsets, p.W1, p.W2, None, None, b.dW1, None,
+                            b.dW2, None, b.dXp, False, b.workspace)
+    dH = b.workspace[:P * F * 4].view(torch.float32).view(P, F)
+    off = b.expert_offsets.tolist()
+    err = {}
+    for e in range(E):
+        r = slice(off[e], off[e + 1])
+        xr, W1, W2 = x[b.pair_token[r].long()].double(), p.W1[e].double(), p.W2[e].double()
+        for what, k, got, want in (("H", d, H[r], xr @ W1.T), ("O", F, O[r], A[r].double() @ W2.T),
+                                   ("dH", d, dH[r], (dO[r].double() @ W2) * (H[r] > 0)), ("dXp", F, b.dXp[r], dH[r].double() @ W1),
+                                   ("dW1", r.stop - r.start, b.dW1[e], dH[r].double().T @ xr),
+                                   ("dW2", r.stop - r.start, b.dW2[e], dO[r].double().T @ A[r].double())):
+            unit = want.abs().max()                          # (squares of 1e36 leave float32, not float64)
+            rel = (((got.double() - want) / unit).square().sum() / (want / unit).square().sum()).sqrt().item()
+            assert rel <= 2.6e-8 * (k / 8 + 6) ** 0.5, (what, e, rel)
+            err[what] = max(rel, err.get(what, 0.0))
+    print(T, d, E, F, scale, {k: f"{v:.2g}" for k, v in err.items()})
+
+
+def test_f32_largest_values_stay_finite():
+    """3.4e38 is above the largest bf16 value: its first term must not become infinite."""
+    import torch
+    import gpu_harness as h
+    cfg = synth.LayerConfig("large", T=40, d=64, E=1, F=64, act="relu", dtype="f32", taus=(1.0,), threshold=0.9, seed=78,
+                            bias_std=0.0)
+    gl = h.GpuLayer(synth.make_layer_inputs(cfg))
+    P = gl.forward(1.0, 0.9)
+    b, p, B = gl.buf, gl.params, h.B
+    x = torch.zeros_like(gl.x)
+    x[b.pair_token[3].long(), 17] = 3.4e38
+    H = torch.zeros_like(b.H)
+    B.evomoe_expert_ffn(gl.ctx, gl.shape, x, b.pair_token, b.expert_offsets, p.W1, None, p.W2, None, H, b.A, b.O)
+    want = x[b.pair_token[:P].long()].double() @ p.W1[0].double().T
+    assert torch.isfinite(H).all()
+    assert ((H[:P].double() - want).abs() <= 2e-7 * want.abs()).all()
