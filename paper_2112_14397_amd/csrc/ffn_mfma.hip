@@ -123,30 +123,21 @@ template <int LAYOUT, int BM, int BN, int BK, int NSTAGE, int NW = 4> struct Geo
     template <int C> __device__ static __forceinline__ int ks_key(int k) { return C >= 128 ? 2 * (k & 3) : (k & 2); }
 };
 
-// Phi(h), the standard normal CDF, as 0.5 + hc*Q(hc^2) with hc = h clamped to |h| <= 4.2: degree-8 minimax
-// fit of Q, |error| < 1.2e-5 -- below the resolution of the bf16 values it is multiplied into -- and no
-// transcendental.  gelu(h) = h*Phi(h);  gelu'(h) = Phi(h) + h*phi(h).
-__device__ __forceinline__ float phi_cdf(float h, float& hc, float& u) {
-    hc = __builtin_amdgcn_fmed3f(h, -4.2f, 4.2f);
-    u = hc * hc;
-    float q = 5.998071484e-11f;
-    q = fmaf(q, u, -5.633320033e-09f);
-    q = fmaf(q, u, 2.343674907e-07f);
-    q = fmaf(q, u, -5.760770819e-06f);
-    q = fmaf(q, u, 9.457441047e-05f);
-    q = fmaf(q, u, -1.114148065e-03f);
-    q = fmaf(q, u, 9.830130264e-03f);
-    q = fmaf(q, u, -6.636036932e-02f);
-    q = fmaf(q, u, 3.989074528e-01f);
-    return fmaf(hc, q, 0.5f);
-}
-// Beyond the fitted range the values stay within 2.5e-4 of the true ones for any h: gelu(h) -> h for large h
-// (Phi(4.2) = 1 - 1.3e-5) and -> max(h, -4.2) * 1.3e-5 for very negative h.
+// gelu(h) = max(h, 0) - |h| Q(|h|) with Q(z) = 1 - Phi(z) = 2^p(z): log2 Q is so smooth that a polynomial of degree four on
+// |h| <= 5.5 gives Q to 6.9e-6 (minimax; float32 evaluation included), and beyond it the term is below 1.7e-7.  Nine VALU
+// instructions, one of them v_exp_f32, which takes two slots.  (Phi as an odd polynomial of degree 17 of h clamped to 4.2:
+// errors of 1.1e-5 |h|, 8.7e-5 in the tails, 13 instructions; GEMM1's epilogue is bound by them.)
 __device__ __forceinline__ float act_fwd_fast(float h, int act) {
     if (act == EVOMOE_RELU) return h > 0.f ? h : 0.f;
-    float hc, u;
-    const float Phi = phi_cdf(h, hc, u);
-    return fmaxf(h, -4.2f) * Phi;
+    float z, pos;
+    asm("v_min_f32 %0, |%1|, %2" : "=v"(z) : "v"(h), "s"(5.5f));        // (as fminf and fmaxf each would get a second instruction
+    asm("v_max_f32 %0, 0, %1" : "=v"(pos) : "v"(h));                    // for signalling NaNs)
+    float q = 0.00470887171f;
+    q = fmaf(q, z, -0.0479916483f);
+    q = fmaf(q, z, -0.462215245f);
+    q = fmaf(q, z, -1.15046859f);
+    q = fmaf(q, z, -1.00001967f);
+    return fmaf(-z, __builtin_amdgcn_exp2f(q), pos);
 }
 // gelu'(h) = Phi(h) + h phi(h) as 0.5 + hc*R(hc^2): it is odd about 1/2 as well, so one degree-10 minimax fit of the whole
 // derivative takes the place of Phi and an exponential (13 VALU slots instead of 17 in an epilogue that they bound).  R is
@@ -167,7 +158,8 @@ __device__ __forceinline__ float act_grad_fast(float h, int act) {
     r = fmaf(r, v, 1.322824408e-03f);
     r = fmaf(r, v, -1.166708504e-02f);
     r = fmaf(r, v, 1.727069277e-01f);
-    return fmaf(hc, r, 0.5f);
+    asm("v_fmaak_f32 %0, %1, %2, 0x3f000000" : "=v"(r) : "v"(hc), "v"(r));     // 0.5 as a literal: half the time of v_fma_f32
+    return r;
 }
 
 // 16 bytes per lane, global -> LDS, no registers in between: lane l's data lands at lds + 16*l.
@@ -182,6 +174,24 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 __device__ __forceinline__ void store_out(bf16_t* p, const float* in) {
     u32x4 v = {pack_bf16x2(in[0], in[1]), pack_bf16x2(in[2], in[3]), pack_bf16x2(in[4], in[5]), pack_bf16x2(in[6], in[7])};
     __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
+}
+// The same through a buffer descriptor of what exists of the output: lanes beyond it store nothing, without a branch around the
+// store, so that a wave's stores can be counted.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_of(const void* base, int bytes) {
+    const uint64_t b = (uint64_t)(uintptr_t)base;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)((uint64_t)hi << 32 | lo), 0,
+                                             __builtin_amdgcn_readfirstlane(bytes), 0x27000);
+}
+__device__ __forceinline__ void store_out(bf16_t* base, int bytes, uint32_t offset, const float* in) {
+    u32x4 v = {pack_bf16x2(in[0], in[1]), pack_bf16x2(in[2], in[3]), pack_bf16x2(in[4], in[5]), pack_bf16x2(in[6], in[7])};
+    __builtin_amdgcn_raw_buffer_store_b128(v, rows_of(base, bytes), offset, 0, 2);      // 2: non-temporal
+}
+__device__ __forceinline__ u32x4 load_in(const bf16_t* base, int bytes, uint32_t offset) {
+    return __builtin_amdgcn_raw_buffer_load_b128(rows_of(base, bytes), offset, 0, 0);
+}
+__device__ __forceinline__ float load_in(const float* base, int bytes, uint32_t offset) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows_of(base, bytes), offset, 0, 0));
 }
 // The global address is a wave-uniform base (an SGPR pair) plus a 32-bit unsigned byte offset per lane.
 __device__ __forceinline__ void load_to_lds(const unsigned char* base, uint32_t voff, const unsigned char* lds_wave_base) {
@@ -269,52 +279,77 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         }
     }
 
-    for (int vtile = vblock;; vtile += gridDim.x, seq += seq_step) {
-        // ---------------- tile -> (problem, expert, origin, contraction range) ----------------
-        if (LAYOUT == L_TN && vtile >= tiles_all) {
-            if (vtile - tiles_all >= qb.tiles) break;
-            bias_final_tile(qb, vtile - tiles_all, offs, NW * 64);
-            continue;
-        }
-        const bool second = (LAYOUT == L_TN) && vtile >= tiles0;
-        const GemmArgs& p = second ? q1 : q0;
-        const int tile = second ? vtile - tiles0 : vtile;
+    // Where a tile lies: problem (TN), expert, origin, contraction range.  NT/NN: place `at` of the sequence; TN: tile number.
+    struct Tile { int second, g, row0, rows, m0, n0, kbeg, kend; };
+    auto locate = [&](int at) {
+        Tile t{};
+        t.second = LAYOUT == L_TN && at >= tiles0;
+        const GemmArgs& p = t.second ? q1 : q0;
         const int nct = (p.N + BN - 1) / BN;
-        const int nmt = (LAYOUT == L_TN) ? (p.M + BM - 1) / BM : 1;
-        int g = 0, row0 = 0, rows = 0, n0 = 0, m0 = 0, kbeg = 0, kend = 0;
         if (LAYOUT == L_TN) {
-            g = tile / (nmt * nct);
+            const int tile = t.second ? at - tiles0 : at, nmt = (p.M + BM - 1) / BM;
+            t.g = tile / (nmt * nct);
             const int rem = tile % (nmt * nct);
-            m0 = (rem / nct) * BM;
-            n0 = (rem % nct) * BN;
-            kbeg = offs[g];
-            kend = offs[g + 1];
+            t.m0 = (rem / nct) * BM;
+            t.n0 = (rem % nct) * BN;
+            t.kbeg = offs[t.g];
+            t.kend = offs[t.g + 1];
         } else {
-            if (seq >= seq_end) break;
-            while (seq >= tstart[cur_e + 1] * nct) ++cur_e;      // resumes where the previous tile's search ended
-            g = cur_e;
-            const int nrt = tstart[g + 1] - tstart[g];           // row tiles of this expert (>= 1 here)
-            const int r = seq - tstart[g] * nct;                 // position inside the expert's nrt * nct tiles
+            while (at >= tstart[cur_e + 1] * nct) ++cur_e;       // resumes where the previous tile's search ended
+            t.g = cur_e;
+            const int nrt = tstart[t.g + 1] - tstart[t.g];       // row tiles of this expert (>= 1 here)
+            const int r = at - tstart[t.g] * nct;                // position inside the expert's nrt * nct tiles
             const int cgs = max(1, min(p.col_group, nct));       // column tiles per group
             const int cg = r / (nrt * cgs);
             const int r2 = r - cg * nrt * cgs;
             const int gc = min(cgs, nct - cg * cgs);             // column tiles of this group (the last may be short)
             const int rt_in = r2 / gc;
-            n0 = (cg * cgs + (r2 - rt_in * gc)) * BN;
-            row0 = offs[g] + rt_in * BM;
-            rows = min(BM, offs[g + 1] - row0);
-            kbeg = 0;
-            kend = p.K;
+            t.n0 = (cg * cgs + (r2 - rt_in * gc)) * BN;
+            t.row0 = offs[t.g] + rt_in * BM;
+            t.rows = min(BM, offs[t.g + 1] - t.row0);
+            t.kend = p.K;
         }
         // the tile's coordinates came through LDS: tell the compiler they are wave-uniform (SGPRs)
-        g = __builtin_amdgcn_readfirstlane(g);
-        row0 = __builtin_amdgcn_readfirstlane(row0);
-        rows = __builtin_amdgcn_readfirstlane(rows);
-        kbeg = __builtin_amdgcn_readfirstlane(kbeg);
-        kend = __builtin_amdgcn_readfirstlane(kend);
+        t.g = __builtin_amdgcn_readfirstlane(t.g);
+        t.row0 = __builtin_amdgcn_readfirstlane(t.row0);
+        t.rows = __builtin_amdgcn_readfirstlane(t.rows);
+        t.n0 = __builtin_amdgcn_readfirstlane(t.n0);
+        t.kbeg = __builtin_amdgcn_readfirstlane(t.kbeg);
+        t.kend = __builtin_amdgcn_readfirstlane(t.kend);
+        return t;
+    };
+
+    // PRE: the next tile's first slab is fetched under this tile's epilogue, into the stage that the epilogue does not use.
+    constexpr bool PRE = LAYOUT != L_TN && EARLY && NW == 8;
+    constexpr int PRE_STORES = WM / 4 * (EPI == E_HA ? 2 : 1);      // at least so many of a wave's stores follow that slab's loads
+    static_assert(!PRE || (PRE_STORES <= 63 && WN == 128 && NW * 4096 <= G::STAGE), "epilogue beside a slab");
+    int par = 0;                    // PRE: stage of the tile's first slab
+    bool begun = false;             // PRE: ... is being fetched already
+    Tile ahead{};
+    // ---------------- global addresses: one scalar base per operand + 32-bit per-lane byte offsets ----
+    // k-contiguous operand: offset of (row, chunk) at k = 0, one register per load instruction.
+    // k-strided operand   : offset = k-row * row bytes + column bytes; every load instruction of a lane
+    //                       has the same column, its k-row is kr0 + a constant.
+    const unsigned char* a_base = nullptr;
+    const unsigned char* b_base = nullptr;
+    uint32_t a_off[G::A_KC ? A_LD : 1], b_off[G::B_KC ? B_LD : 1];
+    uint32_t a_col = 0, b_col = 0;                    // k-strided: column byte offset
+    int kc_chunk = 0, ksA_row = 0, ksB_row = 0;
+
+    for (int vtile = vblock;; vtile += gridDim.x, seq += seq_step) {
+        if (LAYOUT == L_TN && vtile >= tiles_all) {
+            if (vtile - tiles_all >= qb.tiles) break;
+            bias_final_tile(qb, vtile - tiles_all, offs, NW * 64);
+            continue;
+        }
+        if (LAYOUT != L_TN && seq >= seq_end) break;
+        const Tile t = PRE && begun ? ahead : locate(LAYOUT == L_TN ? vtile : seq);
+        const GemmArgs& p = t.second ? q1 : q0;
+        auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };     // (known to be, not when it comes around the loop)
+        const int g = uniform(t.g), row0 = uniform(t.row0), rows = uniform(t.rows), m0 = uniform(t.m0), n0 = uniform(t.n0),
+                  kbeg = uniform(t.kbeg), kend = uniform(t.kend);
         const int nslab = (kend - kbeg + BK - 1) / BK;
         const bool ragged = (kend - kbeg) % BK != 0;     // block-uniform: the last slab is partial
-        const bf16_t* Bg = (LAYOUT == L_TN) ? p.B : p.B + (int64_t)g * p.b_group_stride;
 
         // Everything below that depends on the lane is recomputed for every tile from an opaque copy of the lane
         // number: the values then die with the main loop instead of occupying registers through the epilogue.
@@ -348,53 +383,57 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         // This lane's role in the 1 KB load instruction number (wave + NW*i) of a tile (NW waves):
         //   k-contiguous: row (wave+NW i)*KC_RPI + lane/KC_CH, physical chunk lane%KC_CH -> logical chunk ^ key(row)
         //   k-strided   : k-row (wave+NW i)*RPI + lane/CPR, physical chunk lane%CPR -> logical chunk via block ^ (k & 3)
-        const int kc_row = lane / KC_CH;
-        // key(row) of row (wave + NW i)*KC_RPI + kc_row does not depend on i
-        const int kc_key = (BK == 64) ? ((4 * (wave & 1) + (kc_row >> 1)) & 7) : ((kc_row >> 2) & 3);
-        const int kc_chunk = (lane % KC_CH) ^ kc_key;                           // logical 16 B chunk (8 k's)
-        const int ksA_row = lane / A_CPR, ksB_row = lane / B_CPR;
-        auto ks_col = [&](int pc, int key) { return ((((pc >> 1) ^ key) << 1) | (pc & 1)) * 8; };
-
-        // ---------------- global addresses: one scalar base per operand + 32-bit per-lane byte offsets ----
         // Rows / columns outside the tile are clamped onto valid ones (their products are never stored);
         // the tail of the contraction range is clamped too and then zeroed in LDS.
-        // k-contiguous operand: offset of (row, chunk) at k = 0, one register per load instruction.
-        // k-strided operand   : offset = k-row * row bytes + column bytes; every load instruction of a lane
-        //                       has the same column, its k-row is kr0 + a constant.
-        const unsigned char* a_base;
-        const unsigned char* b_base;
-        uint32_t a_off[G::A_KC ? A_LD : 1], b_off[G::B_KC ? B_LD : 1];
-        uint32_t a_col = 0, b_col = 0;                    // k-strided: column byte offset
-        if (G::A_KC) {
-            a_base = reinterpret_cast<const unsigned char*>(p.A) + (p.a_rows ? (int64_t)0 : (int64_t)row0 * p.lda * 2);
+        auto tokens = [&](const Tile& t, const GemmArgs& p, int lane, uint32_t (&ar)[G::A_KC ? A_LD : 1]) {
+            if (!G::A_KC) return;
 #pragma unroll
             for (int i = 0; i < A_LD; ++i) {
-                const int r = min((wave + NW * i) * KC_RPI + kc_row, rows - 1);
-                const uint32_t ar = p.a_rows ? (uint32_t)p.a_rows[row0 + r] : (uint32_t)r;
-                a_off[i] = (ar * (uint32_t)p.lda + kc_chunk * 8) * 2;
+                const int r = min((wave + NW * i) * KC_RPI + lane / KC_CH, t.rows - 1);
+                ar[G::A_KC ? i : 0] = p.a_rows ? (uint32_t)p.a_rows[t.row0 + r] : (uint32_t)r;
             }
-        } else {
-            a_base = reinterpret_cast<const unsigned char*>(p.A) + (int64_t)kbeg * p.lda * 2;
-            a_col = 2 * min(m0 + ks_col(lane % A_CPR, G::template ks_key<BM>(wave * A_RPI + ksA_row)), p.M - 8);
-        }
-        if (G::B_KC) {
-            b_base = reinterpret_cast<const unsigned char*>(Bg);
+        };
+        auto aim = [&](const Tile& t, const GemmArgs& p, int lane, const uint32_t (&ar)[G::A_KC ? A_LD : 1]) {
+            const bf16_t* Bg = (LAYOUT == L_TN) ? p.B : p.B + (int64_t)t.g * p.b_group_stride;
+            const int kc_row = lane / KC_CH;
+            // key(row) of row (wave + NW i)*KC_RPI + kc_row does not depend on i
+            const int kc_key = (BK == 64) ? ((4 * (wave & 1) + (kc_row >> 1)) & 7) : ((kc_row >> 2) & 3);
+            kc_chunk = (lane % KC_CH) ^ kc_key;                               // logical 16 B chunk (8 k's)
+            ksA_row = lane / A_CPR, ksB_row = lane / B_CPR;
+            auto ks_col = [&](int pc, int key) { return ((((pc >> 1) ^ key) << 1) | (pc & 1)) * 8; };
+            if (G::A_KC) {
+                a_base = reinterpret_cast<const unsigned char*>(p.A) + (p.a_rows ? (int64_t)0 : (int64_t)t.row0 * p.lda * 2);
 #pragma unroll
-            for (int i = 0; i < B_LD; ++i) {
-                const int n = min(n0 + (wave + NW * i) * KC_RPI + kc_row, p.N - 1);
-                b_off[i] = ((uint32_t)n * (uint32_t)p.ldb + kc_chunk * 8) * 2;
+                for (int i = 0; i < A_LD; ++i) a_off[G::A_KC ? i : 0] = (ar[G::A_KC ? i : 0] * (uint32_t)p.lda + kc_chunk * 8) * 2;
+            } else {
+                a_base = reinterpret_cast<const unsigned char*>(p.A) + (int64_t)t.kbeg * p.lda * 2;
+                a_col = 2 * min(t.m0 + ks_col(lane % A_CPR, G::template ks_key<BM>(wave * A_RPI + ksA_row)), p.M - 8);
             }
-        } else {
-            b_base = reinterpret_cast<const unsigned char*>(Bg) + (int64_t)kbeg * p.ldb * 2;
-            b_col = 2 * min(n0 + ks_col(lane % B_CPR, G::template ks_key<BN>(wave * B_RPI + ksB_row)), p.N - 8);
+            if (G::B_KC) {
+                b_base = reinterpret_cast<const unsigned char*>(Bg);
+#pragma unroll
+                for (int i = 0; i < B_LD; ++i) {
+                    const int n = min(t.n0 + (wave + NW * i) * KC_RPI + kc_row, p.N - 1);
+                    b_off[G::B_KC ? i : 0] = ((uint32_t)n * (uint32_t)p.ldb + kc_chunk * 8) * 2;
+                }
+            } else {
+                b_base = reinterpret_cast<const unsigned char*>(Bg) + (int64_t)t.kbeg * p.ldb * 2;
+                b_col = 2 * min(t.n0 + ks_col(lane % B_CPR, G::template ks_key<BN>(wave * B_RPI + ksB_row)), p.N - 8);
+            }
+        };
+        if (!PRE || !begun) {
+            uint32_t ar[G::A_KC ? A_LD : 1];
+            tokens(t, p, lane, ar);
+            aim(t, p, lane, ar);
         }
         const int klen = kend - kbeg;
-        const int kc_lim = 2 * (kend - 8 - kc_chunk * 8);        // k-contiguous: last in-range chunk start (bytes)
         const uint32_t lda2 = (uint32_t)p.lda * 2, ldb2 = (uint32_t)p.ldb * 2;
+        auto stage_of = [&](int slab) { return (PRE ? slab + par : slab) % NSTAGE; };
         // issue load instruction `idx` (A: 0..A_LD-1, then B) of slab `slab` into its stage; addresses
         // are clamped into the contraction range (a no-op except in the last, partial slab)
         auto issue_one = [&](int idx, int slab) {
-            unsigned char* sa = smem + (slab % NSTAGE) * G::STAGE + wave * 1024;
+            unsigned char* sa = smem + stage_of(slab) * G::STAGE + wave * 1024;
+            const int kc_lim = 2 * (kend - 8 - kc_chunk * 8);    // k-contiguous: last in-range chunk start (bytes)
             unsigned char* sb = sa + G::A_BYTES;
             if (idx < A_LD) {
                 const int i = idx;
@@ -414,7 +453,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                 }
             }
         };
-        auto issue = [&](int slab) {
+        auto issue = [&](int slab) {        // (PRE calls it for the next tile's first slab: the contraction range is the same)
 #pragma unroll
             for (int idx = 0; idx < NLD; ++idx) issue_one(idx, slab);
         };
@@ -427,7 +466,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
             const int slab = nslab - 1;
             int lane_z = lane_id;
             asm volatile("" : "+v"(lane_z));
-            unsigned char* sa = smem + (slab % NSTAGE) * G::STAGE + wave * 1024 + lane_z * 16;
+            unsigned char* sa = smem + stage_of(slab) * G::STAGE + wave * 1024 + lane_z * 16;
             unsigned char* sb = sa + G::A_BYTES;
             const int left = klen - slab * BK;                    // k's of the last slab that exist
             const bool chunk_out = kc_chunk * 8 >= left;
@@ -443,7 +482,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         };
         // operand fragment number f (A tiles 0..TM-1, then B tiles) of k-step ks of slab `slab`
         auto read_frag = [&](int f, int slab, int ks, bf16x8* fa, bf16x8* fb) {
-            const unsigned char* sa = smem + (slab % NSTAGE) * G::STAGE;
+            const unsigned char* sa = smem + stage_of(slab) * G::STAGE;
             const unsigned char* sb = sa + G::A_BYTES;
             if (f < TM) {
                 const int i = f;
@@ -497,26 +536,38 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         __builtin_amdgcn_sched_barrier(0);                                                       \
     }
 
-        // the previous tile's epilogue has left the LDS
-        block_sync_lds();
-        // Every load the compiler itself issued during the tile set-up (row indices, spill reloads) has to be
-        // complete, and known to it as complete, before the pipeline starts: a wait that it places inside
-        // the main loop for one of its own loads would also wait for the tile loads issued there.  (The same counter covers
-        // the previous tile's stores: they are drained here as well.)
-        __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
         bf16x8 fa0[TM], fb0[TN_], fa1[TM], fb1[TN_];
-        if (nslab > 0) {
-            // prologue: put NSTAGE-1 slabs in flight, wait for the first
-#pragma unroll
-            for (int s = 0; s < NSTAGE - 1; ++s) {
-                if (s < nslab) issue(s);
-            }
-            if (EARLY && nslab > 1) {
+        if (PRE) {
+            // the first slab went out before the previous tile's epilogue; only that one's stores may still be in flight
+            if (begun) wait_vmcnt<PRE_STORES>(); else issue(0), wait_vmcnt<0>();
+            block_sync_lds();           // it has landed, and the previous epilogue has left the other stage
+            if (nslab > 1) {
 #pragma unroll
                 for (int idx = 0; idx < EARLY_LD; ++idx) issue_one(idx, 1);
-                wait_vmcnt<EARLY_LD>();
-            } else if (nslab >= NSTAGE - 1) wait_vmcnt<(NSTAGE - 2) * NLD>(); else wait_vmcnt<0>();
+            }
+        } else {
+            // the previous tile's epilogue has left the LDS
             block_sync_lds();
+            // Every load the compiler itself issued during the tile set-up (row indices, spill reloads) has to be
+            // complete, and known to it as complete, before the pipeline starts: a wait that it places inside
+            // the main loop for one of its own loads would also wait for the tile loads issued there.  (The same counter covers
+            // the previous tile's stores: they are drained here as well.)
+            __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
+        }
+        if (nslab > 0) {
+            // prologue: put NSTAGE-1 slabs in flight, wait for the first
+            if (!PRE) {
+#pragma unroll
+                for (int s = 0; s < NSTAGE - 1; ++s) {
+                    if (s < nslab) issue(s);
+                }
+                if (EARLY && nslab > 1) {
+#pragma unroll
+                    for (int idx = 0; idx < EARLY_LD; ++idx) issue_one(idx, 1);
+                    wait_vmcnt<EARLY_LD>();
+                } else if (nslab >= NSTAGE - 1) wait_vmcnt<(NSTAGE - 2) * NLD>(); else wait_vmcnt<0>();
+                block_sync_lds();
+            }
             if (nslab == 1 && ragged) {
                 zero_tail();
                 block_sync_lds();
@@ -569,6 +620,27 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         if (WPE > 1) __builtin_amdgcn_s_setprio(1);
         for (; slab + NSTAGE - (EARLY ? 0 : 1) < nslab; ++slab) slab_body(slab, std::true_type{});
         for (; slab + 1 < nslab; ++slab) slab_body(slab, std::false_type{});
+        float bias8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        auto load_bias = [&](int lane) {
+            if (!((EPI == E_HA || EPI == E_BIAS) && LAYOUT != L_TN) || !p.bias) return;
+            const float* from = p.bias + (int64_t)g * p.N + min(n0 + wn * WN + lane % (WN / 8) * 8, p.N - 8);
+            const f32x4 b0 = *reinterpret_cast<const f32x4*>(from), b1 = *reinterpret_cast<const f32x4*>(from + 4);
+            bias8[0] = b0.x; bias8[1] = b0.y; bias8[2] = b0.z; bias8[3] = b0.w;
+            bias8[4] = b1.x; bias8[5] = b1.y; bias8[6] = b1.z; bias8[7] = b1.w;
+        };
+        uint32_t next_rows[G::A_KC ? A_LD : 1];
+        if (PRE) {                 // the bias and the next tile's row numbers arrive under the last slab
+            int lane_b = lane_id;
+            asm volatile("" : "+v"(lane_b));
+            load_bias(lane_b);
+            begun = seq + seq_step < seq_end;
+            if (begun) {
+                ahead = locate(seq + seq_step);
+                int lane_n = lane_id;
+                asm volatile("" : "+v"(lane_n));
+                tokens(ahead, p, lane_n, next_rows);
+            }
+        }
         if (nslab > 0) {           // last slab: nothing left to fetch or to read ahead
             KSTEP(fa0, fb0, true, fa1, fb1, slab, 1, 0, 0, 0);
             if (KS == 4) {
@@ -580,8 +652,127 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
 #undef KSTEP
         if (WPE > 1) __builtin_amdgcn_s_setprio(0);
         block_sync_lds();         // every wave is done reading operands: LDS becomes the epilogue's staging area
+        if (PRE) {
+            par = (par + nslab) & 1;
+            int lane_n = lane_id;
+            asm volatile("" : "+v"(lane_n));
+            if (begun) {
+                aim(ahead, p, lane_n, next_rows);
+                __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0): known to have arrived, so that nothing waits for the slab with them
+                issue(0);
+            }
+        }
 
         // ---------------- epilogue: stage f32 rows through LDS, finish row-major ----------------
+        // Waves of 128 columns, NT/NN, one block per CU: eight rows at a time.  (With two blocks the steps took 3-5 % of dH: one's
+        // epilogue is under the other's MFMAs anyway.)  The rows of one step are written to 4 KB of the wave's own and read
+        // back while the step before is computed and stored; the LDS works a wave's accesses off in order, so that this takes
+        // no wait but the one for the data.  16-byte chunk c of row r lies at c ^ (c >> 4 & 1) ^ (r & 4 ? 8 : 0): the two
+        // half-waves write to, and sixteen lanes read from, different banks.
+        constexpr bool STEPS = LAYOUT != L_TN && WN == 128 && WPE == 1;
+        if constexpr (STEPS) {
+            int lane_e = lane_id;
+            asm volatile("" : "+v"(lane_e));
+            const int lane = lane_e, l32 = lane & 31, kg = lane >> 5, l16 = lane & 15, rq = lane >> 4;
+            float* stg = reinterpret_cast<float*>(smem + (PRE ? (par ^ 1) * G::STAGE : 0)) + wave * 1024;
+            float* put[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) put[j] = stg + kg * 512 + ((j ^ kg) * 32) + (j < 2 ? l32 : l32 ^ 4);
+            const int get = rq * 128 + ((2 * l16) ^ (l16 >> 3)) * 4;
+            const int col = n0 + wn * WN + l16 * 8;
+            // this lane's place in four rows of the output; beyond them for a column that does not exist
+            const uint32_t out_off = col < p.N ? (uint32_t)(rq * p.N + col) * 2 : 0x80000000u;
+            if (!PRE) load_bias(lane);
+            const bool scaled = EPI == E_ACTGRAD && p.row_scale;
+            auto finish = [&](auto act_c) {
+                constexpr int ACT = decltype(act_c)::value;
+                f32x4 v0[2], v1[2];
+                // H and the row weights, several steps ahead: four rows are done in less time than a load takes
+                constexpr int DEPTH = 4;
+                u32x4 hraw[DEPTH];
+                float rsc[DEPTH];
+                // column sums of the tile's valid rows (the bias gradient's share of this tile), f32.  Every tile adds the 64 rows
+                // behind one row of the partial table in the same order -- rows 4 apart one after another, then (0 + 1) +
+                // (2 + 3) -- so that the bias gradient does not depend on the tile that was picked.
+                float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                static_assert(EPI != E_ACTGRAD || WM == 64, "column sums: one row of the table");
+                // four rows: where they begin, and how many of them exist (a descriptor for so few keeps every offset in 32 bits)
+                auto first = [&](int f) { return wm * WM + f * 4; };
+                auto exist = [&](int f) { return max(0, __builtin_amdgcn_readfirstlane(min(4, rows - first(f)))); };
+                auto begin = [&](int f) {
+                    if (f % 2 == 0) {
+#pragma unroll
+                        for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) put[j][rr * 128] = acc[f / 8][j][f / 2 % 4 * 4 + rr];
+                    }
+                    const int it = f % 2;
+                    v0[it] = *reinterpret_cast<const f32x4*>(stg + (get ^ (it * 32)) + it * 512);
+                    v1[it] = *reinterpret_cast<const f32x4*>(stg + (get ^ (it * 32 + 4)) + it * 512);
+                };
+                auto fetch = [&](int f) {
+                    if (EPI != E_ACTGRAD || f >= WM / 4) return;
+                    const int n = exist(f);
+                    hraw[f % DEPTH] = load_in(p.Hin + (int64_t)(row0 + first(f)) * p.N, n * p.N * 2, out_off);
+                    rsc[f % DEPTH] = load_in(p.row_scale + row0 + first(f), scaled ? n * 4 : 0, rq * 4);
+                };
+#pragma unroll
+                for (int f = 0; f < DEPTH - 1; ++f) fetch(f);
+                begin(0);
+#pragma unroll
+                for (int f = 0; f < WM / 4; ++f) {
+                    const int it = f % 2, n = exist(f);
+                    fetch(f + DEPTH - 1);
+                    if (f + 1 < WM / 4) begin(f + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const f32x4 x0 = v0[it], x1 = v1[it];
+                    float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+                    const int64_t at = (int64_t)(row0 + first(f)) * p.N;
+                    if (EPI == E_HA || EPI == E_BIAS) {
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) v[q] += bias8[q];
+                    }
+                    if (EPI == E_ACTGRAD) {
+                        const u32x4 hw = hraw[f % DEPTH];
+                        const float h[8] = {lo_bf16(hw.x), hi_bf16(hw.x), lo_bf16(hw.y), hi_bf16(hw.y),
+                                            lo_bf16(hw.z), hi_bf16(hw.z), lo_bf16(hw.w), hi_bf16(hw.w)};
+                        const float sc = scaled ? rsc[f % DEPTH] : 1.f;
+                        const float rv = rq < n ? 1.f : 0.f;              // rows beyond the tile repeat its last row
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) v[q] *= sc * act_grad_fast(h[q], ACT);
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            cs[q] = fmaf(v[q], rv, cs[q]);
+                            asm volatile("" : "+v"(cs[q]));     // (added up at the end, where they are used, all the v's would be kept)
+                        }
+                    }
+                    store_out(p.out1 + at, n * p.N * 2, out_off, v);
+                    if (EPI == E_HA) {
+                        float a[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) a[q] = act_fwd_fast(v[q], ACT);
+                        store_out(p.out2 + at, n * p.N * 2, out_off, a);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (EPI == E_ACTGRAD && p.colpart) {
+                    // the four lane groups hold different rows of the same columns: add them up, lane group 0 writes
+                    // this wave's sums (rows wm*WM .. +WM-1 of the tile) as one row of the partial table
+                    float* dst = p.colpart + (int64_t)(part_row(g, offs[g]) + (row0 - offs[g]) / 64 + wm) * p.N;
+#pragma unroll
+                    for (int o = 16; o < 64; o <<= 1)
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) cs[q] += __shfl_xor(cs[q], o, 64);
+                    if (rq == 0 && col < p.N && wm * 64 < rows) {      // (64 rows that do not exist have no row in the table)
+                        *reinterpret_cast<f32x4*>(dst + col) = f32x4{cs[0], cs[1], cs[2], cs[3]};
+                        *reinterpret_cast<f32x4*>(dst + col + 4) = f32x4{cs[4], cs[5], cs[6], cs[7]};
+                    }
+                }
+            };
+            // one branch per tile, not per value
+            if ((EPI == E_HA || EPI == E_ACTGRAD) && p.act != EVOMOE_RELU) finish(std::integral_constant<int, EVOMOE_GELU_ERF>{});
+            else finish(std::integral_constant<int, EVOMOE_RELU>{});
+        } else
         {
         // (a fresh opaque copy of the lane number again: the epilogue's lane constants are not carried through
         //  the main loop either)
@@ -600,15 +791,9 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         const int lc = (lane % CPW) * 8;
         const int col = n0 + wn * WN + lc;
         const int col_c = min(col, p.N - 8);
-        float bias8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if ((EPI == E_HA || EPI == E_BIAS) && LAYOUT != L_TN) {
-            if (p.bias) {
-                const f32x4 b0 = *reinterpret_cast<const f32x4*>(p.bias + (int64_t)g * p.N + col_c);
-                const f32x4 b1 = *reinterpret_cast<const f32x4*>(p.bias + (int64_t)g * p.N + col_c + 4);
-                bias8[0] = b0.x; bias8[1] = b0.y; bias8[2] = b0.z; bias8[3] = b0.w;
-                bias8[4] = b1.x; bias8[5] = b1.y; bias8[6] = b1.z; bias8[7] = b1.w;
-            }
-        }
+        // this lane's place in the rows of one store instruction; beyond any of them for a column that does not exist
+        const uint32_t out_off = col < p.N ? (uint32_t)(lane / CPW * p.N + col) * 2 : 0x80000000u;
+        if (!PRE) load_bias(lane);
         // E_ACTGRAD: column sums of the tile's valid rows (the bias gradient's share of this tile), f32.  Every tile adds
         // the 64 rows behind one row of the partial table in the same order -- rows 4 apart one after another, then
         // (0 + 1) + (2 + 3) -- so that the bias gradient does not depend on the tile that was picked.  Waves of 64 rows by
@@ -667,8 +852,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                     }
                     if (ok) store_out(dst, v);
                 } else {
-                    const bool ok = col < p.N && trow < rows;
-                    const int64_t grow = (int64_t)(row0 + min(trow, rows - 1));
+                    // the rows of this iteration that exist (a descriptor for so few keeps every offset in 32 bits)
+                    const int first = wm * WM + pass * ER + it * RPI;
+                    const int exist = max(0, min(RPI, rows - first)) * p.N * 2;
+                    const int64_t at = (int64_t)(row0 + first) * p.N;
                     if (EPI == E_HA || EPI == E_BIAS) {
 #pragma unroll
                         for (int q = 0; q < 8; ++q) v[q] += bias8[q];
@@ -703,7 +890,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                             *reinterpret_cast<f32x4*>(keep + 4) = f32x4{v[4] * rv, v[5] * rv, v[6] * rv, v[7] * rv};
                         }
                     }
-                    if (ok) store_out(p.out1 + grow * p.N + col_c, v);
+                    store_out(p.out1 + at, exist, out_off, v);
                     if (EPI == E_HA) {
                         float a[8];
                         if (p.act == EVOMOE_RELU) {
@@ -713,7 +900,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
 #pragma unroll
                             for (int q = 0; q < 8; ++q) a[q] = act_fwd_fast(v[q], EVOMOE_GELU_ERF);
                         }
-                        if (ok) store_out(p.out2 + grow * p.N + col_c, a);
+                        store_out(p.out2 + at, exist, out_off, a);
                     }
                 }
             }
@@ -775,6 +962,11 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
 // A 64-wide slab takes whole 128-byte lines of a k-contiguous operand: with four stages of 32 k the L1 fetched every
 // line twice (its other half was gone by the next slab; 2831 MB from the L2 per GEMM1 launch at 38 969 pairs, now 1470).  BIG8 against 32-wide slabs: GEMM1 404 -> 366 us at d = 768, F = 3072, 58 330 pairs, 1603 -> 1473
 // at d = 1024, F = 4096, 131 072 pairs; BIG: GEMM2 270 -> 254 and 1026 -> 964 us, dXp 261 -> 252 and 994 -> 962 us.
+// Where its time went with both waves of a SIMD in the epilogue at once (clocks per tile at d = 768): GEMM1 26.6 k main loop, 15 k
+// epilogue, bound by its VALU instructions, 9 k waiting at the ends for loads and for each other; dH 22 k epilogue, H's loads one
+// step ahead.  The next tile's first slab and row numbers under the epilogue, the epilogue in steps that overlap, a shorter
+// gelu and H four steps ahead (48 k and 53 k clocks per tile now): GEMM1 342 -> 326 us at d = 768, F = 3072, 58 330 pairs,
+// 73 -> 65 at 8192 pairs, 950 -> 909 at d = 1024, F = 4096, 87 690 pairs; dH 384 -> 371, - , 942 -> 920.
 // OCT: BIG8 with four stages of 32 k, for the weight gradients (k-strided operands are whole lines at any slab width).
 // DUO: two blocks per compute unit (one's epilogue and stalls hide under the other's MFMAs).
 // LAT: for launches with no more tiles than compute units and a long contraction: what counts then is how fast
