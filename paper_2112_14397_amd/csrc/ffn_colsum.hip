@@ -1,24 +1,16 @@
-// What the weight-gradient launch of the bf16 layer needs beforehand, in one launch: column sums of dO over every expert's
-// rows, split into kColsumSplit row ranges per expert (the first pass of db2; f32 partial sums, added over the row lanes
-// in LDS, no atomics: reproducible bit for bit), and the rows of x gathered into a dense copy.
+// Column sums of the bf16 layer's dO over every expert's rows, split into kColsumSplit row ranges per expert (the first pass of
+// db2; f32 partial sums, added over the row lanes in LDS, no atomics: reproducible bit for bit).
 #include "ffn_internal.h"
 
 namespace evomoe {
 
 // A block streams whole row segments: CL column lanes x 16 bytes are contiguous in a row (up to 4 KB), RL = 256/CL
 // row lanes take alternate rows, four rows of loads in flight per thread.
-// The first gx * E * kColsumSplit blocks (column block fastest, then expert) sum columns, the rest gather: neither needs the
-// other, both only stream memory, and two launches of a few microseconds' work each cost as much again in gaps.
-__global__ __launch_bounds__(256) void gather_colsum_kernel(
+// Blocks: column block fastest, then expert, then row range.
+__global__ __launch_bounds__(256) void colsum_kernel(
     const bf16_t* __restrict__ Mx, int N, int E, const int32_t* __restrict__ expert_offsets, int64_t P_cap,
-    int CL, int gx, int sum_blocks, float* __restrict__ part, const u32x4* __restrict__ x,
-    const int32_t* __restrict__ pair_token, int vec_per_row, u32x4* __restrict__ x_perm)
+    int CL, int gx, float* __restrict__ part)
 {
-    if ((int)blockIdx.x >= sum_blocks) {
-        gather_rows<2>(x, pair_token, clamp_pairs(expert_offsets[E], P_cap), vec_per_row, x_perm,
-                    (int)blockIdx.x - sum_blocks, (int)gridDim.x - sum_blocks);
-        return;
-    }
     constexpr int KV = Elem<bf16_t>::kVec;           // elements per 16-byte load
     extern __shared__ float red[];               // [RL][CL*KV]
     const int RL = 256 / CL;
@@ -70,17 +62,15 @@ size_t colsum_scratch_bytes(const evomoe_shape& s) {
     return (((size_t)kColsumSplit * s.E * s.d * sizeof(float) + 255) & ~(size_t)255) + dh_colpart_bytes(s);
 }
 
-hipError_t launch_gather_colsum(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token, void* x_perm,
-                                const void* Mx, int N, const int32_t* expert_offsets, float* scratch) {
+hipError_t launch_colsum(const Ctx& c, const evomoe_shape& s, const void* Mx, int N, const int32_t* expert_offsets,
+                         float* scratch) {
     constexpr int KV = Elem<bf16_t>::kVec;
     const int vecs = (N + KV - 1) / KV;                       // 16-byte vectors per row
     int CL = vecs >= 256 ? 256 : vecs;                        // column lanes (contiguous in a row)
     if (CL > 128) CL = 256;                                   // 129..255 vectors: two column blocks of 256 lanes
     const int RL = 256 / CL, gx = (vecs + CL - 1) / CL;
-    const int sum_blocks = Mx ? gx * s.E * kColsumSplit : 0, gather_blocks = x ? gather_grid(c, s) : 0;
-    hipLaunchKernelGGL(gather_colsum_kernel, dim3(sum_blocks + gather_blocks), dim3(256),
-                       (size_t)RL * CL * KV * sizeof(float), c.stream, (const bf16_t*)Mx, N, s.E, expert_offsets,
-                       s.P_cap, CL, gx, sum_blocks, scratch, (const u32x4*)x, pair_token, s.d * 2 / 16, (u32x4*)x_perm);
+    hipLaunchKernelGGL(colsum_kernel, dim3(gx * s.E * kColsumSplit), dim3(256), (size_t)RL * CL * KV * sizeof(float),
+                       c.stream, (const bf16_t*)Mx, N, s.E, expert_offsets, s.P_cap, CL, gx, scratch);
     return hipGetLastError();
 }
 

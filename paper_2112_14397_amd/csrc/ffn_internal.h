@@ -22,15 +22,14 @@ hipError_t f32_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, cons
 constexpr int kF32ColsumSplit = 16;
 // the bf16 layer's streaming column sums split every expert's rows into this many ranges: part[split][g][n], added in order
 constexpr int kColsumSplit = 32;
-// leaves part[kColsumSplit][E][N] of the bf16 matrix Mx [P,N] in scratch and the rows x[pair_token[r]] in x_perm (either
-// one is left out if Mx or x is null)
-hipError_t launch_gather_colsum(const Ctx& c, const evomoe_shape& s, const void* x, const int32_t* pair_token, void* x_perm,
-                                const void* Mx, int N, const int32_t* expert_offsets, float* scratch);
+// leaves part[kColsumSplit][E][N] of the bf16 matrix Mx [P,N] in scratch
+hipError_t launch_colsum(const Ctx& c, const evomoe_shape& s, const void* Mx, int N, const int32_t* expert_offsets,
+                         float* scratch);
 // bf16 layer: [partial column sums of dO][column sums of dH for each 64 rows]; float32 layer: [partial column sums of dO][of
 // dH]; a multiple of 256
 size_t colsum_scratch_bytes(const evomoe_shape& s);
 size_t dh_colpart_bytes(const evomoe_shape& s);       // the second part alone (0 for a float32 layer)
-// the backward workspace is [dH : P_cap x F elements, rounded up to 256 B][bias-gradient partial sums][bf16 layer: gathered x]
+// the backward workspace is [dH : P_cap x F elements, rounded up to 256 B][bias-gradient partial sums]
 inline size_t dh_bytes(const evomoe_shape& s) {
     const size_t esz = s.dtype == EVOMOE_BF16 ? 2 : 4;
     return ((size_t)s.P_cap * s.F * esz + 255) & ~(size_t)255;

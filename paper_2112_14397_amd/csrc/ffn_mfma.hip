@@ -32,6 +32,7 @@ struct GemmArgs {
     const bf16_t* B;  int64_t ldb;      // NT: W_g [N,K] (ldb = K);  NN: W_g [K,N] (ldb = N);  TN: R [*,N] (ldb = N)
     int64_t b_group_stride;             // NT/NN: elements between two experts' weight matrices
     const int32_t* a_rows;              // NT: gather of A rows (or null)
+    const int32_t* b_rows;              // TN: gather of R rows (or null)
     const int32_t* expert_offsets;
     int E;
     int64_t P_cap;
@@ -198,6 +199,11 @@ __device__ __forceinline__ void load_to_lds(const unsigned char* base, uint32_t 
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :: "v"(voff), "s"(base), "s"(lds_addr(lds_wave_base)) : "m0", "memory");
 }
+// 4 bytes per lane in the same way: lane l's data lands at lds + 4*l.
+__device__ __forceinline__ void load_dword_to_lds(const int32_t* base, uint32_t voff, const int* lds_wave_base) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+                 :: "v"(voff), "s"(base), "s"(lds_addr(lds_wave_base)) : "m0", "memory");
+}
 // Block barrier that orders LDS traffic only (global loads in flight stay in flight).
 __device__ __forceinline__ void block_sync_lds() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -237,6 +243,12 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);       // wave-uniform: lives in an SGPR
     const int wm = wave >> 1, wn = wave & 1;
     __shared__ int tstart[65];      // NT/NN: number of row tiles before each expert (tstart[E] = all of them)
+    // TN: the R rows' numbers for the next 768 to 1024 k's of the tile, in a ring of pieces of 256, gathered or not: one LDS
+    // read and a multiplication make a load's address.  (Loads of row numbers among the pipeline's own would make every slab wait for
+    // memory twice; a dense copy of the gathered rows took a pass over them, 25 us of 47 with dO's column sums at 58 330
+    // pairs, d = 768.)
+    constexpr int RING = 1024, PIECE = 256;
+    __shared__ int ring[LAYOUT == L_TN ? RING : 1];
     if (tid <= q0.E) offs[tid] = clamp_pairs(q0.expert_offsets[tid], q0.P_cap);
     __syncthreads();
     if (LAYOUT != L_TN) {
@@ -319,12 +331,30 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         return t;
     };
 
+    // TN: piece number n of a tile's row numbers (waves 0 .. 3, 64 each), from the list or, without one, in order; beyond the
+    // expert's rows its last one
+    auto fetch_piece = [&](const Tile& t, int n) {
+        const int kbeg = __builtin_amdgcn_readfirstlane(t.kbeg), klen = __builtin_amdgcn_readfirstlane(t.kend) - kbeg;
+        if (LAYOUT != L_TN || wave >= 4 || n * PIECE >= klen) return;
+        int lane_f = lane_id;
+        asm volatile("" : "+v"(lane_f));
+        const int kr = min(n * PIECE + wave * 64 + lane_f, klen - 1);
+        int* at = ring + (LAYOUT == L_TN ? (uint32_t)(n * PIECE) % RING + wave * 64 : 0);
+        const int32_t* list = (t.second ? q1 : q0).b_rows;
+        if (list) load_dword_to_lds(list + kbeg, (uint32_t)kr * 4, at);
+        else at[LAYOUT == L_TN ? lane_f : 0] = kr;
+    };
+    auto first_pieces = [&](const Tile& t) {
+#pragma unroll
+        for (int n = 0; n < RING / PIECE - 1; ++n) fetch_piece(t, n);
+    };
+
     // PRE: the next tile's first slab is fetched under this tile's epilogue, into the stage that the epilogue does not use.
     constexpr bool PRE = LAYOUT != L_TN && EARLY && NW == 8;
     constexpr int PRE_STORES = WM / 4 * (EPI == E_HA ? 2 : 1);      // at least so many of a wave's stores follow that slab's loads
     static_assert(!PRE || (PRE_STORES <= 63 && WN == 128 && NW * 4096 <= G::STAGE), "epilogue beside a slab");
     int par = 0;                    // PRE: stage of the tile's first slab
-    bool begun = false;             // PRE: ... is being fetched already
+    bool begun = false;             // PRE: ... is being fetched already; TN: the tile's first row numbers are
     Tile ahead{};
     // ---------------- global addresses: one scalar base per operand + 32-bit per-lane byte offsets ----
     // k-contiguous operand: offset of (row, chunk) at k = 0, one register per load instruction.
@@ -343,7 +373,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
             continue;
         }
         if (LAYOUT != L_TN && seq >= seq_end) break;
-        const Tile t = PRE && begun ? ahead : locate(LAYOUT == L_TN ? vtile : seq);
+        const Tile t = (PRE || LAYOUT == L_TN) && begun ? ahead : locate(LAYOUT == L_TN ? vtile : seq);
         const GemmArgs& p = t.second ? q1 : q0;
         auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };     // (known to be, not when it comes around the loop)
         const int g = uniform(t.g), row0 = uniform(t.row0), rows = uniform(t.rows), m0 = uniform(t.m0), n0 = uniform(t.n0),
@@ -417,7 +447,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                     b_off[G::B_KC ? i : 0] = ((uint32_t)n * (uint32_t)p.ldb + kc_chunk * 8) * 2;
                 }
             } else {
-                b_base = reinterpret_cast<const unsigned char*>(Bg) + (int64_t)t.kbeg * p.ldb * 2;
+                b_base = reinterpret_cast<const unsigned char*>(Bg) + (p.b_rows ? (int64_t)0 : (int64_t)t.kbeg * p.ldb * 2);
                 b_col = 2 * min(t.n0 + ks_col(lane % B_CPR, G::template ks_key<BN>(wave * B_RPI + ksB_row)), p.N - 8);
             }
         };
@@ -428,6 +458,14 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         }
         const int klen = kend - kbeg;
         const uint32_t lda2 = (uint32_t)p.lda * 2, ldb2 = (uint32_t)p.ldb * 2;
+        // TN: the R rows that this lane loads of the next slab to be issued, read from the ring a slab ahead
+        uint32_t b_row[LAYOUT == L_TN ? B_LD : 1];
+        const int* ring_lane = ring + (LAYOUT == L_TN ? wave * B_RPI + ksB_row : 0);
+        auto rows_of_slab = [&](int slab) {
+            if (LAYOUT != L_TN) return;
+#pragma unroll
+            for (int i = 0; i < B_LD; ++i) b_row[LAYOUT == L_TN ? i : 0] = (uint32_t)ring_lane[(uint32_t)(slab * BK) % RING + NW * B_RPI * i];
+        };
         auto stage_of = [&](int slab) { return (PRE ? slab + par : slab) % NSTAGE; };
         // issue load instruction `idx` (A: 0..A_LD-1, then B) of slab `slab` into its stage; addresses
         // are clamped into the contraction range (a no-op except in the last, partial slab)
@@ -448,8 +486,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                 if (G::B_KC) {
                     load_to_lds(b_base, b_off[i] + (uint32_t)min(slab * (BK * 2), kc_lim), sb + i * (NW * 1024));
                 } else {
-                    const int kr = min(slab * BK + (wave + NW * i) * B_RPI + ksB_row, klen - 1);
-                    load_to_lds(b_base, __umul24((uint32_t)kr, ldb2) + b_col, sb + i * (NW * 1024));
+                    const uint32_t kr = LAYOUT == L_TN ? b_row[i] : (uint32_t)min(slab * BK + (wave + NW * i) * B_RPI + ksB_row, klen - 1);
+                    load_to_lds(b_base, __umul24(kr, ldb2) + b_col, sb + i * (NW * 1024));
                 }
             }
         };
@@ -546,21 +584,26 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                 for (int idx = 0; idx < EARLY_LD; ++idx) issue_one(idx, 1);
             }
         } else {
-            // the previous tile's epilogue has left the LDS
-            block_sync_lds();
+            if (LAYOUT == L_TN && !begun) first_pieces(t);
             // Every load the compiler itself issued during the tile set-up (row indices, spill reloads) has to be
             // complete, and known to it as complete, before the pipeline starts: a wait that it places inside
             // the main loop for one of its own loads would also wait for the tile loads issued there.  (The same counter covers
             // the previous tile's stores: they are drained here as well.)
             __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
+            // the previous tile's epilogue has left the LDS
+            block_sync_lds();
         }
         if (nslab > 0) {
             // prologue: put NSTAGE-1 slabs in flight, wait for the first
             if (!PRE) {
 #pragma unroll
                 for (int s = 0; s < NSTAGE - 1; ++s) {
-                    if (s < nslab) issue(s);
+                    if (s < nslab) {
+                        rows_of_slab(s);
+                        issue(s);
+                    }
                 }
+                rows_of_slab(NSTAGE - 1);
                 if (EARLY && nslab > 1) {
 #pragma unroll
                     for (int idx = 0; idx < EARLY_LD; ++idx) issue_one(idx, 1);
@@ -614,6 +657,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                 block_sync_lds();
             }
             KSTEP(fa1, fb1, true, fa0, fb0, slab + 1, 0, L0, L1, slab + NSTAGE - 1);
+            if (LOADS && LAYOUT == L_TN) {
+                rows_of_slab(slab + NSTAGE);
+                if (slab * BK % PIECE == 0) fetch_piece(t, slab * BK / PIECE + RING / PIECE - 1);
+            }
         };
         int slab = 0;
         // two blocks per CU: the wave that is feeding the matrix pipe goes ahead of its neighbour's epilogue
@@ -660,6 +707,13 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                 aim(ahead, p, lane_n, next_rows);
                 __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0): known to have arrived, so that nothing waits for the slab with them
                 issue(0);
+            }
+        }
+        if (LAYOUT == L_TN) {     // ... and the ring with the row numbers is free for the next tile's
+            begun = vtile + (int)gridDim.x < tiles_all;
+            if (begun) {
+                ahead = locate(vtile + gridDim.x);
+                first_pieces(ahead);
             }
         }
 
@@ -791,8 +845,6 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         const int lc = (lane % CPW) * 8;
         const int col = n0 + wn * WN + lc;
         const int col_c = min(col, p.N - 8);
-        // this lane's place in the rows of one store instruction; beyond any of them for a column that does not exist
-        const uint32_t out_off = col < p.N ? (uint32_t)(lane / CPW * p.N + col) * 2 : 0x80000000u;
         if (!PRE) load_bias(lane);
         // E_ACTGRAD: column sums of the tile's valid rows (the bias gradient's share of this tile), f32.  Every tile adds
         // the 64 rows behind one row of the partial table in the same order -- rows 4 apart one after another, then
@@ -852,10 +904,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                     }
                     if (ok) store_out(dst, v);
                 } else {
-                    // the rows of this iteration that exist (a descriptor for so few keeps every offset in 32 bits)
-                    const int first = wm * WM + pass * ER + it * RPI;
-                    const int exist = max(0, min(RPI, rows - first)) * p.N * 2;
-                    const int64_t at = (int64_t)(row0 + first) * p.N;
+                    const bool ok = col < p.N && trow < rows;
+                    const int64_t grow = (int64_t)(row0 + min(trow, rows - 1));
                     if (EPI == E_HA || EPI == E_BIAS) {
 #pragma unroll
                         for (int q = 0; q < 8; ++q) v[q] += bias8[q];
@@ -890,7 +940,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                             *reinterpret_cast<f32x4*>(keep + 4) = f32x4{v[4] * rv, v[5] * rv, v[6] * rv, v[7] * rv};
                         }
                     }
-                    store_out(p.out1 + at, exist, out_off, v);
+                    if (ok) store_out(p.out1 + grow * p.N + col_c, v);
                     if (EPI == E_HA) {
                         float a[8];
                         if (p.act == EVOMOE_RELU) {
@@ -900,7 +950,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
 #pragma unroll
                             for (int q = 0; q < 8; ++q) a[q] = act_fwd_fast(v[q], EVOMOE_GELU_ERF);
                         }
-                        store_out(p.out2 + at, exist, out_off, a);
+                        if (ok) store_out(p.out2 + grow * p.N + col_c, a);
                     }
                 }
             }
@@ -1181,7 +1231,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
     GemmArgs a{};
     a.expert_offsets = expert_offsets; a.E = s.E; a.P_cap = s.P_cap; a.act = s.act;
     hipError_t err;
-    // workspace behind dH: [column-sum partials of the streaming kernel][column sums of dH][gathered x]
+    // workspace behind dH: [column-sum partials of the streaming kernel][column sums of dH]
     float* scratch = reinterpret_cast<float*>(static_cast<char*>(dH) + dh_bytes(s));
     float* colpart = reinterpret_cast<float*>(static_cast<char*>(dH) + dh_bytes(s) + colsum_scratch_bytes(s) -
                                               dh_colpart_bytes(s));
@@ -1213,20 +1263,13 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
     // dW2_g = dO_g^T A_g   [d,F]
     w2.A = (const bf16_t*)dO; w2.lda = s.d; w2.B = (const bf16_t*)A; w2.ldb = s.F;
     w2.M = s.d; w2.N = s.F; w2.out1 = (bf16_t*)dW2;
-    // dW1_g = dH_g^T X_g   [F,d]; the token rows are gathered once into a dense copy so that the GEMM
-    // streams them like any other operand
-    const bf16_t* xg = (const bf16_t*)x;
-    bf16_t* xp = nullptr;
-    if (dW1 && pair_token) {
-        xp = reinterpret_cast<bf16_t*>(static_cast<char*>(dH) + dh_bytes(s) + colsum_scratch_bytes(s));
-        xg = xp;
-    }
-    if (xp || db2) {      // one launch: the gather, and the split column sums of dO for db2
-        ProfScope ps(c, xp ? EVOMOE_K_FFN_BWD_DW1 : EVOMOE_K_FFN_BWD_DB);
-        err = launch_gather_colsum(c, s, xp ? x : nullptr, pair_token, xp, db2 ? dO : nullptr, s.d, expert_offsets, scratch);
+    // dW1_g = dH_g^T X_g   [F,d]; the token rows are gathered on load
+    if (db2) {            // the split column sums of dO
+        ProfScope ps(c, EVOMOE_K_FFN_BWD_DB);
+        err = launch_colsum(c, s, dO, s.d, expert_offsets, scratch);
         if (err != hipSuccess) return err;
     }
-    w1.A = (const bf16_t*)dH; w1.lda = s.F; w1.B = xg; w1.ldb = s.d;
+    w1.A = (const bf16_t*)dH; w1.lda = s.F; w1.B = (const bf16_t*)x; w1.ldb = s.d; w1.b_rows = pair_token;
     w1.M = s.F; w1.N = s.d; w1.out1 = (bf16_t*)dW1;
     BiasFinal bf{};
     bf.part1 = colpart; bf.db1 = db1; bf.N1 = s.F;
