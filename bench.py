@@ -41,7 +41,7 @@ DOMINANT_PROFILE_NAME = "grouped_gemm_bf16<2, 4,"
 
 def _gemm_kernels():
     # expert-FFN GEMM launches and how many 2*P*d*F-flop contractions each carries
-    # (ffn_bwd_dw2 is the merged dW2 + dW1 launch; ffn_bwd_dw1 is only the gather of x feeding it, with dO's column sums)
+    # (ffn_bwd_dw2 is the merged dW2 + dW1 launch; ffn_bwd_db is dO's column sums where they have a launch of their own)
     return {"ffn_gemm1": 1, "ffn_gemm2": 1, "ffn_bwd_dh": 1, "ffn_bwd_dx": 1, "ffn_bwd_dw2": 2}
 
 
@@ -322,9 +322,8 @@ def main():
             "dispatch_hist": T * 8, "dispatch_scatter": T * 12 + Pavg * 16,
             "combine": Pavg * d * sz + T * d * sz + Pavg * 8,
             "combine_bwd": 2 * Pavg * d * sz + T * d * sz + Pavg * 12,
-            # (bf16 layer) the gather of x and the column sums of dO, one launch; both types take the bias gradients' other sums
-            # inside the GEMM launches
-            "ffn_bwd_dw1": 3 * Pavg * d * sz + Pavg * 4,
+            # (bf16 layer) the column sums of dO; both types take the bias gradients' other sums inside the GEMM launches
+            "ffn_bwd_db": Pavg * d * sz,
             "dispatch_bwd": Pavg * d * sz + T * d * sz,
             "gate_bwd_dz": T * E * 8 + Pavg * 8 + T * 12,
             "gate_bwd_main": T * d * sz * 3 + T * E * 4,

@@ -92,42 +92,26 @@ __device__ __forceinline__ int clamp_pairs(int P, int64_t P_cap) {
     return (int64_t)P > P_cap ? (int)P_cap : P;
 }
 
-// x_perm[r,:] = x[pair_token[r],:] for r < P, by block `blk` of `nblk` (256 threads, 16 bytes each), U vectors of a thread in
-// flight at a time.  A chip full of blocks has enough in flight with one, and then reads and writes closest together (dispatch
-// with x_perm at 58755 pairs, d = 768: 34.6 us, with two 35.8, with four 36.3); next to the column sums two are best (8192 /
-// 22000 / 58330 pairs: 13.0 / 19.4 / 52.1 us, one 11.9 / 19.2 / 55.1, four 13.7 / 20.7 / 52.1).  32-bit indexes where they
-// hold the number of vectors: their division by the row length is short.
-template <int U, typename Index>
+// x_perm[r,:] = x[pair_token[r],:] for r < P, by block `blk` of `nblk` (256 threads, 16 bytes each), one vector of a thread in
+// flight: a chip full of blocks has enough in flight with one, and then reads and writes closest together (dispatch with x_perm
+// at 58755 pairs, d = 768: 34.6 us, with two 35.8, with four 36.3).  32-bit indexes where they hold the number of vectors:
+// their division by the row length is short.
+template <typename Index>
 __device__ __forceinline__ void gather_vectors(const u32x4* __restrict__ x, const int32_t* __restrict__ pair_token,
                                                Index total, uint32_t vec_per_row, u32x4* __restrict__ x_perm, int blk, int nblk) {
-    const Index step = (Index)nblk * 256;                // (first + U step does not overflow: gather_rows)
-    for (Index first = (Index)blk * 256 + threadIdx.x; first < total; first += U * step) {
-        int tok[U];
-        uint32_t v[U];
-        u32x4 val[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (first + u * step < total) {
-                const Index i = first + u * step, r = i / vec_per_row;
-                v[u] = (uint32_t)(i - r * vec_per_row);
-                tok[u] = pair_token[r];
-            }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (first + u * step < total) val[u] = x[(size_t)tok[u] * vec_per_row + v[u]];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (first + u * step < total) x_perm[first + u * step] = val[u];
+    const Index step = (Index)nblk * 256;                // (i + step does not overflow: gather_rows)
+    for (Index i = (Index)blk * 256 + threadIdx.x; i < total; i += step) {
+        const Index r = i / vec_per_row;
+        x_perm[i] = x[(size_t)pair_token[r] * vec_per_row + (uint32_t)(i - r * vec_per_row)];
     }
 }
-template <int U>
 __device__ __forceinline__ void gather_rows(const u32x4* __restrict__ x, const int32_t* __restrict__ pair_token, int P,
                                             int vec_per_row, u32x4* __restrict__ x_perm, int blk, int nblk) {
     const int64_t total = (int64_t)P * vec_per_row;
-    if (total + (int64_t)nblk * U * 256 < ((int64_t)1 << 32))
-        gather_vectors<U>(x, pair_token, (uint32_t)total, vec_per_row, x_perm, blk, nblk);
+    if (total + (int64_t)nblk * 256 < ((int64_t)1 << 32))
+        gather_vectors(x, pair_token, (uint32_t)total, vec_per_row, x_perm, blk, nblk);
     else
-        gather_vectors<U>(x, pair_token, (uint64_t)total, vec_per_row, x_perm, blk, nblk);
+        gather_vectors(x, pair_token, (uint64_t)total, vec_per_row, x_perm, blk, nblk);
 }
 
 // Optional per-kernel timing with HIP events on the context's stream (measurement aid).

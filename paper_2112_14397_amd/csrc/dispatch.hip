@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(
     const int32_t* __restrict__ expert_offsets, int E, int64_t P_cap, int vec_per_row,
     u32x4* __restrict__ x_perm)
 {
-    gather_rows<1>(x, pair_token, clamp_pairs(expert_offsets[E], P_cap), vec_per_row, x_perm, blockIdx.x, gridDim.x);
+    gather_rows(x, pair_token, clamp_pairs(expert_offsets[E], P_cap), vec_per_row, x_perm, blockIdx.x, gridDim.x);
 }
 
 int gather_grid(const Ctx& c, const evomoe_shape& s) {

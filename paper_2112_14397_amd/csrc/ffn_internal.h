@@ -20,11 +20,8 @@ hipError_t f32_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, cons
                        void* dH);
 // the float32 layer's column sums: row ranges per expert (at most)
 constexpr int kF32ColsumSplit = 16;
-// the bf16 layer's streaming column sums split every expert's rows into this many ranges: part[split][g][n], added in order
+// the bf16 layer's column sums of dO: row ranges per expert (at most), part[range][g][n], added in order
 constexpr int kColsumSplit = 32;
-// leaves part[kColsumSplit][E][N] of the bf16 matrix Mx [P,N] in scratch
-hipError_t launch_colsum(const Ctx& c, const evomoe_shape& s, const void* Mx, int N, const int32_t* expert_offsets,
-                         float* scratch);
 // bf16 layer: [partial column sums of dO][column sums of dH for each 64 rows]; float32 layer: [partial column sums of dO][of
 // dH]; a multiple of 256
 size_t colsum_scratch_bytes(const evomoe_shape& s);

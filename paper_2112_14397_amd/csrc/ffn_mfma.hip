@@ -27,6 +27,8 @@ enum { E_HA = 0, E_BIAS = 1, E_ACTGRAD = 2, E_NONE = 3, E_WGRAD = 4 };
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
+__device__ __forceinline__ int sum_ranges(int rows) { return max(1, min(kColsumSplit, (rows + 63) / 64)); }
+
 struct GemmArgs {
     const bf16_t* A;  int64_t lda;      // NT/NN: A rows [*,K];  TN: L [P,M] (lda = M)
     const bf16_t* B;  int64_t ldb;      // NT: W_g [N,K] (ldb = K);  NN: W_g [K,N] (ldb = N);  TN: R [*,N] (ldb = N)
@@ -53,13 +55,13 @@ __device__ __forceinline__ int part_row(int g, int begin) { return begin / 64 + 
 
 // The last sums of both bias gradients, as further tiles behind the weight gradients' (TN launches).  The first tiles1
 // (expert g = b / gx1, NW * 64 columns each): db1[g, n] (+)= sum over expert g's rows of the table of column sums
-// written by the dH GEMM, in row order.  The rest: db2[i] (+)= sum over the splits of the streaming column sums of dO, in
-// split order.  Reproducible bit for bit.
+// written by the dH GEMM, in row order.  The rest: db2[i] (+)= sum over the row ranges of the column sums of dO, in their
+// order.  Reproducible bit for bit.
 struct BiasFinal {
     const float* part1; float* db1;     // [part_row()][N1] -> [E,N1]
     const float* part2; float* db2;     // [kColsumSplit][n2] -> [n2]
-    size_t n2;
-    int N1;
+    size_t n2;                          // E * N2
+    int N1, N2;
     int gx1, tiles1, tiles;             // column blocks per expert, tiles of db1, of both
     int accumulate;
     const int32_t* offsets;             // expert_offsets
@@ -68,13 +70,15 @@ __device__ __forceinline__ void bias_final_tile(const BiasFinal& q, int b, const
     if (b >= q.tiles1) {
         const size_t i = (size_t)(b - q.tiles1) * nthr + threadIdx.x;
         if (i >= q.n2) return;
+        const int g = (int)(i / (uint32_t)q.N2), ranges = sum_ranges(offs[g + 1] - offs[g]);
         float s = q.accumulate ? q.db2[i] : 0.f;
-        for (int k0 = 0; k0 < kColsumSplit; k0 += 8) {
+        for (int k0 = 0; k0 < ranges; k0 += 8) {
             float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = q.part2[(size_t)(k0 + u) * q.n2 + i];
+            for (int u = 0; u < 8; ++u) v[u] = q.part2[(size_t)min(k0 + u, ranges - 1) * q.n2 + i];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
+            for (int u = 0; u < 8; ++u)
+                if (k0 + u < ranges) s += v[u];
         }
         q.db2[i] = s;
         return;
@@ -95,6 +99,72 @@ __device__ __forceinline__ void bias_final_tile(const BiasFinal& q, int b, const
     }
     for (; i < rows; ++i) sum += src[(int64_t)i * q.N1];
     q.db1[(int64_t)g * q.N1 + n] = sum;
+}
+
+// Column sums of dO over every expert's rows (the first pass of db2): an expert's rows are cut into sum_ranges() ranges, 64 rows
+// each as long as 32 ranges are enough; a tile leaves part[range][expert][column] for 2048 columns at most.
+// Up to 14 MB of dO the tiles run behind dXp's, on the compute units first that have no dXp tile in the last round; beyond, in a
+// launch of their own, which has more waves in flight.  dXp and the sums, us, behind it / on their own: 777 tokens, d = 136,
+// two micro-batches 23 / 33; 8192 pairs of d = 768 64 / 67, 22 073 of d = 512 86 / 87, 58 330 of d = 768 278 / 276, 87 690
+// of d = 1024 719 / 694.
+struct ColumnSums {
+    const bf16_t* M;  int N;            // dO [P,N]
+    float* part;                        // [kColsumSplit][E][N]
+    int wanted;
+};
+// Tile b: column block fastest, then expert, then range.  The first 256 threads of a block: CL column lanes x 16 bytes are
+// contiguous in a row, RL = 256 / CL row lanes take alternate rows, sixteen rows of loads in flight per thread (few waves share a
+// unit behind dXp's tiles: with four, dXp and the sums took 314 us instead of 278); f32 sums, row lanes added in order.
+__device__ __forceinline__ void colsum_tile(const ColumnSums& q, int b, int gx, int CL, const int* offs, int E, float* red) {
+    const int RL = 256 / CL, g = b / gx % E, range = b / (gx * E);
+    const int r0 = offs[g], r1 = offs[g + 1], ranges = sum_ranges(r1 - r0);
+    if (range >= ranges) return;                                  // block-uniform
+    const int cl = threadIdx.x % CL, rl = threadIdx.x / CL;
+    const int n = (b % gx * CL + cl) * 8;
+    const int per = (r1 - r0 + ranges - 1) / ranges, rb = r0 + range * per, re = min(r1, rb + per);
+    const bool on = threadIdx.x < 256 && n < q.N && rl < RL;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (on) {
+        constexpr int U = 16;
+        const uint32_t step = (uint32_t)RL * q.N * 2;
+        for (int r = rb + rl; r < re; r += U * RL) {
+            const int k = (re - r + RL - 1) / RL;                 // this lane's rows that are left; beyond them the last one again
+            const unsigned char* src = reinterpret_cast<const unsigned char*>(q.M + (size_t)r * q.N + n);
+            u32x4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const u32x4*>(src + (size_t)min(u, k - 1) * step);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (u < k) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { acc[2 * e] += lo_bf16(v[u][e]); acc[2 * e + 1] += hi_bf16(v[u][e]); }
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) red[(rl * CL + cl) * 8 + e] = acc[e];
+    }
+    __syncthreads();
+    if (on && rl == 0) {
+        float* dst = q.part + ((size_t)range * E + g) * q.N + n;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float sum = 0.f;
+            for (int l = 0; l < RL; ++l) sum += red[(l * CL + cl) * 8 + e];
+            dst[e] = sum;
+        }
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ int colsum_lanes(int N) { return N / 8 > 128 ? 256 : N / 8; }
+__global__ __launch_bounds__(256) void colsum_kernel(ColumnSums q, const int32_t* __restrict__ expert_offsets, int E, int64_t P_cap) {
+    __shared__ int offs[65];
+    __shared__ float red[256 * 8];
+    if (threadIdx.x <= E) offs[threadIdx.x] = clamp_pairs(expert_offsets[threadIdx.x], P_cap);
+    __syncthreads();
+    const int CL = colsum_lanes(q.N);
+    colsum_tile(q, blockIdx.x, (q.N / 8 + CL - 1) / CL, CL, offs, E, red);
 }
 
 // ---- LDS geometry -------------------------------------------------------------------------------
@@ -214,7 +284,7 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 }
 
 template <int LAYOUT, int EPI, int BM, int BN, int BK, int NSTAGE, int WPE, int NW = 4>
-__global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, GemmArgs q1, int tiles0, int tiles_all, BiasFinal qb)
+__global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, GemmArgs q1, int tiles0, int tiles_all, BiasFinal qb, ColumnSums qs)
 {
     // TN launches carry two independent problems (dW2 and dW1) in one grid, tiles [0, tiles0) and
     // [tiles0, tiles_all), which evens out the last round of the persistent schedule, and behind them the bias
@@ -1004,6 +1074,23 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         }
         }
     }
+
+    if (EPI == E_NONE && qs.wanted) {
+        const int CL = colsum_lanes(qs.N), gx = (qs.N / 8 + CL - 1) / CL;
+        int most = 1;
+        for (int e = 0; e < q0.E; ++e) most = max(most, sum_ranges(offs[e + 1] - offs[e]));
+        const int n = gx * q0.E * most;
+        // A block without a tile of the last round takes as many column sums as a tile is worth, what is left is dealt to all.
+        const int total = tstart[q0.E] * ((q0.N + BN - 1) / BN), grid = gridDim.x, busy = total % grid;
+        const int idle = busy && seq_step == grid ? grid - busy : 0;
+        const int64_t tile_ns = (int64_t)(9000 + 20 * q0.K) * (BM * BN) / 65536;
+        const int64_t sum_ns = 1500 + (int64_t)offs[q0.E] * qs.N * 2 / n / 40;
+        const int fill = (int)min((int64_t)n, idle * (tile_ns / sum_ns));
+        __syncthreads();
+        if (idle && vblock >= busy)
+            for (int b = vblock - busy; b < fill; b += idle) colsum_tile(qs, b, gx, CL, offs, q0.E, reinterpret_cast<float*>(smem));
+        for (int b = fill + grid - 1 - vblock; b < n; b += grid) colsum_tile(qs, b, gx, CL, offs, q0.E, reinterpret_cast<float*>(smem));
+    }
 }
 
 // Tile configurations.  BIG: one block per compute unit, two stages of 64 k, 256 accumulator registers per lane.
@@ -1040,7 +1127,7 @@ struct CfgTny3 { static constexpr int BM = 64, BN = 64, BK = 64, NSTAGE = 3, WPE
 
 template <int LAYOUT, int EPI, class Cfg>
 hipError_t launch_gemm(const Ctx& c, const GemmArgs& a0, int64_t tiles0, const GemmArgs& a1, int64_t tiles1,
-                       BiasFinal b = BiasFinal{}) {
+                       BiasFinal b = BiasFinal{}, const ColumnSums& sums = ColumnSums{}) {
     using G = Geo<LAYOUT, Cfg::BM, Cfg::BN, Cfg::BK, Cfg::NSTAGE, Cfg::NW>;
     auto kern = grouped_gemm_bf16<LAYOUT, EPI, Cfg::BM, Cfg::BN, Cfg::BK, Cfg::NSTAGE, Cfg::WPE, Cfg::NW>;
     static bool configured = false;
@@ -1052,15 +1139,16 @@ hipError_t launch_gemm(const Ctx& c, const GemmArgs& a0, int64_t tiles0, const G
     }
     if (b.db1) { b.gx1 = (b.N1 + Cfg::NW * 64 - 1) / (Cfg::NW * 64); b.tiles1 = a0.E * b.gx1; }
     b.tiles = b.tiles1 + (b.db2 ? (int)((b.n2 + Cfg::NW * 64 - 1) / (Cfg::NW * 64)) : 0);
-    const int64_t cap = (int64_t)c.num_cu * Cfg::WPE, worst = tiles0 + tiles1 + b.tiles;
+    const int64_t cap = (int64_t)c.num_cu * Cfg::WPE, worst = tiles0 + tiles1 + b.tiles +
+                  (sums.wanted ? (int64_t)kColsumSplit * a0.E * ((sums.N + 2047) / 2048) : 0);
     const int grid = (int)(worst < cap ? worst : cap);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(Cfg::NW * 64), G::SMEM, c.stream, a0, a1, (int)tiles0, (int)(tiles0 + tiles1),
-                       b);
+                       b, sums);
     return hipGetLastError();
 }
 template <int LAYOUT, int EPI, class Cfg>
-hipError_t launch_gemm(const Ctx& c, const GemmArgs& a, int64_t worst_tiles) {
-    return launch_gemm<LAYOUT, EPI, Cfg>(c, a, worst_tiles, a, 0);
+hipError_t launch_gemm(const Ctx& c, const GemmArgs& a, int64_t worst_tiles, const ColumnSums& sums) {
+    return launch_gemm<LAYOUT, EPI, Cfg>(c, a, worst_tiles, a, 0, BiasFinal{}, sums);
 }
 
 // Worst-case number of row tiles (launch grids and tables are sized for P_cap rows) ...
@@ -1122,13 +1210,14 @@ template <class... Cfgs> int cheapest_rows(const Ctx& c, const evomoe_shape& s, 
 }
 // Launches the cheapest of the candidates.
 template <int LAYOUT, int EPI, class... Cfgs>
-hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const Choice<Cfgs...>& ch) {
+hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const Choice<Cfgs...>& ch,
+                       const ColumnSums& sums = ColumnSums{}) {
     const int best = cheapest_rows(c, s, a.N, a.K, ch);
     hipError_t err = hipErrorInvalidValue;
     auto run = [&](auto cfg) {
         using Cfg = decltype(cfg);
         a.col_group = col_group_for<Cfg>(a.N, a.K);
-        err = launch_gemm<LAYOUT, EPI, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(a.N));
+        err = launch_gemm<LAYOUT, EPI, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(a.N), sums);
     };
     int n = 0;
     (void)((n++ == best ? (run(Cfgs{}), true) : false) || ...);
@@ -1183,6 +1272,11 @@ template <class... Cfgs> FfnTile tile_at(const Choice<Cfgs...>&, int i) {
 
 }  // namespace
 
+size_t colsum_scratch_bytes(const evomoe_shape& s) {
+    if (s.dtype != EVOMOE_BF16) return ((size_t)kF32ColsumSplit * s.E * (s.d + s.F) * sizeof(float) + 255) & ~(size_t)255;
+    return (((size_t)kColsumSplit * s.E * s.d * sizeof(float) + 255) & ~(size_t)255) + dh_colpart_bytes(s);
+}
+
 // column sums of dH: a row of F floats for every 64 rows of an expert (part_row())
 size_t dh_colpart_bytes(const evomoe_shape& s) {
     if (s.dtype != EVOMOE_BF16) return 0;
@@ -1231,7 +1325,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
     GemmArgs a{};
     a.expert_offsets = expert_offsets; a.E = s.E; a.P_cap = s.P_cap; a.act = s.act;
     hipError_t err;
-    // workspace behind dH: [column-sum partials of the streaming kernel][column sums of dH]
+    // workspace behind dH: [column sums of dO per row range][column sums of dH]
     float* scratch = reinterpret_cast<float*>(static_cast<char*>(dH) + dh_bytes(s));
     float* colpart = reinterpret_cast<float*>(static_cast<char*>(dH) + dh_bytes(s) + colsum_scratch_bytes(s) -
                                               dh_colpart_bytes(s));
@@ -1250,12 +1344,19 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         a.colpart = nullptr; a.a_rows = nullptr; a.row_scale = nullptr;
         if (err != hipSuccess) return err;
     }
-    {   // dXp = dH W1
+    ColumnSums sums{(const bf16_t*)dO, s.d, scratch, db2 != nullptr};
+    if (sums.wanted && expected_pairs(c, s) * s.d * 2 > 14000000) {
+        ProfScope ps(c, EVOMOE_K_FFN_BWD_DB);
+        hipLaunchKernelGGL(colsum_kernel, dim3(kColsumSplit * s.E * ((s.d + 2047) / 2048)), dim3(256), 0, c.stream, sums,
+                           expert_offsets, s.E, s.P_cap);
+        sums.wanted = 0;
+    }
+    {   // dXp = dH W1, and the column sums of dO if they are few
         ProfScope ps(c, EVOMOE_K_FFN_BWD_DX);
         a.A = (const bf16_t*)dH; a.lda = s.F; a.B = (const bf16_t*)W1; a.ldb = s.d;
         a.b_group_stride = (int64_t)s.F * s.d; a.N = s.d; a.K = s.F; a.Hin = nullptr;
         a.out1 = (bf16_t*)dXp;
-        err = launch_best<L_NN, E_NONE>(c, s, a, kDx);
+        err = launch_best<L_NN, E_NONE>(c, s, a, kDx, sums);
         if (err != hipSuccess) return err;
     }
     a.accumulate = accumulate;
@@ -1264,16 +1365,11 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
     w2.A = (const bf16_t*)dO; w2.lda = s.d; w2.B = (const bf16_t*)A; w2.ldb = s.F;
     w2.M = s.d; w2.N = s.F; w2.out1 = (bf16_t*)dW2;
     // dW1_g = dH_g^T X_g   [F,d]; the token rows are gathered on load
-    if (db2) {            // the split column sums of dO
-        ProfScope ps(c, EVOMOE_K_FFN_BWD_DB);
-        err = launch_colsum(c, s, dO, s.d, expert_offsets, scratch);
-        if (err != hipSuccess) return err;
-    }
     w1.A = (const bf16_t*)dH; w1.lda = s.F; w1.B = (const bf16_t*)x; w1.ldb = s.d; w1.b_rows = pair_token;
     w1.M = s.F; w1.N = s.d; w1.out1 = (bf16_t*)dW1;
     BiasFinal bf{};
     bf.part1 = colpart; bf.db1 = db1; bf.N1 = s.F;
-    bf.part2 = scratch; bf.db2 = db2; bf.n2 = (size_t)s.E * s.d; bf.accumulate = accumulate;
+    bf.part2 = scratch; bf.db2 = db2; bf.n2 = (size_t)s.E * s.d; bf.N2 = s.d; bf.accumulate = accumulate;
     bf.offsets = expert_offsets;
     if (!dW2 && !dW1 && !db1 && !db2) return hipSuccess;
     ProfScope ps(c, dW2 ? EVOMOE_K_FFN_BWD_DW2 : dW1 ? EVOMOE_K_FFN_BWD_DW1 : EVOMOE_K_FFN_BWD_DB);
