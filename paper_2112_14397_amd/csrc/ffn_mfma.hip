@@ -1225,7 +1225,7 @@ hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const C
 }
 constexpr Choice<CfgBig8, CfgDuo, CfgMid, CfgSml, CfgTny3>
     kGemm1{{{0, 12.2, 21.9}, {0, 12.4, 27.8}, {0, 9.2, 12.8}, {2.5, 4.4, 10.0}, {3.0, 3.4, 9.0}}},
-    kDh{{{20.8, 13.5, 22.3}, {0, 15.6, 26.0}, {0.3, 10.4, 13.2}, {2.6, 5.4, 10.7}, {2.8, 5.0, 8.8}}};
+    kDh{{{11.0, 8.1, 28.3}, {0, 15.6, 26.0}, {0.3, 10.4, 13.2}, {2.6, 5.4, 10.7}, {2.8, 5.0, 8.8}}};
 constexpr Choice<CfgBig, CfgLat, CfgMid64, CfgSml, CfgTny>
     kGemm2{{{0, 8.8, 20.5}, {0, 6.7, 12.5}, {0, 5.9, 7.8}, {0, 5.9, 10.5}, {0, 5.8, 6.1}}};
 constexpr Choice<CfgBig, CfgLat8, CfgMid64, CfgSml, CfgTny>
