@@ -360,11 +360,39 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
             seq_step = gridDim.x;
         }
     }
+    // A wave without an output (its 64 or 128 rows or its 128 columns do not exist) sits a 256x256 tile out: it fetches its share
+    // of the operands and leaves the matrix pipes to the others.  In launches of less than three rounds it does not: there the
+    // blocks that get ahead find no tile to take, and GEMM1 of 8192 pairs, d = 768, took 70 us instead of 64.
+    // Where no more than half of the blocks have a tile in the last round, two blocks take each of those tiles, one for its
+    // upper and one for its lower 128 rows (waves 0 .. 3, one per SIMD, or 4 .. 7): places [full, full + halves) of the
+    // sequence are upper halves, the next ones lower halves.  Not GEMM1, whose epilogue is as long for one wave per SIMD as for
+    // two (58 330 pairs: 334 us, without 326).  us, before / now: weight gradients of d = 768, F = 3072, 16 experts (4.5 rounds),
+    // 58 330 pairs 485 / 468, 8192 pairs 109 / 106; dH 16 223 pairs 128 / 122, d = 1024, 87 690 pairs 901 / 871; GEMM1 d = 512, 22 073
+    // pairs (345 rows per expert) 98 / 88, d = 1024, 87 690 pairs 945 / 908.
+    constexpr bool SIT_OUT = BM == 256 && BN == 256;
+    constexpr bool HALVES = SIT_OUT && NW == 8 && EPI != E_HA;
+    bool sit_rows = true;
+    int halves = 0, full = LAYOUT == L_TN ? tiles_all : seq_end;
+    if (SIT_OUT) {
+        const int step = LAYOUT == L_TN ? (int)gridDim.x : seq_step;
+        const int begin = LAYOUT == L_TN ? 0 : seq - (step == (int)gridDim.x ? vblock : (int)(blockIdx.x >> 3));
+        const int rem = __builtin_amdgcn_readfirstlane((full - begin) % step);
+        halves = HALVES && 2 * rem <= step ? rem : 0;
+        sit_rows = full - begin >= 3 * step;
+        full -= halves;
+        seq_end += halves;
+    }
+    const int all_places = tiles_all + halves;      // TN
 
-    // Where a tile lies: problem (TN), expert, origin, contraction range.  NT/NN: place `at` of the sequence; TN: tile number.
-    struct Tile { int second, g, row0, rows, m0, n0, kbeg, kend; };
+    // Where a tile lies: problem (TN), expert, origin, contraction range.  NT/NN: its place in the sequence; TN: its number.
+    struct Tile { int second, g, row0, rows, m0, n0, kbeg, kend, half; };
     auto locate = [&](int at) {
         Tile t{};
+        t.half = -1;
+        if (SIT_OUT && at >= full) {
+            t.half = at >= full + halves;
+            at -= t.half ? halves : 0;
+        }
         t.second = LAYOUT == L_TN && at >= tiles0;
         const GemmArgs& p = t.second ? q1 : q0;
         const int nct = (p.N + BN - 1) / BN;
@@ -398,6 +426,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         t.n0 = __builtin_amdgcn_readfirstlane(t.n0);
         t.kbeg = __builtin_amdgcn_readfirstlane(t.kbeg);
         t.kend = __builtin_amdgcn_readfirstlane(t.kend);
+        t.half = __builtin_amdgcn_readfirstlane(t.half);
         return t;
     };
 
@@ -425,6 +454,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
     static_assert(!PRE || (PRE_STORES <= 63 && WN == 128 && NW * 4096 <= G::STAGE), "epilogue beside a slab");
     int par = 0;                    // PRE: stage of the tile's first slab
     bool begun = false;             // PRE: ... is being fetched already; TN: the tile's first row numbers are
+    bool stored = false;            // PRE: this wave has stored the previous tile
     Tile ahead{};
     // ---------------- global addresses: one scalar base per operand + 32-bit per-lane byte offsets ----
     // k-contiguous operand: offset of (row, chunk) at k = 0, one register per load instruction.
@@ -437,9 +467,9 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
     int kc_chunk = 0, ksA_row = 0, ksB_row = 0;
 
     for (int vtile = vblock;; vtile += gridDim.x, seq += seq_step) {
-        if (LAYOUT == L_TN && vtile >= tiles_all) {
-            if (vtile - tiles_all >= qb.tiles) break;
-            bias_final_tile(qb, vtile - tiles_all, offs, NW * 64);
+        if (LAYOUT == L_TN && vtile >= all_places) {
+            if (vtile - all_places >= qb.tiles) break;
+            bias_final_tile(qb, vtile - all_places, offs, NW * 64);
             continue;
         }
         if (LAYOUT != L_TN && seq >= seq_end) break;
@@ -448,6 +478,9 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };     // (known to be, not when it comes around the loop)
         const int g = uniform(t.g), row0 = uniform(t.row0), rows = uniform(t.rows), m0 = uniform(t.m0), n0 = uniform(t.n0),
                   kbeg = uniform(t.kbeg), kend = uniform(t.kend);
+        const int half = uniform(t.half);
+        const bool active = !SIT_OUT || ((half < 0 || half == wm / 2) &&
+                                         (!sit_rows || (n0 + wn * WN < p.N && (LAYOUT == L_TN ? m0 + wm * WM < p.M : wm * WM < rows))));
         const int nslab = (kend - kbeg + BK - 1) / BK;
         const bool ragged = (kend - kbeg) % BK != 0;     // block-uniform: the last slab is partial
 
@@ -631,10 +664,11 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         // fences pin this order.
 #define KSTEP(FA, FB, READ_NEXT, NA, NB, nslb, nks, LD_LO, LD_HI, lslab)                          \
     _Pragma("unroll") for (int q = 0; q < 8; ++q) {                                              \
-        _Pragma("unroll") for (int x = NMF * q / 8; x < NMF * (q + 1) / 8; ++x)                  \
-            acc[x / TN_][x % TN_] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                     \
-                FA[x / TN_], FB[x % TN_], acc[x / TN_][x % TN_], 0, 0, 0);                       \
-        if (READ_NEXT && q < 4) {                                                                \
+        if (ACT)                                                                                 \
+            _Pragma("unroll") for (int x = NMF * q / 8; x < NMF * (q + 1) / 8; ++x)              \
+                acc[x / TN_][x % TN_] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                 \
+                    FA[x / TN_], FB[x % TN_], acc[x / TN_][x % TN_], 0, 0, 0);                   \
+        if (ACT && READ_NEXT && q < 4) {                                                           \
             _Pragma("unroll") for (int f = NFR * q / 4; f < NFR * (q + 1) / 4; ++f)              \
                 read_frag(f, nslb, nks, NA, NB);                                                 \
         }                                                                                        \
@@ -647,7 +681,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         bf16x8 fa0[TM], fb0[TN_], fa1[TM], fb1[TN_];
         if (PRE) {
             // the first slab went out before the previous tile's epilogue; only that one's stores may still be in flight
-            if (begun) wait_vmcnt<PRE_STORES>(); else issue(0), wait_vmcnt<0>();
+            if (begun && stored) wait_vmcnt<PRE_STORES>(); else if (begun) wait_vmcnt<0>(); else issue(0), wait_vmcnt<0>();
+            stored = active;
             block_sync_lds();           // it has landed, and the previous epilogue has left the other stage
             if (nslab > 1) {
 #pragma unroll
@@ -692,8 +727,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         // Slab s: k-steps 0..KS-1 on stage s % NSTAGE.  Fragments of the next k-step are read while the
         // current one multiplies; loads of slab s+NSTAGE-1 go out under k-step 0 into the stage that slab
         // s-1 has finished with; before the last k-step the block makes sure slab s+1 has landed.
-        auto slab_body = [&](int slab, auto loads_c) {
-            constexpr bool LOADS = decltype(loads_c)::value;
+        auto slab_body = [&](int slab, auto loads_c, auto act_c) {
+            constexpr bool LOADS = decltype(loads_c)::value, ACT = decltype(act_c)::value;     // ACT: not sitting out
             if constexpr (EARLY) {
                 // two stages: a slab's first loads go out as soon as its stage is released, under the last k-step of
                 // the slab before the one they are loaded under (LOADS: there is a slab + 2)
@@ -735,8 +770,12 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         int slab = 0;
         // two blocks per CU: the wave that is feeding the matrix pipe goes ahead of its neighbour's epilogue
         if (WPE > 1) __builtin_amdgcn_s_setprio(1);
-        for (; slab + NSTAGE - (EARLY ? 0 : 1) < nslab; ++slab) slab_body(slab, std::true_type{});
-        for (; slab + 1 < nslab; ++slab) slab_body(slab, std::false_type{});
+        auto slabs = [&](auto act_c) {
+            for (; slab + NSTAGE - (EARLY ? 0 : 1) < nslab; ++slab) slab_body(slab, std::true_type{}, act_c);
+            for (; slab + 1 < nslab; ++slab) slab_body(slab, std::false_type{}, act_c);
+        };
+        if (active) slabs(std::true_type{});
+        else slabs(std::bool_constant<!SIT_OUT>{});
         float bias8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         auto load_bias = [&](int lane) {
             if (!((EPI == E_HA || EPI == E_BIAS) && LAYOUT != L_TN) || !p.bias) return;
@@ -758,7 +797,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
                 tokens(ahead, p, lane_n, next_rows);
             }
         }
-        if (nslab > 0) {           // last slab: nothing left to fetch or to read ahead
+        if (nslab > 0 && active) {           // last slab: nothing left to fetch or to read ahead
+            constexpr bool ACT = true;
             KSTEP(fa0, fb0, true, fa1, fb1, slab, 1, 0, 0, 0);
             if (KS == 4) {
                 KSTEP(fa1, fb1, true, fa0, fb0, slab, 2, 0, 0, 0);
@@ -780,7 +820,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
             }
         }
         if (LAYOUT == L_TN) {     // ... and the ring with the row numbers is free for the next tile's
-            begun = vtile + (int)gridDim.x < tiles_all;
+            begun = vtile + (int)gridDim.x < all_places;
             if (begun) {
                 ahead = locate(vtile + gridDim.x);
                 first_pieces(ahead);
@@ -794,6 +834,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         // no wait but the one for the data.  16-byte chunk c of row r lies at c ^ (c >> 4 & 1) ^ (r & 4 ? 8 : 0): the two
         // half-waves write to, and sixteen lanes read from, different banks.
         constexpr bool STEPS = LAYOUT != L_TN && WN == 128 && WPE == 1;
+        if (!active) continue;
         if constexpr (STEPS) {
             int lane_e = lane_id;
             asm volatile("" : "+v"(lane_e));
@@ -1081,7 +1122,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         for (int e = 0; e < q0.E; ++e) most = max(most, sum_ranges(offs[e + 1] - offs[e]));
         const int n = gx * q0.E * most;
         // A block without a tile of the last round takes as many column sums as a tile is worth, what is left is dealt to all.
-        const int total = tstart[q0.E] * ((q0.N + BN - 1) / BN), grid = gridDim.x, busy = total % grid;
+        const int total = tstart[q0.E] * ((q0.N + BN - 1) / BN) + halves, grid = gridDim.x, busy = total % grid;
         const int idle = busy && seq_step == grid ? grid - busy : 0;
         const int64_t tile_ns = (int64_t)(9000 + 20 * q0.K) * (BM * BN) / 65536;
         const int64_t sum_ns = 1500 + (int64_t)offs[q0.E] * qs.N * 2 / n / 40;
