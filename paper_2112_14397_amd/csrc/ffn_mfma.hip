@@ -283,8 +283,15 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
 
+// What a launch carries besides its first problem (nothing else: the arguments of a launch are copied and read every time)
+struct NoExtra {};
+struct TnExtra { GemmArgs q1; BiasFinal bias; };
+template <int LAYOUT, int EPI> struct Extra { using type = NoExtra; };
+template <int EPI> struct Extra<L_TN, EPI> { using type = TnExtra; };
+template <> struct Extra<L_NN, E_NONE> { using type = ColumnSums; };
+
 template <int LAYOUT, int EPI, int BM, int BN, int BK, int NSTAGE, int WPE, int NW = 4>
-__global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, GemmArgs q1, int tiles0, int tiles_all, BiasFinal qb, ColumnSums qs)
+__global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, int tiles0, int tiles_all, typename Extra<LAYOUT, EPI>::type qx)
 {
     // TN launches carry two independent problems (dW2 and dW1) in one grid, tiles [0, tiles0) and
     // [tiles0, tiles_all), which evens out the last round of the persistent schedule, and behind them the bias
@@ -309,6 +316,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int offs[65];
 
+    auto problem = [&](int second) -> const GemmArgs& {
+        if constexpr (LAYOUT == L_TN) return second ? qx.q1 : q0;
+        else return q0;
+    };
     const int tid = threadIdx.x, lane_id = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);       // wave-uniform: lives in an SGPR
     const int wm = wave >> 1, wn = wave & 1;
@@ -394,7 +405,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
             at -= t.half ? halves : 0;
         }
         t.second = LAYOUT == L_TN && at >= tiles0;
-        const GemmArgs& p = t.second ? q1 : q0;
+        const GemmArgs& p = problem(t.second);
         const int nct = (p.N + BN - 1) / BN;
         if (LAYOUT == L_TN) {
             const int tile = t.second ? at - tiles0 : at, nmt = (p.M + BM - 1) / BM;
@@ -439,7 +450,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         asm volatile("" : "+v"(lane_f));
         const int kr = min(n * PIECE + wave * 64 + lane_f, klen - 1);
         int* at = ring + (LAYOUT == L_TN ? (uint32_t)(n * PIECE) % RING + wave * 64 : 0);
-        const int32_t* list = (t.second ? q1 : q0).b_rows;
+        const int32_t* list = problem(t.second).b_rows;
         if (list) load_dword_to_lds(list + kbeg, (uint32_t)kr * 4, at);
         else at[LAYOUT == L_TN ? lane_f : 0] = kr;
     };
@@ -467,14 +478,16 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
     int kc_chunk = 0, ksA_row = 0, ksB_row = 0;
 
     for (int vtile = vblock;; vtile += gridDim.x, seq += seq_step) {
-        if (LAYOUT == L_TN && vtile >= all_places) {
-            if (vtile - all_places >= qb.tiles) break;
-            bias_final_tile(qb, vtile - all_places, offs, NW * 64);
-            continue;
+        if constexpr (LAYOUT == L_TN) {
+            if (vtile >= all_places) {
+                if (vtile - all_places >= qx.bias.tiles) break;
+                bias_final_tile(qx.bias, vtile - all_places, offs, NW * 64);
+                continue;
+            }
         }
         if (LAYOUT != L_TN && seq >= seq_end) break;
         const Tile t = (PRE || LAYOUT == L_TN) && begun ? ahead : locate(LAYOUT == L_TN ? vtile : seq);
-        const GemmArgs& p = t.second ? q1 : q0;
+        const GemmArgs& p = problem(t.second);
         auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };     // (known to be, not when it comes around the loop)
         const int g = uniform(t.g), row0 = uniform(t.row0), rows = uniform(t.rows), m0 = uniform(t.m0), n0 = uniform(t.n0),
                   kbeg = uniform(t.kbeg), kend = uniform(t.kend);
@@ -1116,7 +1129,9 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, G
         }
     }
 
-    if (EPI == E_NONE && qs.wanted) {
+    if constexpr (EPI == E_NONE) {
+        const ColumnSums& qs = qx;
+        if (!qs.wanted) return;
         const int CL = colsum_lanes(qs.N), gx = (qs.N / 8 + CL - 1) / CL;
         int most = 1;
         for (int e = 0; e < q0.E; ++e) most = max(most, sum_ranges(offs[e + 1] - offs[e]));
@@ -1167,8 +1182,8 @@ struct CfgTny { static constexpr int BM = 64, BN = 64, BK = 64, NSTAGE = 4, WPE 
 struct CfgTny3 { static constexpr int BM = 64, BN = 64, BK = 64, NSTAGE = 3, WPE = 3, NW = 4; };
 
 template <int LAYOUT, int EPI, class Cfg>
-hipError_t launch_gemm(const Ctx& c, const GemmArgs& a0, int64_t tiles0, const GemmArgs& a1, int64_t tiles1,
-                       BiasFinal b = BiasFinal{}, const ColumnSums& sums = ColumnSums{}) {
+hipError_t launch_gemm(const Ctx& c, const GemmArgs& a0, int64_t tiles0, int64_t tiles1, int64_t other_tiles,
+                       const typename Extra<LAYOUT, EPI>::type& extra) {
     using G = Geo<LAYOUT, Cfg::BM, Cfg::BN, Cfg::BK, Cfg::NSTAGE, Cfg::NW>;
     auto kern = grouped_gemm_bf16<LAYOUT, EPI, Cfg::BM, Cfg::BN, Cfg::BK, Cfg::NSTAGE, Cfg::WPE, Cfg::NW>;
     static bool configured = false;
@@ -1178,18 +1193,17 @@ hipError_t launch_gemm(const Ctx& c, const GemmArgs& a0, int64_t tiles0, const G
         if (e != hipSuccess) return e;
         configured = true;
     }
-    if (b.db1) { b.gx1 = (b.N1 + Cfg::NW * 64 - 1) / (Cfg::NW * 64); b.tiles1 = a0.E * b.gx1; }
-    b.tiles = b.tiles1 + (b.db2 ? (int)((b.n2 + Cfg::NW * 64 - 1) / (Cfg::NW * 64)) : 0);
-    const int64_t cap = (int64_t)c.num_cu * Cfg::WPE, worst = tiles0 + tiles1 + b.tiles +
-                  (sums.wanted ? (int64_t)kColsumSplit * a0.E * ((sums.N + 2047) / 2048) : 0);
+    const int64_t cap = (int64_t)c.num_cu * Cfg::WPE, worst = tiles0 + tiles1 + other_tiles;
     const int grid = (int)(worst < cap ? worst : cap);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(Cfg::NW * 64), G::SMEM, c.stream, a0, a1, (int)tiles0, (int)(tiles0 + tiles1),
-                       b, sums);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(Cfg::NW * 64), G::SMEM, c.stream, a0, (int)tiles0, (int)(tiles0 + tiles1), extra);
     return hipGetLastError();
 }
-template <int LAYOUT, int EPI, class Cfg>
-hipError_t launch_gemm(const Ctx& c, const GemmArgs& a, int64_t worst_tiles, const ColumnSums& sums) {
-    return launch_gemm<LAYOUT, EPI, Cfg>(c, a, worst_tiles, a, 0, BiasFinal{}, sums);
+// TN: two problems, and the bias gradients' last sums
+template <class Cfg>
+hipError_t launch_tn(const Ctx& c, const GemmArgs& a0, int64_t tiles0, const GemmArgs& a1, int64_t tiles1, BiasFinal b) {
+    if (b.db1) { b.gx1 = (b.N1 + Cfg::NW * 64 - 1) / (Cfg::NW * 64); b.tiles1 = a0.E * b.gx1; }
+    b.tiles = b.tiles1 + (b.db2 ? (int)((b.n2 + Cfg::NW * 64 - 1) / (Cfg::NW * 64)) : 0);
+    return launch_gemm<L_TN, E_WGRAD, Cfg>(c, a0, tiles0, tiles1, b.tiles, TnExtra{a1, b});
 }
 
 // Worst-case number of row tiles (launch grids and tables are sized for P_cap rows) ...
@@ -1251,14 +1265,14 @@ template <class... Cfgs> int cheapest_rows(const Ctx& c, const evomoe_shape& s, 
 }
 // Launches the cheapest of the candidates.
 template <int LAYOUT, int EPI, class... Cfgs>
-hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const Choice<Cfgs...>& ch,
-                       const ColumnSums& sums = ColumnSums{}) {
+hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const Choice<Cfgs...>& ch, int64_t other_tiles = 0,
+                       const typename Extra<LAYOUT, EPI>::type& extra = {}) {
     const int best = cheapest_rows(c, s, a.N, a.K, ch);
     hipError_t err = hipErrorInvalidValue;
     auto run = [&](auto cfg) {
         using Cfg = decltype(cfg);
         a.col_group = col_group_for<Cfg>(a.N, a.K);
-        err = launch_gemm<LAYOUT, EPI, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(a.N), sums);
+        err = launch_gemm<LAYOUT, EPI, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(a.N), 0, other_tiles, extra);
     };
     int n = 0;
     (void)((n++ == best ? (run(Cfgs{}), true) : false) || ...);
@@ -1296,8 +1310,8 @@ hipError_t launch_wgrad(const Ctx& c, const evomoe_shape& s, const GemmArgs* w2,
     const GemmArgs& q1 = w1 ? *w1 : q0;
     auto run = [&](auto cfg) {
         using Cfg = decltype(cfg);
-        return launch_gemm<L_TN, E_WGRAD, Cfg>(c, q0, w2 || w1 ? wgrad_tiles<Cfg>(s, q0.M, q0.N) : 0, q1,
-                                               w2 && w1 ? wgrad_tiles<Cfg>(s, q1.M, q1.N) : 0, bf);
+        return launch_tn<Cfg>(c, q0, w2 || w1 ? wgrad_tiles<Cfg>(s, q0.M, q0.N) : 0, q1,
+                              w2 && w1 ? wgrad_tiles<Cfg>(s, q1.M, q1.N) : 0, bf);
     };
     switch (cheapest_wgrad(c, s, w2, w1)) {
         case 0: return run(CfgOct{});
@@ -1386,9 +1400,10 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         if (err != hipSuccess) return err;
     }
     ColumnSums sums{(const bf16_t*)dO, s.d, scratch, db2 != nullptr};
+    const int sum_tiles = kColsumSplit * s.E * ((s.d + 2047) / 2048);
     if (sums.wanted && expected_pairs(c, s) * s.d * 2 > 14000000) {
         ProfScope ps(c, EVOMOE_K_FFN_BWD_DB);
-        hipLaunchKernelGGL(colsum_kernel, dim3(kColsumSplit * s.E * ((s.d + 2047) / 2048)), dim3(256), 0, c.stream, sums,
+        hipLaunchKernelGGL(colsum_kernel, dim3(sum_tiles), dim3(256), 0, c.stream, sums,
                            expert_offsets, s.E, s.P_cap);
         sums.wanted = 0;
     }
@@ -1397,7 +1412,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         a.A = (const bf16_t*)dH; a.lda = s.F; a.B = (const bf16_t*)W1; a.ldb = s.d;
         a.b_group_stride = (int64_t)s.F * s.d; a.N = s.d; a.K = s.F; a.Hin = nullptr;
         a.out1 = (bf16_t*)dXp;
-        err = launch_best<L_NN, E_NONE>(c, s, a, kDx, sums);
+        err = launch_best<L_NN, E_NONE>(c, s, a, kDx, sums.wanted ? sum_tiles : 0, sums);
         if (err != hipSuccess) return err;
     }
     a.accumulate = accumulate;
