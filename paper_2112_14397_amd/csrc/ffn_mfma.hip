@@ -330,20 +330,26 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, i
     // pairs, d = 768.)
     constexpr int RING = 1024, PIECE = 256;
     __shared__ int ring[LAYOUT == L_TN ? RING : 1];
-    if (tid <= q0.E) offs[tid] = clamp_pairs(q0.expert_offsets[tid], q0.P_cap);
-    __syncthreads();
-    if (LAYOUT != L_TN) {
-        if (tid == 0) {
-            int acc_t = 0;
-            for (int e = 0; e < q0.E; ++e) {
-                tstart[e] = acc_t;
-                acc_t += (offs[e + 1] - offs[e] + BM - 1) / BM;
+    // Lane e of the first wave counts expert e's rows and row tiles; entries beyond the last expert are its end.  (One thread
+    // that walked over the experts, and a walk from expert to expert to find a tile: 64 experts, 22 073 pairs, d = 512, GEMM1
+    // 87.9 us, now 83.7; 16 experts 0.3 to 0.5 us more per launch.)
+    if (wave == 0) {
+        const int begin = clamp_pairs(q0.expert_offsets[min(lane_id, q0.E)], q0.P_cap),
+                  end = clamp_pairs(q0.expert_offsets[min(lane_id + 1, q0.E)], q0.P_cap);
+        if (lane_id == 0) offs[0] = begin;
+        offs[lane_id + 1] = end;
+        if (LAYOUT != L_TN) {
+            int upto = (end - begin + BM - 1) / BM;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int v = __shfl_up(upto, o, 64);
+                if (lane_id >= o) upto += v;
             }
-            tstart[q0.E] = acc_t;
+            if (lane_id == 0) tstart[0] = 0;
+            tstart[lane_id + 1] = upto;
         }
-        __syncthreads();
     }
-    int cur_e = 0;                  // expert of the previous tile: row tiles only grow from tile to tile
+    __syncthreads();
 
     // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.
     // TN: renumber the blocks so that one XCD works on a run of consecutive tiles per round (the tiles of one
@@ -416,18 +422,21 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, i
             t.kbeg = offs[t.g];
             t.kend = offs[t.g + 1];
         } else {
-            while (at >= tstart[cur_e + 1] * nct) ++cur_e;       // resumes where the previous tile's search ended
-            t.g = cur_e;
-            const int nrt = tstart[t.g + 1] - tstart[t.g];       // row tiles of this expert (>= 1 here)
-            const int r = at - tstart[t.g] * nct;                // position inside the expert's nrt * nct tiles
+            int e;                                               // (the lane's number: no register is kept for it)
+            asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(e));
+            const int first = tstart[e], next = tstart[e + 1], begin = offs[e], end = offs[e + 1];
+            t.g = __popcll(__ballot(at >= next * nct));          // lane e looks at expert e: those that lie before the tile
+            const int t0 = __builtin_amdgcn_readlane(first, t.g), nrt = __builtin_amdgcn_readlane(next, t.g) - t0,   // row tiles of this expert (>= 1 here)
+                      o0 = __builtin_amdgcn_readlane(begin, t.g), o1 = __builtin_amdgcn_readlane(end, t.g);
+            const int r = at - t0 * nct;                         // position inside the expert's nrt * nct tiles
             const int cgs = max(1, min(p.col_group, nct));       // column tiles per group
             const int cg = r / (nrt * cgs);
             const int r2 = r - cg * nrt * cgs;
             const int gc = min(cgs, nct - cg * cgs);             // column tiles of this group (the last may be short)
             const int rt_in = r2 / gc;
             t.n0 = (cg * cgs + (r2 - rt_in * gc)) * BN;
-            t.row0 = offs[t.g] + rt_in * BM;
-            t.rows = min(BM, offs[t.g + 1] - t.row0);
+            t.row0 = o0 + rt_in * BM;
+            t.rows = min(BM, o1 - t.row0);
             t.kend = p.K;
         }
         // the tile's coordinates came through LDS: tell the compiler they are wave-uniform (SGPRs)
@@ -1133,8 +1142,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, i
         const ColumnSums& qs = qx;
         if (!qs.wanted) return;
         const int CL = colsum_lanes(qs.N), gx = (qs.N / 8 + CL - 1) / CL;
-        int most = 1;
-        for (int e = 0; e < q0.E; ++e) most = max(most, sum_ranges(offs[e + 1] - offs[e]));
+        int most = sum_ranges(offs[lane_id + 1] - offs[lane_id]);
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) most = max(most, __shfl_xor(most, o, 64));
+        most = __builtin_amdgcn_readfirstlane(most);
         const int n = gx * q0.E * most;
         // A block without a tile of the last round takes as many column sums as a tile is worth, what is left is dealt to all.
         const int total = tstart[q0.E] * ((q0.N + BN - 1) / BN) + halves, grid = gridDim.x, busy = total % grid;
