@@ -103,10 +103,10 @@ __device__ __forceinline__ void bias_final_tile(const BiasFinal& q, int b, const
 
 // Column sums of dO over every expert's rows (the first pass of db2): an expert's rows are cut into sum_ranges() ranges, 64 rows
 // each as long as 32 ranges are enough; a tile leaves part[range][expert][column] for 2048 columns at most.
-// Up to 14 MB of dO the tiles run behind dXp's, on the compute units first that have no dXp tile in the last round; beyond, in a
+// Up to 32 MB of dO the tiles run behind dXp's, on the compute units first that have no dXp tile in the last round; beyond, in a
 // launch of their own, which has more waves in flight.  dXp and the sums, us, behind it / on their own: 777 tokens, d = 136,
-// two micro-batches 23 / 33; 8192 pairs of d = 768 64 / 67, 22 073 of d = 512 86 / 87, 58 330 of d = 768 278 / 276, 87 690
-// of d = 1024 719 / 694.
+// two micro-batches 22 / 33; 8192 pairs of d = 768 59 / 67, 16 223 95 / 103, 22 073 of d = 512 80 / 82, 58 330 of d = 768
+// 283 / 272, 87 690 of d = 1024 710 / 678.
 struct ColumnSums {
     const bf16_t* M;  int N;            // dO [P,N]
     float* part;                        // [kColsumSplit][E][N]
@@ -1415,7 +1415,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
     }
     ColumnSums sums{(const bf16_t*)dO, s.d, scratch, db2 != nullptr};
     const int sum_tiles = kColsumSplit * s.E * ((s.d + 2047) / 2048);
-    if (sums.wanted && expected_pairs(c, s) * s.d * 2 > 14000000) {
+    if (sums.wanted && expected_pairs(c, s) * s.d * 2 > 32000000) {
         ProfScope ps(c, EVOMOE_K_FFN_BWD_DB);
         hipLaunchKernelGGL(colsum_kernel, dim3(sum_tiles), dim3(256), 0, c.stream, sums,
                            expert_offsets, s.E, s.P_cap);
