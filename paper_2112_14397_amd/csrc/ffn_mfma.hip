@@ -1167,8 +1167,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, i
 // BIG8: the same tile worked by eight waves (64x128 each, two per SIMD, 128 accumulator registers): the waves of a SIMD
 // fill each other's stalls and share the epilogue, which is half of a short contraction's tile.
 // A 64-wide slab takes whole 128-byte lines of a k-contiguous operand: with four stages of 32 k the L1 fetched every
-// line twice (its other half was gone by the next slab; 2831 MB from the L2 per GEMM1 launch at 38 969 pairs, now 1470).  BIG8 against 32-wide slabs: GEMM1 404 -> 366 us at d = 768, F = 3072, 58 330 pairs, 1603 -> 1473
-// at d = 1024, F = 4096, 131 072 pairs; BIG: GEMM2 270 -> 254 and 1026 -> 964 us, dXp 261 -> 252 and 994 -> 962 us.
+// line twice (its other half was gone by the next slab; 2831 MB from the L2 per GEMM1 launch at 38 969 pairs, now 1470).
+// BIG8 against 32-wide slabs: GEMM1 404 -> 366 us at d = 768, F = 3072, 58 330 pairs, 1603 -> 1473 at d = 1024, F = 4096, 131 072 pairs; BIG: GEMM2 270 -> 254 and 1026 -> 964 us, dXp 261 -> 252 and 994 -> 962 us.
 // Where its time went with both waves of a SIMD in the epilogue at once (clocks per tile at d = 768): GEMM1 26.6 k main loop, 15 k
 // epilogue, bound by its VALU instructions, 9 k waiting at the ends for loads and for each other; dH 22 k epilogue, H's loads one
 // step ahead.  The next tile's first slab and row numbers under the epilogue, the epilogue in steps that overlap, a shorter
@@ -1254,8 +1254,8 @@ template <class Cfg> int col_group_for(int n, int k) {
 // model picks is within 1-3 % of the best one measured on average (no launch of the sweep above 27 %, those of 10 us or 20 us), where
 // 256-column tiles alone were 40-190 % slower below about 200 rows per expert.  d = 768, F = 3072, 16 experts, us:
 //            pairs     48     512    2048   8192   58330
-//   GEMM1  256-wide    30     30     32     69     366          GEMM2  256-wide   37     40     45     53     254
-//          picked      18     18     30     69     366                 picked     18     20     31     53     254
+//   GEMM1  256-wide    30     30     32     65     326          GEMM2  256-wide   37     40     45     53     254
+//          picked      17     17     30     65     326                 picked     17     20     31     53     254
 struct RoundTime { double fixed, per_round, per_k; };
 template <class Cfg> double round_cost(const Ctx& c, int64_t tiles, double k, const RoundTime& t) {
     const int64_t slots = (int64_t)c.num_cu * Cfg::WPE, last = tiles % slots;
