@@ -1255,7 +1255,7 @@ template <class Cfg> int col_group_for(int n, int k) {
 // 256-column tiles alone were 40-190 % slower below about 200 rows per expert.  d = 768, F = 3072, 16 experts, us:
 //            pairs     48     512    2048   8192   58330
 //   GEMM1  256-wide    30     30     32     65     326          GEMM2  256-wide   37     40     45     53     254
-//          picked      17     17     30     65     326                 picked     17     20     31     53     254
+//          picked      17     18     30     65     326                 picked     17     20     31     53     254
 struct RoundTime { double fixed, per_round, per_k; };
 template <class Cfg> double round_cost(const Ctx& c, int64_t tiles, double k, const RoundTime& t) {
     const int64_t slots = (int64_t)c.num_cu * Cfg::WPE, last = tiles % slots;
