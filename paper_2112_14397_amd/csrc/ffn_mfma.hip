@@ -194,20 +194,23 @@ template <int LAYOUT, int BM, int BN, int BK, int NSTAGE, int NW = 4> struct Geo
     template <int C> __device__ static __forceinline__ int ks_key(int k) { return C >= 128 ? 2 * (k & 3) : (k & 2); }
 };
 
-// gelu(h) = max(h, 0) - |h| Q(|h|) with Q(z) = 1 - Phi(z) = 2^p(z): log2 Q is so smooth that a polynomial of degree four on
-// |h| <= 5.5 gives Q to 6.9e-6 (minimax; float32 evaluation included), and beyond it the term is below 1.7e-7.  Nine VALU
-// instructions, one of them v_exp_f32, which takes two slots.  (Phi as an odd polynomial of degree 17 of h clamped to 4.2:
-// errors of 1.1e-5 |h|, 8.7e-5 in the tails, 13 instructions; GEMM1's epilogue is bound by them.)
+// gelu(h) = max(h, 0) - |h| Q(|h|) with Q(z) = 1 - Phi(z) = 2^p(z): log2 Q is so smooth that a polynomial of degree five on
+// |h| <= 5.5 gives gelu to 9.6e-7 (minimax with the error weighted toward small |h|; float32 evaluation included), and beyond it the
+// term is below 1e-7.  Ten VALU instructions, one of them v_exp_f32, which takes two slots; GEMM1's epilogue is bound by them.
+// (Degree four, one v_fmaak_f32 less, was off by up to 2.1e-5, in places by more than the form before it: Phi as an odd polynomial
+// of degree 17 of h clamped to 4.2, 13 instructions, errors of 1.1e-5 |h|, 8.7e-5 in the tails.  Of GEMM1 it saved 1 %: 868
+// against 877 us at 87 690 pairs, d = 1024.)
 __device__ __forceinline__ float act_fwd_fast(float h, int act) {
     if (act == EVOMOE_RELU) return h > 0.f ? h : 0.f;
     float z, pos;
     asm("v_min_f32 %0, |%1|, %2" : "=v"(z) : "v"(h), "s"(5.5f));        // (as fminf and fmaxf each would get a second instruction
     asm("v_max_f32 %0, 0, %1" : "=v"(pos) : "v"(h));                    // for signalling NaNs)
-    float q = 0.00470887171f;
-    q = fmaf(q, z, -0.0479916483f);
-    q = fmaf(q, z, -0.462215245f);
-    q = fmaf(q, z, -1.15046859f);
-    q = fmaf(q, z, -1.00001967f);
+    float q = -0.000514221328f;
+    q = fmaf(q, z, 0.00736901748f);
+    q = fmaf(q, z, -0.0525218223f);
+    q = fmaf(q, z, -0.459272654f);
+    q = fmaf(q, z, -1.15108872f);
+    q = fmaf(q, z, -1.00000012f);
     return fmaf(-z, __builtin_amdgcn_exp2f(q), pos);
 }
 // gelu'(h) = Phi(h) + h phi(h) as 0.5 + hc*R(hc^2): it is odd about 1/2 as well, so one degree-10 minimax fit of the whole
