@@ -70,8 +70,9 @@ template <> struct Elem<bf16_t> {
 };
 
 // Activation of Eq. ffn (ReLU) and of the experiments (exact GeLU x*Phi(x)); derivatives with ReLU'(0)=0.
+__device__ __forceinline__ float relu(float h) { return __builtin_elementwise_maximum(h, 0.f); }      // (a NaN stays one)
 __device__ __forceinline__ float act_fwd(float h, int act) {
-    if (act == EVOMOE_RELU) return h > 0.f ? h : 0.f;
+    if (act == EVOMOE_RELU) return relu(h);
     return 0.5f * h * (1.0f + erff(h * 0.70710678118654752440f));
 }
 __device__ __forceinline__ float act_grad(float h, int act) {

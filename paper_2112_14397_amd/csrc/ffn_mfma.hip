@@ -201,10 +201,10 @@ template <int LAYOUT, int BM, int BN, int BK, int NSTAGE, int NW = 4> struct Geo
 // of degree 17 of h clamped to 4.2, 13 instructions, errors of 1.1e-5 |h|, 8.7e-5 in the tails.  Of GEMM1 it saved 1 %: 868
 // against 877 us at 87 690 pairs, d = 1024.)
 __device__ __forceinline__ float act_fwd_fast(float h, int act) {
-    if (act == EVOMOE_RELU) return h > 0.f ? h : 0.f;
-    float z, pos;
-    asm("v_min_f32 %0, |%1|, %2" : "=v"(z) : "v"(h), "s"(5.5f));        // (as fminf and fmaxf each would get a second instruction
-    asm("v_max_f32 %0, 0, %1" : "=v"(pos) : "v"(h));                    // for signalling NaNs)
+    if (act == EVOMOE_RELU) return relu(h);
+    const float z = __builtin_elementwise_minimum(__builtin_fabsf(h), 5.5f);      // (a NaN stays one, and with it the result)
+    float pos;
+    asm("v_max_f32 %0, 0, %1" : "=v"(pos) : "v"(h));        // (as fmaxf it would get a second instruction for signalling NaNs)
     float q = -0.000514221328f;
     q = fmaf(q, z, 0.00736901748f);
     q = fmaf(q, z, -0.0525218223f);
@@ -214,12 +214,13 @@ __device__ __forceinline__ float act_fwd_fast(float h, int act) {
     return fmaf(-z, __builtin_amdgcn_exp2f(q), pos);
 }
 // gelu'(h) = Phi(h) + h phi(h) as 0.5 + hc*R(hc^2): it is odd about 1/2 as well, so one degree-10 minimax fit of the whole
-// derivative takes the place of Phi and an exponential (13 VALU slots instead of 17 in an epilogue that they bound).  R is
+// derivative takes the place of Phi and an exponential (14 VALU slots instead of 18 in an epilogue that they bound).  R is
 // expanded about the middle of its range, where float32 Horner steps cancel least: |error| < 4.3e-6 in float32 for
 // |h| <= 4.2 (Phi + h phi as it was taken before: 1.1e-5); beyond, the limits 1 and 0 to 2.4e-4, as before.
 __device__ __forceinline__ float act_grad_fast(float h, int act) {
     if (act == EVOMOE_RELU) return h > 0.f ? 1.f : 0.f;
-    const float hc = __builtin_amdgcn_fmed3f(h, -4.2f, 4.2f);
+    // (a NaN stays one: v_med3_f32, an instruction instead of two, would take it for -4.2)
+    const float hc = __builtin_elementwise_maximum(__builtin_elementwise_minimum(h, 4.2f), -4.2f);
     const float v = fmaf(hc, hc, -8.82f);
     float r = 1.802185568e-12f;
     r = fmaf(r, v, -4.374921728e-11f);

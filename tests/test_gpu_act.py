@@ -1,4 +1,4 @@
-"""The bf16 expert FFN's activation functions in both epilogues (256x256 tiles of eight waves, small tiles)."""
+"""The expert FFN's activation functions, bf16 in both epilogues (256x256 tiles of eight waves, small tiles)."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -46,3 +46,45 @@ def test_gelu_is_off_by_no_more_than_its_polynomial(P, E, F, tile):
         more = (layer.A[at].double() - want).abs() - half
         assert (more <= 1.2e-6).all(), (row, more.max().item(), h.flatten()[more.argmax()].item())
     layer.ctx.close()
+
+
+@pytest.mark.parametrize("act", ["gelu", "relu"])
+@pytest.mark.parametrize("P,E,F,tile", SIZES)
+def test_nan_stays_nan(P, E, F, tile, act):
+    """A NaN in one bias: A has one exactly where H has; dH of gelu too (the derivative of ReLU is taken as 0 there)."""
+    import torch
+    b1 = torch.randn(E, F, generator=torch.Generator("cuda").manual_seed(4), device="cuda")
+    b1[E - 2, 9] = float("nan")
+    layer = Layer(P, E, F, tile, act, b1)
+    B, nan = layer.B, torch.zeros(P, F, dtype=torch.bool, device="cuda")
+    nan[int(layer.offs[E - 2]):int(layer.offs[E - 1]), 9] = True
+    assert torch.equal(layer.H.isnan(), nan)
+    assert torch.equal(layer.A.isnan(), nan)
+    db1 = torch.empty(E, F, device="cuda")
+    ws = torch.empty(B.evomoe_workspace_bytes(layer.shape), dtype=torch.uint8, device="cuda")
+    B.evomoe_expert_ffn_bwd(layer.ctx, layer.shape, layer.dO, layer.H, layer.A, layer.x, None, layer.offs, layer.W1, layer.W2, None,
+                            None, None, db1, None, None, layer.dXp, False, ws)
+    torch.cuda.synchronize()
+    if act == "gelu":
+        assert torch.equal(ws[:P * F * 2].view(torch.bfloat16).view(P, F).isnan(), nan)
+        assert torch.equal(db1.isnan(), b1.isnan())
+    layer.ctx.close()
+
+
+@pytest.mark.parametrize("act", ["gelu", "relu"])
+def test_nan_stays_nan_in_float32(act):
+    import torch
+    import gpu_harness as h
+    B, P, d, E, F = h.B, 100, 64, 2, 64
+    b1 = torch.zeros(E, F, device="cuda")
+    b1[1, 9] = float("nan")
+    x, W1, W2 = torch.ones(P, d, device="cuda"), torch.ones(E, F, d, device="cuda"), torch.ones(E, d, F, device="cuda")
+    H, A, O = torch.empty(P, F, device="cuda"), torch.empty(P, F, device="cuda"), torch.empty(P, d, device="cuda")
+    ctx = B.Context()
+    B.evomoe_expert_ffn(ctx, B.make_shape(P, d, E, F, "f32", act, P), x, None, torch.tensor([0, 33, P], dtype=torch.int32, device="cuda"),
+                        W1, b1, W2, None, H, A, O)
+    torch.cuda.synchronize()
+    want = torch.zeros_like(H, dtype=torch.bool)
+    want[33:, 9] = True
+    assert torch.equal(H.isnan(), want) and torch.equal(A.isnan(), want)
+    ctx.close()
