@@ -928,12 +928,12 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, i
                         const float h[8] = {lo_bf16(hw.x), hi_bf16(hw.x), lo_bf16(hw.y), hi_bf16(hw.y),
                                             lo_bf16(hw.z), hi_bf16(hw.z), lo_bf16(hw.w), hi_bf16(hw.w)};
                         const float sc = scaled ? rsc[f % DEPTH] : 1.f;
-                        const float rv = rq < n ? 1.f : 0.f;              // rows beyond the tile repeat its last row
+                        const bool there = rq < n;      // (beyond the tile: its last row's products, which an infinity may be among)
 #pragma unroll
                         for (int q = 0; q < 8; ++q) v[q] *= sc * act_grad_fast(h[q], ACT);
 #pragma unroll
                         for (int q = 0; q < 8; ++q) {
-                            cs[q] = fmaf(v[q], rv, cs[q]);
+                            cs[q] += there ? v[q] : 0.f;
                             asm volatile("" : "+v"(cs[q]));     // (added up at the end, where they are used, all the v's would be kept)
                         }
                     }
@@ -1060,21 +1060,23 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, i
 #pragma unroll
                             for (int q = 0; q < 8; ++q) v[q] *= sc * act_grad_fast(h[q], EVOMOE_GELU_ERF);
                         }
-                        const float rv = trow < rows ? 1.f : 0.f;     // rows beyond the tile repeat its last row
+                        const bool there = trow < rows;     // rows beyond the tile repeat its last row
+                        float s[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) s[q] = there ? v[q] : 0.f;
                         if (SUM_REGS) {
 #pragma unroll
-                            for (int q = 0; q < 8; ++q) cs[q] = fmaf(v[q], rv, cs[q]);
+                            for (int q = 0; q < 8; ++q) cs[q] += s[q];
                         } else if (SUM_HALVES) {
 #pragma unroll
                             for (int q = 0; q < 4; ++q) {
-                                const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[q] * rv),
-                                                                                __float_as_uint(v[q + 4] * rv), false, false);
+                                const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(s[q]), __float_as_uint(s[q + 4]), false, false);
                                 cs[q] = (cs[q] + __uint_as_float(w[0])) + __uint_as_float(w[1]);
                             }
                         } else if (p.colpart) {
                             float* keep = stg + lr * G::EPI_LD + lc;
-                            *reinterpret_cast<f32x4*>(keep) = f32x4{v[0] * rv, v[1] * rv, v[2] * rv, v[3] * rv};
-                            *reinterpret_cast<f32x4*>(keep + 4) = f32x4{v[4] * rv, v[5] * rv, v[6] * rv, v[7] * rv};
+                            *reinterpret_cast<f32x4*>(keep) = f32x4{s[0], s[1], s[2], s[3]};
+                            *reinterpret_cast<f32x4*>(keep + 4) = f32x4{s[4], s[5], s[6], s[7]};
                         }
                     }
                     if (ok) store_out(p.out1 + grow * p.N + col_c, v);

@@ -127,3 +127,33 @@ def test_infinite_operands_stay_infinite_in_partial_slabs(T, d, E, F, rows):
     backward(A=Ai, x=x)
     same(dW2[0], f64(dO[:n]).T @ f64(Ai[:n]), "dW2")
     same(dW1[0], f64(dH).T @ f64(x[tok]), "dW1")
+
+
+# rows of the first expert (the others have none), d, E, F, capacity, tile of dH: a tile's last rows repeat the last one there is
+@pytest.mark.parametrize("scaled", [False, True])
+@pytest.mark.parametrize("P,d,E,F,rows,tile", [(45, 96, 1, 160, 45, "64x64/4"), (1900, 776, 16, 1544, 1900, "64x128/4"),
+                                               (4095, 512, 1, 4104, 4095, "128x128/4"), (300, 72, 1, 504, 40000, "128x256/4"),
+                                               (45, 96, 1, 160, 100000, "256x256/8")])
+def test_infinite_last_row_does_not_become_nan_in_the_bias_gradient(P, d, E, F, rows, tile, scaled):
+    import torch
+    import gpu_harness as h
+    B, inf = h.B, float("inf")
+    shape = B.make_shape(rows, d, E, F, "bf16", "gelu", rows)
+    assert ffn_tiles(shape, num_cu=torch.cuda.get_device_properties(0).multi_processor_count)[2] == tile
+    g = torch.Generator("cuda").manual_seed(P)
+    rnd = lambda *s: torch.rand(*s, generator=g, device="cuda").bfloat16() + 0.5
+    offs = torch.tensor([0] + [P] * E, dtype=torch.int32, device="cuda")
+    dO, x, W1, W2 = rnd(rows, d), rnd(rows, d), rnd(E, F, d), rnd(E, d, F)
+    H = torch.zeros(rows, F, dtype=torch.bfloat16, device="cuda")          # act'(0) = 1/2
+    tok = torch.arange(rows, dtype=torch.int32, device="cuda")
+    gate = torch.full((rows,), 0.25, device="cuda")
+    dO[P - 1, 3] = inf
+    db1 = torch.empty(E, F, device="cuda")
+    dXp = torch.empty(rows, d, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(B.evomoe_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    ctx = B.Context()
+    B.evomoe_expert_ffn_bwd(ctx, shape, dO, H, H, x, tok, offs, W1, W2, dO if scaled else None, gate if scaled else None, None, db1,
+                            None, None, dXp, False, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(db1[0], torch.full_like(db1[0], inf)) and not db1[1:].any()
+    ctx.close()
