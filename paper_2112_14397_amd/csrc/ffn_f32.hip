@@ -5,9 +5,13 @@
 //   NN  C[r,n] = sum_k A[r,k]       * W_g[k,n]          dH = dO W2,  dXp = dH W1
 //   TN  C_g[m,n] = sum_{r in g} L[r,m] * R[rrow(r),n]   weight gradients (contraction over the ragged rows)
 //
-// Every float32 value is taken apart into three bf16 values whose sum it is, and a product a * b into the six of the nine
-// products of their terms that are above 2^-24 of it: bf16 MFMAs run at sixteen times the rate of float32 ones, so six of them
-// take 0.38 of the time.  The products are exact and each of four partial sums per output has one rounding per 16 k's (the
+// Every float32 value is taken apart into three bf16 values whose sum it is, and a product a * b into the six largest of the
+// nine products of their terms: bf16 MFMAs run at sixteen times the rate of float32 ones, so six of them take 0.38 of the time.
+// Left out are mid * lo and lo * mid, up to 2^-23 of the product each (the first term is cut off, so the second is up to 2^-7 of
+// the value, the third 2^-16), and lo * lo.  A single product is therefore less exact than in float32, a sum more, as below;
+// contractions of up to 16 k's take mid * lo and lo * mid too.  Relative rms error by the number of products (N(0,1) operands;
+// float32 chains of eight / six products / eight): 1 2.5e-8 / 3.4e-8 / 2.5e-8, 2 3.1e-8 / 3.4e-8 / 2.6e-8, 3 3.6e-8 / 3.5e-8 /
+// 2.6e-8, 16 6.0e-8 / 3.8e-8 / 3.1e-8, 17 6.4e-8 / 4.6e-8 / 4.0e-8.  The products are exact and each of four partial sums per output has one rounding per 16 k's (the
 // small products have a sum of their own), where float32 MFMAs round for every k: relative rms error against float64 at 5632
 // pairs, d = 256, E = 8, F = 1024 (float32 MFMAs / here; smaller at every size measured, 64 to 2048 k's): H 1.5e-7 / 7.2e-8,
 // O 2.9e-7 / 1.0e-7, dH 1.6e-7 / 8.2e-8, dXp 2.9e-7 / 1.1e-7, dW 2.4e-7 / 9.7e-8.  With one sum for all six products the
@@ -398,6 +402,28 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
                     spread();
                     products(0, TM - 1);
                     products(TM - 1, TM - 1);
+                }
+                if (kend - kbeg <= 16) {
+                    // block-uniform: mid * lo and lo * mid, from operands read and taken apart again, so that longer contractions
+                    // keep nothing for it
+                    asm volatile("" ::: "memory");
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        read(sa, A_KC, i, va);
+                        read(sb, B_KC, i, vb);
+                    }
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        split8(va[i], fa[0][i], fa[1][i], fa[2][i]);
+                        split8(vb[i], fb[0][i], fb[1][i], fb[2][i]);
+                    }
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TM; ++j) {
+                            small[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1][i], fb[2][j], small[i][j], 0, 0, 0);
+                            small[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[2][i], fb[1][j], small[i][j], 0, 0, 0);
+                        }
                 }
             }
         }

@@ -57,3 +57,36 @@ def test_f32_largest_values_stay_finite():
     want = x[b.pair_token[:P].long()].double() @ p.W1[0].double().T
     assert torch.isfinite(H).all()
     assert ((H[:P].double() - want).abs() <= 2e-7 * want.abs()).all()
+
+
+@pytest.mark.parametrize("d,F,tile", [(64, 128, "32x32/4"), (516, 1028, "64x64/4")])
+def test_f32_weight_gradients_of_a_few_rows(d, F, tile):
+    """Experts with 1 to 17 rows.  n float32 products added one behind the other in chains of eight have a relative rms error of
+    2.52e-8 sqrt((n + 1) / 2), n <= 8, of sqrt((8 + 1) / 2 + 1) above: nothing may be above that (8 % for the
+    samples: the mantissas of a row of dO and one of A are behind all products of a single row)."""
+    import torch
+    import gpu_harness as h
+    from helpers import ffn_tiles
+    B, counts = h.B, [1, 2, 3, 0, 5, 8, 16, 17]
+    E, P = len(counts), sum(counts)
+    offs = [sum(counts[:e]) for e in range(E + 1)]
+    shape = B.make_shape(P, d, E, F, "f32", "relu", P)
+    assert ffn_tiles(shape, num_cu=torch.cuda.get_device_properties(0).multi_processor_count)[4] == tile
+    g = torch.Generator("cuda").manual_seed(d)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    dO, x, A, W1, W2 = rnd(P, d), rnd(P, d), rnd(P, F), rnd(E, F, d), rnd(E, d, F)
+    dW1, dW2, dXp = torch.empty(E, F, d, device="cuda"), torch.empty(E, d, F, device="cuda"), torch.empty(P, d, device="cuda")
+    ws = torch.empty(B.evomoe_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    tok = torch.randperm(P, generator=g, device="cuda").int()
+    ctx = B.Context()
+    B.evomoe_expert_ffn_bwd(ctx, shape, dO, torch.ones_like(A), A, x, tok, torch.tensor(offs, dtype=torch.int32, device="cuda"), W1, W2,
+                            None, None, dW1, None, dW2, None, dXp, False, ws)
+    torch.cuda.synchronize()
+    dH = ws[:P * F * 4].view(torch.float32).view(P, F).double()
+    for e, n in enumerate(counts):
+        r = slice(offs[e], offs[e + 1])
+        for what, got, want in (("dW2", dW2[e], dO[r].double().T @ A[r].double()), ("dW1", dW1[e], dH[r].T @ x[tok[r].long()].double())):
+            err = ((got.double() - want).square().sum() / want.square().sum().clamp(min=1e-300)).sqrt().item()
+            print(what, n, f"{err:.3g}")
+            assert err <= 1.08 * 2.52e-8 * (((min(n, 8) + 1) / 2 + (n > 8)) ** 0.5), (what, n, err)
+    ctx.close()
