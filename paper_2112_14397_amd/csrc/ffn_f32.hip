@@ -435,10 +435,10 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
         const int64_t origin = LAYOUT == L_TN ? ((int64_t)t.g * p.M + t.m0) * p.N : (int64_t)t.row0 * p.N;
         const float* reads = EPI == E_ACTGRAD ? p.Hin + origin : EPI == E_WGRAD && accumulate ? p.out1 + origin : nullptr;
         float* red = reinterpret_cast<float*>(smem + (first ^ 1) * STAGE);      // the stage that the next tile does not start in
-        // behind an infinite or NaN operand the smaller products are NaN; the large ones have what float32 products would give
+        // Behind an infinite or NaN operand the smaller products are NaN; the large ones have what float32 products would give.
+        // (Asked of the small sum: the sum of both overflows where a float32 sum does.)
         auto both = [](float large, float small) {
-            const float v = large + small;
-            return fabsf(v) <= 3.402823466e38f ? v : large;
+            return fabsf(small) <= 3.402823466e38f ? large + small : large;
         };
         auto row_of = [](int i, int r) { return A_PAIR ? 2 * r + i : i * 32 + r; };     // of row r of pass i
         constexpr int NO = B / 32;                      // vectors of four outputs per thread and pass

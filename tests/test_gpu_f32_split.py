@@ -90,3 +90,33 @@ def test_f32_weight_gradients_of_a_few_rows(d, F, tile):
             print(what, n, f"{err:.3g}")
             assert err <= 1.08 * 2.52e-8 * (((min(n, 8) + 1) / 2 + (n > 8)) ** 0.5), (what, n, err)
     ctx.close()
+
+
+def _ffn(offsets, d, F, x, W1):
+    """H of a float32 layer without biases."""
+    import torch
+    import gpu_harness as h
+    B, E, P = h.B, len(offsets) - 1, offsets[-1]
+    shape = B.make_shape(P, d, E, F, "f32", "relu", P)
+    offs = torch.tensor(offsets, dtype=torch.int32, device="cuda")
+    H, A, O = torch.empty(P, F, device="cuda"), torch.empty(P, F, device="cuda"), torch.empty(P, d, device="cuda")
+    ctx = B.Context()
+    B.evomoe_expert_ffn(ctx, shape, x, None, offs, W1, None, torch.zeros(E, d, F, device="cuda"), None, H, A, O)
+    torch.cuda.synchronize()
+    ctx.close()
+    return H
+
+
+@pytest.mark.parametrize("d,F", [(64, 64), (256, 2048)])
+def test_f32_sums_overflow_where_float32_does(d, F):
+    """Products on either side of the largest float32 value, 2^128 - 2^104, by less than the smaller terms of the operands."""
+    import torch
+    x, W1 = torch.zeros(40, d, device="cuda"), torch.zeros(1, F, d, device="cuda")
+    x[:20, 17], x[20:, 17] = 1.99 * 2.0 ** 63, -1.99 * 2.0 ** 63
+    W1[0, :, 17] = torch.linspace(1.0, 1.02, F, device="cuda") * 2.0 ** 64
+    H = _ffn([0, 40], d, F, x, W1)
+    want = (x.double() @ W1[0].double().T).float()
+    assert want.isinf().any() and want.isfinite().any()
+    assert torch.equal(H.isinf(), want.isinf()) and torch.equal(H.sign(), want.sign())
+    ok = want.isfinite()
+    assert ((H - want).abs()[ok] <= 2e-7 * want.abs()[ok]).all()
