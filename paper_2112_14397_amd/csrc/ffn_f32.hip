@@ -144,13 +144,16 @@ template <int BM> __device__ __forceinline__ Offsets scan_offsets(const int32_t*
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 // The three bf16 terms of eight float32 values: hi (cut off, so that no finite value becomes infinite) + mid (rounded) + lo
-// (what is left, eight bits at most) is the value itself.  An infinity or a NaN gives NaN terms behind itself.
+// (what is left, eight bits at most) is the value itself.  An infinity or a NaN gives NaN terms behind itself.  (A signalling NaN
+// is made a quiet one first: cut off, one with a payload in its low half only would be an infinity.  That takes 3 % of the step
+// below.)
 __device__ __forceinline__ void split8(const float* v, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
     u32x4 h, m, l;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const uint32_t b0 = __float_as_uint(v[2 * i]), b1 = __float_as_uint(v[2 * i + 1]);
-        const float r0 = v[2 * i] - __uint_as_float(b0 & 0xffff0000u), r1 = v[2 * i + 1] - __uint_as_float(b1 & 0xffff0000u);
+        const float v0 = __builtin_canonicalizef(v[2 * i]), v1 = __builtin_canonicalizef(v[2 * i + 1]);
+        const uint32_t b0 = __float_as_uint(v0), b1 = __float_as_uint(v1);
+        const float r0 = v0 - __uint_as_float(b0 & 0xffff0000u), r1 = v1 - __uint_as_float(b1 & 0xffff0000u);
         h[i] = __builtin_amdgcn_perm(b1, b0, 0x07060302);
         asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(m[i]) : "v"(r0), "v"(r1));      // (seen through, it would be made twice)
         l[i] = pack_bf16x2(r0 - lo_bf16(m[i]), r1 - hi_bf16(m[i]));
@@ -381,12 +384,12 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
                         c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[TA[u]][i], fb[TB[u]][j], c, 0, 0, 0);
                     }
                 };
-                // the next fragment is split under the products of the ones before it: eight VALU slots per MFMA
+                // the next fragment is split under the products of the ones before it: nine VALU slots per MFMA
                 auto spread = [&]() {
 #pragma unroll
                     for (int u = 0; u < 6; ++u) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 9, 0);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 };

@@ -120,3 +120,18 @@ def test_f32_sums_overflow_where_float32_does(d, F):
     assert torch.equal(H.isinf(), want.isinf()) and torch.equal(H.sign(), want.sign())
     ok = want.isfinite()
     assert ((H - want).abs()[ok] <= 2e-7 * want.abs()[ok]).all()
+
+
+@pytest.mark.parametrize("bits", [0x7f800001, 0x7f80ffff, 0x7fc00000, 0xff800100 - 2 ** 32, 0x7fffffff])
+@pytest.mark.parametrize("d,F", [(64, 64), (256, 2048)])
+def test_f32_nans_stay_nans(bits, d, F):
+    """Also those whose payload a bf16 value does not have."""
+    import torch
+    rnd = lambda *s: torch.randn(*s, generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+    x, W1 = rnd(40, d), rnd(1, F, d)
+    x.view(torch.int32)[7, d - 1] = bits
+    W1.view(torch.int32)[0, 5, 3] = bits
+    H = _ffn([0, 40], d, F, x, W1)
+    want = torch.zeros_like(H, dtype=torch.bool)
+    want[7], want[:, 5] = True, True
+    assert torch.equal(H.isnan(), want) and H[~want].isfinite().all()
