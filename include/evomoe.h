@@ -39,6 +39,8 @@
  *    64-bit).  The bf16 expert FFN (forward and backward) additionally needs
  *    d >= 64, F >= 64, T below 2^24, and T*max(d,F)*2 and d*F*2 below 2^32 bytes
  *    (inside a tile its kernels add 32-bit byte offsets to a 64-bit base).
+ *  - The float32 expert FFN multiplies on the bf16 matrix cores, every value as three bf16 terms, at float32
+ *    accuracy or better.  Values below 2^-110 (7.7e-34) are off by up to 2^-134 there.
  */
 #ifndef EVOMOE_H
 #define EVOMOE_H

@@ -5,7 +5,7 @@
 //   NN  C[r,n] = sum_k A[r,k]       * W_g[k,n]          dH = dO W2,  dXp = dH W1
 //   TN  C_g[m,n] = sum_{r in g} L[r,m] * R[rrow(r),n]   weight gradients (contraction over the ragged rows)
 //
-// Every float32 value is taken apart into three bf16 values whose sum it is, and a product a * b into the six largest of the
+// Every float32 value is taken apart into three bf16 values whose sum it is (of very small ones almost: below), and a product a * b into the six largest of the
 // nine products of their terms: bf16 MFMAs run at sixteen times the rate of float32 ones, so six of them take 0.38 of the time.
 // Left out are mid * lo and lo * mid, up to 2^-23 of the product each (the first term is cut off, so the second is up to 2^-7 of
 // the value, the third 2^-16), and lo * lo.  A single product is therefore less exact than in float32, a sum more, as below;
@@ -16,6 +16,12 @@
 // pairs, d = 256, E = 8, F = 1024 (float32 MFMAs / here; smaller at every size measured, 64 to 2048 k's): H 1.5e-7 / 7.2e-8,
 // O 2.9e-7 / 1.0e-7, dH 1.6e-7 / 8.2e-8, dXp 2.9e-7 / 1.1e-7, dW 2.4e-7 / 9.7e-8.  With one sum for all six products the
 // contractions of 64 k's had larger errors than float32 MFMAs (H 9.5e-8 against 8.8e-8).
+//
+// Range: the terms of values below 2^-110 (7.7e-34) reach below the smallest bf16 subnormal, 2^-133, which the matrix cores do take:
+// each such value is off by up to 2^-134, that is by 2^-24 of itself at 2^-110 and by 2^-8 at the smallest normal float32 value
+// (relative rms error of H with all x between 2^-112 and 2^-111, -116 and -115, -122 and -121: 1.1e-7, 1.4e-6, 9.3e-5; float32
+// MFMAs 8.5e-8).  In a sum with larger products that is nothing; where whole tensors are that small, scale the loss.  Between there and
+// the largest float32 value everything is as above, infinities and NaNs give what float32 products give.
 //
 // What bounds it: a 64x64 tile's slab of 64 k's takes 768 clocks of the matrix pipes, about as many of the VALU for taking the
 // operands apart, and 32 KB from the L2; two blocks per CU overlap these in part.  The operands go to the LDS as they are, by
@@ -144,7 +150,7 @@ template <int BM> __device__ __forceinline__ Offsets scan_offsets(const int32_t*
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 // The three bf16 terms of eight float32 values: hi (cut off, so that no finite value becomes infinite) + mid (rounded) + lo
-// (what is left, eight bits at most) is the value itself.  An infinity or a NaN gives NaN terms behind itself.  (A signalling NaN
+// (what is left, eight bits at most) is the value itself, from 2^-110 on (above).  An infinity or a NaN gives NaN terms behind itself.  (A signalling NaN
 // is made a quiet one first: cut off, one with a payload in its low half only would be an infinity.  That takes 3 % of the step
 // below.)
 __device__ __forceinline__ void split8(const float* v, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
