@@ -145,14 +145,13 @@ __device__ __forceinline__ void colsum_tile(const ColumnSums& q, int b, int gx, 
         for (int e = 0; e < 8; ++e) red[(rl * CL + cl) * 8 + e] = acc[e];
     }
     __syncthreads();
-    if (on && rl == 0) {
-        float* dst = q.part + ((size_t)range * E + g) * q.N + n;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float sum = 0.f;
-            for (int l = 0; l < RL; ++l) sum += red[(l * CL + cl) * 8 + e];
-            dst[e] = sum;
-        }
+    const int first = b % gx * CL * 8, columns = min(CL * 8, q.N - first);
+    float* dst = q.part + ((size_t)range * E + g) * q.N + first;
+    for (int c = threadIdx.x; c < columns; c += blockDim.x) {     // (by 256 / RL threads alone, eight columns each, it took most of
+        float sum = 0.f;                                          // a tile's time for narrow layers, where RL is large)
+#pragma unroll 4
+        for (int l = 0; l < RL; ++l) sum += red[l * CL * 8 + c];
+        dst[c] = sum;
     }
     __syncthreads();
 }
