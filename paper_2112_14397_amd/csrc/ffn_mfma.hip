@@ -104,17 +104,21 @@ __device__ __forceinline__ void bias_final_tile(const BiasFinal& q, int b, const
 // Column sums of dO over every expert's rows (the first pass of db2): an expert's rows are cut into sum_ranges() ranges, 64 rows
 // each as long as 32 ranges are enough; a tile leaves part[range][expert][column] for 2048 columns at most.
 // Up to 32 MB of dO the tiles run behind dXp's, on the compute units first that have no dXp tile in the last round; beyond, in a
-// launch of their own, which has more waves in flight.  dXp and the sums, us, behind it / on their own: 777 tokens, d = 136,
-// two micro-batches 22 / 33; 8192 pairs of d = 768 59 / 67, 16 223 95 / 103, 22 073 of d = 512 80 / 82, 58 330 of d = 768
-// 283 / 272, 87 690 of d = 1024 710 / 678.
+// launch of their own.  dXp and the sums, us, behind it / as two launches (the gap between them not counted): 1000 pairs of d = 136
+// 8.6 / 14.0, 24 787 of d = 144 19 / 22, 8192 of d = 768, E = 64 97 / 104, 16 223 of d = 768, E = 16 94 / 103, 20 000 of d = 768, E = 32
+// 122 / 124, 30 000 of d = 512, E = 8 84 / 81.  Above the line it depends on how many units idle: E = 16, d = 768 at 41, 56, 80 and
+// 90 MB 159 / 167, 176 / 190, 259 / 276, 276 / 278, but E = 32 at 58 MB, where dXp's last round is full, 208 / 192, and 87 690 pairs of
+// d = 1024 710 / 678.
 struct ColumnSums {
     const bf16_t* M;  int N;            // dO [P,N]
     float* part;                        // [kColsumSplit][E][N]
     int wanted;
+    int64_t tile_ns;                    // behind dXp: what a tile takes
 };
 // Tile b: column block fastest, then expert, then range.  The first 256 threads of a block: CL column lanes x 16 bytes are
 // contiguous in a row, RL = 256 / CL row lanes take alternate rows, sixteen rows of loads in flight per thread (few waves share a
-// unit behind dXp's tiles: with four, dXp and the sums took 314 us instead of 278); f32 sums, row lanes added in order.
+// unit behind dXp's tiles: with four, dXp and the sums took 314 us instead of 278 at 58 330 pairs); f32 sums, row lanes added in
+// order.
 __device__ __forceinline__ void colsum_tile(const ColumnSums& q, int b, int gx, int CL, const int* offs, int E, float* red) {
     const int RL = 256 / CL, g = b / gx % E, range = b / (gx * E);
     const int r0 = offs[g], r1 = offs[g + 1], ranges = sum_ranges(r1 - r0);
@@ -1158,9 +1162,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, i
         const int total = tstart[q0.E] * ((q0.N + BN - 1) / BN), grid = gridDim.x, parts = seq_step == grid ? 1 : 8;
         const int busy = (total + parts - 1) / parts % seq_step, idle_each = busy ? seq_step - busy : 0, idle = idle_each * parts;
         const int place = parts == 1 ? vblock : (int)(blockIdx.x >> 3), first = (parts == 1 ? 0 : (int)(blockIdx.x & 7)) * idle_each + place - busy;
-        const int64_t tile_ns = (int64_t)(9000 + 20 * q0.K) * (BM * BN) / 65536;
-        const int64_t sum_ns = 1500 + (int64_t)offs[q0.E] * qs.N * 2 / n / 40;
-        const int fill = (int)min((int64_t)n, idle * (tile_ns / sum_ns));
+        // A sum takes 2 us and a ns for 22 bytes (twelve launches of d = 72 to 2048; us, measured / so: 19 KB 3.1 / 2.9, 33 KB 2.9 / 3.5,
+        // 92 KB 5.9 / 6.2, 240 KB 12.9 / 12.9), a tile what the choice of tiles takes a round for.
+        const int64_t sum_ns = 2000 + (int64_t)offs[q0.E] * qs.N * 2 / n / 22;
+        const int fill = (int)min((int64_t)n, idle * (qs.tile_ns / sum_ns));
         __syncthreads();
         if (idle && place >= busy)
             for (int b = first; b < fill; b += idle) colsum_tile(qs, b, gx, CL, offs, q0.E, reinterpret_cast<float*>(smem));
@@ -1291,7 +1296,9 @@ hipError_t launch_best(const Ctx& c, const evomoe_shape& s, GemmArgs& a, const C
     auto run = [&](auto cfg) {
         using Cfg = decltype(cfg);
         a.col_group = col_group_for<Cfg>(a.N, a.K);
-        err = launch_gemm<LAYOUT, EPI, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(a.N), 0, other_tiles, extra);
+        auto with = extra;
+        if constexpr (EPI == E_NONE) with.tile_ns = (int64_t)(1000 * (ch.t[best].per_round + ch.t[best].per_k * a.K / 1024.0));
+        err = launch_gemm<LAYOUT, EPI, Cfg>(c, a, row_tiles<Cfg>(s) * ctiles<Cfg>(a.N), 0, other_tiles, with);
     };
     int n = 0;
     (void)((n++ == best ? (run(Cfgs{}), true) : false) || ...);
@@ -1418,7 +1425,7 @@ hipError_t mfma_ffn_bwd(const Ctx& c, const evomoe_shape& s, const void* dO, con
         a.colpart = nullptr; a.a_rows = nullptr; a.row_scale = nullptr;
         if (err != hipSuccess) return err;
     }
-    ColumnSums sums{(const bf16_t*)dO, s.d, scratch, db2 != nullptr};
+    ColumnSums sums{(const bf16_t*)dO, s.d, scratch, db2 != nullptr, 0};
     const int sum_tiles = kColsumSplit * s.E * ((s.d + 2047) / 2048);
     if (sums.wanted && expected_pairs(c, s) * s.d * 2 > 32000000) {
         ProfScope ps(c, EVOMOE_K_FFN_BWD_DB);
