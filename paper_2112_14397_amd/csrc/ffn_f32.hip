@@ -182,6 +182,14 @@ __device__ __forceinline__ void all_landed() {
     asm volatile("s_barrier" ::: "memory");
 }
 
+// Weight gradients: an expert of at most so many rows is not worked in 64x64 tiles that go through the LDS, where the start and the end
+// of a tile are most of its time with the two blocks that fit a CU, but by single waves (below), where that makes work for half of
+// the waves.  us, float32 MFMAs / tiles / here: E = 64, d = 196, F = 880, 33 pairs 41 / 67 / 31; d = 280, F = 768, 1231 pairs 54 / 79 /
+// 44, 2500 70 / 77 / 57 (5000, experts of 78 rows, 93 / 104 / 105); E = 16, d = 512, F = 2048, 200 pairs 58 / 79 / 37; E = 16, d = 256,
+// F = 512, 60 pairs 14 / 19 / 12, 600 17 / 18 / 17; E = 4, d = 456, F = 1096, 64 pairs 19 / 20 / 22; E = 1, d = 512, F = 2048, 10 pairs 10 /
+// 12 / 12.  E = 16, d = 228, F = 464, where a third of the experts have so few of 1021 pairs, 16 / 17 / 20.  With a line at 64 rows the
+// experts of 78 rows took 109.
+constexpr int kFewRows = 48;
 // Blocks per CU, for the registers, the LDS and the grid.
 template <int B> constexpr int blocks_per_cu() { return B == 64 ? 2 : 4; }
 
@@ -209,7 +217,17 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
 
     // Consecutive tiles share operand panels, and blocks are dealt round-robin to the 8 XCDs: each XCD walks one
     // contiguous eighth of the tiles, so that its L2 sees the panels and no XCD gets a round more than another.
-    const int total = LAYOUT == L_TN ? tiles_all : row_tiles * ((q.p[0].N + BN - 1) / BN);
+    // TN: the tiles are those of the experts with more than kFewRows rows; lane e knows expert e's place among them, or among the others
+    const int wanted0 = tiles0 / E, wanted1 = tiles_all / E - wanted0;      // TN: an expert's tiles of either problem
+    const int units0 = wanted0 ? ((q.p[0].M + 31) / 32) * ((q.p[0].N + BN - 1) / BN) : 0,      // TN: what few rows are worked in
+              units1 = wanted1 ? ((q.p[1].M + 31) / 32) * ((q.p[1].N + BN - 1) / BN) : 0;
+    uint64_t few = LAYOUT == L_TN && TM == 2 ? __ballot(lane < E && off.count <= kFewRows) : 0;
+    if (__popcll(few) * (units0 + units1) < 2 * (int)gridDim.x) few = 0;
+    const bool mine_few = few >> lane & 1;
+    const uint64_t many = __ballot(lane < E && !mine_few);
+    const int place = __popcll((mine_few ? few : many) & (((uint64_t)1 << lane) - 1));
+    if (LAYOUT == L_TN) tiles0 = wanted0 * __popcll(many);
+    const int total = LAYOUT == L_TN ? tiles0 + wanted1 * __popcll(many) : row_tiles * ((q.p[0].N + BN - 1) / BN);
     int tile = blockIdx.x, tile_end = total, step = gridDim.x;
     if ((gridDim.x & 7) == 0) {
         const int x = blockIdx.x & 7;
@@ -225,8 +243,8 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
         const int nct = (p.N + BN - 1) / BN;
         if (LAYOUT == L_TN) {
             const int i = t.second ? tile - tiles0 : tile, nmt = (p.M + BM - 1) / BM;
-            t.g = i / (nmt * nct);
-            const int rem = i - t.g * nmt * nct;
+            const int nth = i / (nmt * nct), rem = i - nth * nmt * nct;
+            t.g = __ffsll((unsigned long long)__ballot(lane < E && !mine_few && place == nth)) - 1;
             t.m0 = rem / nct * BM;
             t.n0 = rem % nct * BN;
             t.kbeg = __builtin_amdgcn_readlane(off.begin, t.g);
@@ -316,6 +334,11 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
         }
     };
 
+    // Behind an infinite or NaN operand the smaller products are NaN; the large ones have what float32 products would give.
+    // (Asked of the small sum: the sum of both overflows where a float32 sum does.)
+    auto both = [](float large, float small) {
+        return fabsf(small) <= 3.402823466e38f ? large + small : large;
+    };
     int first = 0;                                      // stage of the tile's first slab
     auto start = [&](const Tile& t) {
         aim(t);
@@ -444,11 +467,6 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
         const int64_t origin = LAYOUT == L_TN ? ((int64_t)t.g * p.M + t.m0) * p.N : (int64_t)t.row0 * p.N;
         const float* reads = EPI == E_ACTGRAD ? p.Hin + origin : EPI == E_WGRAD && accumulate ? p.out1 + origin : nullptr;
         float* red = reinterpret_cast<float*>(smem + (first ^ 1) * STAGE);      // the stage that the next tile does not start in
-        // Behind an infinite or NaN operand the smaller products are NaN; the large ones have what float32 products would give.
-        // (Asked of the small sum: the sum of both overflows where a float32 sum does.)
-        auto both = [](float large, float small) {
-            return fabsf(small) <= 3.402823466e38f ? large + small : large;
-        };
         auto row_of = [](int i, int r) { return A_PAIR ? 2 * r + i : i * 32 + r; };     // of row r of pass i
         constexpr int NO = B / 32;                      // vectors of four outputs per thread and pass
 #pragma unroll
@@ -486,6 +504,97 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
                 *reinterpret_cast<f32x4*>(p.out1 + origin + (int64_t)tr * p.N + n) = v;
                 if (EPI == E_HA) *reinterpret_cast<f32x4*>(p.out2 + origin + (int64_t)tr * p.N + n) = a;
             }
+        }
+    }
+    if constexpr (LAYOUT == L_TN && TM == 2) {
+        // Experts with few rows: a wave takes 32 rows by 64 columns of a gradient by itself, its operands straight from memory.  The same
+        // products in the same order as in a tile, whose waves have 16 k's each and whose sums are added in their order.
+        const int experts = __popcll(few), all = experts * (units0 + units1);
+        const int block = (gridDim.x & 7) == 0 ? (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+        for (int u = block * 4 + wave; u < all; u += gridDim.x * 4) {
+            const int second = u >= experts * units0, i = second ? u - experts * units0 : u, per = second ? units1 : units0;
+            const F32Args& p = q.p[second];
+            const int nth = i / per, rem = i - nth * per, nn = (p.N + BN - 1) / BN;
+            const int g = __ffsll((unsigned long long)__ballot(mine_few && place == nth)) - 1;
+            const int kbeg = __builtin_amdgcn_readlane(off.begin, g), count = __builtin_amdgcn_readlane(off.count, g);
+            const int m0 = rem / nn * 32, n0 = rem % nn * BN;
+            const float* A = p.A + (int64_t)kbeg * p.lda + min(m0 + l32, p.M - 1);
+            const float* R[TM];
+#pragma unroll
+            for (int j = 0; j < TM; ++j) R[j] = p.B + min(n0 + j * 32 + l32, p.N - 1);
+            f32x16 sum[TM];
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[j][r] = 0.f;
+#pragma unroll 1
+            for (int k = 0; k < count; k += 16) {
+                const int k0 = k + kg * 8;              // this lane's eight k's
+                int row[8];
+                float va[8], vb[TM][8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    row[e] = kbeg + min(k0 + e, count - 1);
+                    if (p.rows) row[e] = p.rows[row[e]];
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) va[e] = A[min(k0 + e, count - 1) * p.lda];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int j = 0; j < TM; ++j) vb[j][e] = R[j][(int64_t)row[e] * p.ldb];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (k0 + e >= count) {
+                        va[e] = 0.f;
+#pragma unroll
+                        for (int j = 0; j < TM; ++j) vb[j][e] = 0.f;
+                    }
+                bf16x8 fa[3], fb[3];
+                split8(va, fa[0], fa[1], fa[2]);
+#pragma unroll
+                for (int j = 0; j < TM; ++j) {
+                    split8(vb[j], fb[0], fb[1], fb[2]);
+                    f32x16 large, small;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) large[r] = small[r] = 0.f;
+                    constexpr int TA[8] = {0, 0, 1, 1, 0, 2, 1, 2}, TB[8] = {0, 1, 0, 1, 2, 0, 2, 1};
+#pragma unroll
+                    for (int u = 0; u < 6; ++u) {
+                        f32x16& c = u == 0 ? large : small;
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[TA[u]], fb[TB[u]], c, 0, 0, 0);
+                    }
+                    if (count <= 16) {
+#pragma unroll
+                        for (int u = 6; u < 8; ++u) small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[TA[u]], fb[TB[u]], small, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum[j][r] += both(large[r], small[r]);
+                }
+            }
+            float* out = p.out1 + ((int64_t)g * p.M + m0) * p.N + n0 + l32;
+            auto row_at = [&](int r) { return 8 * (r >> 2) + 4 * kg + (r & 3); };
+            if (accumulate) {           // the old gradient, at clamped addresses, before the first store
+                float old[TM][16];
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        old[j][r] = out[(int64_t)min(row_at(r), p.M - 1 - m0) * p.N + min(j * 32, p.N - 1 - n0 - l32)];
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum[j][r] += old[j][r];
+            }
+            auto store = [&](bool whole) {
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (whole || (m0 + row_at(r) < p.M && n0 + j * 32 + l32 < p.N))
+                            out[(int64_t)row_at(r) * p.N + j * 32] = sum[j][r];
+            };
+            if (m0 + 32 <= p.M && n0 + BN <= p.N) store(true); else store(false);
         }
     }
     // the column sums, dealt from the last block on: those have a tile less, or none

@@ -61,13 +61,13 @@ def test_f32_largest_values_stay_finite():
 
 @pytest.mark.parametrize("d,F,tile", [(64, 128, "32x32/4"), (516, 1028, "64x64/4")])
 def test_f32_weight_gradients_of_a_few_rows(d, F, tile):
-    """Experts with 1 to 17 rows.  n float32 products added one behind the other in chains of eight have a relative rms error of
-    2.52e-8 sqrt((n + 1) / 2), n <= 8, of sqrt((8 + 1) / 2 + 1) above: nothing may be above that (8 % for the
+    """Experts with 1 to 49 rows.  n float32 products added one behind the other in chains of eight have a relative rms error of
+    2.52e-8 sqrt((n + 1) / 2), n <= 8, of sqrt((8 + 1) / 2 + 1) above and more beyond 32: nothing may be above that (8 % for the
     samples: the mantissas of a row of dO and one of A are behind all products of a single row)."""
     import torch
     import gpu_harness as h
     from helpers import ffn_tiles
-    B, counts = h.B, [1, 2, 3, 0, 5, 8, 16, 17]
+    B, counts = h.B, [1, 2, 3, 0, 5, 8, 16, 17, 48, 49]
     E, P = len(counts), sum(counts)
     offs = [sum(counts[:e]) for e in range(E + 1)]
     shape = B.make_shape(P, d, E, F, "f32", "relu", P)
@@ -153,3 +153,49 @@ def test_f32_small_values_lose_no_more_than_the_last_terms_range(exponent, d, F)
     size = (xd.square() @ Wd.square().T).sqrt()
     bound = 2.0 ** -134 * Wd.abs().sum(1) + 5 * 2.6e-8 * (d / 8 + 6) ** 0.5 * size
     assert ((H - xd @ Wd.T).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("gathered,accumulate", [(True, False), (False, True)])
+def test_f32_weight_gradients_of_a_few_rows_are_those_of_tiles(gathered, accumulate):
+    """Up to 48 rows of an expert, waves work without the LDS (32 rows by 64 columns of a gradient each) where the launch has two such
+    pieces for every block: the same bits as in 64x64 tiles, which the expert alone is worked in.  No side is a multiple of a piece's."""
+    import torch
+    import gpu_harness as h
+    from helpers import ffn_tiles
+    B, d, F, counts = h.B, 516, 1028, [1, 0, 15, 16, 17, 31, 33, 47, 48, 49, 63, 65, 130, 0]
+    E, P = len(counts), sum(counts)
+    offs = [sum(counts[:e]) for e in range(E + 1)]
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert ffn_tiles(B.make_shape(P, d, E, F, "f32", "relu", P), num_cu=cu)[4] == "64x64/4"
+    tiles = 2 * -(-d // 64) * -(-F // 64)
+    pieces = -(-d // 32) * -(-F // 64) + -(-F // 32) * -(-d // 64)
+    assert pieces < 2 * min(tiles, 2 * cu) and pieces * sum(n <= 48 for n in counts) >= 2 * 2 * cu
+    g = torch.Generator("cuda").manual_seed(8)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    dO, x, A, W1, W2, start1, start2 = rnd(P, d), rnd(P, d), rnd(P, F), rnd(E, F, d), rnd(E, d, F), rnd(E, F, d), rnd(E, d, F)
+    tok = torch.randperm(P, generator=g, device="cuda").int() if gathered else None
+    dXp, ctx = torch.empty(P, d, device="cuda"), B.Context()
+
+    def gradients(experts):
+        first, last = offs[experts[0]], offs[experts[-1] + 1]
+        e = slice(experts[0], experts[-1] + 1)
+        shape = B.make_shape(P, d, len(experts), F, "f32", "relu", max(1, last - first))
+        r = slice(first, max(last, first + 1))
+        dW1, dW2 = start1[e].clone(), start2[e].clone()
+        ws = torch.empty(B.evomoe_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+        part = torch.tensor([offs[i] - first for i in range(experts[0], experts[-1] + 2)], dtype=torch.int32, device="cuda")
+        B.evomoe_expert_ffn_bwd(ctx, shape, dO[r].clone(), torch.ones_like(A[r]), A[r].clone(), x if gathered else x[r].clone(),
+                                tok[r].clone() if gathered else None, part, W1[e].clone(), W2[e].clone(), None, None, dW1, None, dW2,
+                                None, dXp, accumulate, ws)
+        torch.cuda.synchronize()
+        return dW1, dW2
+
+    together = gradients(range(E))
+    for e in range(E):
+        if offs[e] == P:
+            continue                                         # (no row to hand over for the last, empty one)
+        for got, want in zip(together, gradients([e])):
+            assert torch.equal(got[e], want[0]), (e, counts[e])
+    assert torch.equal(together[0][-1], start1[-1] if accumulate else torch.zeros_like(start1[-1]))
+    ctx.close()
+
