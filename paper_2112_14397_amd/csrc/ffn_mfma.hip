@@ -857,8 +857,9 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, i
         }
 
         // ---------------- epilogue: stage f32 rows through LDS, finish row-major ----------------
-        // Waves of 128 columns, NT/NN, one block per CU: eight rows at a time.  (With two blocks the steps took 3-5 % of dH: one's
-        // epilogue is under the other's MFMAs anyway.)  The rows of one step are written to 4 KB of the wave's own and read
+        // Waves of 128 columns, NT/NN, one block per CU: eight rows at a time.  (With two blocks, 128x256 tiles of dH, the
+        // steps took 3-5 % longer: one's epilogue is under the other's MFMAs anyway.  Waves of 64 columns have another layout and
+        // keep the passes below.)  The rows of one step are written to 4 KB of the wave's own and read
         // back while the step before is computed and stored; the LDS works a wave's accesses off in order, so that this takes
         // no wait but the one for the data.  16-byte chunk c of row r lies at c ^ (c >> 4 & 1) ^ (r & 4 ? 8 : 0): the two
         // half-waves write to, and sixteen lanes read from, different banks.
@@ -1260,8 +1261,12 @@ template <class Cfg> int col_group_for(int n, int k) {
 // a little per flop but leave less of the last, partly filled round idle and waste less in the padding of each
 // expert's last row tile.  Where several blocks share a compute unit and the last round does not give every unit all
 // of them, that round is cheaper: 0.55 of a round at least, rising with the blocks per unit that it needs.  The numbers
-// are fits to launches over d x F from 136 x 264 to 1024 x 4096, 1 to 64 experts and 1 to 90 000 pairs; the shape the
-// model picks is within 1-3 % of the best one measured on average (no launch of the sweep above 27 %, those of 10 us or 20 us), where
+// are fits to launches over d x F from 136 x 264 to 1024 x 4096, 1 to 64 experts and 1 to 90 000 pairs.  They price a last round
+// that is worked in half tiles as a whole one.  Against every candidate measured, over 22 layers of 2000 to 87 690 pairs, the picks are
+// slower than the best by (mean, most; %) GEMM1 2.6, 21, GEMM2 1.4, 14, dH 3.4, 23, dXp 1.0, 14, weight gradients 1.0, 5; the largest:
+// dH and GEMM1 of 20 000 pairs, d = 256, F = 1024, E = 16 46 and 40 us where 128x128 and 64x128 tiles take 38 and 33, dH of 8192 pairs,
+// d = 512, E = 64 62 (128x128: 52), dXp of 16 384, d = 768, E = 32 124 (128x256: 109).  dH of 8192 / 11 000 / 16 223 pairs, d = 768,
+// E = 16, 256x256 by eight waves 70 / 93 / 120, 128x256 73 / 97 / 126, 128x128 74 / 92 / 126, picked the first, the third, the first.
 // 256-column tiles alone were 40-190 % slower below about 200 rows per expert.  d = 768, F = 3072, 16 experts, us:
 //            pairs     48     512    2048   8192   58330
 //   GEMM1  256-wide    30     30     32     65     326          GEMM2  256-wide   37     40     45     53     254

@@ -155,8 +155,9 @@ def test_f32_small_values_lose_no_more_than_the_last_terms_range(exponent, d, F)
     assert ((H - xd @ Wd.T).abs() <= bound).all()
 
 
-@pytest.mark.parametrize("gathered,accumulate", [(True, False), (False, True)])
-def test_f32_weight_gradients_of_a_few_rows_are_those_of_tiles(gathered, accumulate):
+@pytest.mark.parametrize("gathered,accumulate,which", [(True, False, "both"), (False, True, "both"), (True, True, "dW1"),
+                                                       (False, False, "dW2")])
+def test_f32_weight_gradients_of_a_few_rows_are_those_of_tiles(gathered, accumulate, which):
     """Up to 48 rows of an expert, waves work without the LDS (32 rows by 64 columns of a gradient each) where the launch has two such
     pieces for every block: the same bits as in 64x64 tiles, which the expert alone is worked in.  No side is a multiple of a piece's."""
     import torch
@@ -169,7 +170,9 @@ def test_f32_weight_gradients_of_a_few_rows_are_those_of_tiles(gathered, accumul
     assert ffn_tiles(B.make_shape(P, d, E, F, "f32", "relu", P), num_cu=cu)[4] == "64x64/4"
     tiles = 2 * -(-d // 64) * -(-F // 64)
     pieces = -(-d // 32) * -(-F // 64) + -(-F // 32) * -(-d // 64)
-    assert pieces < 2 * min(tiles, 2 * cu) and pieces * sum(n <= 48 for n in counts) >= 2 * 2 * cu
+    if which != "both":
+        tiles, pieces = tiles // 2, pieces // 2              # (either problem has about half of the pieces)
+    assert pieces + 8 < 2 * min(tiles, 2 * cu) and (pieces - 8) * sum(n <= 48 for n in counts) >= 2 * 2 * cu
     g = torch.Generator("cuda").manual_seed(8)
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
     dO, x, A, W1, W2, start1, start2 = rnd(P, d), rnd(P, d), rnd(P, F), rnd(E, F, d), rnd(E, d, F), rnd(E, F, d), rnd(E, d, F)
@@ -185,10 +188,10 @@ def test_f32_weight_gradients_of_a_few_rows_are_those_of_tiles(gathered, accumul
         ws = torch.empty(B.evomoe_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
         part = torch.tensor([offs[i] - first for i in range(experts[0], experts[-1] + 2)], dtype=torch.int32, device="cuda")
         B.evomoe_expert_ffn_bwd(ctx, shape, dO[r].clone(), torch.ones_like(A[r]), A[r].clone(), x if gathered else x[r].clone(),
-                                tok[r].clone() if gathered else None, part, W1[e].clone(), W2[e].clone(), None, None, dW1, None, dW2,
-                                None, dXp, accumulate, ws)
+                                tok[r].clone() if gathered else None, part, W1[e].clone(), W2[e].clone(), None, None,
+                                dW1 if which != "dW2" else None, None, dW2 if which != "dW1" else None, None, dXp, accumulate, ws)
         torch.cuda.synchronize()
-        return dW1, dW2
+        return {"both": (dW1, dW2), "dW1": (dW1,), "dW2": (dW2,)}[which]
 
     together = gradients(range(E))
     for e in range(E):
@@ -196,6 +199,7 @@ def test_f32_weight_gradients_of_a_few_rows_are_those_of_tiles(gathered, accumul
             continue                                         # (no row to hand over for the last, empty one)
         for got, want in zip(together, gradients([e])):
             assert torch.equal(got[e], want[0]), (e, counts[e])
-    assert torch.equal(together[0][-1], start1[-1] if accumulate else torch.zeros_like(start1[-1]))
+    first = start2 if which == "dW2" else start1
+    assert torch.equal(together[0][-1], first[-1] if accumulate else torch.zeros_like(first[-1]))
     ctx.close()
 
