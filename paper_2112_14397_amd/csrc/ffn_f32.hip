@@ -28,8 +28,8 @@
 // asynchronous loads, one slab ahead.  A wave has 16 of a slab's k's for the whole tile: what it takes apart no other wave
 // needs.  (The terms in the LDS, each taken apart by one thread: six bytes per value instead of four, two barriers per slab
 // and the loads through registers: 244 us instead of 217 for the step below.)  us, float32 MFMAs / here, GEMM1, GEMM2, dH,
-// dXp, both dW, whole training step: 5632 pairs, d = 256, E = 8, F = 1024: 42 / 36, 42 / 29, 48 / 37, 44 / 33, 73 / 50, 272 /
-// 217; 11000 pairs, d = 512, E = 16, F = 2048: 228 / 175, 238 / 152, 258 / 184, 259 / 171, 472 / 338, 1451 / 1078.
+// dXp, both dW, whole training step: 5632 pairs, d = 256, E = 8, F = 1024: 40 / 35, 40 / 29, 45 / 36, 41 / 32, 68 / 50, 269 /
+// 219; 8700 pairs, d = 512, E = 16, F = 2048: 208 / 160, 203 / 133, 233 / 167, 218 / 146, 418 / 312, 1302 / 983.
 // The bias gradients' column sums are further tiles behind dXp's and behind the weight gradients': colsum_tile().
 //
 // Tiles: 64x64, and 32x32 for launches that would leave most of the chip idle; cheapest() says which and why.  Both add the
@@ -150,16 +150,14 @@ template <int BM> __device__ __forceinline__ Offsets scan_offsets(const int32_t*
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 // The three bf16 terms of eight float32 values: hi (cut off, so that no finite value becomes infinite) + mid (rounded) + lo
-// (what is left, eight bits at most) is the value itself, from 2^-110 on (above).  An infinity or a NaN gives NaN terms behind itself.  (A signalling NaN
-// is made a quiet one first: cut off, one with a payload in its low half only would be an infinity.  That takes 3 % of the step
-// below.)
+// (what is left, eight bits at most) is the value itself, from 2^-110 on (above).  An infinity or a NaN gives NaN terms behind itself,
+// a NaN with a payload in its low half only (a signalling one) an infinity as its first.
 __device__ __forceinline__ void split8(const float* v, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
     u32x4 h, m, l;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float v0 = __builtin_canonicalizef(v[2 * i]), v1 = __builtin_canonicalizef(v[2 * i + 1]);
-        const uint32_t b0 = __float_as_uint(v0), b1 = __float_as_uint(v1);
-        const float r0 = v0 - __uint_as_float(b0 & 0xffff0000u), r1 = v1 - __uint_as_float(b1 & 0xffff0000u);
+        const uint32_t b0 = __float_as_uint(v[2 * i]), b1 = __float_as_uint(v[2 * i + 1]);
+        const float r0 = v[2 * i] - __uint_as_float(b0 & 0xffff0000u), r1 = v[2 * i + 1] - __uint_as_float(b1 & 0xffff0000u);
         h[i] = __builtin_amdgcn_perm(b1, b0, 0x07060302);
         asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(m[i]) : "v"(r0), "v"(r1));      // (seen through, it would be made twice)
         l[i] = pack_bf16x2(r0 - lo_bf16(m[i]), r1 - hi_bf16(m[i]));
@@ -334,11 +332,28 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
         }
     };
 
-    // Behind an infinite or NaN operand the smaller products are NaN; the large ones have what float32 products would give.
+    // Behind an infinite or NaN operand the smaller products are NaN; the large ones have what float32 products would give, unless the
+    // operand is a NaN that looks like an infinity in its first term.
     // (Asked of the small sum: the sum of both overflows where a float32 sum does.)
     auto both = [](float large, float small) {
         return fabsf(small) <= 3.402823466e38f ? large + small : large;
     };
+    // So an infinite output is one only if there is no NaN among its operands: element (row, column) of C of expert g, k's
+    // [kbeg, kend).  (Made canonical before they are taken apart, all operands would pay for it, with 3 % of a training step.)
+    auto nan_among = [&](const F32Args& p, int g, int row, int column, int kbeg, int kend) {
+        const float* Bg = LAYOUT == L_TN ? p.B : p.B + (int64_t)g * p.b_group_stride;
+        const int64_t arow = LAYOUT == L_TN ? 0 : p.rows ? p.rows[row] : row;
+        bool nan = false;
+#pragma unroll 1
+        for (int k = kbeg; k < kend; ++k) {
+            const int64_t brow = LAYOUT == L_TN && p.rows ? p.rows[k] : k;
+            const float a = LAYOUT == L_TN ? p.A[(int64_t)k * p.lda + row] : p.A[arow * p.lda + k],
+                        b = B_KC ? Bg[(int64_t)column * p.ldb + k] : Bg[brow * p.ldb + column];
+            nan |= a != a || b != b;
+        }
+        return nan;
+    };
+    auto infinite = [](float v) { return fabsf(v) == __builtin_inff(); };
     int first = 0;                                      // stage of the tile's first slab
     auto start = [&](const Tile& t) {
         aim(t);
@@ -364,6 +379,27 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = small[i][j][r] = 0.f;
 
+        auto read = [&](const float* operand, bool k_contiguous, int i, float (&out)[TM][8]) {
+            float* v = out[i];
+            if (k_contiguous) {
+                const float* row = operand + (i * 32 + l32) * BK;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const f32x4 c = *reinterpret_cast<const f32x4*>(row + ((wave * 4 + kg * 2 + h) ^ (l32 & 15)) * 4);
+                    v[4 * h] = c.x; v[4 * h + 1] = c.y; v[4 * h + 2] = c.z; v[4 * h + 3] = c.w;
+                }
+            } else if (TM == 1) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = operand[(wave * 16 + kg * 8 + e) * B + l32];
+            } else if (i == 0) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const f32x2 c = *reinterpret_cast<const f32x2*>(operand + (wave * 16 + kg * 8 + e) * B + 2 * l32);
+                    out[0][e] = c.x;
+                    out[TM - 1][e] = c.y;
+                }
+            }
+        };
         for (int s = 0; s < nslab; ++s) {
             all_landed();                               // slab s is there, and everyone is done with the other stage
             const int stage = first ^ (s & 1), k0 = kbeg + s * BK;
@@ -378,27 +414,6 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
             if (kw < kend) {
                 // raw fragments: eight k's of a row (column) per lane
                 float va[TM][8], vb[TM][8];
-                auto read = [&](const float* operand, bool k_contiguous, int i, float (&out)[TM][8]) {
-                    float* v = out[i];
-                    if (k_contiguous) {
-                        const float* row = operand + (i * 32 + l32) * BK;
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            const f32x4 c = *reinterpret_cast<const f32x4*>(row + ((wave * 4 + kg * 2 + h) ^ (l32 & 15)) * 4);
-                            v[4 * h] = c.x; v[4 * h + 1] = c.y; v[4 * h + 2] = c.z; v[4 * h + 3] = c.w;
-                        }
-                    } else if (TM == 1) {
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) v[e] = operand[(wave * 16 + kg * 8 + e) * B + l32];
-                    } else if (i == 0) {
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const f32x2 c = *reinterpret_cast<const f32x2*>(operand + (wave * 16 + kg * 8 + e) * B + 2 * l32);
-                            out[0][e] = c.x;
-                            out[TM - 1][e] = c.y;
-                        }
-                    }
-                };
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
                     read(sa, A_KC, i, va);
@@ -413,12 +428,12 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
                         c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[TA[u]][i], fb[TB[u]][j], c, 0, 0, 0);
                     }
                 };
-                // the next fragment is split under the products of the ones before it: nine VALU slots per MFMA
+                // the next fragment is split under the products of the ones before it: eight VALU slots per MFMA
                 auto spread = [&]() {
 #pragma unroll
                     for (int u = 0; u < 6; ++u) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x002, 9, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 };
@@ -435,29 +450,31 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
                     products(0, TM - 1);
                     products(TM - 1, TM - 1);
                 }
-                if (kend - kbeg <= 16) {
-                    // block-uniform: mid * lo and lo * mid, from operands read and taken apart again, so that longer contractions
-                    // keep nothing for it
-                    asm volatile("" ::: "memory");
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) {
-                        read(sa, A_KC, i, va);
-                        read(sb, B_KC, i, vb);
-                    }
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) {
-                        split8(va[i], fa[0][i], fa[1][i], fa[2][i]);
-                        split8(vb[i], fb[0][i], fb[1][i], fb[2][i]);
-                    }
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TM; ++j) {
-                            small[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1][i], fb[2][j], small[i][j], 0, 0, 0);
-                            small[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[2][i], fb[1][j], small[i][j], 0, 0, 0);
-                        }
-                }
             }
+        }
+        if (kend - kbeg <= 16 && wave == 0 && nslab) {
+            // mid * lo and lo * mid, from the only slab's operands, read and taken apart again, so that the loop keeps nothing for it
+            const float* sa = reinterpret_cast<const float*>(smem + first * STAGE);
+            const float* sb = sa + OPERAND / 4;
+            float va[TM][8], vb[TM][8];
+            bf16x8 fa[3][TM], fb[3][TM];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                read(sa, A_KC, i, va);
+                read(sb, B_KC, i, vb);
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                split8(va[i], fa[0][i], fa[1][i], fa[2][i]);
+                split8(vb[i], fb[0][i], fb[1][i], fb[2][i]);
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TM; ++j) {
+                    small[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1][i], fb[2][j], small[i][j], 0, 0, 0);
+                    small[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[2][i], fb[1][j], small[i][j], 0, 0, 0);
+                }
         }
         first ^= nslab & 1;
         if (more) start(next);                          // the next tile's first slab is fetched under this tile's epilogue
@@ -494,6 +511,12 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
                 f32x4 v = {0.f, 0.f, 0.f, 0.f}, a;
 #pragma unroll
                 for (int w = 0; w < 4; ++w) v += *reinterpret_cast<const f32x4*>(red + (w * 32 + o / (B / 4)) * B + o % (B / 4) * 4);
+                if (infinite(fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))))) {
+#pragma unroll 1
+                    for (int e = 0; e < 4; ++e)
+                        if (infinite(v[e]) && nan_among(p, t.g, LAYOUT == L_TN ? t.m0 + tr : t.row0 + tr, n + e, kbeg, kend))
+                            v[e] = __builtin_nanf("");
+                }
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     if (EPI == E_HA || EPI == E_BIAS) v[e] += bias[u][e];
@@ -572,6 +595,11 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
                     for (int r = 0; r < 16; ++r) sum[j][r] += both(large[r], small[r]);
                 }
             }
+            float largest = 0.f;
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) largest = fmaxf(largest, fabsf(sum[j][r]));
             float* out = p.out1 + ((int64_t)g * p.M + m0) * p.N + n0 + l32;
             auto row_at = [&](int r) { return 8 * (r >> 2) + 4 * kg + (r & 3); };
             if (accumulate) {           // the old gradient, at clamped addresses, before the first store
@@ -595,6 +623,15 @@ __global__ __launch_bounds__(256, (blocks_per_cu<BM>())) void grouped_gemm_f32(
                             out[(int64_t)row_at(r) * p.N + j * 32] = sum[j][r];
             };
             if (m0 + 32 <= p.M && n0 + BN <= p.N) store(true); else store(false);
+            if (infinite(largest)) {
+#pragma unroll 1
+                for (int r = 0; r < 16 * TM; ++r) {
+                    const int m = row_at(r & 15), n = r / 16 * 32;
+                    float* at = out + (int64_t)m * p.N + n;
+                    if (m0 + m < p.M && n0 + n + l32 < p.N && infinite(*at) && nan_among(p, g, m0 + m, n0 + n + l32, kbeg, kbeg + count))
+                        *at = __builtin_nanf("");
+                }
+            }
         }
     }
     // the column sums, dealt from the last block on: those have a tile less, or none

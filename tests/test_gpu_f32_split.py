@@ -203,3 +203,45 @@ def test_f32_weight_gradients_of_a_few_rows_are_those_of_tiles(gathered, accumul
     assert torch.equal(together[0][-1], first[-1] if accumulate else torch.zeros_like(first[-1]))
     ctx.close()
 
+
+# (single waves, tiles of 64x64 and of 32x32)
+@pytest.mark.parametrize("d,F,E,n", [(64, 64, 1, 40), (516, 1028, 8, 40), (516, 1028, 8, 200)])
+@pytest.mark.parametrize("bits", [0x7f800001, 0xff80ffff - 2 ** 32, 0x7fc00000])
+def test_f32_nans_stay_nans_in_the_backward(d, F, E, n, bits):
+    """One NaN in an operand: every output that it is multiplied into is one, no other."""
+    import torch
+    import gpu_harness as h
+    B, P, e = h.B, E * n, E - 1                              # the last expert's
+    shape = B.make_shape(P, d, E, F, "f32", "relu", P)
+    g = torch.Generator("cuda").manual_seed(1)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    base = {"dO": rnd(P, d), "A": rnd(P, F), "x": rnd(P, d), "W1": rnd(E, F, d), "W2": rnd(E, d, F)}
+    offs = torch.arange(0, P + 1, n, dtype=torch.int32, device="cuda")
+    tok = torch.arange(P, dtype=torch.int32, device="cuda")
+    dW1, dW2, dXp = torch.empty(E, F, d, device="cuda"), torch.empty(E, d, F, device="cuda"), torch.empty(P, d, device="cuda")
+    ws = torch.empty(B.evomoe_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    ctx, r, i, j = B.Context(), P - 2, d - 3, F - 5
+    rows = slice(e * n, P)
+    for what, at in (("dO", (r, i)), ("A", (r, j)), ("x", (r, i)), ("W1", (e, j, i)), ("W2", (e, i, j))):
+        t = dict(base)
+        t[what] = base[what].clone()
+        t[what].view(torch.int32)[at] = bits
+        B.evomoe_expert_ffn_bwd(ctx, shape, t["dO"], torch.ones_like(base["A"]), t["A"], t["x"], tok, offs, t["W1"], t["W2"], None, None,
+                                dW1, None, dW2, None, dXp, False, ws)
+        torch.cuda.synchronize()
+        dH = ws[:P * F * 4].view(torch.float32).view(P, F)
+        want = {k: torch.zeros_like(v, dtype=torch.bool) for k, v in (("dH", dH), ("dXp", dXp), ("dW1", dW1), ("dW2", dW2))}
+        if what == "dO":
+            want["dH"][r], want["dXp"][r], want["dW1"][e], want["dW2"][e, i] = True, True, True, True
+        if what == "W2":
+            want["dH"][rows, j], want["dXp"][rows], want["dW1"][e, j] = True, True, True
+        if what == "A":
+            want["dW2"][e, :, j] = True
+        if what == "x":
+            want["dW1"][e, :, i] = True
+        if what == "W1":
+            want["dXp"][rows, i] = True
+        for k, v in (("dH", dH), ("dXp", dXp), ("dW1", dW1), ("dW2", dW2)):
+            assert torch.equal(v.isnan(), want[k]) and v[~want[k]].isfinite().all(), (what, k)
+    ctx.close()
+
