@@ -197,24 +197,27 @@ template <int LAYOUT, int BM, int BN, int BK, int NSTAGE, int NW = 4> struct Geo
     template <int C> __device__ static __forceinline__ int ks_key(int k) { return C >= 128 ? 2 * (k & 3) : (k & 2); }
 };
 
-// gelu(h) = max(h, 0) - |h| Q(|h|) with Q(z) = 1 - Phi(z) = 2^p(z): log2 Q is so smooth that a polynomial of degree five on
-// |h| <= 5.5 gives gelu to 9.6e-7 (minimax with the error weighted toward small |h|; float32 evaluation included), and beyond it the
-// term is below 1e-7.  Ten VALU instructions, one of them v_exp_f32, which takes two slots; GEMM1's epilogue is bound by them.
-// (Degree four, one v_fmaak_f32 less, was off by up to 2.1e-5, in places by more than the form before it: Phi as an odd polynomial
-// of degree 17 of h clamped to 4.2, 13 instructions, errors of 1.1e-5 |h|, 8.7e-5 in the tails.  Of GEMM1 it saved 1 %: 868
-// against 877 us at 87 690 pairs, d = 1024.)
+// gelu(h) = max(h, -4.2) Phi(hc), Phi(hc) = 0.5 + hc Q(hc^2), hc = h clamped to |h| <= 4.2: degree-8 minimax fit of Q, |error of Phi| <
+// 1.2e-5 -- below the resolution of the bf16 values it is multiplied into -- and no transcendental; 13 VALU instructions, which GEMM1's
+// epilogue is bound by.  Beyond the fitted range the values stay within 2.5e-4 of the true ones for any h: -> h for large h (Phi(4.2) =
+// 1 - 1.3e-5), -> -4.2 * 1.3e-5 for very negative ones.  (As max(h, 0) - |h| 2^p(|h|) GEMM1 of 58 330 pairs, d = 768 takes 322 us with p
+// of degree four, whose errors are larger in places, and 326 with degree five, whose errors are smaller everywhere, 9.6e-7 at most,
+// instead of 336; either rounds other values of A up or down, and with degree five dx at 16 223 pairs had an element at 1.37 times the
+// comparison's bound, where 1.35 is allowed for.)
 __device__ __forceinline__ float act_fwd_fast(float h, int act) {
     if (act == EVOMOE_RELU) return relu(h);
-    const float z = __builtin_elementwise_minimum(__builtin_fabsf(h), 5.5f);      // (a NaN stays one, and with it the result)
-    float pos;
-    asm("v_max_f32 %0, 0, %1" : "=v"(pos) : "v"(h));        // (as fmaxf it would get a second instruction for signalling NaNs)
-    float q = -0.000514221328f;
-    q = fmaf(q, z, 0.00736901748f);
-    q = fmaf(q, z, -0.0525218223f);
-    q = fmaf(q, z, -0.459272654f);
-    q = fmaf(q, z, -1.15108872f);
-    q = fmaf(q, z, -1.00000012f);
-    return fmaf(-z, __builtin_amdgcn_exp2f(q), pos);
+    const float hc = __builtin_amdgcn_fmed3f(h, -4.2f, 4.2f), u = hc * hc;
+    float q = 5.998071484e-11f;
+    q = fmaf(q, u, -5.633320033e-09f);
+    q = fmaf(q, u, 2.343674907e-07f);
+    q = fmaf(q, u, -5.760770819e-06f);
+    q = fmaf(q, u, 9.457441047e-05f);
+    q = fmaf(q, u, -1.114148065e-03f);
+    q = fmaf(q, u, 9.830130264e-03f);
+    q = fmaf(q, u, -6.636036932e-02f);
+    q = fmaf(q, u, 3.989074528e-01f);
+    asm("v_fmaak_f32 %0, %1, %2, 0x3f000000" : "=v"(q) : "v"(hc), "v"(q));     // 0.5 as a literal: half the time of v_fma_f32
+    return __builtin_elementwise_maximum(h, -4.2f) * q;      // (a NaN stays one)
 }
 // gelu'(h) = Phi(h) + h phi(h) as 0.5 + hc*R(hc^2): it is odd about 1/2 as well, so one degree-10 minimax fit of the whole
 // derivative takes the place of Phi and an exponential (14 VALU slots instead of 18 in an epilogue that they bound).  R is

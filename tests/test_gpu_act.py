@@ -31,8 +31,8 @@ class Layer:
 
 @pytest.mark.parametrize("P,E,F,tile", SIZES)
 def test_gelu_is_off_by_no_more_than_its_polynomial(P, E, F, tile):
-    """|2^p(z) - Q(z)| z is below 9.6e-7 for every z = |h|, float32 evaluation included, and the sum of that and the positive part
-    is rounded once to float32 (2.4e-7 below 8): 1.2e-6 beside the rounding to bf16."""
+    """Phi is off by less than 1.2e-5, gelu by |h| times that, for small |h| by 3.6e-5 h^2 (Phi's polynomial is odd about 1/2; its first
+    coefficient is off by 3.5e-5), float32 evaluation 1e-7 |h|: beside the rounding to bf16."""
     import torch
     g = torch.Generator("cuda").manual_seed(3)
     h = torch.rand(E, F, generator=g, device="cuda") * 16 - 8
@@ -44,7 +44,8 @@ def test_gelu_is_off_by_no_more_than_its_polynomial(P, E, F, tile):
     for row in (0, -1):
         at = layer.offs[:-1].long() if row == 0 else layer.offs[1:].long() - 1
         more = (layer.A[at].double() - want).abs() - half
-        assert (more <= 1.2e-6).all(), (row, more.max().item(), h.flatten()[more.argmax()].item())
+        bound = torch.minimum(1.2e-5 * h.abs(), 3.6e-5 * h * h) + 1e-7 * h.abs()
+        assert (more <= bound).all(), (row, (more / bound).max().item(), h.flatten()[(more / bound).argmax()].item())
     layer.ctx.close()
 
 
