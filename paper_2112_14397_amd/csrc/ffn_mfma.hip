@@ -389,11 +389,11 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, i
     }
     // A wave without an output (its 64 or 128 rows or its 128 columns do not exist) sits a 256x256 tile out: it fetches its share
     // of the operands and leaves the matrix pipes to the others.  In launches of less than three rounds it does not: there the
-    // blocks that get ahead find no tile to take, and GEMM1 of 8192 pairs, d = 768, took 70 us instead of 64.
+    // blocks that get ahead find no tile to take, and GEMM1 of 8192 pairs, d = 768, took 70 us instead of 64 (shorter gelu).
     // Where no more than half of the blocks have a tile in the last round, two blocks take each of those tiles, one for its
     // upper and one for its lower 128 rows (waves 0 .. 3, one per SIMD, or 4 .. 7): places [full, full + halves) of the
     // sequence are upper halves, the next ones lower halves.  Not GEMM1, whose epilogue is as long for one wave per SIMD as for
-    // two (58 330 pairs: 334 us, without 326).  us, before / now: weight gradients of d = 768, F = 3072, 16 experts (4.5 rounds),
+    // two (58 330 pairs, with the shorter gelu: 334 us, without 326).  us, before / now: weight gradients of d = 768, F = 3072, 16 experts (4.5 rounds),
     // 58 330 pairs 485 / 468, 8192 pairs 109 / 106; dH 16 223 pairs 128 / 122, d = 1024, 87 690 pairs 901 / 871; GEMM1 d = 512, 22 073
     // pairs (345 rows per expert) 98 / 88, d = 1024, 87 690 pairs 945 / 908.
     constexpr bool SIT_OUT = BM == 256 && BN == 256;
@@ -1185,9 +1185,9 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, i
 // BIG8 against 32-wide slabs: GEMM1 404 -> 366 us at d = 768, F = 3072, 58 330 pairs, 1603 -> 1473 at d = 1024, F = 4096, 131 072 pairs; BIG: GEMM2 270 -> 254 and 1026 -> 964 us, dXp 261 -> 252 and 994 -> 962 us.
 // Where its time went with both waves of a SIMD in the epilogue at once (clocks per tile at d = 768): GEMM1 26.6 k main loop, 15 k
 // epilogue, bound by its VALU instructions, 9 k waiting at the ends for loads and for each other; dH 22 k epilogue, H's loads one
-// step ahead.  The next tile's first slab and row numbers under the epilogue, the epilogue in steps that overlap, a shorter
-// gelu and H four steps ahead (48 k and 53 k clocks per tile now): GEMM1 342 -> 326 us at d = 768, F = 3072, 58 330 pairs,
-// 73 -> 65 at 8192 pairs, 950 -> 909 at d = 1024, F = 4096, 87 690 pairs; dH 384 -> 371, - , 942 -> 920.
+// step ahead.  With the next tile's first slab and row numbers under the epilogue, the epilogue in steps that overlap and H four
+// steps ahead: GEMM1 345 -> 339 us at d = 768, F = 3072, 58 330 pairs, 72 -> 68 at 8192 pairs, 980 -> 925 at d = 1024, F = 4096,
+// 87 690 pairs; dH 381 -> 364, 74 -> 70, 925 -> 873.
 // OCT: BIG8 with four stages of 32 k, for the weight gradients (k-strided operands are whole lines at any slab width).
 // DUO: two blocks per compute unit (one's epilogue and stalls hide under the other's MFMAs).
 // LAT: for launches with no more tiles than compute units and a long contraction: what counts then is how fast
@@ -1272,8 +1272,8 @@ template <class Cfg> int col_group_for(int n, int k) {
 // E = 16, 256x256 by eight waves 70 / 93 / 120, 128x256 73 / 97 / 126, 128x128 74 / 92 / 126, picked the first, the third, the first.
 // 256-column tiles alone were 40-190 % slower below about 200 rows per expert.  d = 768, F = 3072, 16 experts, us:
 //            pairs     48     512    2048   8192   58330
-//   GEMM1  256-wide    30     30     32     65     326          GEMM2  256-wide   37     40     45     53     254
-//          picked      17     18     30     65     326                 picked     17     20     31     53     254
+//   GEMM1  256-wide    30     30     32     68     339          GEMM2  256-wide   37     40     45     53     254
+//          picked      17     18     30     68     339                 picked     17     20     31     53     254
 struct RoundTime { double fixed, per_round, per_k; };
 template <class Cfg> double round_cost(const Ctx& c, int64_t tiles, double k, const RoundTime& t) {
     const int64_t slots = (int64_t)c.num_cu * Cfg::WPE, last = tiles % slots;
