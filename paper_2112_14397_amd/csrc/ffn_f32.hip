@@ -5,17 +5,18 @@
 //   NN  C[r,n] = sum_k A[r,k]       * W_g[k,n]          dH = dO W2,  dXp = dH W1
 //   TN  C_g[m,n] = sum_{r in g} L[r,m] * R[rrow(r),n]   weight gradients (contraction over the ragged rows)
 //
-// Every float32 value is taken apart into three bf16 values whose sum it is (of very small ones almost: below), and a product a * b into the six largest of the
-// nine products of their terms: bf16 MFMAs run at sixteen times the rate of float32 ones, so six of them take 0.38 of the time.
-// Left out are mid * lo and lo * mid, up to 2^-23 of the product each (the first term is cut off, so the second is up to 2^-7 of
-// the value, the third 2^-16), and lo * lo.  A single product is therefore less exact than in float32, a sum more, as below;
-// contractions of up to 16 k's take mid * lo and lo * mid too.  Relative rms error by the number of products (N(0,1) operands;
-// float32 chains of eight / six products / eight): 1 2.5e-8 / 3.4e-8 / 2.5e-8, 2 3.1e-8 / 3.4e-8 / 2.6e-8, 3 3.6e-8 / 3.5e-8 /
-// 2.6e-8, 16 6.0e-8 / 3.8e-8 / 3.1e-8, 17 6.4e-8 / 4.6e-8 / 4.0e-8.  The products are exact and each of four partial sums per output has one rounding per 16 k's (the
-// small products have a sum of their own), where float32 MFMAs round for every k: relative rms error against float64 at 5632
-// pairs, d = 256, E = 8, F = 1024 (float32 MFMAs / here; smaller at every size measured, 64 to 2048 k's): H 1.5e-7 / 7.2e-8,
-// O 2.9e-7 / 1.0e-7, dH 1.6e-7 / 8.2e-8, dXp 2.9e-7 / 1.1e-7, dW 2.4e-7 / 9.7e-8.  With one sum for all six products the
-// contractions of 64 k's had larger errors than float32 MFMAs (H 9.5e-8 against 8.8e-8).
+// Every float32 value is taken apart into three bf16 values whose sum it is (of very small ones almost: below), and a product
+// a * b into the six largest of the nine products of their terms: bf16 MFMAs run at sixteen times the rate of float32 ones, so
+// six of them take 0.38 of the time.  Left out are mid * lo and lo * mid, up to 2^-23 of the product each (the first term is cut off,
+// so the second is up to 2^-7 of the value, the third 2^-16), and lo * lo.  A single product is therefore less exact than in
+// float32, a sum more, as below; contractions of up to 16 k's take mid * lo and lo * mid too.  Relative rms error by the number
+// of products (N(0,1) operands; float32 chains of eight / six products / eight): 1 2.5e-8 / 3.4e-8 / 2.5e-8, 2 3.1e-8 / 3.4e-8 /
+// 2.6e-8, 3 3.6e-8 / 3.5e-8 / 2.6e-8, 16 6.0e-8 / 3.8e-8 / 3.1e-8, 17 6.4e-8 / 4.6e-8 / 4.0e-8.  The products are exact and each
+// of four partial sums per output has one rounding per 16 k's (the small products have a sum of their own), where float32 MFMAs
+// round for every k: relative rms error against float64 at 5632 pairs, d = 256, E = 8, F = 1024 (float32 MFMAs / here; smaller
+// at every size measured, 64 to 2048 k's): H 1.5e-7 / 7.2e-8, O 2.9e-7 / 1.0e-7, dH 1.6e-7 / 8.2e-8, dXp 2.9e-7 / 1.1e-7, dW
+// 2.4e-7 / 9.7e-8.  With one sum for all six products the contractions of 64 k's had larger errors than float32 MFMAs (H 9.5e-8
+// against 8.8e-8).
 //
 // Range: the terms of values below 2^-110 (7.7e-34) reach below the smallest bf16 subnormal, 2^-133, which the matrix cores do take:
 // each such value is off by up to 2^-134, that is by 2^-24 of itself at 2^-110 and by 2^-8 at the smallest normal float32 value

@@ -393,7 +393,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void grouped_gemm_bf16(GemmArgs q0, i
     // Where no more than half of the blocks have a tile in the last round, two blocks take each of those tiles, one for its
     // upper and one for its lower 128 rows (waves 0 .. 3, one per SIMD, or 4 .. 7): places [full, full + halves) of the
     // sequence are upper halves, the next ones lower halves.  Not GEMM1, whose epilogue is as long for one wave per SIMD as for
-    // two (58 330 pairs, with the shorter gelu: 334 us, without 326).  us, before / now: weight gradients of d = 768, F = 3072, 16 experts (4.5 rounds),
+    // two (58 330 pairs, with the shorter gelu: 334 us, without 326).  us, before / now: weight gradients of d = 768, F = 3072, 16
+    // experts (4.5 rounds),
     // 58 330 pairs 485 / 468, 8192 pairs 109 / 106; dH 16 223 pairs 128 / 122, d = 1024, 87 690 pairs 901 / 871; GEMM1 d = 512, 22 073
     // pairs (345 rows per expert) 98 / 88, d = 1024, 87 690 pairs 945 / 908.
     constexpr bool SIT_OUT = BM == 256 && BN == 256;
